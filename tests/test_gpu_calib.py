@@ -95,6 +95,38 @@ def test_online_appends_span_sort_chunks_and_merge_paths(sizes):
         _check_against_oracle(A, c, allv[:lo].astype(np.float64), test, [0.05, 0.2], brute=lo <= 30000)
 
 
+@pytest.mark.parametrize("base,sizes", [(0, (1, 3, 4, 5)), (1000, (16, 63, 64, 65)), (5000, (255, 256, 257)), (37, (511, 512, 513, 1024, 1025)),
+                                        (2047, (1, 2049, 4096, 4097)), ((1 << 19) - 300, (100, 200, 1, 17))])
+def test_small_appends_at_the_edges_of_their_kernels(base, sizes):
+    """Batches sorted inside the merge (up to 256 scores into up to 2^19 keys) and by one workgroup of 64 ... 1024
+    threads (512 ... 8192 keys), one below, at and above each limit; ties with the set and inside the batch, NaN, zeros
+    of both signs and infinities in the batch.  Integer work: every comparison exact."""
+    import paper_2509_15148_amd as A
+    announce("calib small appends", base, sizes)
+    allv = np.round(lognormal_scores(base + sum(sizes), seed=base + 9), 2)
+    lo = base
+    for i, n in enumerate(sizes):                              # special values at the batch's ends and inside
+        special = np.array([np.nan, np.inf, -np.inf, -0.0, 0.0, 1e-45, np.nan], dtype=np.float32)
+        if n > 16:
+            allv[lo + 1:lo + 4] = special[:3]
+            allv[lo + n - 4:lo + n] = special[3:]
+        lo += n
+    c = A.Calib(base + sum(sizes))
+    if base:
+        A.atts_calibrate_online(c, dev(allv[:base]))
+    test = np.concatenate([lognormal_scores(100, seed=78), allv[:50], allv[-50:]])
+    lo = base
+    for n in sizes:
+        A.atts_calibrate_online(c, dev(allv[lo:lo + n]))
+        lo += n
+        out = torch.empty(lo, dtype=torch.float32, device="cuda")
+        A.atts_calib_export(c, out)
+        held, finite = out.cpu().numpy(), allv[:lo][~np.isnan(allv[:lo])]
+        nan = lo - len(finite)
+        assert np.isnan(held[:nan]).all() and np.array_equal(held[nan:], np.sort(finite))
+        _check_against_oracle(A, c, allv[:lo].astype(np.float64), test, [0.05, 0.2], brute=lo <= 30000)
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
