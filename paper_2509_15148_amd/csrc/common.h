@@ -146,6 +146,9 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
 // The kernel for at most 16 rows of A (skinny.hip): launch_gemm hands it the calls it serves.
 bool gemm_skinny_ok(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);
 int32_t launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
+// The kernel for products of few tiles (small.hip), any shape; launch_gemm hands it the calls that leave the chip idle otherwise.
+int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
+int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
 // true if the EPI_QKV_ROPE epilogue can serve this QKV projection (else: EPI_STORE_ACT + launch_rope_split)
 bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t head_dim, bool a_rows_padded);
 // vt [rows, ldv]: zero columns [R, ldv) of every row (the attention kernel reads whole 64-key tiles of V^T).

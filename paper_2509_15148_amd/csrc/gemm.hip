@@ -7,6 +7,7 @@
 //   gemm_bf16_wide_kernel   aligned bf16 shapes (every projection of the bf16 models): 8 wavefronts,
 //                           384 x 256, 256 x 256 or 128 x 256 output tiles, operand slabs of 128 bytes
 //                           per row DMA-ed global -> LDS in whole 128-byte lines, explicit waits.
+//   gemm_small_kernel       (small.hip) products of few tiles, any shape and dtype
 //   gemm_nt_kernel          any shape, bf16 or fp32 (v_mfma_f32_32x32x2_f32): 4 wavefronts (2 x 2),
 //                           tile BM x BN, 128-byte slabs through registers with bounds checks,
 //                           double-buffered, one barrier per slab; LDS chunk index XOR (row >> 1) & 7.
@@ -959,12 +960,24 @@ bool use_big_tile(int32_t M, int32_t N) {
     return ceil_div(M, 256) * ceil_div(N, 256) >= 192;
 }
 
+// Products of few tiles go to the kernel with 32 x 32 tiles and K split over a workgroup's wavefronts (small.hip).  Its time
+// grows with its tiles, the general kernel's with its rounds of 128 x 128 tiles; they meet at about 2048 small tiles per
+// round in fp32 (1024 x 2048 x 1024: 86.3 us against 88.4; 300 x 8000 x 512: 58.1 against 49.0) and 768 in bf16, whose
+// matrix instructions take a sixteenth of the time so that the unshared operand reads count (1024 x 1024 x 256: 6.7 us
+// against 8.8; 24 x 32000 x 1000: 21.1 against 20.5; 300 x 8000 x 512: 25.0 against 13.6).
+bool use_small_tile(int32_t dtype, int32_t M, int32_t N) {
+    const int64_t rounds = ceil_div(ceil_div(M, 128) * ceil_div(N, 128), 256);
+    return ceil_div(M, 32) * ceil_div(N, 32) <= rounds * (dtype == ATTS_DTYPE_F32 ? 2048 : 768);
+}
+
 // The aligned bf16 kernel serves every call it can (its DMA ring also streams weights well when the tiles are
 // few); everything else goes to the general kernel.
 template <typename T, int EPI>
 int32_t launch_epi(const GemmArgs& g, hipStream_t stream) {
-    if (sizeof(T) == 2 && fast_path_ok(ATTS_DTYPE_BF16, EPI, g)) return launch_fast<EPI>(g, stream);
+    constexpr int32_t dtype = sizeof(T) == 2 ? ATTS_DTYPE_BF16 : ATTS_DTYPE_F32;
+    if (fast_path_ok(dtype, EPI, g)) return launch_fast<EPI>(g, stream);
     int32_t n_cols = (EPI == EPI_SWIGLU) ? 2 * g.N : g.N;
+    if (EPI != EPI_PARTIAL_F32 && use_small_tile(dtype, g.M, n_cols)) return launch_gemm_small(dtype, (GemmEpilogue)EPI, g, stream);
     if (use_big_tile(g.M, n_cols)) return launch_cfg<T, 256, 256, EPI>(g, stream);
     return launch_cfg<T, 128, 128, EPI>(g, stream);
 }
@@ -1023,7 +1036,9 @@ int32_t lmhead_num_partials(int32_t dtype, int32_t M, int32_t N, int32_t Kd, boo
     if (lmhead_exchanged_ok(dtype, M, N, Kd, Kd, Kd)) return N / 384 * 4;
     GemmArgs g{};
     g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
-    const int bn = (fast_path_ok(dtype, EPI_LMHEAD, g) || use_big_tile(M, N)) ? 256 : 128;
+    const bool fast = fast_path_ok(dtype, EPI_LMHEAD, g);
+    if (!fast && use_small_tile(dtype, M, N)) return small_lmhead_partials(N);
+    const int bn = (fast || use_big_tile(M, N)) ? 256 : 128;
     return (int32_t)ceil_div(N, bn) * 2;
 }
 int32_t lmhead_max_partials(int32_t N) { return (int32_t)ceil_div(N, 128) * 2; }

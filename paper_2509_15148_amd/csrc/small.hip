@@ -1,0 +1,195 @@
+// NT GEMM for products too small to fill the chip with 128 x 128 tiles:  acc[M, N] = A[M, Kd] . W[N, Kd]^T.
+//
+// A small model's projections (the fp32 one: 320 rows, 128 to 512 features) are 3 to 24 tiles of the general kernel, each
+// walking the whole K range by itself: what bounds them is the chain of matrix instructions of one wavefront (an fp32
+// 32 x 32 x 2 step occupies the matrix pipe for 64 cycles, 64 of them per 32-deep slab of a 64 x 64 wave tile), while most
+// compute units idle.  Here a workgroup of four wavefronts owns one 32 x 32 tile (32 x 64 for SwiGLU and the LM head) and
+// the four split its K range, each in a contiguous quarter:
+//   * operands go global -> registers (16 bytes per lane and step, A and W rows alike; the operands of such products sit
+//     in the L2s), kSmallUnroll steps requested ahead of their matrix instructions, two buffers; no LDS, no barrier in
+//     the loop;
+//   * the four partial sums meet once in LDS and are added in wavefront order (no atomics: bit-reproducible).
+// Against 128 x 128 tiles: fp32 320 x 128 x 512 45.3 -> 7.1 us, 320 x 512 x 128 15.3 -> 3.7, 1024 x 512 x 512 45.6 -> 13.4,
+// 64 x 4096 x 4096 330 -> 35; bf16 320 x 512 x 512 11.7 -> 4.4.  The scoring pass of the fp32 model (2 layers, 320 rows):
+// 267 -> 104 us.
+#include "common.h"
+
+namespace atts {
+namespace {
+
+constexpr int kSmallWaves = 4;
+constexpr int kSmallUnroll = 4;
+
+struct SmallDims {
+    int32_t M, N, Kd;
+    int64_t lda, ldw, ldc;
+    int32_t n_part, nt_m;
+};
+
+// One step: lane (row = l % 32, half = l / 32) holds 16 bytes of its row, at byte 32 step + 16 half.  bf16: the operand of
+// one 32 x 32 x 16 product.  fp32: four floats = four 32 x 32 x 2 products (the k order inside a step is permuted alike for
+// both operands, which leaves the dot product unchanged).
+template <typename T> struct SmallMma;
+template <> struct SmallMma<bf16> {
+    static __device__ __forceinline__ void mma(const uint4& a, const uint4& w, f32x16& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, w), c, 0, 0, 0);
+    }
+};
+template <> struct SmallMma<float> {
+    static __device__ __forceinline__ void mma(const uint4& a, const uint4& w, f32x16& c) {
+        const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, w);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], c, 0, 0, 0);
+    }
+};
+
+template <typename T, int EPI, int NI>
+__global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char* __restrict__ gA, const char* __restrict__ gW,
+                                                                      void* __restrict__ g_out, const int32_t* __restrict__ g_targets,
+                                                                      float2* __restrict__ g_partials, float* __restrict__ g_target_logit,
+                                                                      const SmallDims d) {
+    constexpr int ES = (int)sizeof(T), N_OUT = EPI == EPI_SWIGLU ? 32 : 32 * NI;
+    static_assert((EPI == EPI_SWIGLU || EPI == EPI_LMHEAD) == (NI == 2), "tile width");
+    __shared__ float part[kSmallWaves][NI][16][64];
+    const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));    // scalar: the K loop's branches must be too
+    const int tm = (int)blockIdx.x % d.nt_m, tn = (int)blockIdx.x / d.nt_m;
+    const int m0 = tm * 32, n0 = tn * N_OUT;
+
+    // rows and columns past the end repeat the last one (their results are dropped); 16-byte pieces past the end are zero
+    const char* ap = gA + (int64_t)min(m0 + l32, d.M - 1) * d.lda * ES + 16 * half;
+    const char* wp[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int row = EPI == EPI_SWIGLU ? min(n0 + l32, d.N - 1) + j * d.N : min(n0 + 32 * j + l32, d.N - 1);
+        wp[j] = gW + (int64_t)row * d.ldw * ES + 16 * half;
+    }
+    const int k_bytes = d.Kd * ES;
+    const int n_steps = (k_bytes + 31) / 32;
+    const int s0 = wave * n_steps / kSmallWaves, s1 = (wave + 1) * n_steps / kSmallWaves;
+    struct Frags {
+        uint4 a[kSmallUnroll], w[NI][kSmallUnroll];
+    };
+    auto load = [&](Frags& f, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kSmallUnroll; ++u) {
+            const int64_t off = (int64_t)(s + u) * 32;
+            const bool ok = s + u < s1 && off + 16 * half < k_bytes;
+            f.a[u] = ok ? *reinterpret_cast<const uint4*>(ap + off) : make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) f.w[j][u] = ok ? *reinterpret_cast<const uint4*>(wp[j] + off) : make_uint4(0, 0, 0, 0);
+        }
+    };
+    f32x16 acc[NI];
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    auto mma = [&](const Frags& f) __attribute__((always_inline)) {      // steps past the end multiply zeros
+#pragma unroll
+        for (int u = 0; u < kSmallUnroll; ++u)
+#pragma unroll
+            for (int j = 0; j < NI; ++j) SmallMma<T>::mma(f.a[u], f.w[j][u], acc[j]);
+    };
+    Frags fa, fb;
+    load(fa, s0);
+    for (int s = s0; s < s1; s += 2 * kSmallUnroll) {
+        load(fb, s + kSmallUnroll);
+        mma(fa);
+        if (s + kSmallUnroll < s1) {                                        // scalar
+            load(fa, s + 2 * kSmallUnroll);
+            mma(fb);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) part[wave][j][v][lane] = acc[j][v];
+    __syncthreads();
+
+    // wavefront w finishes entries v = 4 w .. 4 w + 3 of every block: rows m0 + 8 w + 4 half + (v & 3), column l32
+    float z[NI][4];
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            float s = part[0][j][4 * wave + b][lane];
+#pragma unroll
+            for (int w = 1; w < kSmallWaves; ++w) s += part[w][j][4 * wave + b][lane];
+            z[j][b] = s;
+        }
+    const int row0 = m0 + 8 * wave + 4 * half, col = n0 + l32;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        const int row = row0 + b;
+        if constexpr (EPI == EPI_LMHEAD) {
+            const bool row_ok = row < d.M;                                  // uniform over the 32 lanes that share `half`
+            const int tcol = row_ok ? g_targets[row] - n0 : -1;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int j = 0; j < NI; ++j) {
+                if (col + 32 * j < d.N) mx = fmaxf(mx, z[j][b]);
+                if (tcol == 32 * j + l32) g_target_logit[row] = z[j][b];
+            }
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+            float sum = 0.f;
+            if (mx > -INFINITY) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+                    if (col + 32 * j < d.N) sum += __expf(z[j][b] - mx);
+            }
+#pragma unroll
+            for (int o = 1; o < 32; o <<= 1) sum += __shfl_xor(sum, o);
+            if (row_ok && l32 == 0) g_partials[(int64_t)row * d.n_part + tn] = make_float2(mx, sum);
+        } else {
+            if (row >= d.M || col >= d.N) continue;
+            const int64_t idx = (int64_t)row * d.ldc + col;
+            if constexpr (EPI == EPI_SWIGLU) {
+                const float gate = z[0][b], up = z[1][b];
+                // hardware reciprocal, as in the tiled kernels
+                reinterpret_cast<T*>(g_out)[idx] = from_f32<T>(gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate)) * up);
+            } else if constexpr (EPI == EPI_STORE_ACT) {
+                reinterpret_cast<T*>(g_out)[idx] = from_f32<T>(z[0][b]);
+            } else if constexpr (EPI == EPI_RESID_F32) {
+                float* p = reinterpret_cast<float*>(g_out) + idx;
+                *p = *p + z[0][b];
+            } else {
+                reinterpret_cast<float*>(g_out)[idx] = z[0][b];
+            }
+        }
+    }
+}
+
+template <typename T, int EPI>
+int32_t launch_small_epi(const GemmArgs& g, hipStream_t stream) {
+    constexpr int NI = EPI == EPI_SWIGLU || EPI == EPI_LMHEAD ? 2 : 1, N_OUT = EPI == EPI_LMHEAD ? 64 : 32;
+    SmallDims d{g.M, g.N, g.Kd, g.lda, g.ldw, g.ldc, g.n_part, (int32_t)ceil_div(g.M, 32)};
+    hipLaunchKernelGGL((gemm_small_kernel<T, EPI, NI>), dim3((unsigned)(d.nt_m * ceil_div(g.N, N_OUT))), dim3(64 * kSmallWaves), 0, stream,
+                       reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), g.out, g.targets, g.partials, g.target_logit, d);
+    ATTS_LAUNCH_CHECK("gemm_small_kernel");
+    return ATTS_OK;
+}
+
+template <typename T>
+int32_t launch_small_t(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
+    switch (epi) {
+        case EPI_STORE_ACT: return launch_small_epi<T, EPI_STORE_ACT>(g, stream);
+        case EPI_STORE_F32: return launch_small_epi<T, EPI_STORE_F32>(g, stream);
+        case EPI_RESID_F32: return launch_small_epi<T, EPI_RESID_F32>(g, stream);
+        case EPI_SWIGLU: return launch_small_epi<T, EPI_SWIGLU>(g, stream);
+        case EPI_LMHEAD: return launch_small_epi<T, EPI_LMHEAD>(g, stream);
+        default: break;
+    }
+    return fail(ATTS_ERR_INVALID_ARG, "gemm (small product): epilogue %d is not served", (int)epi);
+}
+
+}  // namespace
+
+int32_t small_lmhead_partials(int32_t N) { return (int32_t)ceil_div(N, 64); }
+
+int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
+    return dtype == ATTS_DTYPE_F32 ? launch_small_t<float>(epi, g, stream) : launch_small_t<bf16>(epi, g, stream);
+}
+
+}  // namespace atts

@@ -40,6 +40,50 @@ def test_gemm_nt_matches_float64_matmul(dtype, shape):
     assert np.allclose(c.cpu().numpy(), ref, rtol=1e-5, atol=2e-5 * math.sqrt(Kd))
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", [
+    (31, 33, 8), (32, 32, 16), (33, 65, 24), (64, 96, 40), (20, 31, 136),      # edges of 32 x 32 tiles; K from one step to ragged quarters
+    (1024, 768, 72), (1024, 769, 72),                                          # bf16: 768 small tiles, and one column of tiles more
+    (1024, 2048, 72), (1024, 2049, 72),                                        # fp32: 2048 small tiles, and more: 128 x 128 tiles
+    (130, 33000, 40), (17, 66000, 24)])                                        # two and three rounds of 128 x 128 tiles
+def test_gemm_small_products(dtype, shape):
+    """Shapes at the edges of the kernel for products of few tiles and of the rule that chooses it, against the float64
+    product.  Bound: a sum of K products rounds at most K times to 2^-24 of its absolute sum (here a few per cent of that)."""
+    import paper_2509_15148_amd as A
+    M, N, Kd = shape
+    announce("gemm small", dtype, shape)
+    a, w = _rand((M, Kd), 51, dtype), _rand((N, Kd), 52, dtype)
+    c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_gemm_nt(a.cuda(), w.cuda(), c)
+    torch.cuda.synchronize()
+    ref = a.double().numpy() @ w.double().numpy().T
+    bound = Kd * 2.0 ** -24 * (np.abs(a.double().numpy()) @ np.abs(w.double().numpy()).T) + 1e-30
+    assert (np.abs(c.cpu().numpy() - ref) <= bound).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", [(1, 8, 1), (32, 40, 64), (33, 24, 65), (70, 72, 6145), (300, 72, 9001)])
+def test_lmhead_small_products(dtype, shape):
+    """The LM head where its product has few tiles: row and vocabulary counts at the edges of 32 x 64 tiles, and a
+    vocabulary that takes larger tiles.  The logits are sums of K products (error at most K 2^-24 of their absolute sum)
+    and the log-sum-exp adds a few roundings of values below 2^4."""
+    import paper_2509_15148_amd as A
+    B, d, V = shape
+    announce("lmhead small", dtype, shape)
+    x, w = _rand((B, d), 61, dtype, scale=2.0), _rand((V, d), 62, dtype, scale=4.0 / math.sqrt(d))
+    tgt = torch.from_numpy(np.random.default_rng(4).integers(0, V, B).astype(np.int32))
+    tgt[0], tgt[-1] = V - 1, 0
+    lp = torch.full((B,), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_lmhead_logprobs(x.cuda(), w.cuda(), tgt.cuda(), lp, ws(A.atts_lmhead_workspace_bytes(B, V)))
+    lp2 = torch.full((B,), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_lmhead_logprobs_static(x.cuda(), w.cuda(), tgt.cuda(), lp2)
+    torch.cuda.synchronize()
+    ref = torch.log_softmax(x.double() @ w.double().t(), dim=-1).gather(1, tgt.long()[:, None])[:, 0].numpy()
+    most = float((x.double().abs() @ w.double().abs().t()).max())
+    assert (np.abs(lp.cpu().numpy() - ref) <= 2 * d * 2.0 ** -24 * most + 32 * 2.0 ** -20).all()
+    assert torch.equal(lp, lp2)
+
+
 def test_gemm_aligned_last_tile_rows_in_a_second_launch():
     """27 x 38 tiles of 384 x 256 = 1026 = four rounds of 256 and two tiles over: the aligned bf16 path gives the last
     tile row to a launch of its own with 128-row tiles (26 x 38 = 988 tiles in four rounds, then 384 rows as 114 small
