@@ -160,7 +160,7 @@ __device__ __forceinline__ void start_accumulators(f32x16 (&acc)[MI][NI], int m0
 // address each element as a wave-uniform base (scalar arithmetic) plus one 32-bit lane offset: the checked form costs
 // about 25 instructions and a branch or two per element, which at 96 - 192 elements per lane and tile was a tenth of the
 // gate/up tile's time with the matrix pipe idle.
-template <typename T, int MI, int NI, int EPI, bool kWide = false>
+template <typename T, int MI, int NI, int EPI, bool kWide = false, bool kRaggedB = false>
 __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0, int n0, int wm, int wn, int l32, int half,
                                                    int tn, void* __restrict__ g_out, const int32_t* __restrict__ g_targets,
                                                    float2* __restrict__ g_partials, float* __restrict__ g_target_logit,
@@ -365,7 +365,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0
         const int vrow0 = m0 + wm * WM + 4 * half;     // every vocabulary row of the tile exists (whole tiles, checked on the host)
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
-            const int col = n0 + wn * WN + 32 * j + l32;              // scoring row; < g.N (whole tiles too)
+            const int col = n0 + wn * WN + 32 * j + l32;              // scoring row; < g.N unless kRaggedB
             float mx = acc[0][j][0];
 #pragma unroll
             for (int i = 0; i < MI; ++i)
@@ -379,7 +379,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0
             // The target's vocabulary entry relative to this lane's first one: the lane holds entries 32 i + 8 a + b
             // (b < 4).  Only about one wave in twelve holds any of its 128 scoring rows' targets, so the selection of the
             // accumulator entry sits behind a branch that is mostly not taken.
-            const int trel = g_targets[col] - vrow0;
+            const int trel = !kRaggedB || col < g.N ? g_targets[col] - vrow0 : -1;
             if (trel >= 0 && trel < WM && (trel & 4) == 0) {
                 const int ti = trel >> 5, tv = ((trel >> 3) & 3) * 4 + (trel & 3);
                 float z = 0.f;
@@ -394,8 +394,64 @@ __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0
             const float m = fmaxf(mx, mx_o);
             float tot = 0.f;
             if (m > -INFINITY) tot = sum * __expf(mx - m) + sum_o * __expf(mx_o - m);   // a half with no entry: 0 * exp(-inf) = 0
-            if (half == 0) g_partials[(int64_t)col * g.n_part + part] = make_float2(m, tot);
+            if (half == 0 && (!kRaggedB || col < g.N)) g_partials[(int64_t)col * g.n_part + part] = make_float2(m, tot);
         }
+    }
+}
+
+// EPI_LMHEAD_T with any number of scoring rows (columns; those past g.N are dropped) and one partial per row and tile: the
+// wavefronts that share columns merge theirs in LDS (free by now), in wavefront order.
+template <int MI, int NI>
+__device__ __forceinline__ void lmhead_tile_epilogue(f32x16 (&acc)[MI][NI], int m0, int n0, int wm, int wn, int l32, int half,
+                                                     char* smem, const int32_t* __restrict__ g_targets,
+                                                     float2* __restrict__ g_partials, float* __restrict__ g_target_logit,
+                                                     const GemmDims& g) {
+    constexpr int WM = 32 * MI, WN = 32 * NI, BN = 2 * WN, kWm = 4;
+    float2* red = reinterpret_cast<float2*>(smem);                    // [kWm][BN] (max, sum of exponentials)
+    const int vrow0 = m0 + wm * WM + 4 * half;
+    block_barrier();                                                  // every wave is through with the last slab
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+        const int c = wn * WN + 32 * j + l32, col = n0 + c;
+        float mx = acc[0][j][0];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int v = (i == 0 ? 1 : 0); v < 16; ++v) mx = fmaxf(mx, acc[i][j][v]);
+        mx = fmaxf(mx, __shfl_xor(mx, 32));                           // the other half of the lane pair: the rows in between
+        float sum = 0.f;
+        if (mx > -INFINITY) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) sum += __expf(acc[i][j][v] - mx);
+        }
+        sum += __shfl_xor(sum, 32);
+        // the target's vocabulary entry relative to this lane's first one: the lane holds entries 32 i + 8 a + b (b < 4)
+        const int trel = col < g.N ? g_targets[col] - vrow0 : -1;
+        if (trel >= 0 && trel < WM && (trel & 4) == 0) {
+            const int ti = trel >> 5, tv = ((trel >> 3) & 3) * 4 + (trel & 3);
+            float z = 0.f;
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) z = (ti == i && tv == v) ? acc[i][j][v] : z;
+            g_target_logit[col] = z;
+        }
+        if (half == 0) red[wm * BN + c] = make_float2(mx, sum);
+    }
+    __syncthreads();
+    const int c = threadIdx.x;
+    if (c < BN && n0 + c < g.N) {
+        float mx = red[c].x;
+#pragma unroll
+        for (int w = 1; w < kWm; ++w) mx = fmaxf(mx, red[w * BN + c].x);
+        float sum = 0.f;
+        if (mx > -INFINITY) {
+#pragma unroll
+            for (int w = 0; w < kWm; ++w) sum += red[w * BN + c].y * __expf(red[w * BN + c].x - mx);
+        }
+        g_partials[(int64_t)(n0 + c) * g.n_part + m0 / (kWm * WM)] = make_float2(mx, sum);
     }
 }
 
@@ -528,7 +584,10 @@ __global__ __launch_bounds__(kThreads) void gemm_nt_kernel(const char* __restric
 // a 384 x 256 tile.  A slab is four MFMA k-steps; the DMA of the following slabs is issued under the first two
 // (under the first alone with two stages), one wait + barrier per slab at its end.
 // ---------------------------------------------------------------------------------------------
-template <int EPI, int kWavesM, int MI, int NI = 4 /* 32-column blocks per wave: 4 = 256-column tiles, 2 = 128-column tiles */>
+// kRaggedB: any number of W rows (the last column tile is partly filled; its missing rows repeat existing ones and their
+// columns are dropped).
+template <int EPI, int kWavesM, int MI, int NI = 4 /* 32-column blocks per wave: 4 = 256-column tiles, 2 = 128-column tiles */,
+          bool kRaggedB = false>
 __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const char* __restrict__ gA,
                                                                        const char* __restrict__ gW,
                                                                        void* __restrict__ g_out,
@@ -545,8 +604,8 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
     constexpr int ROWS_PER_DMA = 1024 / BKB;                     // 8
     constexpr int DMA_A = BM / ROWS_PER_DMA / kWaves, DMA_B = BN / ROWS_PER_DMA / kWaves;
     static_assert(DMA_A % 2 == 0 && DMA_B % 2 == 0, "the swizzle parity of a DMA instruction must not depend on the wave");
-    constexpr bool kDeep = BM == 256;                            // five-unit ring, A two slabs ahead
-    constexpr int kStages = BM == 128 ? 3 : 2;                   // whole-slab stages otherwise (160 KB of LDS)
+    constexpr bool kDeep = BM == 256 && BN == 256;               // five-unit ring, A two slabs ahead
+    constexpr int kStages = BM == 384 ? 2 : 3;                   // whole-slab stages otherwise (at most 160 KB of LDS)
     constexpr int UNIT_A = BM * BKB, UNIT_B = BN * BKB;
     static_assert(!kDeep || UNIT_A == UNIT_B, "ring units must have one size");
 
@@ -567,7 +626,7 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
     // the first slab of the next tile under the last slab of the current one, so that the DMA ring never runs dry at a
     // tile boundary and the epilogue's stores overlap that request.  (The host launches one workgroup per CU then;
     // with a grid of n_tiles workgroups the loop body runs once.)
-    constexpr bool kTileLoop = !kDeep && kStages == 2;
+    constexpr bool kTileLoop = MI == 3;
     // Tile rows per group of the XCD-aware order.  The one-round calls of the 256-row tile do better with taller groups
     // (an XCD then touches fewer W columns, which come cold from HBM, at the price of more A rows, which the Infinity
     // Cache holds): O projection at 7B 3.79 -> 3.66 ms per step with 12 against 8, the other shapes within 0.5 %.
@@ -585,6 +644,8 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
     uint32_t a_lane_off[2], b_lane_off[2];
     const char* a_base[DMA_A];
     const char* b_base[DMA_B];
+    int b_split = -1;           // kRaggedB: this wave's instruction whose eight rows reach past the last W row, and what takes
+    uint32_t b_back = 0;        // its lanes back to that row
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         const int sw = (4 * p + (dq >> 1)) & 7;
@@ -604,6 +665,19 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
                 const int jw = r0 / WN, jj = r0 % WN;
                 wrow = (int64_t)(jj / H) * g.N + jw * H + jj % H;
             }
+            if (kRaggedB) {
+                if (j == 0) b_split = -1;
+                const int last = g.N - 1 - (n0 + r0);                 // offset of the last W row from this instruction's first
+                if (g.N < 8) {                                        // every instruction reads rows 0 .. N - 1
+                    wrow = -n0;
+                    b_back = (uint32_t)(dq - min(dq, g.N - 1)) * (uint32_t)(g.ldw * 2);
+                } else if (last < 0) {                                // all past the end: any eight rows will do
+                    wrow = g.N - 8 - n0;
+                } else if (last < 7) {
+                    b_split = j;
+                    b_back = (uint32_t)(dq - min(dq, last)) * (uint32_t)(g.ldw * 2);
+                }
+            }
             b_base[j] = gW + (n0 + wrow) * g.ldw * 2;
         }
     };
@@ -622,7 +696,7 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
         char* dst = smem + b_slot(k);
 #pragma unroll
         for (int j = 0; j < DMA_B; ++j)
-            __builtin_amdgcn_global_load_lds(ATTS_GPTR(b_base[j] + b_lane_off[j & 1]),
+            __builtin_amdgcn_global_load_lds(ATTS_GPTR(b_base[j] + (b_lane_off[j & 1] - (kRaggedB && (j == b_split || g.N < 8) ? b_back : 0u))),
                                              ATTS_LPTR(dst + (wave * DMA_B + j) * 1024), 16, 0, 0);
         b_lane_off[0] += BKB;
         b_lane_off[1] += BKB;
@@ -788,8 +862,11 @@ __global__ __launch_bounds__(128 * kWavesM) void gemm_bf16_wide_kernel(const cha
         // not hoisted out of the tile loop (it would sit in registers all through the main loop)
         int l32_e = l32, half_e = half;
         if (kTileLoop) asm volatile("" : "+v"(l32_e), "+v"(half_e));
-        gemm_epilogue_impl<bf16, MI, NI, EPI, true>(acc, m0, n0, wm, wn, l32_e, half_e, tn, out, g_targets, g_partials, g_target_logit,
-                                              g_rope, g_vt, g);
+        if constexpr (EPI == EPI_LMHEAD_T && !kTileLoop)
+            lmhead_tile_epilogue<MI, NI>(acc, m0, n0, wm, wn, l32_e, half_e, smem, g_targets, g_partials, g_target_logit, g);
+        else
+            gemm_epilogue_impl<bf16, MI, NI, EPI, true, kRaggedB>(acc, m0, n0, wm, wn, l32_e, half_e, tn, out, g_targets, g_partials, g_target_logit,
+                                                  g_rope, g_vt, g);
         if (!(kTileLoop && more)) break;
         start_accumulators<MI, NI, EPI, true>(acc, tc.tm * BM, tc.tn * N_OUT, wm, wn, l32_e, half_e, g_out, g);
     }
@@ -852,7 +929,7 @@ int32_t device_cu_count(int* out) {
     return ATTS_OK;
 }
 
-template <int EPI, int MI, int NI = 4>
+template <int EPI, int MI, int NI = 4, bool kRaggedB = false>
 int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
     constexpr int n_out = (EPI == EPI_SWIGLU) ? 32 * NI : 64 * NI;
     constexpr int BM = kWavesM * MI * 32;
@@ -863,11 +940,11 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
     d.ldv = g.ldv;
     d.n_rot_heads = g.n_rot_heads;
     d.nt_m = (int)ceil_div(g.M, BM);
-    d.nt_n = g.N / n_out;
+    d.nt_n = (int)ceil_div(g.N, n_out);     // whole tiles, except the columns of the exchanged LM head
     d.k_slices = fast_k_slices(EPI, d.nt_m * d.nt_n, g.Kd / 64);
     d.slice_pitch = (int64_t)g.M * g.ldc;
     const size_t lds = 160 * 1024;
-    ATTS_TRY_RC((allow_dynamic_lds<gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI>>(lds)));
+    ATTS_TRY_RC((allow_dynamic_lds<gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI, kRaggedB>>(lds)));
     // 384-row tiles without a K split: one workgroup per CU (a workgroup takes a CU's whole LDS), each walking
     // every n_cu-th tile with the next tile's first slab requested under the current tile's last
     int grid = d.nt_m * d.nt_n * d.k_slices;
@@ -879,7 +956,7 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
         if (n_cu >= 8 && grid > n_cu) grid = n_cu;
         d.round = grid;
     }
-    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI>), dim3(grid), dim3(128 * kWavesM), lds, stream,
+    hipLaunchKernelGGL((gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI, kRaggedB>), dim3(grid), dim3(128 * kWavesM), lds, stream,
                        reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), g.out, g.targets, g.partials,
                        g.target_logit, g.rope, g.vt, d);
     ATTS_LAUNCH_CHECK("gemm_bf16_wide_kernel");
@@ -1024,16 +1101,32 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 
 }  // namespace
 
-// The LM head with the operands exchanged: the vocabulary tiles exactly by 384 rows and the scoring rows by 256 columns.
-// No row of padding is computed (4096 scoring rows are 10.67 tiles of 384 in the other orientation), the tile count drops
-// (7B: 6336 instead of 6534, 25 rounds instead of 26) and the epilogue reduces inside the lanes.
-static bool lmhead_exchanged_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw) {
-    return dtype == ATTS_DTYPE_BF16 && N % 384 == 0 && M % 256 == 0 && Kd % kWideBK == 0 && Kd >= kMinSlabs * kWideBK &&
-           lda * 2 * 17 < (1ll << 31) && ldw * 2 * 17 < (1ll << 31);
+// The LM head with the operands exchanged: vocabulary entries are the rows of the tiles, scoring rows (any number, read in
+// place without padding) their columns; the epilogue reduces inside the lanes.
+//   more than 128 scoring rows: 384 x 256 tiles, vocabulary a multiple of 384.  No row of padding is computed in the
+//       long direction (4096 scoring rows are 10.67 tiles of 384 in the other orientation) and the tile count drops (7B: 6336
+//       instead of 6534, 25 rounds instead of 26).  Rows that the caller has not padded (385 of 152,064 x 3584): 503 us
+//       against 825 with the general kernel; padded ones 519 against 558 with 256 x 256 tiles the other way round (1397:
+//       1262 against 1441).  257 to 384 padded rows stay one row of 384 x 256 tiles: 482 against 517 for two columns of
+//       tiles (70B head, 381 rows: 748 against 889).
+//   up to 128: 256 x 128 tiles, vocabulary a multiple of 256.  Bound by the vocabulary matrix streaming by once: three
+//       stages of 48 KB keep 96 KB a CU in flight.  64 rows of 152,064 x 3584 217 us (5.0 TB/s; general kernel
+//       484), 128 rows 226 (unpadded: 496; padded, 128 x 256 tiles the other way round: 248).  128 x 128 tiles, two
+//       workgroups a CU, read the scoring rows twice as often: 229 and 256.
+static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw) {
+    return dtype == ATTS_DTYPE_BF16 && Kd % kWideBK == 0 && Kd >= kMinSlabs * kWideBK && lda * 2 * 17 < (1ll << 31) && ldw * 2 * 17 < (1ll << 31);
+}
+static bool lmhead_exchanged_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw, bool a_rows_padded) {
+    if (a_rows_padded && M > 256 && M <= 384) return false;
+    return N % 384 == 0 && M > 128 && lmhead_aligned_k(dtype, Kd, lda, ldw);
+}
+static bool lmhead_few_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw) {
+    return N % 256 == 0 && M > 0 && M <= 128 && lmhead_aligned_k(dtype, Kd, lda, ldw);
 }
 
 int32_t lmhead_num_partials(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded) {
-    if (lmhead_exchanged_ok(dtype, M, N, Kd, Kd, Kd)) return N / 384 * 4;
+    if (lmhead_few_ok(dtype, M, N, Kd, Kd, Kd)) return N / 256;
+    if (lmhead_exchanged_ok(dtype, M, N, Kd, Kd, Kd, a_rows_padded)) return N / 384 * 4;
     GemmArgs g{};
     g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
     const bool fast = fast_path_ok(dtype, EPI_LMHEAD, g);
@@ -1069,13 +1162,15 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
         return fail(ATTS_ERR_INVALID_ARG, "gemm: wrong partial count for the LM-head epilogue");
     if (epi == EPI_PARTIAL_F32 && g.n_slices != gemm_partial_slices(dtype, g.M, g.N, g.Kd, g.a_rows_padded))
         return fail(ATTS_ERR_INVALID_ARG, "gemm: wrong slice count for the partial-sum epilogue");
-    if (epi == EPI_LMHEAD && lmhead_exchanged_ok(dtype, g.M, g.N, g.Kd, g.lda, g.ldw)) {
+    const bool few = epi == EPI_LMHEAD && lmhead_few_ok(dtype, g.M, g.N, g.Kd, g.lda, g.ldw);
+    if (few || (epi == EPI_LMHEAD && lmhead_exchanged_ok(dtype, g.M, g.N, g.Kd, g.lda, g.ldw, g.a_rows_padded))) {
         if (!g.targets || !g.partials || !g.target_logit) return fail(ATTS_ERR_INVALID_ARG, "gemm: LM-head epilogue without its buffers");
         GemmArgs x = g;
         x.a = g.w; x.lda = g.ldw; x.M = g.N;
         x.w = g.a; x.ldw = g.lda; x.N = g.M;
         x.a_rows_padded = false;
-        return launch_wide_tile<EPI_LMHEAD_T, 3>(x, stream);
+        if (few) return launch_wide_tile<EPI_LMHEAD_T, 2, 2, true>(x, stream);
+        return x.N % 256 ? launch_wide_tile<EPI_LMHEAD_T, 3, 4, true>(x, stream) : launch_wide_tile<EPI_LMHEAD_T, 3>(x, stream);
     }
     if (epi == EPI_QKV_ROPE) {
         if (!qkv_rope_fusable(dtype, g.M, g.N, g.Kd, 128, g.a_rows_padded) || !g.rope || !g.vt || g.ldv < g.M || g.ldv % 4 ||

@@ -84,6 +84,28 @@ def test_lmhead_small_products(dtype, shape):
     assert torch.equal(lp, lp2)
 
 
+@pytest.mark.parametrize("B", [1, 7, 8, 9, 127, 128, 129, 255, 257, 300, 519])
+def test_lmhead_exchanged_takes_any_number_of_rows(B):
+    """Vocabulary entries as tile rows, scoring rows as columns read in place: one to 128 rows (128-column tiles) and more
+    (256-column tiles), the last column tile filled by one, seven and eight rows and all but one.  The scoring rows end
+    where their allocation does.  Bound as in test_lmhead_small_products."""
+    import paper_2509_15148_amd as A
+    d, V = 832, 2304
+    announce("lmhead exchanged rows", B)
+    x, w = _rand((B, d), 71, torch.bfloat16, scale=2.0), _rand((V, d), 72, torch.bfloat16, scale=4.0 / math.sqrt(d))
+    tgt = torch.from_numpy(np.random.default_rng(5).integers(0, V, B).astype(np.int32))
+    tgt[0], tgt[-1] = 0, V - 1
+    lp = torch.full((B + 8,), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_lmhead_logprobs(x.cuda(), w.cuda(), tgt.cuda(), lp[:B], ws(A.atts_lmhead_workspace_bytes(B, V)))
+    lp2 = torch.full((B,), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_lmhead_logprobs_static(x.cuda(), w.cuda(), tgt.cuda(), lp2)
+    torch.cuda.synchronize()
+    ref = torch.log_softmax(x.double() @ w.double().t(), dim=-1).gather(1, tgt.long()[:, None])[:, 0].numpy()
+    most = float((x.double().abs() @ w.double().abs().t()).max())
+    assert (np.abs(lp[:B].cpu().numpy() - ref) <= 2 * d * 2.0 ** -24 * most + 32 * 2.0 ** -20).all()
+    assert torch.equal(lp[:B], lp2) and torch.isnan(lp[B:]).all()
+
+
 def test_gemm_aligned_last_tile_rows_in_a_second_launch():
     """27 x 38 tiles of 384 x 256 = 1026 = four rounds of 256 and two tiles over: the aligned bf16 path gives the last
     tile row to a launch of its own with 128-row tiles (26 x 38 = 988 tiles in four rounds, then 384 rows as 114 small
