@@ -890,26 +890,81 @@ bool fast_path_ok(int32_t dtype, int epi, const GemmArgs& g) {
            g.Kd >= kMinSlabs * kWideBK && g.lda * 2 * 17 < (1ll << 31) && g.ldw * 2 * 17 < (1ll << 31);
 }
 
-// Tile height of the aligned kernel: 384-row tiles move 1/6 fewer operand bytes per flop through L2 -> LDS than
-// 256-row ones and are taken when they do not cost whole extra rounds of workgroups over the 256 CUs.
-int fast_tile_rows(int epi, const GemmArgs& g) {
-    const int n_out = epi == EPI_SWIGLU ? 128 : 256;
-    if (g.M <= 128) return 128;                         // one half-height tile row: half the MFMA work per weight byte
-    if (!(g.M % 384 == 0 || g.a_rows_padded) || g.M <= 256) return 256;
-    const int64_t nt_n = g.N / n_out;
-    const int64_t t256 = ceil_div(g.M, 256) * nt_n, t384 = ceil_div(g.M, 384) * nt_n;
-    const int64_t cost256 = ceil_div(t256, 256) * 2, cost384 = ceil_div(t384, 256) * 3;   // rounds x tile height
-    return cost384 * 9 <= cost256 * 10 ? 384 : 256;   // a 384-row tile runs ~10 % closer to the MFMA peak
+// ---- tile shape and K split of an aligned call ----------------------------------------------------------------------
+// Time of one tile of the aligned kernel, in microseconds: a slab of 64 k elements takes 0.86 / 1.53 / 2.05 for 128 / 256 /
+// 384 rows of 256 W rows and 0.58 for 128 x 128, and about 5 go into start, first slabs and epilogue.  Fitted to QKV,
+// gate/up and down projections of the 7B and 70B widths at 200 to 1494 rows (K = 3584, 8192, 18944; within 10 %).  A launch
+// takes its rounds of 256 tiles; so the taller tile wins only where it does not add a partly filled round:
+//   7B QKV     774 rows  128-row tiles  57 us (126 tiles), 256-row  90, 384-row 126
+//   7B gate/up 516 rows  128-row tiles 174 us (3 rounds),  256-row 196, 384-row 250;  1094 rows 335, 305, 290
+double fast_tile_us(int rows, bool narrow, int64_t slabs) {
+    const double a = narrow ? 0.58 : (rows == 128 ? 0.86 : (rows == 256 ? 1.53 : 2.05));
+    return a * (double)slabs + 5.0;
+}
+bool tile_rows_allowed(int rows, const GemmArgs& g) {
+    if (rows == 128) return g.M % 128 == 0 || g.a_rows_padded;
+    if (rows == 256) return g.M > 128;                           // whole tiles or padded rows: fast_path_ok
+    return g.M > 256 && (g.M % 384 == 0 || g.a_rows_padded);
 }
 
-// K slices per tile for the partial-sum epilogue: when the tiles alone leave most of the chip idle (few rows and a
-// narrow output: the weight-streaming regime), the K range is cut so that about one workgroup per CU runs.
-int fast_k_slices(int epi, int n_tiles, int nk) {
-    if (epi != EPI_PARTIAL_F32 || n_tiles >= 128) return 1;
-    int s = 256 / n_tiles;                                   // never more workgroups than CUs: no second round
-    const int max_s = nk / 6;                                // every slice still walks several slabs
-    if (s > max_s) s = max_s;
-    return s < 1 ? 1 : s;
+struct TilePlan {
+    int rows, slices;        // slices > 1: partial sums per K slice (EPI_PARTIAL_F32; 128-row tiles are 128 columns wide there)
+    double us;
+    int head_m, tail_rows;   // tail_rows != 0: rows [0, head_m) in tiles of `rows`, the rest in a second launch of this height
+};
+
+// Tile height of a call without a K split.  A last round of 384-row tiles that would leave most CUs idle (32B-class O and
+// down projections: 1820 tiles = 7.1 rounds of 256) is avoided by giving the last tile rows to a second launch of smaller
+// tiles: 89 tile rows in 7 full rounds, then 640 rows as 100 tiles of 128 rows; 5 % faster there.
+TilePlan direct_plan(int epi, const GemmArgs& g) {
+    const int n_out = epi == EPI_SWIGLU ? 128 : 256;
+    const int64_t nt_n = g.N / n_out, slabs = g.Kd / kWideBK;
+    auto rounds_us = [&](int rows, int64_t m) {
+        return (double)ceil_div(ceil_div(m, rows) * nt_n, 256) * fast_tile_us(rows, false, slabs);
+    };
+    TilePlan best{};
+    for (int rows : {384, 256, 128}) {
+        if (!tile_rows_allowed(rows, g)) continue;
+        // the LM head's epilogue reduces every row across lanes: with 128-row tiles it would take a third of the time
+        if (rows == 128 && g.M > 128 && epi == EPI_LMHEAD) continue;
+        const double us = rounds_us(rows, g.M);
+        if (best.rows == 0 || us < best.us * 0.98) best = TilePlan{rows, 1, us, 0, 0};
+    }
+    if (epi == EPI_QKV_ROPE || g.M <= 384 || !tile_rows_allowed(384, g)) return best;     // its V^T output is not addressed by row alone
+    const int64_t nt_m = ceil_div(g.M, 384);
+    for (int drop = 1; drop <= 3 && drop < nt_m; ++drop)
+        for (int tail : {256, 128}) {
+            const int head_m = (int)(nt_m - drop) * 384;
+            // readable rows: the caller's, or up to the next multiple of 768
+            if (head_m + ceil_div(g.M - head_m, tail) * tail > (int64_t)(g.a_rows_padded ? align_up((size_t)g.M, 768) : (size_t)g.M)) continue;
+            const double us = rounds_us(384, head_m) + rounds_us(tail, g.M - head_m) + 4.0;     // a launch more
+            if (us < best.us * 0.96) best = TilePlan{384, 1, us, head_m, tail};
+        }
+    return best;
+}
+
+// Tile height and K slices per tile for the partial-sum epilogue: where the tiles alone leave most of the chip idle
+// (few rows, a narrow output), the K range is cut so that about one workgroup per CU runs; never more than CUs (no second
+// round), and every slice still walks several slabs.  Every slice's sums are written and read once more (at the 4.5 TB/s
+// a copy reaches), which at a few hundred rows weighs as much as the tiles: 7B O + down with their residual passes, 298 rows:
+// 128 x 128 tiles, 3 slices 96 us; 256 x 256, 9 slices 105.  70B, 774 rows: 256-row tiles, 2 slices, 443 us against 785
+// for the same 128 tiles unsplit.
+TilePlan partial_plan(const GemmArgs& g) {
+    const int64_t slabs = g.Kd / kWideBK;
+    const TilePlan none{0, 1, 0.0, 0, 0};
+    TilePlan best = none;
+    for (int rows : {384, 256, 128}) {
+        if (!tile_rows_allowed(rows, g)) continue;
+        const bool narrow = rows == 128;
+        const int64_t tiles = ceil_div(g.M, rows) * (g.N / (narrow ? 128 : 256));
+        int64_t s = 256 / tiles;
+        if (s > slabs / 6) s = slabs / 6;
+        if (s < 2) continue;
+        const double us = fast_tile_us(rows, narrow, ceil_div(slabs, s)) + (double)s * g.M * g.N * 8 / 4.5e6 + 4.0;
+        if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0};
+    }
+    if (best.rows == 0 || (g.M > 128 && direct_plan(EPI_RESID_F32, g).us < best.us)) return none;
+    return best;
 }
 
 // Compute units of the current device (asked once per device).
@@ -941,7 +996,7 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
     d.n_rot_heads = g.n_rot_heads;
     d.nt_m = (int)ceil_div(g.M, BM);
     d.nt_n = (int)ceil_div(g.N, n_out);     // whole tiles, except the columns of the exchanged LM head
-    d.k_slices = fast_k_slices(EPI, d.nt_m * d.nt_n, g.Kd / 64);
+    d.k_slices = EPI == EPI_PARTIAL_F32 ? g.n_slices : 1;
     d.slice_pitch = (int64_t)g.M * g.ldc;
     const size_t lds = 160 * 1024;
     ATTS_TRY_RC((allow_dynamic_lds<gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI, kRaggedB>>(lds)));
@@ -964,51 +1019,34 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
 }
 
 template <int EPI>
+int32_t launch_tile_rows(int rows, const GemmArgs& g, hipStream_t stream) {
+    if (rows == 128) return launch_wide_tile<EPI, 1>(g, stream);
+    return rows == 256 ? launch_wide_tile<EPI, 2>(g, stream) : launch_wide_tile<EPI, 3>(g, stream);
+}
+
+template <int EPI>
 int32_t launch_fast(const GemmArgs& g, hipStream_t stream) {
-    const int rows = fast_tile_rows(EPI, g);
-    if (rows == 128) {
-        // narrow outputs that split K: 128-column tiles double the tiles, so half as many K slices fill the chip
-        if constexpr (EPI == EPI_PARTIAL_F32) return launch_wide_tile<EPI, 1, 2>(g, stream);
-        return launch_wide_tile<EPI, 1>(g, stream);
+    if constexpr (EPI == EPI_PARTIAL_F32) {
+        const int rows = partial_plan(g).rows;
+        if (rows == 0) return fail(ATTS_ERR_SHAPE, "gemm: no K split for this shape");
+        return rows == 128 ? launch_wide_tile<EPI, 1, 2>(g, stream) : launch_tile_rows<EPI>(rows, g, stream);
     }
-    if (rows == 384) {
-        // A last round of tiles that would leave most CUs idle (32B-class O and down projections: 1820 tiles = 7.1 rounds
-        // of 256) is avoided by giving the last tile rows to a second launch with 128-row tiles: 89 tile rows in 7 full
-        // rounds, then 640 rows as 100 small tiles, each a third of the work.  Taken when the round count of the cost
-        // model (rounds x tile height, small tiles priced 40 % dearer per row) drops by 4 % or more.
-        constexpr bool kRowsShift = EPI != EPI_QKV_ROPE && EPI != EPI_PARTIAL_F32;   // outputs addressed by row alone
-        constexpr int n_out = (EPI == EPI_SWIGLU) ? 128 : 256;
-        const int64_t nt_n = g.N / n_out, nt_m = ceil_div(g.M, 384);
-        int best_h = 0;
-        if (kRowsShift && nt_m > 4) {
-            const double single = (double)ceil_div(nt_m * nt_n, 256) * 3;
-            double best = single * 0.96;
-            for (int drop = 1; drop <= 3; ++drop) {
-                const int64_t h = nt_m - drop, rem = g.M - h * 384;
-                const double c = (double)ceil_div(h * nt_n, 256) * 3 + (double)ceil_div(ceil_div(rem, 128) * nt_n, 256) * 1.4 + 0.05;
-                if (c < best) { best = c; best_h = (int)h; }
-            }
-        }
-        if (best_h > 0) {
-            GemmArgs head = g;
-            head.M = best_h * 384;
-            ATTS_TRY_RC((launch_wide_tile<EPI, 3>(head, stream)));
-            GemmArgs tail = g;
-            const int64_t r0 = head.M;
-            constexpr int64_t out_bytes = (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) ? 4 : 2;
-            tail.M = g.M - head.M;
-            tail.a = static_cast<const char*>(g.a) + r0 * g.lda * 2;
-            if (g.out) tail.out = static_cast<char*>(g.out) + r0 * g.ldc * out_bytes;
-            if (EPI == EPI_LMHEAD) {
-                tail.targets = g.targets + r0;
-                tail.partials = g.partials + r0 * g.n_part;
-                tail.target_logit = g.target_logit + r0;
-            }
-            return launch_wide_tile<EPI, 1>(tail, stream);
-        }
-        return launch_wide_tile<EPI, 3>(g, stream);
+    const TilePlan plan = direct_plan(EPI, g);
+    if (plan.tail_rows == 0) return launch_tile_rows<EPI>(plan.rows, g, stream);
+    GemmArgs head = g, tail = g;
+    head.M = plan.head_m;
+    ATTS_TRY_RC((launch_wide_tile<EPI, 3>(head, stream)));
+    const int64_t r0 = head.M;
+    constexpr int64_t out_bytes = (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) ? 4 : 2;
+    tail.M = g.M - head.M;
+    tail.a = static_cast<const char*>(g.a) + r0 * g.lda * 2;
+    if (g.out) tail.out = static_cast<char*>(g.out) + r0 * g.ldc * out_bytes;
+    if (EPI == EPI_LMHEAD) {
+        tail.targets = g.targets + r0;
+        tail.partials = g.partials + r0 * g.n_part;
+        tail.target_logit = g.target_logit + r0;
     }
-    return launch_wide_tile<EPI, 2>(g, stream);
+    return launch_tile_rows<EPI>(plan.tail_rows, tail, stream);
 }
 
 template <typename T, int BM, int BN, int EPI>
@@ -1107,8 +1145,9 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 //       long direction (4096 scoring rows are 10.67 tiles of 384 in the other orientation) and the tile count drops (7B: 6336
 //       instead of 6534, 25 rounds instead of 26).  Rows that the caller has not padded (385 of 152,064 x 3584): 503 us
 //       against 825 with the general kernel; padded ones 519 against 558 with 256 x 256 tiles the other way round (1397:
-//       1262 against 1441).  257 to 384 padded rows stay one row of 384 x 256 tiles: 482 against 517 for two columns of
-//       tiles (70B head, 381 rows: 748 against 889).
+//       1262 against 1441).  Padded rows take the other orientation where its rounds of tiles are fewer by more than the
+//       9 % its epilogue costs at least: 257 to 384 rows (one row of 384 x 256 tiles, 482 against 517; 70B head 748 against 889),
+//       196 rows of the 70B head (540 against 630), 1090 (1953 against 2136).
 //   up to 128: 256 x 128 tiles, vocabulary a multiple of 256.  Bound by the vocabulary matrix streaming by once: three
 //       stages of 48 KB keep 96 KB a CU in flight.  64 rows of 152,064 x 3584 217 us (5.0 TB/s; general kernel
 //       484), 128 rows 226 (unpadded: 496; padded, 128 x 256 tiles the other way round: 248).  128 x 128 tiles, two
@@ -1117,8 +1156,12 @@ static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw
     return dtype == ATTS_DTYPE_BF16 && Kd % kWideBK == 0 && Kd >= kMinSlabs * kWideBK && lda * 2 * 17 < (1ll << 31) && ldw * 2 * 17 < (1ll << 31);
 }
 static bool lmhead_exchanged_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw, bool a_rows_padded) {
-    if (a_rows_padded && M > 256 && M <= 384) return false;
-    return N % 384 == 0 && M > 128 && lmhead_aligned_k(dtype, Kd, lda, ldw);
+    if (N % 384 != 0 || M <= 128 || !lmhead_aligned_k(dtype, Kd, lda, ldw)) return false;
+    if (!a_rows_padded || N % 256 != 0) return true;                  // the other orientation would be the general kernel's
+    GemmArgs g{};
+    g.M = M; g.N = N; g.Kd = Kd; g.lda = lda; g.ldw = ldw; g.a_rows_padded = true;
+    const double us = (double)ceil_div(N / 384 * ceil_div(M, 256), 256) * fast_tile_us(384, false, Kd / kWideBK);
+    return us <= 1.09 * direct_plan(EPI_LMHEAD, g).us;
 }
 static bool lmhead_few_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw) {
     return N % 256 == 0 && M > 0 && M <= 128 && lmhead_aligned_k(dtype, Kd, lda, ldw);
@@ -1147,9 +1190,7 @@ int32_t gemm_partial_slices(int32_t dtype, int32_t M, int32_t N, int32_t Kd, boo
     g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
     if (gemm_skinny_ok(dtype, EPI_PARTIAL_F32, g)) return skinny_partial_slices(N, Kd);
     if (!fast_path_ok(dtype, EPI_PARTIAL_F32, g)) return 1;
-    const int bm = fast_tile_rows(EPI_PARTIAL_F32, g);
-    const int64_t tiles = ceil_div(M, bm) * (N / (bm == 128 ? 128 : 256));
-    return fast_k_slices(EPI_PARTIAL_F32, (int)tiles, Kd / 64);
+    return partial_plan(g).slices;
 }
 
 int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {

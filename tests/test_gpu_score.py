@@ -72,6 +72,24 @@ def test_small_models_ragged_shapes(cfg, P, K, T):
     assert np.array_equal(sc, sc2)
 
 
+@pytest.mark.parametrize("P,K,T", [(2, 1, 128), (44, 2, 128), (45, 3, 115), (8, 4, 128), (6, 3, 257), (160, 4, 250), (100, 6, 250)])
+def test_row_counts_between_tiles(P, K, T):
+    """130 to 1600 rows of an aligned bf16 model: the tile height of every projection (128, 256 or 384 rows), the K split of
+    the narrow ones and the orientation of the LM head (128 to 1500 scoring rows) follow from the rounds of tiles, and most
+    of these row counts end in a partly filled tile.  Repeated runs agree bit for bit."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(1, 1024, 8, 2, 128, 4096, 2304, "bf16")
+    announce("score rows", P, K, T)
+    w_dev, prefix, drafts = _case(cfg, P, K, T, seed=P * 1000 + K)
+    lp, sc, flag = _run_gpu(A, cfg, w_dev, prefix, drafts)
+    ref_lp, ref_s = O.score_drafts(weights_to_numpy(w_dev), cfg, prefix, drafts)
+    assert flag == 0
+    assert np.abs(lp - ref_lp).max() <= TOL["bf16"], np.abs(lp - ref_lp).max()
+    assert np.abs(sc - ref_s).max() <= TOL["bf16"]
+    _, sc2, _ = _run_gpu(A, cfg, w_dev, prefix, drafts, want_lp=False)
+    assert np.array_equal(sc, sc2)
+
+
 def test_variable_draft_lengths_and_padding_ids():
     import paper_2509_15148_amd as A
     cfg = ModelConfig(2, 256, 4, 2, 128, 512, 1000, "bf16")
