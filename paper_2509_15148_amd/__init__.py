@@ -15,6 +15,9 @@ def __getattr__(name):
     if _BINDING is None:
         _BINDING = importlib.import_module(".binding", __name__)
     try:
-        return getattr(_BINDING, name)
+        value = getattr(_BINDING, name)
     except AttributeError:
         raise AttributeError(f"module {__name__!r} has no attribute {name!r}") from None
+    if name.startswith(("atts_", "Atts", "ERR_", "SCORE_")) or name in ("Model", "Prefix", "Calib"):
+        globals()[name] = value         # entry points are looked up on every call: found directly from now on
+    return value

@@ -82,8 +82,13 @@ def _check(rc: int) -> None:
         raise AttsError(rc, _lib.atts_last_error_string().decode())
 
 
+# The current stream's handle without building a torch.cuda.Stream object for it: 0.4 us instead of 3.1, which is a third
+# of the host time of a short call (append + verdict of 16 scores: two calls whose kernels take 8 us together).
+_raw_stream = torch._C._cuda_getCurrentRawStream
+
+
 def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
 
 
 def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> ctypes.c_void_p:
