@@ -380,7 +380,7 @@ def atts_classify_conditional(cal_scores: torch.Tensor, cal_offsets: torch.Tenso
     if ranks.numel() != M or classes.numel() != M or (pvalues is not None and pvalues.numel() != M):
         raise AttsError(ERR_INVALID_ARG, "ranks / pvalues / classes must have one element per test score")
     arr = (ctypes.c_double * max(len(alphas), 1))(*[float(a) for a in alphas])
-    if n_inputs > 0:                       # the library wants non-NULL arrays; an empty tensor has no address
+    if n_inputs > 0 and (M == 0 or cal_scores.numel() == 0):    # the library wants non-NULL arrays; an empty tensor has no address
         spare = torch.zeros(1, dtype=torch.float32, device=cal_offsets.device)
         cal_scores = cal_scores if cal_scores.numel() else spare
         if M == 0:

@@ -69,6 +69,25 @@ def test_ragged_inputs_against_the_oracle(seed):
     assert p1 is None and np.array_equal(r1, r2) and np.array_equal(c1, c2)
 
 
+def test_set_sizes_around_the_held_blocks():
+    """Calibration sets at the edges of sixteen scores, of a 64-score block and of the four blocks held in registers, with
+    candidate counts at the edges of a block; NaN, infinities and zeros of both signs on both sides."""
+    import paper_2509_15148_amd as A
+    announce("conditional held blocks")
+    rng = np.random.default_rng(7)
+    m_sizes = [15, 16, 17, 48, 49, 79, 81, 192, 193, 255, 256, 257, 272, 320, 321]
+    k_sizes = [1, 63, 64, 65, 127, 128, 129, 2, 64, 65, 1, 130, 64, 3, 66]
+    special = np.array([np.nan, np.inf, -np.inf, -0.0, 0.0], np.float32)
+
+    def scores(n):
+        v = np.round(rng.lognormal(size=n), 2).astype(np.float32)
+        at = rng.permutation(n)[:len(special)]
+        v[at] = special[:len(at)]
+        return v
+    for alphas in ([0.25], [0.01, 0.05, 0.2, 0.3, 0.3, 0.5, 0.9, 0.99]):
+        _check(A, [scores(m) for m in m_sizes], [scores(k) for k in k_sizes], alphas)
+
+
 def test_many_small_inputs():
     """4096 inputs x 64 own calibration scores x 64 candidates (the batch shape bench.py times); the reject
     fraction per level is close to alpha (budget control per input, Sec. "Budget Prediction")."""
