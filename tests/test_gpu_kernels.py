@@ -229,6 +229,21 @@ def _tree_attention_reference(qkv, P, K, T, nq, nkv, hd):
     (torch.bfloat16, (200, 21, 200, 16, 2, 128), 1.5e-2),  # the same kernel (288 workgroups), drafts and prefix not aligned to its tiles
 ])
 def test_shared_prefix_attention(dtype, shape, tol):
+    _attention_case(dtype, shape, tol)
+
+
+# Bounds of the general kernel: fp32 as above (probabilities and sums round to 2^-24 of values below 3); bf16 outputs round to
+# 2^-9 of values below 3.
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.bfloat16, 1.5e-2)])
+@pytest.mark.parametrize("hd", [8, 16, 24, 40, 64, 72, 136, 256])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_general_attention_head_sizes(dtype, tol, hd, offset):
+    """Head sizes below, at and above a wavefront's lanes (several keys per pass, one, several passes), key counts around
+    whole groups of keys, and a buffer that does not start at a multiple of 16 bytes."""
+    _attention_case(dtype, (21, 3, 14, 4, 2, hd), tol, offset)
+
+
+def _attention_case(dtype, shape, tol, offset=0):
     import paper_2509_15148_amd as A
     P, K, T, nq, nkv, hd = shape
     announce("attention", dtype, shape)
@@ -236,7 +251,9 @@ def test_shared_prefix_attention(dtype, shape, tol):
     qkv = _rand((R, (nq + 2 * nkv) * hd), 31, dtype, scale=1.5)
     out = torch.full((R, nq * hd), float("nan"), dtype=dtype, device="cuda")
     wsb = A.atts_attention_workspace_bytes(dtype, R, nkv, hd)
-    A.atts_attention_shared_prefix(qkv.cuda(), out, P, K, T, nq, nkv, hd, ws(wsb) if wsb else None)
+    room = torch.empty(qkv.numel() + offset, dtype=dtype, device="cuda")
+    room[offset:].copy_(qkv.flatten())
+    A.atts_attention_shared_prefix(room[offset:].view(qkv.shape), out, P, K, T, nq, nkv, hd, ws(wsb) if wsb else None)
     torch.cuda.synchronize()
     ref = _tree_attention_reference(qkv, P, K, T, nq, nkv, hd)
     err = np.abs(out.float().cpu().numpy() - ref).max()
