@@ -295,18 +295,26 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
     const bool split_qkv = plan.qkv > 1;
 
     {
+        // with the first layer's norm; the fused QKV epilogue writes only the R real columns of V^T
         StageTimer t_(ATTS_STAGE_EMBED, st);
-        ATTS_TRY(launch_embed(d.dtype, m->tok_embed, d.vocab, d.d_model, prefix_ids, draft_ids, draft_lens, s, row0, h, m->err_flag, st));
-        ATTS_TRY(launch_rope_table(rope, s, row0, d.head_dim, d.rope_theta, st));
-        // the fused QKV epilogue writes only the R real columns of V^T
-        if (fuse_rope) ATTS_TRY(launch_zero_vt_tail(d.dtype, vt, (int64_t)kvd, R, ws.ldv, st));
+        ATTS_TRY(launch_tree_start(d.dtype, m->tok_embed, d.vocab, d.d_model, prefix_ids, draft_ids, draft_lens, s, row0, h,
+                                   d.n_layers > 0 ? m->attn_norm[0] : nullptr, d.rms_eps, xn, rope, d.head_dim, d.rope_theta,
+                                   fuse_rope ? vt : nullptr, (int64_t)kvd, ws.ldv, m->err_flag, st));
     }
     char* xn0 = xn + (size_t)row0 * d.d_model * es;
-    bool xn_ready = false;      // xn already holds the attention norm of this layer (written with the previous residual update)
+    bool xn_ready = true;       // xn already holds the attention norm of this layer (written with the embedding or the previous residual update)
     for (int l = 0; l < d.n_layers; ++l) {
         if (!xn_ready) {
             StageTimer t_(ATTS_STAGE_NORM, st);
             ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->attn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
+        }
+        // keys / values of the cached prefix rows into place (other rows than the projection's)
+        CopyBlocks cached;
+        if (pre) {
+            const char* kc = pre->k_cache + (size_t)l * pre->capacity * kvd * es;
+            add_copy(d.dtype, cached, kc, kvd, qkv + (size_t)qd * es, qkv_out, row0, kvd);
+            if (pre->uses_vt) add_copy(d.dtype, cached, pre->v_cache + (size_t)l * kvd * pre->cap_ld * es, pre->cap_ld, vt, ws.ldv, kvd, row0);
+            else add_copy(d.dtype, cached, pre->v_cache + (size_t)l * pre->capacity * kvd * es, kvd, qkv + (size_t)(qd + kvd) * es, qkv_out, row0, kvd);
         }
         GemmArgs g{};
         g.a = xn + (size_t)row0 * d.d_model * es; g.w = m->wqkv[l]; g.out = qkv + (size_t)row0 * qkv_out * es;
@@ -318,7 +326,8 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
             ATTS_TRY(launch_qkv_finish(d.dtype, kpart, plan.qkv, (int64_t)M * qkv_out, rope + (size_t)row0 * (d.head_dim / 2), M,
                                        d.n_q_heads, d.n_kv_heads, d.head_dim, qkv + (size_t)row0 * qkv_out * es,
-                                       vt + (size_t)row0 * es, ws.ldv, st));
+                                       vt + (size_t)row0 * es, ws.ldv, cached, st));
+            cached.n = 0;
         } else if (fuse_rope) {
             // QKV projection with RoPE and the V transpose applied to the accumulators
             g.rope = rope + (size_t)row0 * (d.head_dim / 2); g.vt = vt + (size_t)row0 * es; g.ldv = ws.ldv;
@@ -334,32 +343,33 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             ATTS_TRY(launch_rope_split(d.dtype, qkv, rope, s, row0, d.n_q_heads, d.n_kv_heads, d.head_dim, vt, ws.ldv, st));
         }
         if (pre) {
-            // keys / values of the cached prefix rows into place; in save mode the new rows' into the cache
             StageTimer t_(ATTS_STAGE_ROPE, st);
-            char* kc = pre->k_cache + (size_t)l * pre->capacity * kvd * es;
-            char* wk = qkv + (size_t)qd * es;                                   // key columns of workspace row 0
-            ATTS_TRY(launch_copy2d(d.dtype, kc, kvd, wk, qkv_out, row0, kvd, st));
-            if (save) ATTS_TRY(launch_copy2d(d.dtype, wk + (size_t)row0 * qkv_out * es, qkv_out, kc + (size_t)row0 * kvd * es, kvd, M, kvd, st));
-            if (pre->uses_vt) {
-                char* vc = pre->v_cache + (size_t)l * kvd * pre->cap_ld * es;
-                ATTS_TRY(launch_copy2d(d.dtype, vc, pre->cap_ld, vt, ws.ldv, kvd, row0, st));
-                if (save) ATTS_TRY(launch_copy2d(d.dtype, vt + (size_t)row0 * es, ws.ldv, vc + (size_t)row0 * es, pre->cap_ld, kvd, M, st));
-            } else {
-                char* vc = pre->v_cache + (size_t)l * pre->capacity * kvd * es;
-                char* wv = qkv + (size_t)(qd + kvd) * es;
-                ATTS_TRY(launch_copy2d(d.dtype, vc, kvd, wv, qkv_out, row0, kvd, st));
-                if (save) ATTS_TRY(launch_copy2d(d.dtype, wv + (size_t)row0 * qkv_out * es, qkv_out, vc + (size_t)row0 * kvd * es, kvd, M, kvd, st));
+            ATTS_TRY(launch_copies(d.dtype, cached, st));
+            if (save) {                                        // the new rows' keys / values into the cache
+                CopyBlocks fresh;
+                char* kc = pre->k_cache + (size_t)l * pre->capacity * kvd * es;
+                add_copy(d.dtype, fresh, qkv + ((size_t)row0 * qkv_out + qd) * es, qkv_out, kc + (size_t)row0 * kvd * es, kvd, M, kvd);
+                if (pre->uses_vt) {
+                    char* vc = pre->v_cache + (size_t)l * kvd * pre->cap_ld * es;
+                    add_copy(d.dtype, fresh, vt + (size_t)row0 * es, ws.ldv, vc + (size_t)row0 * es, pre->cap_ld, kvd, M);
+                } else {
+                    char* vc = pre->v_cache + (size_t)l * pre->capacity * kvd * es;
+                    add_copy(d.dtype, fresh, qkv + ((size_t)row0 * qkv_out + qd + kvd) * es, qkv_out, vc + (size_t)row0 * kvd * es, kvd, M, kvd);
+                }
+                ATTS_TRY(launch_copies(d.dtype, fresh, st));
             }
         }
         if (tree) {
             // keys / values of the whole tree as rows into the continuation cache of this layer (pre != nullptr)
             char* kc = tree->kc + (size_t)l * tree->layer_bytes;
             char* vc = tree->vc + (size_t)l * tree->layer_bytes;
-            ATTS_TRY(launch_copy2d(d.dtype, pre->k_cache + (size_t)l * pre->capacity * kvd * es, kvd, kc, kvd, row0, kvd, st));
+            CopyBlocks rows;
+            add_copy(d.dtype, rows, pre->k_cache + (size_t)l * pre->capacity * kvd * es, kvd, kc, kvd, row0, kvd);
             if (pre->uses_vt)
                 ATTS_TRY(launch_transpose_to_rows(d.dtype, pre->v_cache + (size_t)l * kvd * pre->cap_ld * es, pre->cap_ld, vc, kvd, row0, kvd, st));
             else
-                ATTS_TRY(launch_copy2d(d.dtype, pre->v_cache + (size_t)l * pre->capacity * kvd * es, kvd, vc, kvd, row0, kvd, st));
+                add_copy(d.dtype, rows, pre->v_cache + (size_t)l * pre->capacity * kvd * es, kvd, vc, kvd, row0, kvd);
+            ATTS_TRY(launch_copies(d.dtype, rows, st));
             ATTS_TRY(launch_tree_rows_to_cache(d.dtype, qkv + (size_t)qd * es, qkv_out, kc, kvd, s.P, s.T, tree->Tc, M, kvd, st));
             ATTS_TRY(launch_tree_rows_to_cache(d.dtype, qkv + (size_t)(qd + kvd) * es, qkv_out, vc, kvd, s.P, s.T, tree->Tc, M, kvd, st));
         }
@@ -409,6 +419,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             ATTS_TRY(launch_resid_norm(d.dtype, h0, kpart, plan.down, (int64_t)M * d.d_model, xn_ready ? m->attn_norm[l + 1] : nullptr,
                                        d.rms_eps, M, d.d_model, xn0, st));
         } else {
+            xn_ready = false;
             StageTimer t_(ATTS_STAGE_GEMM_DOWN, st);
             ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
         }
@@ -659,7 +670,7 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
     float* logits = reinterpret_cast<float*>(base + cs.logits);
     float2* rope = reinterpret_cast<float2*>(base + cs.rope);
     // (cos, sin) rows of the positions new tokens can take: P + 1 ... P + T + n_new - 1 (indexed by absolute position)
-    ATTS_TRY(launch_rope_table(rope, ScoreShape{P, 1, cs.Tc}, P, d.head_dim, d.rope_theta, st));
+    ATTS_TRY(launch_rope_table(rope, P, cs.Tc, d.head_dim, d.rope_theta, st));
     // the projections of a step that have a narrow output cut their K range over the chip, one partial result per slice
     SplitPlan plan = split_plan(d, K);
     plan.qkv = gemm_partial_slices(d.dtype, K, qkv_out, d.d_model, padded);     // the QKV sums always pass through fp32 here
@@ -683,8 +694,9 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
     // 3. one row per branch and step: token t - 1 goes in at branch position len_j + t - 1 and predicts token t
     for (int t = 1; t < n_new; ++t) {
         const BranchPos pos{draft_lens, T, t - 1};
-        ATTS_TRY(launch_embed_rows(d.dtype, m->tok_embed, d.vocab, d.d_model, out_ids + (t - 1), n_new, K, h, m->err_flag, st));
-        bool xn_ready = false;
+        ATTS_TRY(launch_embed_norm_rows(d.dtype, m->tok_embed, d.vocab, d.d_model, out_ids + (t - 1), n_new, K, h,
+                                        d.n_layers > 0 ? m->attn_norm[0] : nullptr, d.rms_eps, xn, m->err_flag, st));
+        bool xn_ready = true, xs_ready = false;
         for (int l = 0; l < d.n_layers; ++l) {
             char* kc = tree.kc + (size_t)l * tree.layer_bytes;
             char* vc = tree.vc + (size_t)l * tree.layer_bytes;
@@ -718,15 +730,16 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
             if (plan.down > 1) {
                 g.out = kpart; g.n_slices = plan.down;
                 ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
-                xn_ready = l + 1 < d.n_layers;
-                ATTS_TRY(launch_resid_norm(d.dtype, h, kpart, plan.down, (int64_t)K * d.d_model, xn_ready ? m->attn_norm[l + 1] : nullptr,
-                                           d.rms_eps, K, d.d_model, xn, st));
+                xn_ready = l + 1 < d.n_layers;                 // with the norm that follows: the next layer's, or the final one
+                xs_ready = !xn_ready;
+                ATTS_TRY(launch_resid_norm(d.dtype, h, kpart, plan.down, (int64_t)K * d.d_model, xn_ready ? m->attn_norm[l + 1] : m->final_norm,
+                                           d.rms_eps, K, d.d_model, xn_ready ? xn : xs, st));
             } else {
                 ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
                 xn_ready = false;
             }
         }
-        ATTS_TRY(launch_norm_strided_rows(d.dtype, h, m->final_norm, d.rms_eps, d.d_model, 0, 1, BranchPos{nullptr, 0, 0}, K, xs, st));
+        if (!xs_ready) ATTS_TRY(launch_norm_strided_rows(d.dtype, h, m->final_norm, d.rms_eps, d.d_model, 0, 1, BranchPos{nullptr, 0, 0}, K, xs, st));
         ATTS_TRY(next_token(t));
     }
     return ATTS_OK;

@@ -151,8 +151,6 @@ int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hi
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
 // true if the EPI_QKV_ROPE epilogue can serve this QKV projection (else: EPI_STORE_ACT + launch_rope_split)
 bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t head_dim, bool a_rows_padded);
-// vt [rows, ldv]: zero columns [R, ldv) of every row (the attention kernel reads whole 64-key tiles of V^T).
-int32_t launch_zero_vt_tail(int32_t dtype, void* vt, int64_t rows, int32_t R, int64_t ldv, hipStream_t stream);
 
 // lp[b] = target_logit[b] - logsumexp over the n_part partials of row b; rows with valid[b] == 0
 // (or b beyond) get 0.  valid may be NULL.
@@ -165,26 +163,46 @@ struct ScoreShape {
     int32_t B() const { return K * T; }
 };
 
-int32_t launch_embed(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d,
-                     const int32_t* prefix_ids, const int32_t* draft_ids, const int32_t* draft_lens,
-                     ScoreShape s, int32_t row0, float* h, int32_t* err_flag, hipStream_t stream);
+// Start of a pass over rows [row0, R) of the token tree: h = embeddings, with a gain vector xn = rmsnorm(h; gain) (both
+// indexed by absolute row); cs[r][i] = (cos, sin)(pos(r) theta^(-2 i / hd)), i < hd / 2; vt != NULL: columns [R, ldv) of the
+// vt_rows rows of V^T zeroed (the attention kernel reads whole 64-key tiles of it).
+int32_t launch_tree_start(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* prefix_ids,
+                          const int32_t* draft_ids, const int32_t* draft_lens, ScoreShape s, int32_t row0, float* h, const float* gain,
+                          float eps, void* xn, float2* cs, int32_t hd, float theta, void* vt, int64_t vt_rows, int64_t ldv,
+                          int32_t* err_flag, hipStream_t stream);
 int32_t launch_rmsnorm(int32_t dtype, const float* h, const float* gain, float eps, int32_t rows, int32_t d,
                        void* out, hipStream_t stream);
 // Several launchers take row0: only rows [row0, R) of the token tree are produced (rows before it belong to a
 // cached prefix); buffers are always indexed by absolute row.
-// rope table per row of the token tree: cs[r][i] = (cos, sin)(pos(r) * theta^(-2 i / hd)), i < hd / 2
-int32_t launch_rope_table(float2* cs, ScoreShape s, int32_t row0, int32_t hd, float theta, hipStream_t stream);
+// rotary table by absolute position, rows [first, first + rows): cs[r][i] = (cos, sin)(r * theta^(-2 i / hd)), i < hd / 2
+int32_t launch_rope_table(float2* cs, int32_t first, int32_t rows, int32_t hd, float theta, hipStream_t stream);
 // In-place rotate-half RoPE on the q and k columns of qkv [R, (nq + 2 nkv) hd]; writes V transposed
 // to vt [nkv, hd, ldv] (ldv >= R) when vt != NULL.
 int32_t launch_rope_split(int32_t dtype, void* qkv, const float2* cs, ScoreShape s, int32_t row0, int32_t nq, int32_t nkv,
                           int32_t hd, void* vt, int64_t ldv, hipStream_t stream);
 int32_t launch_transpose_v(int32_t dtype, const void* qkv, int32_t row0, int32_t R, int32_t nq, int32_t nkv, int32_t hd,
                            void* vt, int64_t ldv, hipStream_t stream);
+// Blocks dst[r][c] = src[r][c], rows x cols elements of the model dtype, pitches in elements, copied by one launch.
+struct CopyBlock {
+    const void* src;
+    void* dst;
+    int64_t src_ld, dst_ld, rows, cols;
+    bool wide;               // both sides and pitches at multiples of 16 bytes
+};
+struct CopyBlocks {
+    static constexpr int kMax = 2;
+    CopyBlock b[kMax];
+    int32_t n = 0;
+};
+void add_copy(int32_t dtype, CopyBlocks& jobs, const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int64_t rows, int64_t cols);
+int64_t copy_workgroups(int32_t dtype, const CopyBlocks& jobs);
+int32_t launch_copies(int32_t dtype, const CopyBlocks& jobs, hipStream_t stream);
 // acc [n_slices][rows, (nq + 2 nkv) hd] fp32 (partial sums of a K-split QKV projection, added here in slice order) -> RoPE
 // on the q / k heads (cs, qkv, vt already point at the first of the `rows` rows / columns), stored to qkv; v heads to
-// vt [nkv hd, ldv]
+// vt [nkv hd, ldv]; `copies` are done in the same launch (they must touch other rows / columns)
 int32_t launch_qkv_finish(int32_t dtype, const float* acc, int32_t n_slices, int64_t slice_pitch, const float2* cs, int32_t rows,
-                          int32_t nq, int32_t nkv, int32_t hd, void* qkv, void* vt, int64_t ldv, hipStream_t stream);
+                          int32_t nq, int32_t nkv, int32_t hd, void* qkv, void* vt, int64_t ldv, const CopyBlocks& copies,
+                          hipStream_t stream);
 // K slices an EPI_PARTIAL_F32 projection of this shape is cut into (1: cutting would not help, the caller takes the
 // direct epilogue instead).  Depends on the shape only.
 int32_t gemm_partial_slices(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded);
@@ -193,9 +211,6 @@ int32_t skinny_partial_slices(int32_t N, int32_t Kd);     // the same for the ke
 // gain != NULL: then xn[r] = rmsnorm(h[r]; gain) in the model dtype (residual update and the next norm in one pass)
 int32_t launch_resid_norm(int32_t dtype, float* h, const float* partials, int32_t n_slices, int64_t slice_pitch, const float* gain,
                           float eps, int32_t rows, int32_t d, void* xn, hipStream_t stream);
-// dst[r][c] = src[r][c], rows x cols elements of the model dtype, pitches in elements
-int32_t launch_copy2d(int32_t dtype, const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int64_t rows, int64_t cols,
-                      hipStream_t stream);
 // xs[b] = rmsnorm(h[row(b)]) for the B = K T scoring rows; targets[b] / valid[b] from the draft ids.
 int32_t launch_gather_norm(int32_t dtype, const float* h, const float* gain, float eps, int32_t d,
                            const int32_t* draft_ids, const int32_t* draft_lens, int32_t vocab, ScoreShape s,
@@ -208,8 +223,9 @@ int32_t launch_tree_rows_to_cache(int32_t dtype, const void* src, int64_t src_ld
                                   int32_t Tc, int32_t rows, int32_t cols, hipStream_t stream);
 int32_t launch_transpose_to_rows(int32_t dtype, const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int32_t rows,
                                  int32_t cols, hipStream_t stream);
-int32_t launch_embed_rows(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* ids, int64_t stride,
-                          int32_t rows, float* h, int32_t* err_flag, hipStream_t stream);
+// h[j] = embedding of ids[j stride] (an id outside the vocabulary is read as 0 and sets the flag); gain != NULL: xn[j] = rmsnorm(h[j]; gain)
+int32_t launch_embed_norm_rows(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* ids, int64_t stride,
+                               int32_t rows, float* h, const float* gain, float eps, void* xn, int32_t* err_flag, hipStream_t stream);
 // Branch j of a continuation holds len_j = lens[j] draft tokens (read as clamped to [1, T]; T when lens is NULL) and `done`
 // generated ones: at(j) = len_j + done is the position, inside the branch, of the row a decoding step appends.
 struct BranchPos {

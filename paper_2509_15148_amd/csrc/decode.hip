@@ -42,20 +42,6 @@ __global__ __launch_bounds__(256) void transpose_to_rows_kernel(const T* __restr
     }
 }
 
-// h[j] = embedding of ids[j * stride]  (an id outside the vocabulary is read as 0 and sets the flag)
-template <typename T>
-__global__ __launch_bounds__(256) void embed_rows_kernel(const T* __restrict__ emb, int vocab, int d, const int32_t* __restrict__ ids,
-                                                         int64_t stride, float* __restrict__ h, int32_t* __restrict__ err_flag) {
-    const int j = blockIdx.x;
-    int id = ids[(int64_t)j * stride];
-    if (id < 0 || id >= vocab) {
-        if (threadIdx.x == 0) *err_flag = 1;
-        id = 0;
-    }
-    const T* src = emb + (int64_t)id * d;
-    for (int c = threadIdx.x; c < d; c += 256) h[(int64_t)j * d + c] = to_f32<T>(src[c]);
-}
-
 // One decode row per branch: acc [n_slices][Kr, (nq + 2 nkv) hd] fp32 partial sums (added in slice order) -> q (rotated) to
 // q_out [Kr, nq hd]; k (rotated) and v to row `P + j Tc + pos.at(j)` of the layer's key / value cache.  cs: (cos, sin)
 // rows indexed by absolute position.
@@ -607,14 +593,6 @@ int32_t launch_transpose_to_rows(int32_t dtype, const void* src, int64_t src_ld,
     DISPATCH_T(dtype, hipLaunchKernelGGL(transpose_to_rows_kernel<T>, grid, dim3(256), 0, stream, (const T*)src, src_ld, (T*)dst,
                                          dst_ld, rows, cols);)
     ATTS_LAUNCH_CHECK("transpose_to_rows_kernel");
-    return ATTS_OK;
-}
-
-int32_t launch_embed_rows(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* ids, int64_t stride,
-                          int32_t rows, float* h, int32_t* err_flag, hipStream_t stream) {
-    DISPATCH_T(dtype, hipLaunchKernelGGL(embed_rows_kernel<T>, dim3(rows), dim3(256), 0, stream, (const T*)tok_embed, vocab, d, ids,
-                                         stride, h, err_flag);)
-    ATTS_LAUNCH_CHECK("embed_rows_kernel");
     return ATTS_OK;
 }
 

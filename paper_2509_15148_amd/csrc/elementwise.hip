@@ -32,32 +32,6 @@ __device__ __forceinline__ float block_sum(float v, float* red /* [kBlock / 64] 
 // Row of the token tree -> (is it a draft row, which draft, which position in the draft)
 __device__ __forceinline__ int tree_position(int r, int P, int T) { return r < P ? r : P + (r - P) % T; }
 
-// ---- S0: embedding gather ------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void embed_kernel(const T* __restrict__ emb, int vocab, int d,
-                                                    const int32_t* __restrict__ prefix_ids,
-                                                    const int32_t* __restrict__ draft_ids,
-                                                    const int32_t* __restrict__ draft_lens, int P, int Tn, int row0,
-                                                    float* __restrict__ h, int32_t* __restrict__ err_flag) {
-    const int r = row0 + blockIdx.x;
-    int id;
-    bool padding = false;
-    if (r < P) {
-        id = prefix_ids[r];
-    } else {
-        int k = (r - P) / Tn, t = (r - P) % Tn;
-        id = draft_ids[(int64_t)k * Tn + t];
-        padding = draft_lens && t >= draft_lens[k];
-    }
-    if (id < 0 || id >= vocab) {
-        if (!padding && threadIdx.x == 0) *err_flag = 1;
-        id = 0;
-    }
-    const T* src = emb + (int64_t)id * d;
-    float* dst = h + (int64_t)r * d;
-    for (int c = threadIdx.x; c < d; c += blockDim.x) dst[c] = to_f32<T>(src[c]);
-}
-
 // ---- S1: RMSNorm over rows of the fp32 residual stream ---------------------------------------
 // One row per workgroup, 16-byte loads; up to 4 float4 per thread (d <= 4096) stay in registers between the
 // sum-of-squares pass and the scaling pass, longer rows are read again (from L2).  d % 4 == 0.
@@ -113,6 +87,139 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
                                                       float eps, int d, T* __restrict__ out) {
     __shared__ float red[4];
     rmsnorm_row<T>(h + (int64_t)blockIdx.x * d, gain, eps, d, out + (int64_t)blockIdx.x * d, red);
+}
+
+// ---- S0: start of a pass: embedding gather + first norm, rotary table, tail of V^T ----------------------------
+// h = embedding of id (an id outside the vocabulary is read as 0 by the caller) and, with a gain vector, xn = rmsnorm(h).  16-byte
+// loads of the embedding row (rows are multiples of 16 bytes); up to kKeep pieces per thread stay in registers between
+// the passes, longer rows are read again.
+template <typename T>
+__device__ __forceinline__ void embed_norm_row(const T* __restrict__ src, int d, float* __restrict__ h, const float* __restrict__ gain,
+                                               float eps, T* __restrict__ xn, float* red) {
+    constexpr int V = 16 / (int)sizeof(T), kKeep = 2;
+    const int n = d / V;
+    auto load = [&](int c, float (&x)[V]) __attribute__((always_inline)) {
+        const uint4 raw = *reinterpret_cast<const uint4*>(src + c * V);
+        const T* e = reinterpret_cast<const T*>(&raw);
+#pragma unroll
+        for (int u = 0; u < V; ++u) x[u] = to_f32<T>(e[u]);
+    };
+    float keep[kKeep][V], ss = 0.f;
+    auto store_h = [&](int c, const float (&x)[V]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < V; u += 4) *reinterpret_cast<float4*>(h + c * V + u) = make_float4(x[u], x[u + 1], x[u + 2], x[u + 3]);
+#pragma unroll
+        for (int u = 0; u < V; ++u) ss += x[u] * x[u];
+    };
+    auto store_n = [&](int c, const float (&x)[V], float inv) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < V; u += 4) {
+            const float4 g = *reinterpret_cast<const float4*>(gain + c * V + u);
+            store4<T>(xn + c * V + u, make_float4(x[u] * inv * g.x, x[u + 1] * inv * g.y, x[u + 2] * inv * g.z, x[u + 3] * inv * g.w));
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < kKeep; ++q) {
+        const int c = threadIdx.x + 256 * q;
+        if (c < n) {
+            load(c, keep[q]);
+            store_h(c, keep[q]);
+        }
+    }
+    for (int c = threadIdx.x + 256 * kKeep; c < n; c += 256) {
+        float x[V];
+        load(c, x);
+        store_h(c, x);
+    }
+    if (!gain) return;                                          // block-uniform
+    ss = block_sum<256>(ss, red);
+    const float inv = rsqrtf(ss / (float)d + eps);
+#pragma unroll
+    for (int q = 0; q < kKeep; ++q) {
+        const int c = threadIdx.x + 256 * q;
+        if (c < n) store_n(c, keep[q], inv);
+    }
+    for (int c = threadIdx.x + 256 * kKeep; c < n; c += 256) {
+        float x[V];
+        load(c, x);
+        store_n(c, x, inv);
+    }
+}
+
+// Everything a pass needs before its first projection, in one launch (each of these is a few microseconds by itself, most of
+// it the launch): workgroups [0, R - row0) embed a row each and apply the first layer's norm; the next rope_wgs fill the
+// rotary table, (cos, sin)(pos(r) theta^(-2 i / hd)) in fp64, rounded once; the last zero columns [R, ldv) of V^T for a
+// producer that writes only the R real ones.  128 rows of the 7B width: 5.7 us for 8.9 + 4.7 + 4.9 in three launches (each
+// with element-wise loads of the embedding); 1152 rows 13.8 for 13.8 + 4.8 + 7.0.
+struct StartDims {
+    int32_t vocab, d, P, T, row0, R, half, rope_wgs;
+    double log_theta_over_half;
+    float eps;
+    int64_t ldv, vt_rows;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void tree_start_kernel(const T* __restrict__ emb, const int32_t* __restrict__ prefix_ids,
+                                                         const int32_t* __restrict__ draft_ids, const int32_t* __restrict__ draft_lens,
+                                                         float* __restrict__ h, const float* __restrict__ gain, T* __restrict__ xn,
+                                                         float2* __restrict__ cs, T* __restrict__ vt, int32_t* __restrict__ err_flag,
+                                                         const StartDims s) {
+    __shared__ float red[4];
+    const int rows = s.R - s.row0;
+    if ((int)blockIdx.x < rows) {
+        const int r = s.row0 + (int)blockIdx.x;
+        int id;
+        bool padding = false;
+        if (r < s.P) {
+            id = prefix_ids[r];
+        } else {
+            const int k = (r - s.P) / s.T, t = (r - s.P) % s.T;
+            id = draft_ids[(int64_t)k * s.T + t];
+            padding = draft_lens && t >= draft_lens[k];
+        }
+        if (id < 0 || id >= s.vocab) {
+            if (!padding && threadIdx.x == 0) *err_flag = 1;
+            id = 0;
+        }
+        embed_norm_row<T>(emb + (int64_t)id * s.d, s.d, h + (int64_t)r * s.d, gain, s.eps, xn + (int64_t)r * s.d, red);
+    } else if ((int)blockIdx.x < rows + s.rope_wgs) {
+        const int64_t idx = (int64_t)((int)blockIdx.x - rows) * 256 + threadIdx.x;     // up to 2^24 rows x 128 pairs
+        if (idx >= (int64_t)rows * s.half) return;
+        const int r = s.row0 + (int)(idx / s.half), i = (int)(idx % s.half);
+        const double ang = (double)tree_position(r, s.P, s.T) * exp(-(double)i * s.log_theta_over_half);
+        double sn, c;
+        sincos(ang, &sn, &c);
+        cs[(int64_t)r * s.half + i] = make_float2((float)c, (float)sn);
+    } else {
+        const int tail = (int)(s.ldv - s.R);
+        const int64_t i = (int64_t)((int)blockIdx.x - rows - s.rope_wgs) * 256 + threadIdx.x;
+        if (i < s.vt_rows * tail) vt[(i / tail) * s.ldv + s.R + (i % tail)] = from_f32<T>(0.f);
+    }
+}
+
+// One decoding step's rows: h[j] = embedding of ids[j stride], xn[j] = rmsnorm(h[j]; gain)
+template <typename T>
+__global__ __launch_bounds__(256) void embed_norm_rows_kernel(const T* __restrict__ emb, int vocab, int d, const int32_t* __restrict__ ids,
+                                                              int64_t stride, float* __restrict__ h, const float* __restrict__ gain,
+                                                              float eps, T* __restrict__ xn, int32_t* __restrict__ err_flag) {
+    __shared__ float red[4];
+    const int j = blockIdx.x;
+    int id = ids[(int64_t)j * stride];
+    if (id < 0 || id >= vocab) {
+        if (threadIdx.x == 0) *err_flag = 1;
+        id = 0;
+    }
+    embed_norm_row<T>(emb + (int64_t)id * d, d, h + (int64_t)j * d, gain, eps, xn + (int64_t)j * d, red);
+}
+
+// (cos, sin) rows by absolute position, for decoding
+__global__ void rope_table_kernel(float2* __restrict__ cs, int first, int rows, int half, double log_theta_over_half) {
+    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (int64_t)rows * half) return;
+    const int r = first + (int)(idx / half), i = (int)(idx % half);
+    const double ang = (double)r * exp(-(double)i * log_theta_over_half);
+    double s, c;
+    sincos(ang, &s, &c);
+    cs[(int64_t)r * half + i] = make_float2((float)c, (float)s);
 }
 
 // ---- residual update from K-slice partial sums, fused with the next RMSNorm ------------------------------
@@ -194,18 +301,6 @@ __global__ __launch_bounds__(256) void resid_norm_kernel(float* __restrict__ h, 
     }
 }
 
-// ---- rotary table per row: (cos, sin)(pos(r) * theta^(-2 i / hd)) in fp64, rounded once ----------
-__global__ void rope_table_kernel(float2* __restrict__ cs, int row0, int R, int P, int Tn, int half,
-                                  double log_theta_over_half) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;     // up to 2^24 rows x 128 pairs
-    if (idx >= (int64_t)(R - row0) * half) return;
-    const int r = row0 + (int)(idx / half), i = (int)(idx % half);
-    double ang = (double)tree_position(r, P, Tn) * exp(-(double)i * log_theta_over_half);
-    double s, c;
-    sincos(ang, &s, &c);
-    cs[(int64_t)r * half + i] = make_float2((float)c, (float)s);
-}
-
 // ---- S2 epilogue (unfused): rotate q and k in place -------------------------------------------
 // One thread per (row, head, pair).  Heads 0 .. nq + nkv - 1 of the qkv row are rotated.
 template <typename T>
@@ -246,24 +341,52 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const T* __restrict__ 
     }
 }
 
-// dst[r][c] = src[r][c] for a rows x cols block of two pitched arrays (prefix cache <-> workspace)
+// Up to kMaxCopies blocks of pitched arrays, dst[r][c] = src[r][c] (prefix cache <-> workspace), by the workgroups from `wg0`
+// on; 16 bytes per thread, or element by element where a block does not start and continue at multiples of 16 bytes and at
+// the end of its rows.
 template <typename T>
-__global__ __launch_bounds__(256) void copy2d_kernel(const T* __restrict__ src, int64_t src_ld, T* __restrict__ dst,
-                                                     int64_t dst_ld, int64_t rows, int64_t cols) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= rows * cols) return;
-    const int64_t r = i / cols, c = i % cols;
-    dst[r * dst_ld + c] = src[r * src_ld + c];
+__device__ __forceinline__ void copy_blocks(const CopyBlocks& jobs, int wg) {
+    constexpr int V = 16 / (int)sizeof(T);
+    int64_t i = (int64_t)wg * 256 + threadIdx.x;
+#pragma unroll
+    for (int j = 0; j < CopyBlocks::kMax; ++j) {
+        if (j >= jobs.n) return;
+        const CopyBlock& b = jobs.b[j];
+        const int64_t pieces = (b.cols + V - 1) / V, total = b.rows * pieces;
+        if (i < total) {
+            const int64_t r = i / pieces, c = (i % pieces) * V;
+            const T* src = reinterpret_cast<const T*>(b.src) + r * b.src_ld + c;
+            T* dst = reinterpret_cast<T*>(b.dst) + r * b.dst_ld + c;
+            if (b.wide && c + V <= b.cols) {
+                *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+            } else {
+                for (int u = 0; u < V && c + u < b.cols; ++u) dst[u] = src[u];
+            }
+            return;
+        }
+        i -= total;
+    }
+}
+template <typename T>
+__global__ __launch_bounds__(256) void copy_blocks_kernel(const CopyBlocks jobs) {
+    copy_blocks<T>(jobs, (int)blockIdx.x);
 }
 
 // Finish of a K-split QKV projection: acc [n_slices][rows, (nq + 2 nkv) hd] holds the fp32 partial sums of the K slices,
 // added here in slice order.  One thread per (row, head, rotation pair i < hd / 2): q and k heads are rotated
 // (rotate-half RoPE, table row cs[r]) and stored to the qkv row, v heads are stored to the transposed copy
-// vt [nkv hd, ldv] at column r.
+// vt [nkv hd, ldv] at column r.  The workgroups from finish_wgs on put the cached prefix rows in place (other rows of the same
+// buffers): one launch of 7.2 us where finish, key copy and value copy took
+// 6.0 + 4.8 + 4.8 (128 rows, prefix 512, 7B width).
 template <typename T>
 __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict__ acc, int n_slices, int64_t pitch,
                                                          const float2* __restrict__ cs, int rows, int nq, int nkv, int hd,
-                                                         T* __restrict__ qkv, T* __restrict__ vt, int64_t ldv) {
+                                                         T* __restrict__ qkv, T* __restrict__ vt, int64_t ldv, int finish_wgs,
+                                                         const CopyBlocks jobs) {
+    if ((int)blockIdx.x >= finish_wgs) {
+        copy_blocks<T>(jobs, (int)blockIdx.x - finish_wgs);
+        return;
+    }
     const int half = hd >> 1, heads = nq + 2 * nkv;
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= (int64_t)rows * heads * half) return;
@@ -296,15 +419,6 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
         p[0] = from_f32<T>(x1);
         p[(int64_t)half * ldv] = from_f32<T>(x2);
     }
-}
-
-// Zero columns [R, ldv) of every row of V^T (for a producer that writes only the R real columns).
-template <typename T>
-__global__ __launch_bounds__(256) void zero_vt_tail_kernel(T* __restrict__ vt, int64_t rows, int R, int64_t ldv) {
-    const int tail = (int)(ldv - R);
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= rows * tail) return;
-    vt[(i / tail) * ldv + R + (i % tail)] = from_f32<T>(0.f);
 }
 
 // ---- S6: gather the scoring rows, final RMSNorm, targets -----------------------------------------
@@ -359,12 +473,29 @@ __global__ __launch_bounds__(256) void score_reduce_kernel(const float* __restri
         __VA_ARGS__                                  \
     }
 
-int32_t launch_embed(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* prefix_ids,
-                     const int32_t* draft_ids, const int32_t* draft_lens, ScoreShape s, int32_t row0, float* h,
-                     int32_t* err_flag, hipStream_t stream) {
-    DISPATCH_T(dtype, hipLaunchKernelGGL(embed_kernel<T>, dim3(s.R() - row0), dim3(256), 0, stream, (const T*)tok_embed, vocab, d,
-                                         prefix_ids, draft_ids, draft_lens, s.P, s.T, row0, h, err_flag);)
-    ATTS_LAUNCH_CHECK("embed_kernel");
+int32_t launch_tree_start(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* prefix_ids,
+                          const int32_t* draft_ids, const int32_t* draft_lens, ScoreShape s, int32_t row0, float* h, const float* gain,
+                          float eps, void* xn, float2* cs, int32_t hd, float theta, void* vt, int64_t vt_rows, int64_t ldv,
+                          int32_t* err_flag, hipStream_t stream) {
+    StartDims t{};
+    t.vocab = vocab; t.d = d; t.P = s.P; t.T = s.T; t.row0 = row0; t.R = s.R(); t.half = hd / 2; t.eps = eps;
+    t.log_theta_over_half = log((double)theta) / (double)t.half;
+    const int64_t rows = t.R - row0, rope = ceil_div(rows * t.half, 256);
+    t.rope_wgs = (int32_t)rope;
+    t.ldv = ldv;
+    t.vt_rows = vt ? vt_rows : 0;
+    const int64_t zero = vt ? ceil_div(vt_rows * (ldv - t.R), 256) : 0;
+    DISPATCH_T(dtype, hipLaunchKernelGGL(tree_start_kernel<T>, dim3((unsigned)(rows + rope + zero)), dim3(256), 0, stream, (const T*)tok_embed,
+                                         prefix_ids, draft_ids, draft_lens, h, gain, (T*)xn, cs, (T*)vt, err_flag, t);)
+    ATTS_LAUNCH_CHECK("tree_start_kernel");
+    return ATTS_OK;
+}
+
+int32_t launch_embed_norm_rows(int32_t dtype, const void* tok_embed, int32_t vocab, int32_t d, const int32_t* ids, int64_t stride,
+                               int32_t rows, float* h, const float* gain, float eps, void* xn, int32_t* err_flag, hipStream_t stream) {
+    DISPATCH_T(dtype, hipLaunchKernelGGL(embed_norm_rows_kernel<T>, dim3(rows), dim3(256), 0, stream, (const T*)tok_embed, vocab, d, ids,
+                                         stride, h, gain, eps, (T*)xn, err_flag);)
+    ATTS_LAUNCH_CHECK("embed_norm_rows_kernel");
     return ATTS_OK;
 }
 
@@ -375,10 +506,9 @@ int32_t launch_rmsnorm(int32_t dtype, const float* h, const float* gain, float e
     return ATTS_OK;
 }
 
-int32_t launch_rope_table(float2* cs, ScoreShape s, int32_t row0, int32_t hd, float theta, hipStream_t stream) {
+int32_t launch_rope_table(float2* cs, int32_t first, int32_t rows, int32_t hd, float theta, hipStream_t stream) {
     const int half = hd / 2;
-    const int64_t total = (int64_t)(s.R() - row0) * half;
-    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream, cs, row0, s.R(), s.P, s.T, half,
+    hipLaunchKernelGGL(rope_table_kernel, dim3((unsigned)ceil_div((int64_t)rows * half, 256)), dim3(256), 0, stream, cs, first, rows, half,
                        log((double)theta) / (double)half);
     ATTS_LAUNCH_CHECK("rope_table_kernel");
     return ATTS_OK;
@@ -391,16 +521,6 @@ int32_t launch_transpose_v(int32_t dtype, const void* qkv, int32_t row0, int32_t
     DISPATCH_T(dtype, hipLaunchKernelGGL(transpose_v_kernel<T>, grid, dim3(256), 0, stream, (const T*)qkv, row0, R, ld,
                                          (nq + nkv) * hd, hd, (T*)vt, ldv);)
     ATTS_LAUNCH_CHECK("transpose_v_kernel");
-    return ATTS_OK;
-}
-
-int32_t launch_zero_vt_tail(int32_t dtype, void* vt, int64_t rows, int32_t R, int64_t ldv, hipStream_t stream) {
-    const int tail = (int)(ldv - R);
-    if (tail <= 0 || rows <= 0) return ATTS_OK;
-    const int64_t total = rows * tail;
-    DISPATCH_T(dtype, hipLaunchKernelGGL(zero_vt_tail_kernel<T>, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream,
-                                         (T*)vt, rows, R, ldv);)
-    ATTS_LAUNCH_CHECK("zero_vt_tail_kernel");
     return ATTS_OK;
 }
 
@@ -417,10 +537,11 @@ int32_t launch_rope_split(int32_t dtype, void* qkv, const float2* cs, ScoreShape
 }
 
 int32_t launch_qkv_finish(int32_t dtype, const float* acc, int32_t n_slices, int64_t slice_pitch, const float2* cs, int32_t rows,
-                          int32_t nq, int32_t nkv, int32_t hd, void* qkv, void* vt, int64_t ldv, hipStream_t stream) {
-    const int64_t total = (int64_t)rows * (nq + 2 * nkv) * (hd / 2);
-    DISPATCH_T(dtype, hipLaunchKernelGGL(qkv_finish_kernel<T>, dim3((unsigned)ceil_div(total, 256)), dim3(256), 0, stream, acc,
-                                         n_slices, slice_pitch, cs, rows, nq, nkv, hd, (T*)qkv, (T*)vt, ldv);)
+                          int32_t nq, int32_t nkv, int32_t hd, void* qkv, void* vt, int64_t ldv, const CopyBlocks& copies,
+                          hipStream_t stream) {
+    const int64_t finish = ceil_div((int64_t)rows * (nq + 2 * nkv) * (hd / 2), 256);
+    DISPATCH_T(dtype, hipLaunchKernelGGL(qkv_finish_kernel<T>, dim3((unsigned)(finish + copy_workgroups(dtype, copies))), dim3(256), 0, stream,
+                                         acc, n_slices, slice_pitch, cs, rows, nq, nkv, hd, (T*)qkv, (T*)vt, ldv, (int)finish, copies);)
     ATTS_LAUNCH_CHECK("qkv_finish_kernel");
     return ATTS_OK;
 }
@@ -435,12 +556,22 @@ int32_t launch_resid_norm(int32_t dtype, float* h, const float* partials, int32_
     return ATTS_OK;
 }
 
-int32_t launch_copy2d(int32_t dtype, const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int64_t rows, int64_t cols,
-                      hipStream_t stream) {
-    if (rows <= 0 || cols <= 0) return ATTS_OK;
-    DISPATCH_T(dtype, hipLaunchKernelGGL(copy2d_kernel<T>, dim3((unsigned)ceil_div(rows * cols, 256)), dim3(256), 0, stream,
-                                         (const T*)src, src_ld, (T*)dst, dst_ld, rows, cols);)
-    ATTS_LAUNCH_CHECK("copy2d_kernel");
+void add_copy(int32_t dtype, CopyBlocks& jobs, const void* src, int64_t src_ld, void* dst, int64_t dst_ld, int64_t rows, int64_t cols) {
+    if (rows <= 0 || cols <= 0) return;
+    const int64_t es = (int64_t)dtype_size(dtype);
+    const bool wide = ((reinterpret_cast<uintptr_t>(src) | reinterpret_cast<uintptr_t>(dst) | (uintptr_t)(src_ld * es) | (uintptr_t)(dst_ld * es)) & 15) == 0;
+    jobs.b[jobs.n++] = CopyBlock{src, dst, src_ld, dst_ld, rows, cols, wide};
+}
+int64_t copy_workgroups(int32_t dtype, const CopyBlocks& jobs) {
+    const int64_t v = 16 / (int64_t)dtype_size(dtype);
+    int64_t pieces = 0;
+    for (int j = 0; j < jobs.n; ++j) pieces += jobs.b[j].rows * ceil_div(jobs.b[j].cols, v);
+    return ceil_div(pieces, 256);
+}
+int32_t launch_copies(int32_t dtype, const CopyBlocks& jobs, hipStream_t stream) {
+    if (jobs.n == 0) return ATTS_OK;
+    DISPATCH_T(dtype, hipLaunchKernelGGL(copy_blocks_kernel<T>, dim3((unsigned)copy_workgroups(dtype, jobs)), dim3(256), 0, stream, jobs);)
+    ATTS_LAUNCH_CHECK("copy_blocks_kernel");
     return ATTS_OK;
 }
 

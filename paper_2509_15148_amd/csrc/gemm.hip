@@ -963,7 +963,9 @@ TilePlan partial_plan(const GemmArgs& g) {
         const double us = fast_tile_us(rows, narrow, ceil_div(slabs, s)) + (double)s * g.M * g.N * 8 / 4.5e6 + 4.0;
         if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0};
     }
-    if (best.rows == 0 || (g.M > 128 && direct_plan(EPI_RESID_F32, g).us < best.us)) return none;
+    // without the split the norm that follows is a pass of its own (10 bytes an element less what the sums' pass moves anyway)
+    const double norm_us = 4.0 + (double)g.M * g.N * 6 / 4.5e6;
+    if (best.rows == 0 || (g.M > 128 && direct_plan(EPI_RESID_F32, g).us + norm_us < best.us)) return none;
     return best;
 }
 

@@ -90,6 +90,22 @@ def test_row_counts_between_tiles(P, K, T):
     assert np.array_equal(sc, sc2)
 
 
+@pytest.mark.parametrize("cfg,P,K,T", [
+    (ModelConfig(1, 2304, 4, 2, 16, 64, 50, "fp32"), 5, 2, 3),          # embedding rows longer than a thread block keeps in registers
+    (ModelConfig(1, 4352, 4, 2, 16, 64, 50, "bf16"), 5, 2, 3),
+    (ModelConfig(0, 264, 4, 2, 16, 64, 50, "bf16"), 9, 3, 4),           # no layer, no first norm
+])
+def test_start_of_a_pass_row_lengths(cfg, P, K, T):
+    import paper_2509_15148_amd as A
+    announce("score start", cfg, P, K, T)
+    w_dev, prefix, drafts = _case(cfg, P, K, T, seed=77)
+    lp, sc, flag = _run_gpu(A, cfg, w_dev, prefix, drafts)
+    ref_lp, ref_s = O.score_drafts(weights_to_numpy(w_dev), cfg, prefix, drafts)
+    assert flag == 0
+    assert np.abs(lp - ref_lp).max() <= TOL[cfg.dtype], np.abs(lp - ref_lp).max()
+    assert np.abs(sc - ref_s).max() <= TOL[cfg.dtype]
+
+
 def test_variable_draft_lengths_and_padding_ids():
     import paper_2509_15148_amd as A
     cfg = ModelConfig(2, 256, 4, 2, 128, 512, 1000, "bf16")
