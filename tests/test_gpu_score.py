@@ -94,6 +94,9 @@ def test_row_counts_between_tiles(P, K, T):
     (ModelConfig(1, 2304, 4, 2, 16, 64, 50, "fp32"), 5, 2, 3),          # embedding rows longer than a thread block keeps in registers
     (ModelConfig(1, 4352, 4, 2, 16, 64, 50, "bf16"), 5, 2, 3),
     (ModelConfig(0, 264, 4, 2, 16, 64, 50, "bf16"), 9, 3, 4),           # no layer, no first norm
+    (ModelConfig(2, 4352, 4, 2, 128, 1024, 768, "bf16"), 3, 2, 5),      # the same for the residual update that adds K slices:
+    (ModelConfig(2, 4352, 4, 2, 128, 1024, 768, "bf16"), 10, 5, 12),    # 13, 70 and 610 rows
+    (ModelConfig(2, 4352, 4, 2, 128, 1024, 768, "bf16"), 10, 5, 120),
 ])
 def test_start_of_a_pass_row_lengths(cfg, P, K, T):
     import paper_2509_15148_amd as A
