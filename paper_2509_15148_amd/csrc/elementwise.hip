@@ -45,26 +45,37 @@ __device__ __forceinline__ void store4<bf16>(bf16* dst, float4 v) {
     o[0] = (bf16)v.x; o[1] = (bf16)v.y; o[2] = (bf16)v.z; o[3] = (bf16)v.w;
     *reinterpret_cast<bf16x4*>(dst) = o;
 }
-
 template <typename T>
-__device__ __forceinline__ void rmsnorm_row(const float* __restrict__ x, const float* __restrict__ gain, float eps, int d,
-                                            T* __restrict__ o, float* red) {
+__device__ __forceinline__ float4 load4(const T* src);
+template <>
+__device__ __forceinline__ float4 load4<float>(const float* src) { return *reinterpret_cast<const float4*>(src); }
+template <>
+__device__ __forceinline__ float4 load4<bf16>(const bf16* src) {
+    const bf16x4 v = *reinterpret_cast<const bf16x4*>(src);
+    return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+}
+
+// The row's values come as pieces of four from `first` in the sum-of-squares pass, and from `again` where a row is too long
+// for the registers.  Embedding, norm kernel and scoring rows take the sum in this one order: the same row has the same norm in each.
+template <typename T, typename First, typename Again>
+__device__ __forceinline__ void rmsnorm_pieces(First first, Again again, const float* __restrict__ gain, float eps, int d,
+                                               T* __restrict__ o, float* red) {
     constexpr int kKeep = 4;
     const int n4 = d >> 2;
-    const float4* x4 = reinterpret_cast<const float4*>(x);
     const float4* g4 = reinterpret_cast<const float4*>(gain);
     float4 keep[kKeep];
     float ss = 0.f;
 #pragma unroll
     for (int q = 0; q < kKeep; ++q) {
         const int c = threadIdx.x + 256 * q;
-        keep[q] = c < n4 ? x4[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        keep[q] = c < n4 ? first(c) : make_float4(0.f, 0.f, 0.f, 0.f);
         ss += keep[q].x * keep[q].x + keep[q].y * keep[q].y + keep[q].z * keep[q].z + keep[q].w * keep[q].w;
     }
     for (int c = threadIdx.x + 256 * kKeep; c < n4; c += 256) {
-        const float4 v = x4[c];
+        const float4 v = first(c);
         ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     }
+    if (!gain) return;                                          // block-uniform
     ss = block_sum<256>(ss, red);
     const float inv = rsqrtf(ss / (float)d + eps);
 #pragma unroll
@@ -77,9 +88,16 @@ __device__ __forceinline__ void rmsnorm_row(const float* __restrict__ x, const f
         }
     }
     for (int c = threadIdx.x + 256 * kKeep; c < n4; c += 256) {
-        const float4 v = x4[c], g = g4[c];
+        const float4 v = again(c), g = g4[c];
         store4<T>(o + 4 * c, make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w));
     }
+}
+
+template <typename T>
+__device__ __forceinline__ void rmsnorm_row(const float* __restrict__ x, const float* __restrict__ gain, float eps, int d,
+                                            T* __restrict__ o, float* red) {
+    auto load = [&](int c) __attribute__((always_inline)) { return load4<float>(x + 4 * c); };
+    rmsnorm_pieces<T>(load, load, gain, eps, d, o, red);
 }
 
 template <typename T>
@@ -90,60 +108,19 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
 }
 
 // ---- S0: start of a pass: embedding gather + first norm, rotary table, tail of V^T ----------------------------
-// h = embedding of id (an id outside the vocabulary is read as 0 by the caller) and, with a gain vector, xn = rmsnorm(h).  16-byte
-// loads of the embedding row (rows are multiples of 16 bytes); up to kKeep pieces per thread stay in registers between
-// the passes, longer rows are read again.
+// h = embedding of id (an id outside the vocabulary is read as 0 by the caller) and, with a gain vector, xn = rmsnorm(h).
+// Pieces of four elements (rows are multiples of 16 bytes), in the norm's own order: with pieces of eight, a sum of another
+// order moved the bf16 roundings of the first layer, and with them the whole pass by 1.8e-4, for no gain in time.
 template <typename T>
 __device__ __forceinline__ void embed_norm_row(const T* __restrict__ src, int d, float* __restrict__ h, const float* __restrict__ gain,
                                                float eps, T* __restrict__ xn, float* red) {
-    constexpr int V = 16 / (int)sizeof(T), kKeep = 2;
-    const int n = d / V;
-    auto load = [&](int c, float (&x)[V]) __attribute__((always_inline)) {
-        const uint4 raw = *reinterpret_cast<const uint4*>(src + c * V);
-        const T* e = reinterpret_cast<const T*>(&raw);
-#pragma unroll
-        for (int u = 0; u < V; ++u) x[u] = to_f32<T>(e[u]);
+    auto load = [&](int c) __attribute__((always_inline)) { return load4<T>(src + 4 * c); };
+    auto load_and_store = [&](int c) __attribute__((always_inline)) {
+        const float4 v = load(c);
+        store4<float>(h + 4 * c, v);
+        return v;
     };
-    float keep[kKeep][V], ss = 0.f;
-    auto store_h = [&](int c, const float (&x)[V]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < V; u += 4) *reinterpret_cast<float4*>(h + c * V + u) = make_float4(x[u], x[u + 1], x[u + 2], x[u + 3]);
-#pragma unroll
-        for (int u = 0; u < V; ++u) ss += x[u] * x[u];
-    };
-    auto store_n = [&](int c, const float (&x)[V], float inv) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < V; u += 4) {
-            const float4 g = *reinterpret_cast<const float4*>(gain + c * V + u);
-            store4<T>(xn + c * V + u, make_float4(x[u] * inv * g.x, x[u + 1] * inv * g.y, x[u + 2] * inv * g.z, x[u + 3] * inv * g.w));
-        }
-    };
-#pragma unroll
-    for (int q = 0; q < kKeep; ++q) {
-        const int c = threadIdx.x + 256 * q;
-        if (c < n) {
-            load(c, keep[q]);
-            store_h(c, keep[q]);
-        }
-    }
-    for (int c = threadIdx.x + 256 * kKeep; c < n; c += 256) {
-        float x[V];
-        load(c, x);
-        store_h(c, x);
-    }
-    if (!gain) return;                                          // block-uniform
-    ss = block_sum<256>(ss, red);
-    const float inv = rsqrtf(ss / (float)d + eps);
-#pragma unroll
-    for (int q = 0; q < kKeep; ++q) {
-        const int c = threadIdx.x + 256 * q;
-        if (c < n) store_n(c, keep[q], inv);
-    }
-    for (int c = threadIdx.x + 256 * kKeep; c < n; c += 256) {
-        float x[V];
-        load(c, x);
-        store_n(c, x, inv);
-    }
+    rmsnorm_pieces<T>(load_and_store, load, gain, eps, d, xn, red);
 }
 
 // Everything a pass needs before its first projection, in one launch (each of these is a few microseconds by itself, most of

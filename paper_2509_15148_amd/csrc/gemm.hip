@@ -1114,8 +1114,9 @@ int32_t launch_t(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
     return fail(ATTS_ERR_INVALID_ARG, "unknown GEMM epilogue %d", (int)epi);
 }
 
-__global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const float* __restrict__ target_logit,
-                                      int B, int n_part, const uint8_t* __restrict__ valid, float* __restrict__ lp) {
+template <int kHeld>
+__global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const float* __restrict__ target_logit, int B, int n_part,
+                                      const uint8_t* __restrict__ valid, float* __restrict__ lp) {
     // one wavefront per row
     const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -1124,28 +1125,39 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
         if (lane == 0) lp[row] = 0.f;
         return;
     }
-    // one pass, eight partials per lane in flight, a running maximum per lane (two passes with one load at a time were a
-    // chain of fifty load latencies: 4096 rows of 1584 partials 32.4 -> 12.3 us, 385 of 1188 15.8 -> 7.2)
+    // Two passes over the row's partials, the sum against the row's final maximum and in the order of the columns.  The first
+    // 64 kHeld are requested at once and held in registers in between, the rest eight at a time (one load at a time was a
+    // chain of fifty load latencies: 4096 rows of 1584 partials 31.4 -> 12.1 us, 385 rows 11.8 -> 5.2; one pass with a running
+    // maximum per lane 11.3 and 5.3, for other roundings of the sum).
     const float2* p = partials + (int64_t)row * n_part;
-    float m = -INFINITY, s = 0.f;
-    for (int i0 = lane; i0 < n_part; i0 += 64 * 8) {
-        float2 q[8];
-        float top = m;
+    const float2 none = make_float2(-INFINITY, 0.f);
+    float2 held[kHeld];
+    float mx = -INFINITY;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            q[u] = i0 + 64 * u < n_part ? p[i0 + 64 * u] : make_float2(-INFINITY, 0.f);
-            top = fmaxf(top, q[u].x);
-        }
-        if (top > m) s *= __expf(m - top);              // m = -inf: s is 0
-        m = top;
+    for (int u = 0; u < kHeld; ++u) held[u] = lane + 64 * u < n_part ? p[lane + 64 * u] : none;
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (q[u].y > 0.f) s += q[u].y * __expf(q[u].x - m);
+    for (int u = 0; u < kHeld; ++u) mx = fmaxf(mx, held[u].x);
+    for (int i0 = lane + 64 * kHeld; i0 < n_part; i0 += 64 * 8) {
+        float x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = i0 + 64 * u < n_part ? p[i0 + 64 * u].x : -INFINITY;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mx = fmaxf(mx, x[u]);
     }
-    float mx = m;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    float sum = mx > m ? s * __expf(m - mx) : s;
+    float sum = 0.f;
+#pragma unroll
+    for (int u = 0; u < kHeld; ++u)
+        if (held[u].y > 0.f) sum += held[u].y * __expf(held[u].x - mx);
+    for (int i0 = lane + 64 * kHeld; i0 < n_part; i0 += 64 * 8) {
+        float2 q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = i0 + 64 * u < n_part ? p[i0 + 64 * u] : none;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (q[u].y > 0.f) sum += q[u].y * __expf(q[u].x - mx);
+    }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
     if (lane == 0) lp[row] = target_logit[row] - (mx + __logf(sum));
@@ -1244,8 +1256,11 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
 int32_t launch_lmhead_combine(const float2* partials, const float* target_logit, int32_t B, int32_t n_part,
                               const uint8_t* valid, float* lp, hipStream_t stream) {
     const int rows_per_block = 4;
-    hipLaunchKernelGGL(lmhead_combine_kernel, dim3((unsigned)ceil_div(B, rows_per_block)), dim3(64 * rows_per_block), 0,
-                       stream, partials, target_logit, B, n_part, valid, lp);
+    const dim3 grid((unsigned)ceil_div(B, rows_per_block)), block(64 * rows_per_block);
+    if (n_part <= 64 * 8)
+        hipLaunchKernelGGL(lmhead_combine_kernel<8>, grid, block, 0, stream, partials, target_logit, B, n_part, valid, lp);
+    else
+        hipLaunchKernelGGL(lmhead_combine_kernel<32>, grid, block, 0, stream, partials, target_logit, B, n_part, valid, lp);
     ATTS_LAUNCH_CHECK("lmhead_combine_kernel");
     return ATTS_OK;
 }

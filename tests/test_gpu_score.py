@@ -1,4 +1,6 @@
 """End-to-end parity of atts_score_drafts with the oracle (K independent fp64 causal forwards)."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -107,6 +109,22 @@ def test_start_of_a_pass_row_lengths(cfg, P, K, T):
     assert flag == 0
     assert np.abs(lp - ref_lp).max() <= TOL[cfg.dtype], np.abs(lp - ref_lp).max()
     assert np.abs(sc - ref_s).max() <= TOL[cfg.dtype]
+
+
+@pytest.mark.parametrize("d", [1024, 4352])
+def test_first_norm_has_the_bits_of_the_norm_kernel(d):
+    """A first layer whose two output projections are zero hands the embeddings on unchanged, so the layer after it must
+    see the norm (taken by the norm kernel there, with the embedding gather in a model without that layer) bit for bit."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(1, d, 8, 2, 128, 256, 768, "bf16")
+    announce("score first norm", d)
+    w, prefix, drafts = _case(cfg, 100, 6, 250, seed=5)
+    longer = {k: (v + v if isinstance(v, list) else v) for k, v in w.items()}
+    for name in ("wo", "w_down"):
+        longer[name] = [torch.zeros_like(w[name][0]), w[name][0]]
+    lp, sc, _ = _run_gpu(A, cfg, w, prefix, drafts)
+    lp2, sc2, _ = _run_gpu(A, dataclasses.replace(cfg, n_layers=2), longer, prefix, drafts)
+    assert np.array_equal(lp, lp2) and np.array_equal(sc, sc2)
 
 
 def test_variable_draft_lengths_and_padding_ids():
