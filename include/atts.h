@@ -105,7 +105,8 @@ int32_t atts_model_create(const atts_model_desc* desc, const atts_weights* weigh
 int32_t atts_model_destroy(atts_model* model);
 
 /* Bytes of device workspace atts_score_drafts needs for a prefix of P tokens and K drafts
- * of at most T_max tokens. */
+ * of at most T_max tokens.  Never less for a larger P, K or T_max: a workspace for the largest call of a
+ * program serves its smaller ones. */
 int32_t atts_workspace_bytes(const atts_model* model, int32_t P, int32_t K, int32_t T_max, size_t* out_bytes);
 
 /* Verification ("How to perform rejection sampling via conformal prediction", paragraph
@@ -254,6 +255,43 @@ int32_t atts_attention_shared_prefix(int32_t dtype, const void* qkv, void* out,
                                      int32_t P, int32_t K, int32_t T,
                                      int32_t n_q, int32_t n_kv, int32_t hd,
                                      void* workspace, size_t workspace_bytes, void* hip_stream);
+
+/* ------------------------------------------------------------------------------------
+ * Which kernels the matrix products of a call take (host only, no device is touched; for tests and measurements)
+ *
+ *   atts_gemm_routes   atts_gemm_nt of this shape, and the LM head of atts_lmhead_logprobs with M rows and N
+ *                      vocabulary entries
+ *   atts_pass_routes   the products of one pass of a model: scoring with everything computed, scoring against a
+ *                      cached prefix of P rows, or one decoding step of a continuation (n_new as there), with
+ *                      the bytes of workspace the call needs
+ * ---------------------------------------------------------------------------------- */
+#define ATTS_KERNEL_GENERAL_128 0   /* any shape, 128 x 128 tiles                                              */
+#define ATTS_KERNEL_GENERAL_256 1   /* any shape, 256 x 256 tiles                                              */
+#define ATTS_KERNEL_SMALL       2   /* products of few tiles                                                   */
+#define ATTS_KERNEL_FEW_ROWS    3   /* at most 16 rows                                                         */
+#define ATTS_KERNEL_ALIGNED     4   /* aligned bf16 shapes                                                     */
+#define ATTS_KERNEL_EXCHANGED   5   /* aligned bf16 LM head, vocabulary entries as tile rows                   */
+
+#define ATTS_PASS_SCORE        0
+#define ATTS_PASS_SCORE_CACHED 1
+#define ATTS_PASS_CONTINUE     2
+
+typedef struct {
+    int32_t kernel;                 /* ATTS_KERNEL_*                                                           */
+    int32_t tile_rows;              /* rows of a tile of the aligned kernels, else 0                           */
+    int32_t slices;                 /* slices the inner dimension is cut into over workgroups (1: not)         */
+    int32_t head_rows, tail_rows;   /* tail_rows != 0: the rows from head_rows on take a second launch with tiles of tail_rows */
+} atts_gemm_route;
+
+typedef struct {
+    atts_gemm_route qkv, o, gate_up, down, lm_head;
+    int32_t qkv_fused;              /* rotary embedding and transposed values in the projection's epilogue or finish */
+    size_t workspace_bytes;
+} atts_pass_route;
+
+int32_t atts_gemm_routes(int32_t dtype, int32_t M, int32_t N, int32_t Kdim, atts_gemm_route* gemm, atts_gemm_route* lm_head);
+int32_t atts_pass_routes(const atts_model_desc* desc, int32_t pass, int32_t P, int32_t K, int32_t T_max, int32_t n_new,
+                         atts_pass_route* out);
 
 /* ------------------------------------------------------------------------------------
  * Stage timing of atts_score_drafts (measurement aid, off by default, not thread-safe)

@@ -34,7 +34,7 @@ EXPORTS = (
     "atts_calibrate_online", "atts_classify_ordinal", "atts_classify_conditional", "atts_calib_export",
     "atts_calib_import", "atts_classic_workspace_bytes", "atts_classic_normalize", "atts_classic_threshold",
     "atts_classic_prediction_sets",
-    "atts_profile_enable", "atts_profile_read",
+    "atts_gemm_routes", "atts_pass_routes", "atts_profile_enable", "atts_profile_read",
 )
 
 STAGES = ("embed", "norm", "gemm_qkv", "rope", "attention", "gemm_o", "gemm_gate_up", "gemm_down", "gather_norm",
@@ -59,6 +59,19 @@ class _Weights(ctypes.Structure):
                 ("attn_norm", ctypes.POINTER(ctypes.c_void_p)), ("wqkv", ctypes.POINTER(ctypes.c_void_p)),
                 ("wo", ctypes.POINTER(ctypes.c_void_p)), ("ffn_norm", ctypes.POINTER(ctypes.c_void_p)),
                 ("w_gate_up", ctypes.POINTER(ctypes.c_void_p)), ("w_down", ctypes.POINTER(ctypes.c_void_p))]
+
+
+KERNEL_GENERAL_128, KERNEL_GENERAL_256, KERNEL_SMALL, KERNEL_FEW_ROWS, KERNEL_ALIGNED, KERNEL_EXCHANGED = range(6)
+PASS_SCORE, PASS_SCORE_CACHED, PASS_CONTINUE = range(3)
+
+
+class GemmRoute(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "tile_rows", "slices", "head_rows", "tail_rows")]
+
+
+class PassRoute(ctypes.Structure):
+    _fields_ = [(n, GemmRoute) for n in ("qkv", "o", "gate_up", "down", "lm_head")] + \
+        [("qkv_fused", ctypes.c_int32), ("workspace_bytes", ctypes.c_size_t)]
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
@@ -430,6 +443,23 @@ def atts_classic_prediction_sets(scores: torch.Tensor, tau: torch.Tensor, member
         raise AttsError(ERR_INVALID_ARG, "member must have one element per score, tau one element")
     _check(_lib.atts_classic_prediction_sets(_ptr(scores, torch.float32, "scores"), ctypes.c_int64(scores.numel()),
                                              _ptr(tau, torch.float32, "tau"), _ptr(member, torch.uint8, "member"), _stream()))
+
+
+def atts_gemm_routes(dtype: torch.dtype, M: int, N: int, Kdim: int):
+    """(route of atts_gemm_nt, route of the LM head with M rows and N vocabulary entries)"""
+    gemm, head = GemmRoute(), GemmRoute()
+    _check(_lib.atts_gemm_routes(_dtype_code(dtype), M, N, Kdim, ctypes.byref(gemm), ctypes.byref(head)))
+    return gemm, head
+
+
+def atts_pass_routes(cfg, pass_kind: int, P: int, K: int, T_max: int, n_new: int = 1) -> PassRoute:
+    """cfg: a model configuration with the matrices' torch dtype as `torch_dtype`, or a _ModelDesc"""
+    desc = cfg if isinstance(cfg, _ModelDesc) else _ModelDesc(
+        cfg.n_layers, cfg.d_model, cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.d_ffn, cfg.vocab,
+        _dtype_code(cfg.torch_dtype), cfg.rope_theta, cfg.rms_eps)
+    out = PassRoute()
+    _check(_lib.atts_pass_routes(ctypes.byref(desc), pass_kind, P, K, T_max, n_new, ctypes.byref(out)))
+    return out
 
 
 def atts_profile_enable(on: bool) -> None:

@@ -82,35 +82,62 @@ void prof_clear() {
     g_prof.clear();
 }
 
-// Sub-buffers of the scoring workspace, each 256-byte aligned.
-struct Workspace {
-    size_t h, xn, qkv, kpart, vt, ao, act, rope, xs, targets, valid, partials, zt, lp, total;
-    int64_t ldv;
-    int32_t n_part;
-};
-
 // GEMM inputs of the bf16 path are allocated in whole tiles (768 rows = a multiple of both tile heights): the
 // aligned kernel then serves every row count (it reads the pad rows, whatever they hold, and drops their results).
 bool pads_rows(const atts_model_desc& d) { return d.dtype == ATTS_DTYPE_BF16; }
 constexpr int kSplitQkvRows = 128;
 
-// K-split projections (few rows, narrow output) store one partial result per K slice; the three of a layer (QKV, O,
-// down) use the same buffer one after the other.  Slices per projection for M rows through the model:
-struct SplitPlan {
-    int32_t qkv, o, down;        // 1 = not split (direct epilogue)
-    size_t bytes;                // of the shared partial buffer
+// Sub-buffers of the scoring workspace, each 256-byte aligned.
+//
+// K-split projections (few rows, narrow output) store one partial result per K slice.  The three of a layer store them in one
+// place, one after the other: from the end of the act rows in use (padded to whole tiles) on, over buffers in which nothing is
+// alive between the projection and the pass that adds the slices, and a projection is cut into no more slices than fit there:
+//   QKV   up to qkv
+//   O     up to ao    (the attention is through with qkv, the next layer writes it anew; xs ... lp are written after the layers)
+//   down  up to vt    (with ao, and what is added behind lp where these buffers are too small)
+// vt and rope stay out of it: their tail columns and rows are written once for all layers.  One place: with QKV's and O's sums
+// in the rows of act that gate/up then writes, a pass of 128 rows took 1 % longer.  No size falls when P, K or T_max grows: a
+// workspace for a program's largest call serves its smaller ones.
+struct Workspace {
+    size_t h, xn, act, qkv, xs, targets, valid, partials, zt, lp, ao, vt, rope, total;
+    int64_t ldv;
+    int32_t n_part;
 };
-SplitPlan split_plan(const atts_model_desc& d, int64_t M) {
-    SplitPlan p{1, 1, 1, 0};
-    if (M < 1 || M > (1 << 24)) return p;
+
+GemmArgs gemm_shape(const atts_model_desc& d, int64_t M, int32_t N, int32_t Kd, size_t room = 0) {
+    GemmArgs g{};
+    g.M = (int32_t)M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.ldc = N; g.a_rows_padded = pads_rows(d);
+    g.room = room;
+    return g;
+}
+
+// Where the sums of a pass of M rows lie, and how many bytes there are for them.
+struct SumsRoom {
+    size_t at_qkv, at_o, at_down;      // offsets of the sums in the workspace
+    size_t qkv, o, down;               // bytes from there on
+};
+SumsRoom sums_room(const atts_model_desc& d, const Workspace& w, int64_t M) {
+    const size_t rows = pads_rows(d) ? align_up((size_t)M, 768) : (size_t)M;
+    const size_t at = w.act + align_up(rows * d.d_ffn * dtype_size(d.dtype), 256);
     const int32_t qd = d.n_q_heads * d.head_dim, qkv_out = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
-    const bool padded = pads_rows(d);
-    if (M <= kSplitQkvRows) p.qkv = gemm_partial_slices(d.dtype, (int32_t)M, qkv_out, d.d_model, padded);
-    p.o = gemm_partial_slices(d.dtype, (int32_t)M, d.d_model, qd, padded);
-    p.down = gemm_partial_slices(d.dtype, (int32_t)M, d.d_model, d.d_ffn, padded);
-    auto need = [&](int32_t slices, int64_t n) { return slices > 1 ? (size_t)slices * (size_t)M * (size_t)n * sizeof(float) : (size_t)0; };
-    p.bytes = std::max(need(p.qkv, qkv_out), std::max(need(p.o, d.d_model), need(p.down, d.d_model)));
-    return p;
+    // where that is too little for QKV or O (70B, O, 584 to 768 rows), from the start of act
+    auto start = [&](int32_t N, int32_t Kd, size_t end) {
+        const size_t wanted = (size_t)gemm_route(d.dtype, EPI_PARTIAL_F32, gemm_shape(d, M, N, Kd, SIZE_MAX)).slices * M * N * sizeof(float);
+        return at + wanted <= end ? at : w.act;
+    };
+    const size_t at_qkv = start(qkv_out, d.d_model, w.qkv), at_o = start(d.d_model, qd, w.ao);
+    return SumsRoom{at_qkv, at_o, at, w.qkv - at_qkv, w.ao - at_o, w.vt - at};
+}
+
+// K slices per projection for M rows through the model; 1 = not split (direct epilogue).
+struct SplitPlan {
+    int32_t qkv, o, down;
+};
+SplitPlan split_plan(const atts_model_desc& d, int64_t M, const SumsRoom& room) {
+    const int32_t qd = d.n_q_heads * d.head_dim, qkv_out = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
+    auto slices = [&](int32_t N, int32_t Kd, size_t room) { return gemm_route(d.dtype, EPI_PARTIAL_F32, gemm_shape(d, M, N, Kd, room)).slices; };
+    return SplitPlan{M <= kSplitQkvRows ? slices(qkv_out, d.d_model, room.qkv) : 1, slices(d.d_model, qd, room.o),
+                     slices(d.d_model, d.d_ffn, room.down)};
 }
 
 Workspace carve(const atts_model_desc& d, ScoreShape s) {
@@ -127,21 +154,32 @@ Workspace carve(const atts_model_desc& d, ScoreShape s) {
     };
     w.h = take(R * d.d_model * sizeof(float));
     w.xn = take(Ra * d.d_model * es);
+    const size_t used = (pads_rows(d) ? align_up(R, 768) : R) * (size_t)d.d_ffn * es;
+    size_t spare = (Ra - (pads_rows(d) ? align_up(R, 768) : R)) * (size_t)d.d_ffn * es;
+    if (pads_rows(d)) {
+        // a feed-forward layer narrower than 3.5 d_model (the published widths have 3.5 to 5.4) would leave the sums less room
+        const int32_t qd = d.n_q_heads * d.head_dim, qkv_out = qd + 2 * d.n_kv_heads * d.head_dim;
+        const size_t sums = std::max(partial_bytes_bound(d.dtype, std::min(s.R(), kSplitQkvRows), qkv_out, d.d_model, true),
+                                     partial_bytes_bound(d.dtype, s.R(), d.d_model, qd, true));
+        spare = std::max(spare, std::min(sums, (size_t)768 * d.d_model * es * 7 / 2));
+    }
+    w.act = take(used + spare);
     w.qkv = take(R * (size_t)(d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim * es);
-    // partial sums of the K-split projections: the call computes all R rows, or the K T draft rows after a cached prefix
-    w.kpart = take(std::max(split_plan(d, (int64_t)R).bytes, split_plan(d, (int64_t)B).bytes));
-    w.ldv = (int64_t)align_up(R, 64);
-    w.vt = take(attention_uses_vt(d.dtype, d.head_dim) ? (size_t)d.n_kv_heads * d.head_dim * w.ldv * es : 0);
-    w.ao = take(Ra * (size_t)d.n_q_heads * d.head_dim * es);
-    w.act = take(Ra * (size_t)d.d_ffn * es);
-    w.rope = take(R * (size_t)(d.head_dim / 2) * sizeof(float2));
     w.xs = take(Ba * d.d_model * es);
     w.targets = take(B * sizeof(int32_t));
     w.valid = take(B);
-    w.n_part = lmhead_num_partials(d.dtype, s.B(), d.vocab, d.d_model, pads_rows(d));
-    w.partials = take(B * (size_t)w.n_part * sizeof(float2));
+    w.n_part = gemm_route(d.dtype, EPI_LMHEAD, gemm_shape(d, (int64_t)B, d.vocab, d.d_model)).n_part;
+    w.partials = take((size_t)lmhead_partials_bound(d.dtype, s.B(), d.vocab, d.d_model, pads_rows(d)) * sizeof(float2));
     w.zt = take(B * sizeof(float));
     w.lp = take(B * sizeof(float));
+    const size_t ao = align_up(Ra * (size_t)d.n_q_heads * d.head_dim * es, 256);
+    // room for the sums of any split of `down` up to R rows, where the buffers do not have it (7B: 257 to 1800 rows)
+    const size_t down_end = w.act + align_up(used, 256) + partial_bytes_bound(d.dtype, s.R(), d.d_model, d.d_ffn, pads_rows(d));
+    if (off + ao < down_end) take(down_end - ao - off);
+    w.ao = take(ao);
+    w.ldv = (int64_t)align_up(R, 64);
+    w.vt = take(attention_uses_vt(d.dtype, d.head_dim) ? (size_t)d.n_kv_heads * d.head_dim * w.ldv * es : 0);
+    w.rope = take(R * (size_t)(d.head_dim / 2) * sizeof(float2));
     w.total = off;
     return w;
 }
@@ -150,6 +188,20 @@ int32_t check_score_shape(const char* fn, int32_t P, int32_t K, int32_t T) {
     if (P < 1 || K < 1 || T < 1) return fail(ATTS_ERR_INVALID_ARG, "%s: P = %d, K = %d, T_max = %d must all be >= 1", fn, P, K, T);
     if ((int64_t)P + T > (1 << 20)) return fail(ATTS_ERR_INVALID_ARG, "%s: P + T_max = %lld exceeds 1048576", fn, (long long)P + T);
     if ((int64_t)P + (int64_t)K * T > (1 << 24)) return fail(ATTS_ERR_INVALID_ARG, "%s: P + K T_max exceeds 2^24 rows", fn);
+    return ATTS_OK;
+}
+
+int32_t check_model(const char* fn, const atts_model_desc& d) {
+    if (d.dtype != ATTS_DTYPE_F32 && d.dtype != ATTS_DTYPE_BF16)
+        return fail(ATTS_ERR_INVALID_ARG, "%s: unknown dtype %d", fn, d.dtype);
+    if (d.n_layers < 0 || d.d_model < 1 || d.n_q_heads < 1 || d.n_kv_heads < 1 || d.head_dim < 2 || d.d_ffn < 1 || d.vocab < 1)
+        return fail(ATTS_ERR_INVALID_ARG, "%s: non-positive dimension", fn);
+    if (d.n_q_heads % d.n_kv_heads) return fail(ATTS_ERR_SHAPE, "%s: n_kv_heads must divide n_q_heads", fn);
+    if (d.head_dim % 2 || d.head_dim > 256) return fail(ATTS_ERR_SHAPE, "%s: head_dim must be even and <= 256", fn);
+    const size_t es = dtype_size(d.dtype);
+    if ((d.d_model * es) % 16 || (d.d_ffn * es) % 16 || ((size_t)d.n_q_heads * d.head_dim * es) % 16 || (d.head_dim * es) % 16)
+        return fail(ATTS_ERR_SHAPE, "%s: d_model, d_ffn and head_dim rows must be multiples of 16 bytes", fn);
+    if (!(d.rms_eps >= 0.f) || !(d.rope_theta > 0.f)) return fail(ATTS_ERR_INVALID_ARG, "%s: bad rms_eps / rope_theta", fn);
     return ATTS_OK;
 }
 
@@ -173,16 +225,7 @@ int32_t atts_model_create(const atts_model_desc* desc, const atts_weights* w, at
     *out = nullptr;
     if (!desc || !w) return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: desc / weights is NULL");
     const atts_model_desc& d = *desc;
-    if (d.dtype != ATTS_DTYPE_F32 && d.dtype != ATTS_DTYPE_BF16)
-        return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: unknown dtype %d", d.dtype);
-    if (d.n_layers < 0 || d.d_model < 1 || d.n_q_heads < 1 || d.n_kv_heads < 1 || d.head_dim < 2 || d.d_ffn < 1 || d.vocab < 1)
-        return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: non-positive dimension");
-    if (d.n_q_heads % d.n_kv_heads) return fail(ATTS_ERR_SHAPE, "atts_model_create: n_kv_heads must divide n_q_heads");
-    if (d.head_dim % 2 || d.head_dim > 256) return fail(ATTS_ERR_SHAPE, "atts_model_create: head_dim must be even and <= 256");
-    const size_t es = dtype_size(d.dtype);
-    if ((d.d_model * es) % 16 || (d.d_ffn * es) % 16 || ((size_t)d.n_q_heads * d.head_dim * es) % 16 || (d.head_dim * es) % 16)
-        return fail(ATTS_ERR_SHAPE, "atts_model_create: d_model, d_ffn and head_dim rows must be multiples of 16 bytes");
-    if (!(d.rms_eps >= 0.f) || !(d.rope_theta > 0.f)) return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: bad rms_eps / rope_theta");
+    ATTS_TRY(check_model("atts_model_create", d));
     if (!w->tok_embed || !w->final_norm || !w->lm_head) return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: NULL embedding / final norm / LM head");
     if (d.n_layers > 0 && (!w->attn_norm || !w->wqkv || !w->wo || !w->ffn_norm || !w->w_gate_up || !w->w_down))
         return fail(ATTS_ERR_INVALID_ARG, "atts_model_create: NULL per-layer pointer array");
@@ -286,11 +329,13 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
     // (a continuation call wants the value rows in the qkv buffer: the unfused path leaves them there)
     const bool fuse_rope = vt != nullptr && !tree && row0 % 4 == 0 && qkv_rope_fusable(d.dtype, M, qkv_out, d.d_model, d.head_dim, padded);
     float* h0 = h + (size_t)row0 * d.d_model;
-    // few rows: projections with a narrow output cut their K range over the chip (one partial result per slice in
-    // kpart); the consumers add the slices in order: the QKV finish (RoPE / V transpose), and the residual update, which
+    // few rows: projections with a narrow output cut their K range over the chip (one partial result per slice);
+    // the consumers add the slices in order: the QKV finish (RoPE / V transpose), and the residual update, which
     // also applies the RMSNorm that follows it
-    float* kpart = reinterpret_cast<float*>(base + ws.kpart);
-    SplitPlan plan = split_plan(d, M);
+    const SumsRoom room = sums_room(d, ws, M);
+    SplitPlan plan = split_plan(d, M, room);
+    float *sums_qkv = reinterpret_cast<float*>(base + room.at_qkv), *sums_o = reinterpret_cast<float*>(base + room.at_o);
+    float* sums_down = reinterpret_cast<float*>(base + room.at_down);
     if (!fuse_rope) plan.qkv = 1;
     const bool split_qkv = plan.qkv > 1;
 
@@ -321,10 +366,10 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
         g.M = M; g.N = qkv_out; g.Kd = d.d_model;
         g.lda = d.d_model; g.ldw = d.d_model; g.ldc = qkv_out; g.a_rows_padded = padded;
         if (split_qkv) {
-            g.out = kpart; g.n_slices = plan.qkv;
+            g.out = sums_qkv; g.n_slices = plan.qkv; g.room = room.qkv;
             StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
             ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
-            ATTS_TRY(launch_qkv_finish(d.dtype, kpart, plan.qkv, (int64_t)M * qkv_out, rope + (size_t)row0 * (d.head_dim / 2), M,
+            ATTS_TRY(launch_qkv_finish(d.dtype, sums_qkv, plan.qkv, (int64_t)M * qkv_out, rope + (size_t)row0 * (d.head_dim / 2), M,
                                        d.n_q_heads, d.n_kv_heads, d.head_dim, qkv + (size_t)row0 * qkv_out * es,
                                        vt + (size_t)row0 * es, ws.ldv, cached, st));
             cached.n = 0;
@@ -381,13 +426,13 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
         g.a = ao + (size_t)row0 * qd * es; g.w = m->wo[l]; g.out = h0; g.M = M; g.N = d.d_model; g.Kd = qd;
         g.lda = qd; g.ldw = qd; g.ldc = d.d_model; g.a_rows_padded = padded;
         if (plan.o > 1) {
-            g.out = kpart; g.n_slices = plan.o;
+            g.out = sums_o; g.n_slices = plan.o; g.room = room.o;
             {
                 StageTimer t_(ATTS_STAGE_GEMM_O, st);
                 ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
             }
             StageTimer t_(ATTS_STAGE_NORM, st);
-            ATTS_TRY(launch_resid_norm(d.dtype, h0, kpart, plan.o, (int64_t)M * d.d_model, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
+            ATTS_TRY(launch_resid_norm(d.dtype, h0, sums_o, plan.o, (int64_t)M * d.d_model, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
         } else {
             {
                 StageTimer t_(ATTS_STAGE_GEMM_O, st);
@@ -397,7 +442,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
         }
         g = GemmArgs{};
-        g.a = xn0; g.w = m->w_gate_up[l]; g.out = act + (size_t)row0 * d.d_ffn * es;
+        g.a = xn0; g.w = m->w_gate_up[l]; g.out = act;             // act: the M rows of this pass from its start on
         g.M = M; g.N = d.d_ffn; g.Kd = d.d_model;
         g.lda = d.d_model; g.ldw = d.d_model; g.ldc = d.d_ffn; g.a_rows_padded = padded;
         {
@@ -405,10 +450,10 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             ATTS_TRY(launch_gemm(d.dtype, EPI_SWIGLU, g, st));
         }
         g = GemmArgs{};
-        g.a = act + (size_t)row0 * d.d_ffn * es; g.w = m->w_down[l]; g.out = h0; g.M = M; g.N = d.d_model; g.Kd = d.d_ffn;
+        g.a = act; g.w = m->w_down[l]; g.out = h0; g.M = M; g.N = d.d_model; g.Kd = d.d_ffn;
         g.lda = d.d_ffn; g.ldw = d.d_ffn; g.ldc = d.d_model; g.a_rows_padded = padded;
         if (plan.down > 1) {
-            g.out = kpart; g.n_slices = plan.down;
+            g.out = sums_down; g.n_slices = plan.down; g.room = room.down;
             {
                 StageTimer t_(ATTS_STAGE_GEMM_DOWN, st);
                 ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
@@ -416,7 +461,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             // with the next layer's attention norm (none after the last layer: the final norm runs on the scoring rows only)
             xn_ready = l + 1 < d.n_layers;
             StageTimer t_(ATTS_STAGE_NORM, st);
-            ATTS_TRY(launch_resid_norm(d.dtype, h0, kpart, plan.down, (int64_t)M * d.d_model, xn_ready ? m->attn_norm[l + 1] : nullptr,
+            ATTS_TRY(launch_resid_norm(d.dtype, h0, sums_down, plan.down, (int64_t)M * d.d_model, xn_ready ? m->attn_norm[l + 1] : nullptr,
                                        d.rms_eps, M, d.d_model, xn0, st));
         } else {
             xn_ready = false;
@@ -575,9 +620,12 @@ int32_t atts_score_drafts_cached(const atts_prefix* p, const int32_t* draft_ids,
 
 namespace {
 struct ContinueSpace {
-    size_t scoring, kc, vc, h, xn, ao, act, xs, kpart, q, logits, argmax, rope, total;
+    // Partial sums of a decoding step's projections: from the scoring workspace's act on (that pass is over, and of its buffers
+    // only h, which lies before, is read once more) to the end of `kpart`, which by itself holds the one full QKV result.
+    size_t sums, kpart, kc, vc, h, xn, ao, act, xs, q, logits, argmax, rope, total;
     int32_t Tc;
     size_t layer_bytes;
+    size_t room() const { return kc - sums; }
 };
 
 ContinueSpace carve_continue(const atts_model_desc& d, int32_t P, int32_t Kr, int32_t T, int32_t n_new) {
@@ -589,13 +637,15 @@ ContinueSpace carve_continue(const atts_model_desc& d, int32_t P, int32_t Kr, in
     c.Tc = T + n_new;
     const size_t Rc = (size_t)P + (size_t)Kr * c.Tc;
     c.layer_bytes = align_up(Rc * kvd * es, 256);
-    size_t off = align_up(carve(d, ScoreShape{P, Kr, T}).total, 256);
-    c.scoring = 0;
+    const Workspace scoring = carve(d, ScoreShape{P, Kr, T});
+    c.sums = scoring.act;
+    size_t off = scoring.total;
     auto take = [&](size_t bytes) {
         size_t at = off;
         off += align_up(bytes, 256);
         return at;
     };
+    c.kpart = take((size_t)Kr * qkv_out * sizeof(float));
     c.kc = take(L * c.layer_bytes);
     c.vc = take(L * c.layer_bytes);
     c.h = take((size_t)Kr * d.d_model * sizeof(float));
@@ -603,18 +653,19 @@ ContinueSpace carve_continue(const atts_model_desc& d, int32_t P, int32_t Kr, in
     c.ao = take(rows_a * qd * es);
     c.act = take(rows_a * (size_t)d.d_ffn * es);
     c.xs = take(rows_a * d.d_model * es);
-    // a decoding step's projections with a narrow output: one partial result per K slice (or the one full result)
-    {
-        SplitPlan sp = split_plan(d, Kr);
-        sp.qkv = gemm_partial_slices(d.dtype, Kr, (int32_t)qkv_out, d.d_model, pads_rows(d));
-        c.kpart = take(std::max(sp.bytes, (size_t)sp.qkv * Kr * qkv_out * sizeof(float)));
-    }
     c.q = take((size_t)Kr * qd * es);
     c.logits = take((size_t)Kr * d.vocab * sizeof(float));
     c.argmax = take(argmax_scratch_bytes(Kr));
     c.rope = take(((size_t)P + c.Tc) * (d.head_dim / 2) * sizeof(float2));
     c.total = off;
     return c;
+}
+
+SplitPlan decode_split_plan(const atts_model_desc& d, int32_t Kr, const ContinueSpace& c) {
+    SplitPlan plan = split_plan(d, Kr, SumsRoom{c.sums, c.sums, c.sums, c.room(), c.room(), c.room()});
+    // the QKV sums of a step always pass through fp32
+    plan.qkv = gemm_route(d.dtype, EPI_PARTIAL_F32, gemm_shape(d, Kr, (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim, d.d_model, c.room())).slices;
+    return plan;
 }
 
 int32_t check_continue_shape(const char* fn, const atts_prefix* p, int32_t Kr, int32_t T, int32_t n_new) {
@@ -665,15 +716,14 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
     char* ao = base + cs.ao;
     char* act = base + cs.act;
     char* xs = base + cs.xs;
-    float* kpart = reinterpret_cast<float*>(base + cs.kpart);
+    float* sums = reinterpret_cast<float*>(base + cs.sums);
     char* q = base + cs.q;
     float* logits = reinterpret_cast<float*>(base + cs.logits);
     float2* rope = reinterpret_cast<float2*>(base + cs.rope);
     // (cos, sin) rows of the positions new tokens can take: P + 1 ... P + T + n_new - 1 (indexed by absolute position)
     ATTS_TRY(launch_rope_table(rope, P, cs.Tc, d.head_dim, d.rope_theta, st));
     // the projections of a step that have a narrow output cut their K range over the chip, one partial result per slice
-    SplitPlan plan = split_plan(d, K);
-    plan.qkv = gemm_partial_slices(d.dtype, K, qkv_out, d.d_model, padded);     // the QKV sums always pass through fp32 here
+    const SplitPlan plan = decode_split_plan(d, K, cs);
 
     auto next_token = [&](int t) -> int32_t {     // xs holds the normalised last hidden states: logits, arg max -> out_ids[:, t]
         GemmArgs g{};
@@ -702,20 +752,20 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
             char* vc = tree.vc + (size_t)l * tree.layer_bytes;
             if (!xn_ready) ATTS_TRY(launch_rmsnorm(d.dtype, h, m->attn_norm[l], d.rms_eps, K, d.d_model, xn, st));
             GemmArgs g{};
-            g.a = xn; g.w = m->wqkv[l]; g.out = kpart; g.M = K; g.N = qkv_out; g.Kd = d.d_model;
+            g.a = xn; g.w = m->wqkv[l]; g.out = sums; g.M = K; g.N = qkv_out; g.Kd = d.d_model;
             g.lda = d.d_model; g.ldw = d.d_model; g.ldc = qkv_out; g.a_rows_padded = padded;
-            g.n_slices = plan.qkv;
+            g.n_slices = plan.qkv; g.room = cs.room();
             ATTS_TRY(launch_gemm(d.dtype, plan.qkv > 1 ? EPI_PARTIAL_F32 : EPI_STORE_F32, g, st));
-            ATTS_TRY(launch_decode_qkv_finish(d.dtype, kpart, plan.qkv, (int64_t)K * qkv_out, rope, K, d.n_q_heads, d.n_kv_heads,
+            ATTS_TRY(launch_decode_qkv_finish(d.dtype, sums, plan.qkv, (int64_t)K * qkv_out, rope, K, d.n_q_heads, d.n_kv_heads,
                                               d.head_dim, P, cs.Tc, pos, q, kc, vc, st));
             ATTS_TRY(launch_attn_decode(d.dtype, q, kc, vc, ao, K, P, cs.Tc, pos, d.n_q_heads, d.n_kv_heads, d.head_dim, st));
             g = GemmArgs{};
             g.a = ao; g.w = m->wo[l]; g.out = h; g.M = K; g.N = d.d_model; g.Kd = qd;
             g.lda = qd; g.ldw = qd; g.ldc = d.d_model; g.a_rows_padded = padded;
             if (plan.o > 1) {
-                g.out = kpart; g.n_slices = plan.o;
+                g.out = sums; g.n_slices = plan.o; g.room = cs.room();
                 ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
-                ATTS_TRY(launch_resid_norm(d.dtype, h, kpart, plan.o, (int64_t)K * d.d_model, m->ffn_norm[l], d.rms_eps, K, d.d_model, xn, st));
+                ATTS_TRY(launch_resid_norm(d.dtype, h, sums, plan.o, (int64_t)K * d.d_model, m->ffn_norm[l], d.rms_eps, K, d.d_model, xn, st));
             } else {
                 ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
                 ATTS_TRY(launch_rmsnorm(d.dtype, h, m->ffn_norm[l], d.rms_eps, K, d.d_model, xn, st));
@@ -728,11 +778,11 @@ int32_t continue_tokens(const char* fn, const atts_prefix* p, const int32_t* dra
             g.a = act; g.w = m->w_down[l]; g.out = h; g.M = K; g.N = d.d_model; g.Kd = d.d_ffn;
             g.lda = d.d_ffn; g.ldw = d.d_ffn; g.ldc = d.d_model; g.a_rows_padded = padded;
             if (plan.down > 1) {
-                g.out = kpart; g.n_slices = plan.down;
+                g.out = sums; g.n_slices = plan.down; g.room = cs.room();
                 ATTS_TRY(launch_gemm(d.dtype, EPI_PARTIAL_F32, g, st));
                 xn_ready = l + 1 < d.n_layers;                 // with the norm that follows: the next layer's, or the final one
                 xs_ready = !xn_ready;
-                ATTS_TRY(launch_resid_norm(d.dtype, h, kpart, plan.down, (int64_t)K * d.d_model, xn_ready ? m->attn_norm[l + 1] : m->final_norm,
+                ATTS_TRY(launch_resid_norm(d.dtype, h, sums, plan.down, (int64_t)K * d.d_model, xn_ready ? m->attn_norm[l + 1] : m->final_norm,
                                            d.rms_eps, K, d.d_model, xn_ready ? xn : xs, st));
             } else {
                 ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
@@ -770,6 +820,62 @@ int32_t atts_model_check(const atts_model* m, void* hip_stream, int32_t* host_fl
     ATTS_HIP_TRY(hipStreamSynchronize(st));
     ATTS_HIP_TRY(hipMemsetAsync(m->err_flag, 0, sizeof(int32_t), st));
     ATTS_HIP_TRY(hipStreamSynchronize(st));
+    return ATTS_OK;
+}
+
+// ---------------------------------------------------------------------------- routes
+
+namespace {
+void show_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, atts_gemm_route* out) {
+    const GemmRoute r = gemm_route(dtype, epi, g);
+    *out = atts_gemm_route{r.kernel, r.tile_rows, r.slices, r.head_rows, r.tail_rows};
+}
+}  // namespace
+
+int32_t atts_gemm_routes(int32_t dtype, int32_t M, int32_t N, int32_t Kdim, atts_gemm_route* gemm, atts_gemm_route* lm_head) {
+    if (!gemm || !lm_head) return fail(ATTS_ERR_INVALID_ARG, "atts_gemm_routes: NULL argument");
+    if (dtype != ATTS_DTYPE_F32 && dtype != ATTS_DTYPE_BF16) return fail(ATTS_ERR_INVALID_ARG, "atts_gemm_routes: unknown dtype %d", dtype);
+    if (M < 1 || N < 1 || Kdim < 1) return fail(ATTS_ERR_INVALID_ARG, "atts_gemm_routes: M, N, Kdim must be >= 1");
+    GemmArgs g{};
+    g.M = M; g.N = N; g.Kd = Kdim; g.lda = Kdim; g.ldw = Kdim; g.ldc = N;
+    show_route(dtype, EPI_STORE_F32, g, gemm);
+    show_route(dtype, EPI_LMHEAD, g, lm_head);
+    return ATTS_OK;
+}
+
+int32_t atts_pass_routes(const atts_model_desc* desc, int32_t pass, int32_t P, int32_t K, int32_t T_max, int32_t n_new, atts_pass_route* out) {
+    if (!desc || !out) return fail(ATTS_ERR_INVALID_ARG, "atts_pass_routes: NULL argument");
+    if (pass < ATTS_PASS_SCORE || pass > ATTS_PASS_CONTINUE) return fail(ATTS_ERR_INVALID_ARG, "atts_pass_routes: unknown pass %d", pass);
+    const atts_model_desc& d = *desc;
+    ATTS_TRY(check_model("atts_pass_routes", d));
+    ATTS_TRY(check_score_shape("atts_pass_routes", P, K, T_max));
+    const int32_t qd = d.n_q_heads * d.head_dim, qkv_out = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
+    const Workspace ws = carve(d, ScoreShape{P, K, T_max});
+    int32_t M = pass == ATTS_PASS_SCORE ? P + K * T_max : K * T_max, row0 = pass == ATTS_PASS_SCORE ? 0 : P;
+    SumsRoom room = sums_room(d, ws, M);
+    SplitPlan plan;
+    *out = atts_pass_route{};
+    if (pass == ATTS_PASS_CONTINUE) {
+        if (K > 768 || n_new < 1 || (int64_t)P + T_max + n_new > (1 << 20)) return fail(ATTS_ERR_INVALID_ARG, "atts_pass_routes: K, n_new out of range");
+        const ContinueSpace cs = carve_continue(d, P, K, T_max, n_new);
+        M = K;
+        room = SumsRoom{cs.sums, cs.sums, cs.sums, cs.room(), cs.room(), cs.room()};
+        plan = decode_split_plan(d, K, cs);
+        out->workspace_bytes = cs.total;
+    } else {
+        plan = split_plan(d, M, room);
+        // as forward_tree: only the fused form of the projection is split
+        out->qkv_fused = attention_uses_vt(d.dtype, d.head_dim) && row0 % 4 == 0 && qkv_rope_fusable(d.dtype, M, qkv_out, d.d_model, d.head_dim, pads_rows(d));
+        if (!out->qkv_fused) plan.qkv = 1;
+        out->workspace_bytes = ws.total;
+    }
+    const GemmEpilogue qkv_direct = pass == ATTS_PASS_CONTINUE ? EPI_STORE_F32 : (out->qkv_fused ? EPI_QKV_ROPE : EPI_STORE_ACT);
+    show_route(d.dtype, plan.qkv > 1 ? EPI_PARTIAL_F32 : qkv_direct, gemm_shape(d, M, qkv_out, d.d_model, room.qkv), &out->qkv);
+    show_route(d.dtype, plan.o > 1 ? EPI_PARTIAL_F32 : EPI_RESID_F32, gemm_shape(d, M, d.d_model, qd, room.o), &out->o);
+    show_route(d.dtype, EPI_SWIGLU, gemm_shape(d, M, d.d_ffn, d.d_model), &out->gate_up);
+    show_route(d.dtype, plan.down > 1 ? EPI_PARTIAL_F32 : EPI_RESID_F32, gemm_shape(d, M, d.d_model, d.d_ffn, room.down), &out->down);
+    show_route(d.dtype, pass == ATTS_PASS_CONTINUE ? EPI_STORE_F32 : EPI_LMHEAD, gemm_shape(d, pass == ATTS_PASS_CONTINUE ? K : K * T_max, d.vocab, d.d_model),
+               &out->lm_head);
     return ATTS_OK;
 }
 
@@ -838,14 +944,13 @@ int32_t static_scratch_ptr(void** out) {
 // target logits.  Shared by the two entry points below.
 int32_t lmhead_on_scratch(int32_t dtype, const void* x, const void* w, const int32_t* targets, int32_t B, int32_t d,
                           int32_t V, float* logprobs, void* scratch_area, hipStream_t st) {
-    const int n_part = lmhead_num_partials(dtype, B, V, d, false);
     float2* partials = static_cast<float2*>(scratch_area);
     float* zt = reinterpret_cast<float*>(static_cast<char*>(scratch_area) + align_up((size_t)B * lmhead_max_partials(V) * sizeof(float2), 256));
     GemmArgs g{};
     g.a = x; g.w = w; g.M = B; g.N = V; g.Kd = d; g.lda = d; g.ldw = d;
-    g.targets = targets; g.partials = partials; g.target_logit = zt; g.n_part = n_part;
+    g.targets = targets; g.partials = partials; g.target_logit = zt; g.n_part = gemm_route(dtype, EPI_LMHEAD, g).n_part;
     ATTS_TRY(launch_gemm(dtype, EPI_LMHEAD, g, st));
-    return launch_lmhead_combine(partials, zt, B, n_part, nullptr, logprobs, st);
+    return launch_lmhead_combine(partials, zt, B, g.n_part, nullptr, logprobs, st);
 }
 
 int32_t check_lmhead_args(const char* fn, int32_t dtype, const void* x, const void* w, const int32_t* targets, int32_t B, int32_t d,

@@ -110,7 +110,7 @@ enum GemmEpilogue : int32_t {
                          // v heads stored transposed to vt [n_kv, 128, ldv].  head_dim 128, aligned bf16 shapes only.
     EPI_LMHEAD_T = 7,    // EPI_LMHEAD with the operands exchanged (rows of the product = vocabulary entries, columns = scoring
                          // rows): launch_gemm takes it by itself for EPI_LMHEAD calls whose shape allows it
-    EPI_PARTIAL_F32 = 6, // out (float) [n_slices][M, ldc]: the K range is cut into n_slices = gemm_partial_slices(...)
+    EPI_PARTIAL_F32 = 6, // out (float) [n_slices][M, ldc]: the K range is cut into n_slices = gemm_route(...).slices
                          // slices whose partial sums are stored one after the other (pitch M ldc floats); the consumer
                          // adds them in slice order.  For projections with few rows and a narrow output, whose tiles
                          // alone would leave most of the chip idle while the weights stream by.  No atomics: the
@@ -128,24 +128,39 @@ struct GemmArgs {
     const int32_t* targets;  // [M] target column per row
     float2* partials;        // [M, n_part] (running max, sum of exp) per column slab
     float* target_logit;     // [M]
-    int32_t n_part;          // number of column slabs = lmhead_num_partials(...) of this call
+    int32_t n_part;          // number of column slabs = gemm_route(...).n_part of this call
     // EPI_QKV_ROPE only:
     const float2* rope;      // [M, 64] (cos, sin) per row and rotation pair
     void* vt;                // [n_kv, 128, ldv] transposed V
     int64_t ldv;
     int32_t n_rot_heads;     // n_q + n_kv: heads (of 128 columns) that are rotated; the rest are V heads
     // EPI_PARTIAL_F32 only:
-    int32_t n_slices;        // must equal gemm_partial_slices(dtype, M, N, Kd, a_rows_padded)
+    int32_t n_slices;        // slices stored = gemm_route(...).slices
+    size_t room;             // bytes `out` has for them: no more slices than fit
 };
 
-// Column slabs (partials per row) the LM-head epilogue of this call writes; lmhead_max_partials bounds it for any
-// dtype / Kd / padding (workspace sizing).
-int32_t lmhead_num_partials(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded);
+// The kernel, tile and K split a call takes; depends on the epilogue, the shape, a_rows_padded and room only.  The launch
+// follows it, buffers are sized by it, and atts_pass_routes / atts_gemm_routes show it.
+struct GemmRoute {
+    int32_t kernel;          // ATTS_KERNEL_*
+    int32_t tile_rows;       // aligned kernels: rows of a tile (of the vocabulary where the operands are exchanged)
+    int32_t slices;          // EPI_PARTIAL_F32: K slices; 1: cutting would not help, the caller takes the direct epilogue
+    int32_t head_rows, tail_rows;   // tail_rows != 0: rows [0, head_rows) in tiles of tile_rows, the rest in a second launch of tail_rows
+    int32_t n_part;          // EPI_LMHEAD: column slabs (partials per row)
+};
+GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);
+// Bytes of sums that an EPI_PARTIAL_F32 call with at most M rows can store (never less for more rows).
+size_t partial_bytes_bound(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded);
+// Bounds of B n_part, for buffers: over any call with at most B rows (never less for more rows), and per row for any dtype
+// and inner dimension.
+int64_t lmhead_partials_bound(int32_t dtype, int32_t B, int32_t N, int32_t Kd, bool a_rows_padded);
 int32_t lmhead_max_partials(int32_t N);
 int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 // The kernel for at most 16 rows of A (skinny.hip): launch_gemm hands it the calls it serves.
 bool gemm_skinny_ok(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);
 int32_t launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
+int32_t skinny_partial_slices(const GemmArgs& g);         // K slices of its EPI_PARTIAL_F32 form, at most as many as g.room holds
+size_t skinny_partial_bound(int32_t M, int32_t N, int32_t Kd);    // bytes of its sums, for any call with at most M rows
 // The kernel for products of few tiles (small.hip), any shape; launch_gemm hands it the calls that leave the chip idle otherwise.
 int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
@@ -203,10 +218,6 @@ int32_t launch_copies(int32_t dtype, const CopyBlocks& jobs, hipStream_t stream)
 int32_t launch_qkv_finish(int32_t dtype, const float* acc, int32_t n_slices, int64_t slice_pitch, const float2* cs, int32_t rows,
                           int32_t nq, int32_t nkv, int32_t hd, void* qkv, void* vt, int64_t ldv, const CopyBlocks& copies,
                           hipStream_t stream);
-// K slices an EPI_PARTIAL_F32 projection of this shape is cut into (1: cutting would not help, the caller takes the
-// direct epilogue instead).  Depends on the shape only.
-int32_t gemm_partial_slices(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded);
-int32_t skinny_partial_slices(int32_t N, int32_t Kd);     // the same for the kernel that serves at most 16 rows
 // h[r] += sum over the slices (in slice order) of partials[s][r]  for `rows` rows of d floats (slice pitch in floats);
 // gain != NULL: then xn[r] = rmsnorm(h[r]; gain) in the model dtype (residual update and the next norm in one pass)
 int32_t launch_resid_norm(int32_t dtype, float* h, const float* partials, int32_t n_slices, int64_t slice_pitch, const float* gain,

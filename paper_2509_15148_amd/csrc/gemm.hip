@@ -950,7 +950,7 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
 // 128 x 128 tiles, 3 slices 96 us; 256 x 256, 9 slices 105.  70B, 774 rows: 256-row tiles, 2 slices, 443 us against 785
 // for the same 128 tiles unsplit.
 TilePlan partial_plan(const GemmArgs& g) {
-    const int64_t slabs = g.Kd / kWideBK;
+    const int64_t slabs = g.Kd / kWideBK, fitting = (int64_t)(g.room / ((size_t)g.M * g.N * sizeof(float)));
     const TilePlan none{0, 1, 0.0, 0, 0};
     TilePlan best = none;
     for (int rows : {384, 256, 128}) {
@@ -959,6 +959,7 @@ TilePlan partial_plan(const GemmArgs& g) {
         const int64_t tiles = ceil_div(g.M, rows) * (g.N / (narrow ? 128 : 256));
         int64_t s = 256 / tiles;
         if (s > slabs / 6) s = slabs / 6;
+        if (s > fitting) s = fitting;
         if (s < 2) continue;
         const double us = fast_tile_us(rows, narrow, ceil_div(slabs, s)) + (double)s * g.M * g.N * 8 / 4.5e6 + 4.0;
         if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0};
@@ -1027,28 +1028,26 @@ int32_t launch_tile_rows(int rows, const GemmArgs& g, hipStream_t stream) {
 }
 
 template <int EPI>
-int32_t launch_fast(const GemmArgs& g, hipStream_t stream) {
+int32_t launch_fast(const GemmRoute& r, const GemmArgs& g, hipStream_t stream) {
     if constexpr (EPI == EPI_PARTIAL_F32) {
-        const int rows = partial_plan(g).rows;
-        if (rows == 0) return fail(ATTS_ERR_SHAPE, "gemm: no K split for this shape");
-        return rows == 128 ? launch_wide_tile<EPI, 1, 2>(g, stream) : launch_tile_rows<EPI>(rows, g, stream);
+        return r.tile_rows == 128 ? launch_wide_tile<EPI, 1, 2>(g, stream) : launch_tile_rows<EPI>(r.tile_rows, g, stream);
+    } else {
+        if (r.tail_rows == 0) return launch_tile_rows<EPI>(r.tile_rows, g, stream);
+        GemmArgs head = g, tail = g;
+        head.M = r.head_rows;
+        ATTS_TRY_RC((launch_wide_tile<EPI, 3>(head, stream)));
+        const int64_t r0 = head.M;
+        constexpr int64_t out_bytes = (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) ? 4 : 2;
+        tail.M = g.M - head.M;
+        tail.a = static_cast<const char*>(g.a) + r0 * g.lda * 2;
+        if (g.out) tail.out = static_cast<char*>(g.out) + r0 * g.ldc * out_bytes;
+        if (EPI == EPI_LMHEAD) {
+            tail.targets = g.targets + r0;
+            tail.partials = g.partials + r0 * g.n_part;
+            tail.target_logit = g.target_logit + r0;
+        }
+        return launch_tile_rows<EPI>(r.tail_rows, tail, stream);
     }
-    const TilePlan plan = direct_plan(EPI, g);
-    if (plan.tail_rows == 0) return launch_tile_rows<EPI>(plan.rows, g, stream);
-    GemmArgs head = g, tail = g;
-    head.M = plan.head_m;
-    ATTS_TRY_RC((launch_wide_tile<EPI, 3>(head, stream)));
-    const int64_t r0 = head.M;
-    constexpr int64_t out_bytes = (EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) ? 4 : 2;
-    tail.M = g.M - head.M;
-    tail.a = static_cast<const char*>(g.a) + r0 * g.lda * 2;
-    if (g.out) tail.out = static_cast<char*>(g.out) + r0 * g.ldc * out_bytes;
-    if (EPI == EPI_LMHEAD) {
-        tail.targets = g.targets + r0;
-        tail.partials = g.partials + r0 * g.n_part;
-        tail.target_logit = g.target_logit + r0;
-    }
-    return launch_tile_rows<EPI>(plan.tail_rows, tail, stream);
 }
 
 template <typename T, int BM, int BN, int EPI>
@@ -1087,27 +1086,32 @@ bool use_small_tile(int32_t dtype, int32_t M, int32_t N) {
     return ceil_div(M, 32) * ceil_div(N, 32) <= rounds * (dtype == ATTS_DTYPE_F32 ? 2048 : 768);
 }
 
-// The aligned bf16 kernel serves every call it can (its DMA ring also streams weights well when the tiles are
-// few); everything else goes to the general kernel.
 template <typename T, int EPI>
-int32_t launch_epi(const GemmArgs& g, hipStream_t stream) {
-    constexpr int32_t dtype = sizeof(T) == 2 ? ATTS_DTYPE_BF16 : ATTS_DTYPE_F32;
-    if (fast_path_ok(dtype, EPI, g)) return launch_fast<EPI>(g, stream);
-    int32_t n_cols = (EPI == EPI_SWIGLU) ? 2 * g.N : g.N;
-    if (EPI != EPI_PARTIAL_F32 && use_small_tile(dtype, g.M, n_cols)) return launch_gemm_small(dtype, (GemmEpilogue)EPI, g, stream);
-    if (use_big_tile(g.M, n_cols)) return launch_cfg<T, 256, 256, EPI>(g, stream);
-    return launch_cfg<T, 128, 128, EPI>(g, stream);
+int32_t launch_epi(const GemmRoute& r, const GemmArgs& g, hipStream_t stream) {
+    switch (r.kernel) {
+        case ATTS_KERNEL_ALIGNED:
+            if constexpr (sizeof(T) == 2) return launch_fast<EPI>(r, g, stream);
+            break;
+        case ATTS_KERNEL_SMALL: return launch_gemm_small(sizeof(T) == 2 ? ATTS_DTYPE_BF16 : ATTS_DTYPE_F32, (GemmEpilogue)EPI, g, stream);
+        case ATTS_KERNEL_GENERAL_256:
+            if constexpr (EPI != EPI_PARTIAL_F32) return launch_cfg<T, 256, 256, EPI>(g, stream);
+            break;
+        case ATTS_KERNEL_GENERAL_128:
+            if constexpr (EPI != EPI_PARTIAL_F32) return launch_cfg<T, 128, 128, EPI>(g, stream);
+            break;
+    }
+    return fail(ATTS_ERR_SHAPE, "gemm: no kernel for epilogue %d of this shape", EPI);
 }
 
 template <typename T>
-int32_t launch_t(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
+int32_t launch_t(const GemmRoute& r, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
     switch (epi) {
-        case EPI_STORE_ACT: return launch_epi<T, EPI_STORE_ACT>(g, stream);
-        case EPI_STORE_F32: return launch_epi<T, EPI_STORE_F32>(g, stream);
-        case EPI_RESID_F32: return launch_epi<T, EPI_RESID_F32>(g, stream);
-        case EPI_SWIGLU: return launch_epi<T, EPI_SWIGLU>(g, stream);
-        case EPI_LMHEAD: return launch_epi<T, EPI_LMHEAD>(g, stream);
-        case EPI_PARTIAL_F32: return launch_epi<T, EPI_PARTIAL_F32>(g, stream);
+        case EPI_STORE_ACT: return launch_epi<T, EPI_STORE_ACT>(r, g, stream);
+        case EPI_STORE_F32: return launch_epi<T, EPI_STORE_F32>(r, g, stream);
+        case EPI_RESID_F32: return launch_epi<T, EPI_RESID_F32>(r, g, stream);
+        case EPI_SWIGLU: return launch_epi<T, EPI_SWIGLU>(r, g, stream);
+        case EPI_LMHEAD: return launch_epi<T, EPI_LMHEAD>(r, g, stream);
+        case EPI_PARTIAL_F32: return launch_epi<T, EPI_PARTIAL_F32>(r, g, stream);
         case EPI_QKV_ROPE: break;   // fast path only, dispatched by launch_gemm
         case EPI_LMHEAD_T: break;   // taken by launch_gemm itself, never asked for
     }
@@ -1181,27 +1185,76 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw) {
     return dtype == ATTS_DTYPE_BF16 && Kd % kWideBK == 0 && Kd >= kMinSlabs * kWideBK && lda * 2 * 17 < (1ll << 31) && ldw * 2 * 17 < (1ll << 31);
 }
-static bool lmhead_exchanged_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw, bool a_rows_padded) {
-    if (N % 384 != 0 || M <= 128 || !lmhead_aligned_k(dtype, Kd, lda, ldw)) return false;
-    if (!a_rows_padded || N % 256 != 0) return true;                  // the other orientation would be the general kernel's
-    GemmArgs g{};
-    g.M = M; g.N = N; g.Kd = Kd; g.lda = lda; g.ldw = ldw; g.a_rows_padded = true;
-    const double us = (double)ceil_div(N / 384 * ceil_div(M, 256), 256) * fast_tile_us(384, false, Kd / kWideBK);
+static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
+    if (g.N % 384 != 0 || g.M <= 128 || !lmhead_aligned_k(dtype, g.Kd, g.lda, g.ldw)) return false;
+    if (!g.a_rows_padded || g.N % 256 != 0) return true;              // the other orientation would be the general kernel's
+    const double us = (double)ceil_div(g.N / 384 * ceil_div(g.M, 256), 256) * fast_tile_us(384, false, g.Kd / kWideBK);
     return us <= 1.09 * direct_plan(EPI_LMHEAD, g).us;
 }
-static bool lmhead_few_ok(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int64_t lda, int64_t ldw) {
-    return N % 256 == 0 && M > 0 && M <= 128 && lmhead_aligned_k(dtype, Kd, lda, ldw);
+static bool lmhead_few_ok(int32_t dtype, const GemmArgs& g) {
+    return g.N % 256 == 0 && g.M <= 128 && lmhead_aligned_k(dtype, g.Kd, g.lda, g.ldw);
 }
 
-int32_t lmhead_num_partials(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded) {
-    if (lmhead_few_ok(dtype, M, N, Kd, Kd, Kd)) return N / 256;
-    if (lmhead_exchanged_ok(dtype, M, N, Kd, Kd, Kd, a_rows_padded)) return N / 384 * 4;
+GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
+    GemmRoute r{ATTS_KERNEL_GENERAL_128, 0, 1, 0, 0, 0};
+    if (epi == EPI_LMHEAD && lmhead_few_ok(dtype, g)) {
+        r.kernel = ATTS_KERNEL_EXCHANGED; r.tile_rows = 256; r.n_part = g.N / 256;
+        return r;
+    }
+    if (epi == EPI_LMHEAD && lmhead_exchanged_ok(dtype, g)) {
+        r.kernel = ATTS_KERNEL_EXCHANGED; r.tile_rows = 384; r.n_part = g.N / 384 * 4;
+        return r;
+    }
+    // The aligned bf16 kernel serves every call it can (its DMA ring also streams weights well when the tiles are few).  A
+    // decoding step (at most 16 rows) streams the weights once: narrow outputs (partial-sum epilogue) go to the kernel that
+    // cuts K over single wavefronts; wide outputs (SwiGLU, logits) already give the aligned kernel enough tiles, and it
+    // streams them as fast, so they only go there when it cannot serve the shape.
+    const bool fast = fast_path_ok(dtype, epi, g);
+    if (gemm_skinny_ok(dtype, epi, g) && (epi == EPI_PARTIAL_F32 || !fast)) {
+        r.kernel = ATTS_KERNEL_FEW_ROWS;
+        if (epi == EPI_PARTIAL_F32) r.slices = skinny_partial_slices(g);
+        return r;
+    }
+    if (fast) {
+        const TilePlan plan = epi == EPI_PARTIAL_F32 ? partial_plan(g) : direct_plan(epi, g);
+        r.kernel = ATTS_KERNEL_ALIGNED; r.tile_rows = plan.rows; r.slices = plan.slices;
+        r.head_rows = plan.head_m; r.tail_rows = plan.tail_rows;
+        r.n_part = g.N / 256 * 2;
+        return r;
+    }
+    const int32_t n_cols = epi == EPI_SWIGLU ? 2 * g.N : g.N;
+    if (use_small_tile(dtype, g.M, n_cols)) {
+        r.kernel = ATTS_KERNEL_SMALL; r.n_part = small_lmhead_partials(g.N);
+    } else {
+        const bool big = use_big_tile(g.M, n_cols);
+        r.kernel = big ? ATTS_KERNEL_GENERAL_256 : ATTS_KERNEL_GENERAL_128;
+        r.n_part = (int32_t)ceil_div(g.N, big ? 256 : 128) * 2;
+    }
+    return r;
+}
+
+size_t partial_bytes_bound(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded) {
+    if (dtype != ATTS_DTYPE_BF16) return 0;
+    size_t bytes = skinny_partial_bound(M, N, Kd);
     GemmArgs g{};
     g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
-    const bool fast = fast_path_ok(dtype, EPI_LMHEAD, g);
-    if (!fast && use_small_tile(dtype, M, N)) return small_lmhead_partials(N);
-    const int bn = (fast || use_big_tile(M, N)) ? 256 : 128;
-    return (int32_t)ceil_div(N, bn) * 2;
+    const size_t max_slices = (size_t)Kd / kWideBK / 6;              // as partial_plan: and at most one round of tiles
+    if (max_slices < 2 || !fast_path_ok(dtype, EPI_PARTIAL_F32, g)) return bytes;
+    for (int rows : {128, 256, 384}) {
+        if (rows > 128 && M <= rows - 128) continue;                 // 256-row tiles from 129 rows on, 384 from 257
+        const size_t by_slices = max_slices * (size_t)M * N * sizeof(float), by_tiles = (size_t)256 * rows * (rows == 128 ? 128 : 256) * sizeof(float);
+        const size_t b = by_slices < by_tiles ? by_slices : by_tiles;
+        if (b > bytes) bytes = b;
+    }
+    return bytes;
+}
+
+int64_t lmhead_partials_bound(int32_t dtype, int32_t B, int32_t N, int32_t Kd, bool a_rows_padded) {
+    const int64_t any = lmhead_max_partials(N);
+    if (!lmhead_aligned_k(dtype, Kd, Kd, Kd) || N % 256 != 0) return B * any;
+    if (B <= 128) return (int64_t)B * (N / 256);
+    const int64_t first = a_rows_padded ? (int64_t)N / 256 * 2 : any, exchanged = N % 384 == 0 ? (int64_t)N / 384 * 4 : 0;
+    return B * (first > exchanged ? first : exchanged);
 }
 int32_t lmhead_max_partials(int32_t N) { return (int32_t)ceil_div(N, 128) * 2; }
 
@@ -1211,46 +1264,33 @@ bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t h
     return head_dim == 128 && fast_path_ok(dtype, EPI_QKV_ROPE, g);
 }
 
-int32_t gemm_partial_slices(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded) {
-    GemmArgs g{};
-    g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
-    if (gemm_skinny_ok(dtype, EPI_PARTIAL_F32, g)) return skinny_partial_slices(N, Kd);
-    if (!fast_path_ok(dtype, EPI_PARTIAL_F32, g)) return 1;
-    return partial_plan(g).slices;
-}
-
 int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
     const size_t es = dtype_size(dtype);
     if (g.M <= 0 || g.N <= 0 || g.Kd <= 0) return fail(ATTS_ERR_SHAPE, "gemm: empty shape %d x %d x %d", g.M, g.N, g.Kd);
     if ((g.Kd * es) % 16 || (g.lda * es) % 16 || (g.ldw * es) % 16)
         return fail(ATTS_ERR_SHAPE, "gemm: K (%d) and leading dimensions must be multiples of 16 bytes", g.Kd);
     if (((uintptr_t)g.a | (uintptr_t)g.w) & 15) return fail(ATTS_ERR_INVALID_ARG, "gemm: operands must be 16-byte aligned");
-    if (epi == EPI_LMHEAD && g.n_part != lmhead_num_partials(dtype, g.M, g.N, g.Kd, g.a_rows_padded))
-        return fail(ATTS_ERR_INVALID_ARG, "gemm: wrong partial count for the LM-head epilogue");
-    if (epi == EPI_PARTIAL_F32 && g.n_slices != gemm_partial_slices(dtype, g.M, g.N, g.Kd, g.a_rows_padded))
+    const GemmRoute r = gemm_route(dtype, epi, g);
+    if (epi == EPI_LMHEAD && g.n_part != r.n_part) return fail(ATTS_ERR_INVALID_ARG, "gemm: wrong partial count for the LM-head epilogue");
+    if (epi == EPI_PARTIAL_F32 && (r.slices < 2 || g.n_slices != r.slices))
         return fail(ATTS_ERR_INVALID_ARG, "gemm: wrong slice count for the partial-sum epilogue");
-    const bool few = epi == EPI_LMHEAD && lmhead_few_ok(dtype, g.M, g.N, g.Kd, g.lda, g.ldw);
-    if (few || (epi == EPI_LMHEAD && lmhead_exchanged_ok(dtype, g.M, g.N, g.Kd, g.lda, g.ldw, g.a_rows_padded))) {
+    if (r.kernel == ATTS_KERNEL_EXCHANGED) {
         if (!g.targets || !g.partials || !g.target_logit) return fail(ATTS_ERR_INVALID_ARG, "gemm: LM-head epilogue without its buffers");
         GemmArgs x = g;
         x.a = g.w; x.lda = g.ldw; x.M = g.N;
         x.w = g.a; x.ldw = g.lda; x.N = g.M;
         x.a_rows_padded = false;
-        if (few) return launch_wide_tile<EPI_LMHEAD_T, 2, 2, true>(x, stream);
+        if (r.tile_rows == 256) return launch_wide_tile<EPI_LMHEAD_T, 2, 2, true>(x, stream);
         return x.N % 256 ? launch_wide_tile<EPI_LMHEAD_T, 3, 4, true>(x, stream) : launch_wide_tile<EPI_LMHEAD_T, 3>(x, stream);
     }
     if (epi == EPI_QKV_ROPE) {
         if (!qkv_rope_fusable(dtype, g.M, g.N, g.Kd, 128, g.a_rows_padded) || !g.rope || !g.vt || g.ldv < g.M || g.ldv % 4 ||
             g.n_rot_heads < 1 || g.n_rot_heads * 128 >= g.N)
             return fail(ATTS_ERR_SHAPE, "gemm: the fused QKV epilogue does not apply to this call");
-        return launch_fast<EPI_QKV_ROPE>(g, stream);
+        return launch_fast<EPI_QKV_ROPE>(r, g, stream);
     }
-    // A decoding step (at most 16 rows) streams the weights once.  Narrow outputs (partial-sum epilogue) go to the
-    // kernel that cuts K over single wavefronts; wide outputs (SwiGLU, logits) already give the aligned kernel
-    // enough tiles, and it streams them as fast, so they only go there when it cannot serve the shape.
-    if (gemm_skinny_ok(dtype, epi, g) && (epi == EPI_PARTIAL_F32 || !fast_path_ok(dtype, epi, g)))
-        return launch_gemm_skinny(epi, g, stream);
-    return dtype == ATTS_DTYPE_F32 ? launch_t<float>(epi, g, stream) : launch_t<bf16>(epi, g, stream);
+    if (r.kernel == ATTS_KERNEL_FEW_ROWS) return launch_gemm_skinny(epi, g, stream);
+    return dtype == ATTS_DTYPE_F32 ? launch_t<float>(r, epi, g, stream) : launch_t<bf16>(r, epi, g, stream);
 }
 
 int32_t launch_lmhead_combine(const float2* partials, const float* target_logit, int32_t B, int32_t n_part,

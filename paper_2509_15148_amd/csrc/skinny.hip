@@ -120,11 +120,12 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void gemm_skinny_kernel(const bf
 
 // K steps per slice of the partial-sum form: about four wavefronts per CU stream fastest (measured: fewer leave CUs
 // idle, many more shorten every wavefront's run), each with at least two buffers of k-steps
-int32_t skinny_steps_per_slice(int32_t N, int32_t Kd) {
-    const int64_t n_groups = ceil_div(N, 32), n_steps = Kd / kStepElems;
+int32_t skinny_steps_per_slice(const GemmArgs& g) {
+    const int64_t n_groups = ceil_div(g.N, 32), n_steps = g.Kd / kStepElems;
     int64_t s = kSkinnyWavesTarget / n_groups;
-    const int64_t max_s = n_steps / (2 * kSkinnyUnroll);
+    const int64_t max_s = n_steps / (2 * kSkinnyUnroll), fitting = (int64_t)(g.room / ((size_t)g.M * g.N * sizeof(float)));
     if (s > max_s) s = max_s;
+    if (s > fitting) s = fitting;
     if (s < 1) s = 1;
     return (int32_t)align_up((size_t)ceil_div(n_steps, s), 2 * kSkinnyUnroll);
 }
@@ -141,7 +142,7 @@ int32_t launch_skinny_epi(const GemmArgs& g, hipStream_t stream) {
     d.steps_per_slice = d.n_steps;
     d.slice_pitch = 0;
     if (EPI == EPI_PARTIAL_F32) {
-        d.steps_per_slice = skinny_steps_per_slice(g.N, g.Kd);
+        d.steps_per_slice = skinny_steps_per_slice(g);
         d.k_slices = (int32_t)ceil_div(d.n_steps, d.steps_per_slice);
         d.slice_pitch = (int64_t)g.M * g.ldc;
     }
@@ -160,8 +161,12 @@ bool gemm_skinny_ok(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
            (int64_t)g.N * (epi == EPI_SWIGLU ? 2 : 1) < (1ll << 30);
 }
 
-int32_t skinny_partial_slices(int32_t N, int32_t Kd) {
-    return (int32_t)ceil_div(Kd / kStepElems, skinny_steps_per_slice(N, Kd));
+int32_t skinny_partial_slices(const GemmArgs& g) { return (int32_t)ceil_div(g.Kd / kStepElems, skinny_steps_per_slice(g)); }
+
+size_t skinny_partial_bound(int32_t M, int32_t N, int32_t Kd) {
+    const int64_t by_waves = kSkinnyWavesTarget / ceil_div(N, 32), by_steps = Kd / kStepElems / (2 * kSkinnyUnroll);
+    const int64_t s = by_waves < by_steps ? by_waves : by_steps;
+    return s < 2 ? 0 : (size_t)s * (size_t)(M < kSkinnyRows ? M : kSkinnyRows) * N * sizeof(float);
 }
 
 int32_t launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {

@@ -7,7 +7,7 @@ import torch
 
 from oracle import atts_oracle as O
 from synth import WORKLOADS, ModelConfig, make_token_ids, make_weights
-from util import announce, dev, weights_to_numpy, ws
+from util import announce, dev, dirty_ws, weights_to_numpy, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -125,6 +125,56 @@ def test_first_norm_has_the_bits_of_the_norm_kernel(d):
     lp, sc, _ = _run_gpu(A, cfg, w, prefix, drafts)
     lp2, sc2, _ = _run_gpu(A, dataclasses.replace(cfg, n_layers=2), longer, prefix, drafts)
     assert np.array_equal(lp, lp2) and np.array_equal(sc, sc2)
+
+
+def test_workspace_of_the_largest_call_serves_smaller_ones():
+    """A loop allocates once for its longest drafts.  Shorter ones, whose projections are cut along K where the longest's are
+    not, run in that workspace, and give the same bits as in one of their own size."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(1, 3584, 28, 4, 128, 18944, 2304, "bf16")
+    w, prefix, drafts = _case(cfg, 512, 16, 256, seed=3)
+    model = A.Model(cfg, w)
+    largest = dirty_ws(A.atts_workspace_bytes(model, 512, 16, 256))
+    pre = A.Prefix(model, capacity=512)
+    A.atts_prefix_extend(pre, dev(prefix), largest)
+    cut = set()
+    for T in (256, 216, 200, 48, 8, 1):
+        need = A.atts_workspace_bytes(model, 512, 16, T)
+        assert need <= largest.numel()
+        for kind in (A.PASS_SCORE, A.PASS_SCORE_CACHED):
+            announce("score in the largest call's workspace", T, kind)
+            route = A.atts_pass_routes(cfg, kind, 512, 16, T)
+            assert need == route.workspace_bytes
+            cut |= {(T, kind)} if route.down.slices > 1 else set()
+            out = []
+            for space in (largest, dirty_ws(need)):
+                lp, sc = (torch.full(shape, float("nan"), device="cuda") for shape in ((16, T), (16,)))
+                if kind == A.PASS_SCORE:
+                    A.atts_score_drafts(model, dev(prefix), dev(drafts[:, :T]), None, 0, lp, sc, space)
+                else:
+                    A.atts_score_drafts_cached(pre, dev(drafts[:, :T]), None, 0, lp, sc, space)
+                out.append((lp, sc))
+                largest.fill_(255)
+            assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+            assert bool(torch.isfinite(out[0][0]).all()) and bool(torch.isfinite(out[0][1]).all())
+    assert (216, A.PASS_SCORE_CACHED) in cut and (48, A.PASS_SCORE) in cut and (256, A.PASS_SCORE) not in cut
+
+
+@pytest.mark.parametrize("P,K,T", [(8, 8, 14), (9, 9, 12)])
+def test_partial_sums_in_little_room(P, K, T):
+    """Many heads over a narrow model: the buffers that hold the K slices of the output projection are small for it, so fewer
+    slices are taken than the shape allows.  The oracle's bound; NaN in the workspace."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(1, 768, 128, 4, 128, 64, 768, "bf16")
+    announce("score little room", P, K, T)
+    few, many = (A.atts_pass_routes(c, A.PASS_SCORE, P, K, T).o.slices for c in (cfg, dataclasses.replace(cfg, d_ffn=16384)))
+    assert 2 <= few < many
+    w, prefix, drafts = _case(cfg, P, K, T, seed=P)
+    model = A.Model(cfg, w)
+    lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
+    ref_lp, ref_s = O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)
+    assert np.abs(lp.cpu().numpy() - ref_lp).max() <= TOL["bf16"] and np.abs(sc.cpu().numpy() - ref_s).max() <= TOL["bf16"]
 
 
 def test_variable_draft_lengths_and_padding_ids():

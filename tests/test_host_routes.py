@@ -1,0 +1,60 @@
+"""CPU-side checks of the sizes and routes the library chooses on the host (nothing is launched, no device is touched)."""
+import random
+
+import pytest
+
+import paper_2509_15148_amd as A
+from synth import WORKLOADS, ModelConfig
+
+MODELS = {
+    "tiny": WORKLOADS["tiny"].model,
+    "7b": ModelConfig(28, 3584, 28, 4, 128, 18944, 152064, "bf16"),
+    "32b": ModelConfig(64, 5120, 40, 8, 128, 27648, 152064, "bf16"),
+    "70b": ModelConfig(80, 8192, 64, 8, 128, 28672, 128256, "bf16"),
+    "hd64": ModelConfig(2, 1024, 16, 4, 64, 2816, 32000, "bf16"),
+    "odd": ModelConfig(2, 136, 4, 1, 24, 200, 515, "bf16"),
+    "narrow_ffn": ModelConfig(2, 2048, 16, 16, 128, 64, 50304, "bf16"),
+    "odd_vocab": ModelConfig(2, 768, 6, 6, 128, 3072, 384 * 131, "bf16"),
+}
+
+
+def _bytes(cfg, kind, P, K, T, n_new=1):
+    return A.atts_pass_routes(cfg, kind, P, K, T, n_new).workspace_bytes
+
+
+@pytest.mark.parametrize("name", MODELS)
+def test_a_larger_call_never_needs_a_smaller_workspace(name):
+    """A program allocates for its largest prefix, draft count and draft length and then makes smaller calls."""
+    cfg, rng = MODELS[name], random.Random(name)
+    for _ in range(3000):
+        P, K, T = (int(2 ** rng.uniform(0, 11)) for _ in range(3))
+        K = min(K, 64)
+        more = [x + (rng.choice((0, 1, 7, 40, 300)) if rng.random() < 0.6 else 0) for x in (P, K, T)]
+        assert _bytes(cfg, A.PASS_SCORE, *more) >= _bytes(cfg, A.PASS_SCORE, P, K, T), (P, K, T, more)
+        n = rng.choice((1, 2, 33))
+        assert _bytes(cfg, A.PASS_CONTINUE, *more, n + rng.choice((0, 1, 20))) >= _bytes(cfg, A.PASS_CONTINUE, P, K, T, n), (P, K, T, more)
+    rows = [_bytes(cfg, A.PASS_SCORE, 512, 1, T) for T in range(1, 2600)]            # every row count: tile and split boundaries
+    assert all(a <= b for a, b in zip(rows, rows[1:]))
+
+
+@pytest.mark.parametrize("name", ["7b", "32b", "70b"])
+def test_the_published_widths_have_room_for_every_split(name):
+    """Splits are chosen by rows and shape; at these widths the room for their sums never takes slices away."""
+    cfg = MODELS[name]
+    for rows in list(range(1, 400)) + list(range(400, 4100, 37)):
+        a, b = (A.atts_pass_routes(cfg, A.PASS_SCORE_CACHED, P, 1, rows) for P in (4, 8000))
+        for product in ("qkv", "o", "down"):
+            assert getattr(a, product).slices == getattr(b, product).slices, (rows, product)
+
+
+def test_route_entry_points_validate_arguments():
+    cfg = MODELS["7b"]
+    for bad in (lambda: A.atts_pass_routes(cfg, 3, 1, 1, 1), lambda: A.atts_pass_routes(cfg, 0, 0, 1, 1),
+                lambda: A.atts_pass_routes(cfg, A.PASS_CONTINUE, 1, 769, 1, 1), lambda: A.atts_pass_routes(cfg, A.PASS_CONTINUE, 1, 1, 1, 0),
+                lambda: A.atts_gemm_routes(cfg.torch_dtype, 0, 1, 8)):
+        with pytest.raises(A.AttsError) as e:
+            bad()
+        assert e.value.code == A.ERR_INVALID_ARG
+    with pytest.raises(A.AttsError) as e:
+        A.atts_pass_routes(ModelConfig(1, 66, 4, 2, 16, 128, 100, "bf16"), 0, 1, 1, 1)
+    assert e.value.code == A.ERR_SHAPE

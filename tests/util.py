@@ -20,6 +20,11 @@ def ws(nbytes):
     return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device="cuda")
 
 
+def dirty_ws(nbytes):
+    """A workspace full of NaN in every type: a value read before it is written shows."""
+    return torch.full((max(int(nbytes), 256),), 255, dtype=torch.uint8, device="cuda")
+
+
 def announce(*what):
     """Name the case before the GPU step runs, flushed, so a lost box still tells which case it was."""
     print("[case]", *what, flush=True)
