@@ -270,8 +270,9 @@ __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0
 #pragma unroll
                         for (int q = 0; q < 8; ++q) {
                             const int r = 32 * i + 8 * (2 * a2 + (q >> 2)) + (q & 3);
-                            const int rc = kChecked ? min(r, max(rows_left - 1 - 4 * half, 0)) : r;     // a row that exists
-                            const float2* crow = reinterpret_cast<const float2*>(cbase + (int64_t)rc * 64 * sizeof(float2) + c_lane);
+                            // a row that exists: at most M - 1, also for a wave wholly past it (rc is negative there)
+                            const int rc = kChecked ? min(r, rows_left - 1 - 4 * half) : r;
+                            const float2* crow = reinterpret_cast<const float2*>(cbase + (int64_t)rc * (64 * (int)sizeof(float2)) + c_lane);
                             cs[q][0] = crow[0];
                             cs[q][1] = crow[32];
                         }

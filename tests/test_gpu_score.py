@@ -7,7 +7,7 @@ import torch
 
 from oracle import atts_oracle as O
 from synth import WORKLOADS, ModelConfig, make_token_ids, make_weights
-from util import announce, dev, dirty_ws, weights_to_numpy, ws
+from util import announce, dev, dirty_ws, tight_ws, weights_to_numpy, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -175,6 +175,28 @@ def test_partial_sums_in_little_room(P, K, T):
     A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
     ref_lp, ref_s = O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)
     assert np.abs(lp.cpu().numpy() - ref_lp).max() <= TOL["bf16"] and np.abs(sc.cpu().numpy() - ref_s).max() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("heads,P,K,T,tile", [((8, 2), 1, 1, 128, 128), ((8, 2), 100, 6, 250, 128), ((24, 8), 1, 8, 192, 256), ((24, 8), 1, 24, 128, 384),
+                                              ((24, 8), 2, 24, 128, 384), ((24, 8), 6, 24, 128, 384), ((24, 8), 3, 30, 150, 384)])
+def test_the_pass_reads_nothing_past_its_workspace(heads, P, K, T, tile):
+    """The workspace ends where its allocation ends, its last buffer is the rotary table, and the last row of tiles of the fused
+    QKV projection holds one to six rows, or some waves' worth: waves past the last row take the table's last row."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(1, 1024, *heads, 128, 256, 768, "bf16")
+    announce("score tight workspace", heads, P, K, T, tile)
+    route = A.atts_pass_routes(cfg, A.PASS_SCORE, P, K, T)
+    assert route.qkv_fused and route.qkv.tile_rows == tile
+    w, prefix, drafts = _case(cfg, P, K, T, seed=9)
+    model = A.Model(cfg, w)
+    need = A.atts_workspace_bytes(model, P, K, T)
+    out = []
+    for space in (tight_ws(need), ws(need + (8 << 20))):
+        lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+        A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, space)
+        torch.cuda.synchronize()
+        out.append(lp)
+    assert torch.equal(*out) and bool(torch.isfinite(out[0]).all())
 
 
 def test_variable_draft_lengths_and_padding_ids():

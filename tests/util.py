@@ -25,6 +25,15 @@ def dirty_ws(nbytes):
     return torch.full((max(int(nbytes), 256),), 255, dtype=torch.uint8, device="cuda")
 
 
+def tight_ws(nbytes):
+    """A workspace that ends with its allocation (whole 2 MiB pages of its own): nothing behind it belongs to the process."""
+    need = (max(int(nbytes), 256) + 255) // 256 * 256
+    page = 2 << 20
+    torch.cuda.empty_cache()
+    room = torch.empty(-(-max(need, 32 << 20) // page) * page, dtype=torch.uint8, device="cuda")
+    return room[room.numel() - need:]
+
+
 def announce(*what):
     """Name the case before the GPU step runs, flushed, so a lost box still tells which case it was."""
     print("[case]", *what, flush=True)
