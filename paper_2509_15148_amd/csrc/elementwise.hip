@@ -55,24 +55,37 @@ __device__ __forceinline__ float4 load4<bf16>(const bf16* src) {
     return make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
 }
 
-// The row's values come as pieces of four from `first` in the sum-of-squares pass, and from `again` where a row is too long
-// for the registers.  Embedding, norm kernel and scoring rows take the sum in this one order: the same row has the same norm in each.
-template <typename T, typename First, typename Again>
-__device__ __forceinline__ void rmsnorm_pieces(First first, Again again, const float* __restrict__ gain, float eps, int d,
+// The row's values come as pieces of four from `load`; `seen` gets each of them once, behind the loads that are requested
+// together.  Embedding, norm kernel and scoring rows take the sum in this one order: the same row has the same norm in each.
+template <typename T, typename Load, typename Seen>
+__device__ __forceinline__ void rmsnorm_pieces(Load load, Seen seen, const float* __restrict__ gain, float eps, int d,
                                                T* __restrict__ o, float* red) {
     constexpr int kKeep = 4;
     const int n4 = d >> 2;
     const float4* g4 = reinterpret_cast<const float4*>(gain);
-    float4 keep[kKeep];
+    float4 keep[kKeep], g[kKeep];
     float ss = 0.f;
 #pragma unroll
     for (int q = 0; q < kKeep; ++q) {
         const int c = threadIdx.x + 256 * q;
-        keep[q] = c < n4 ? first(c) : make_float4(0.f, 0.f, 0.f, 0.f);
+        keep[q] = c < n4 ? load(c) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (gain) {                                                 // on their way with the row, not behind its sum
+#pragma unroll
+        for (int q = 0; q < kKeep; ++q) {
+            const int c = threadIdx.x + 256 * q;
+            g[q] = c < n4 ? g4[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kKeep; ++q) {
+        const int c = threadIdx.x + 256 * q;
+        if (c < n4) seen(c, keep[q]);
         ss += keep[q].x * keep[q].x + keep[q].y * keep[q].y + keep[q].z * keep[q].z + keep[q].w * keep[q].w;
     }
     for (int c = threadIdx.x + 256 * kKeep; c < n4; c += 256) {
-        const float4 v = first(c);
+        const float4 v = load(c);
+        seen(c, v);
         ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
     }
     if (!gain) return;                                          // block-uniform
@@ -81,15 +94,13 @@ __device__ __forceinline__ void rmsnorm_pieces(First first, Again again, const f
 #pragma unroll
     for (int q = 0; q < kKeep; ++q) {
         const int c = threadIdx.x + 256 * q;
-        if (c < n4) {
-            const float4 g = g4[c];
-            store4<T>(o + 4 * c, make_float4(keep[q].x * inv * g.x, keep[q].y * inv * g.y, keep[q].z * inv * g.z,
-                                             keep[q].w * inv * g.w));
-        }
+        if (c < n4)
+            store4<T>(o + 4 * c, make_float4(keep[q].x * inv * g[q].x, keep[q].y * inv * g[q].y, keep[q].z * inv * g[q].z,
+                                             keep[q].w * inv * g[q].w));
     }
     for (int c = threadIdx.x + 256 * kKeep; c < n4; c += 256) {
-        const float4 v = again(c), g = g4[c];
-        store4<T>(o + 4 * c, make_float4(v.x * inv * g.x, v.y * inv * g.y, v.z * inv * g.z, v.w * inv * g.w));
+        const float4 v = load(c), gc = g4[c];
+        store4<T>(o + 4 * c, make_float4(v.x * inv * gc.x, v.y * inv * gc.y, v.z * inv * gc.z, v.w * inv * gc.w));
     }
 }
 
@@ -97,7 +108,7 @@ template <typename T>
 __device__ __forceinline__ void rmsnorm_row(const float* __restrict__ x, const float* __restrict__ gain, float eps, int d,
                                             T* __restrict__ o, float* red) {
     auto load = [&](int c) __attribute__((always_inline)) { return load4<float>(x + 4 * c); };
-    rmsnorm_pieces<T>(load, load, gain, eps, d, o, red);
+    rmsnorm_pieces<T>(load, [](int, const float4&) {}, gain, eps, d, o, red);
 }
 
 template <typename T>
@@ -115,12 +126,8 @@ template <typename T>
 __device__ __forceinline__ void embed_norm_row(const T* __restrict__ src, int d, float* __restrict__ h, const float* __restrict__ gain,
                                                float eps, T* __restrict__ xn, float* red) {
     auto load = [&](int c) __attribute__((always_inline)) { return load4<T>(src + 4 * c); };
-    auto load_and_store = [&](int c) __attribute__((always_inline)) {
-        const float4 v = load(c);
-        store4<float>(h + 4 * c, v);
-        return v;
-    };
-    rmsnorm_pieces<T>(load_and_store, load, gain, eps, d, xn, red);
+    auto seen = [&](int c, const float4& v) __attribute__((always_inline)) { store4<float>(h + 4 * c, v); };
+    rmsnorm_pieces<T>(load, seen, gain, eps, d, xn, red);
 }
 
 // Everything a pass needs before its first projection, in one launch (each of these is a few microseconds by itself, most of

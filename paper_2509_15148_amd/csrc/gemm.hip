@@ -1153,8 +1153,10 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
     for (int o = 1; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     float sum = 0.f;
 #pragma unroll
-    for (int u = 0; u < kHeld; ++u)
-        if (held[u].y > 0.f) sum += held[u].y * __expf(held[u].x - mx);
+    for (int u = 0; u < kHeld; ++u) {
+        const float with = sum + held[u].y * __expf(held[u].x - mx);
+        sum = held[u].y > 0.f ? with : sum;                          // selected, not branched over
+    }
     for (int i0 = lane + 64 * kHeld; i0 < n_part; i0 += 64 * 8) {
         float2 q[8];
 #pragma unroll
@@ -1300,6 +1302,8 @@ int32_t launch_lmhead_combine(const float2* partials, const float* target_logit,
     const dim3 grid((unsigned)ceil_div(B, rows_per_block)), block(64 * rows_per_block);
     if (n_part <= 64 * 8)
         hipLaunchKernelGGL(lmhead_combine_kernel<8>, grid, block, 0, stream, partials, target_logit, B, n_part, valid, lp);
+    else if (n_part <= 64 * 16)
+        hipLaunchKernelGGL(lmhead_combine_kernel<16>, grid, block, 0, stream, partials, target_logit, B, n_part, valid, lp);
     else
         hipLaunchKernelGGL(lmhead_combine_kernel<32>, grid, block, 0, stream, partials, target_logit, B, n_part, valid, lp);
     ATTS_LAUNCH_CHECK("lmhead_combine_kernel");
