@@ -118,6 +118,13 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const float* __restrict__ 
     rmsnorm_row<T>(h + (int64_t)blockIdx.x * d, gain, eps, d, out + (int64_t)blockIdx.x * d, red);
 }
 
+// (cos, sin)(pos theta^(-2 i / hd)), in fp64, rounded once
+__device__ __forceinline__ float2 rope_pair(int pos, int i, double log_theta_over_half) {
+    double s, c;
+    sincos((double)pos * exp(-(double)i * log_theta_over_half), &s, &c);
+    return make_float2((float)c, (float)s);
+}
+
 // ---- S0: start of a pass: embedding gather + first norm, rotary table, tail of V^T ----------------------------
 // h = embedding of id (an id outside the vocabulary is read as 0 by the caller) and, with a gain vector, xn = rmsnorm(h).
 // Pieces of four elements (rows are multiples of 16 bytes), in the norm's own order: with pieces of eight, a sum of another
@@ -131,12 +138,12 @@ __device__ __forceinline__ void embed_norm_row(const T* __restrict__ src, int d,
 }
 
 // Everything a pass needs before its first projection, in one launch (each of these is a few microseconds by itself, most of
-// it the launch): workgroups [0, R - row0) embed a row each and apply the first layer's norm; the next rope_wgs fill the
+// it the launch): the first row_wgs workgroups embed a row each and apply the first layer's norm; the next rope_wgs fill the
 // rotary table, (cos, sin)(pos(r) theta^(-2 i / hd)) in fp64, rounded once; the last zero columns [R, ldv) of V^T for a
 // producer that writes only the R real ones.  128 rows of the 7B width: 5.7 us for 8.9 + 4.7 + 4.9 in three launches (each
 // with element-wise loads of the embedding); 1152 rows 13.8 for 13.8 + 4.8 + 7.0.
 struct StartDims {
-    int32_t vocab, d, P, T, row0, R, half, rope_wgs;
+    int32_t vocab, d, P, T, row0, R, half, row_wgs, rope_wgs;
     double log_theta_over_half;
     float eps;
     int64_t ldv, vt_rows;
@@ -149,7 +156,7 @@ __global__ __launch_bounds__(256) void tree_start_kernel(const T* __restrict__ e
                                                          const StartDims s) {
     __shared__ float red[4];
     const int rows = s.R - s.row0;
-    if ((int)blockIdx.x < rows) {
+    if ((int)blockIdx.x < s.row_wgs) {
         const int r = s.row0 + (int)blockIdx.x;
         int id;
         bool padding = false;
@@ -165,17 +172,14 @@ __global__ __launch_bounds__(256) void tree_start_kernel(const T* __restrict__ e
             id = 0;
         }
         embed_norm_row<T>(emb + (int64_t)id * s.d, s.d, h + (int64_t)r * s.d, gain, s.eps, xn + (int64_t)r * s.d, red);
-    } else if ((int)blockIdx.x < rows + s.rope_wgs) {
-        const int64_t idx = (int64_t)((int)blockIdx.x - rows) * 256 + threadIdx.x;     // up to 2^24 rows x 128 pairs
+    } else if ((int)blockIdx.x < s.row_wgs + s.rope_wgs) {
+        const int64_t idx = (int64_t)((int)blockIdx.x - s.row_wgs) * 256 + threadIdx.x;     // up to 2^24 rows x 128 pairs
         if (idx >= (int64_t)rows * s.half) return;
         const int r = s.row0 + (int)(idx / s.half), i = (int)(idx % s.half);
-        const double ang = (double)tree_position(r, s.P, s.T) * exp(-(double)i * s.log_theta_over_half);
-        double sn, c;
-        sincos(ang, &sn, &c);
-        cs[(int64_t)r * s.half + i] = make_float2((float)c, (float)sn);
+        cs[(int64_t)r * s.half + i] = rope_pair(tree_position(r, s.P, s.T), i, s.log_theta_over_half);
     } else {
         const int tail = (int)(s.ldv - s.R);
-        const int64_t i = (int64_t)((int)blockIdx.x - rows - s.rope_wgs) * 256 + threadIdx.x;
+        const int64_t i = (int64_t)((int)blockIdx.x - s.row_wgs - s.rope_wgs) * 256 + threadIdx.x;
         if (i < s.vt_rows * tail) vt[(i / tail) * s.ldv + s.R + (i % tail)] = from_f32<T>(0.f);
     }
 }
@@ -200,10 +204,7 @@ __global__ void rope_table_kernel(float2* __restrict__ cs, int first, int rows, 
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (int64_t)rows * half) return;
     const int r = first + (int)(idx / half), i = (int)(idx % half);
-    const double ang = (double)r * exp(-(double)i * log_theta_over_half);
-    double s, c;
-    sincos(ang, &s, &c);
-    cs[(int64_t)r * half + i] = make_float2((float)c, (float)s);
+    cs[(int64_t)r * half + i] = rope_pair(r, i, log_theta_over_half);
 }
 
 // ---- residual update from K-slice partial sums, fused with the next RMSNorm ------------------------------
@@ -466,13 +467,24 @@ int32_t launch_tree_start(int32_t dtype, const void* tok_embed, int32_t vocab, i
     StartDims t{};
     t.vocab = vocab; t.d = d; t.P = s.P; t.T = s.T; t.row0 = row0; t.R = s.R(); t.half = hd / 2; t.eps = eps;
     t.log_theta_over_half = log((double)theta) / (double)t.half;
-    const int64_t rows = t.R - row0, rope = ceil_div(rows * t.half, 256);
-    t.rope_wgs = (int32_t)rope;
     t.ldv = ldv;
     t.vt_rows = vt ? vt_rows : 0;
-    const int64_t zero = vt ? ceil_div(vt_rows * (ldv - t.R), 256) : 0;
-    DISPATCH_T(dtype, hipLaunchKernelGGL(tree_start_kernel<T>, dim3((unsigned)(rows + rope + zero)), dim3(256), 0, stream, (const T*)tok_embed,
-                                         prefix_ids, draft_ids, draft_lens, h, gain, (T*)xn, cs, (T*)vt, err_flag, t);)
+    const int64_t rows = t.R - row0, rope = ceil_div(rows * t.half, 256), zero = vt ? ceil_div(vt_rows * (ldv - t.R), 256) : 0;
+    auto launch = [&](int64_t row_wgs, int64_t rope_wgs, int64_t zero_wgs) {
+        t.row_wgs = (int32_t)row_wgs;
+        t.rope_wgs = (int32_t)rope_wgs;
+        DISPATCH_T(dtype, hipLaunchKernelGGL(tree_start_kernel<T>, dim3((unsigned)(row_wgs + rope_wgs + zero_wgs)), dim3(256), 0, stream,
+                                             (const T*)tok_embed, prefix_ids, draft_ids, draft_lens, h, gain, (T*)xn, cs, (T*)vt, err_flag, t);)
+    };
+    // a launch of 2^32 threads or more runs a part of them without an error: together the parts reach that at 11.2 million rows
+    // (head_dim 256), by themselves none does below the 2^24 rows a call may have
+    if (rows + rope + zero < (1 << 24)) {
+        launch(rows, rope, zero);
+    } else {
+        launch(rows, 0, 0);
+        ATTS_LAUNCH_CHECK("tree_start_kernel");
+        launch(0, rope, zero);
+    }
     ATTS_LAUNCH_CHECK("tree_start_kernel");
     return ATTS_OK;
 }

@@ -1084,7 +1084,8 @@ bool use_big_tile(int32_t M, int32_t N) {
 // against 8.8; 24 x 32000 x 1000: 21.1 against 20.5; 300 x 8000 x 512: 25.0 against 13.6).
 bool use_small_tile(int32_t dtype, int32_t M, int32_t N) {
     const int64_t rounds = ceil_div(ceil_div(M, 128) * ceil_div(N, 128), 256);
-    return ceil_div(M, 32) * ceil_div(N, 32) <= rounds * (dtype == ATTS_DTYPE_F32 ? 2048 : 768);
+    const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32);
+    return tiles <= rounds * (dtype == ATTS_DTYPE_F32 ? 2048 : 768) && tiles < (1 << 24);      // 2^32 threads a launch
 }
 
 template <typename T, int EPI>

@@ -199,6 +199,29 @@ def test_the_pass_reads_nothing_past_its_workspace(heads, P, K, T, tile):
     assert torch.equal(*out) and bool(torch.isfinite(out[0]).all())
 
 
+def test_more_rows_than_one_launch_has_threads_for():
+    """11.5 million rows, head_dim 256: a workgroup for each row and for 256 rotary pairs each would be 4.4e9 threads, and a
+    launch has at most 2^32.  No layers, so that the scores follow from a table over pairs of tokens."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(0, 8, 1, 1, 256, 8, 16, "bf16")
+    P, K, T = 3, 720000, 16
+    announce("score many rows", P, K, T)
+    w = make_weights(cfg, 5, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(7)
+    ids = lambda *shape: torch.randint(0, cfg.vocab, shape, dtype=torch.int32, device="cuda", generator=g)
+    prefix, drafts = ids(P), ids(K, T)
+    model = A.Model(cfg, w)
+    lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_score_drafts(model, prefix, drafts, None, 0, lp, sc, ws(A.atts_workspace_bytes(model, P, K, T)))
+    assert A.atts_model_check(model) == 0
+    h = w["tok_embed"].double()
+    x = h * torch.rsqrt((h * h).mean(dim=1, keepdim=True) + cfg.rms_eps) * w["final_norm"].double()
+    table = torch.log_softmax(x @ w["lm_head"].double().t(), dim=1)
+    before = torch.cat([prefix[-1:].expand(K, 1), drafts[:, :-1]], dim=1).long()
+    ref = table[before, drafts.long()]
+    assert float((lp - ref).abs().max()) <= TOL["bf16"] and float((sc + ref.mean(dim=1)).abs().max()) <= TOL["bf16"]
+
+
 def test_variable_draft_lengths_and_padding_ids():
     import paper_2509_15148_amd as A
     cfg = ModelConfig(2, 256, 4, 2, 128, 512, 1000, "bf16")
