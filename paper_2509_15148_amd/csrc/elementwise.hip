@@ -328,9 +328,10 @@ __global__ __launch_bounds__(256) void transpose_v_kernel(const T* __restrict__ 
     }
 }
 
-// Up to kMaxCopies blocks of pitched arrays, dst[r][c] = src[r][c] (prefix cache <-> workspace), by the workgroups from `wg0`
-// on; 16 bytes per thread, or element by element where a block does not start and continue at multiples of 16 bytes and at
-// the end of its rows.
+// Up to CopyBlocks::kMax blocks of pitched arrays, dst[r][c] = src[r][c] (prefix cache <-> workspace), by workgroups 0, 1, ...
+// of a launch or a part of one.  A block whose rows start at multiples of 16 bytes on both sides takes 16 bytes per thread (the
+// end of its rows element by element); any other one element per thread, so that a wavefront's accesses stay together:
+// V^T of an extension whose prefix length is not a multiple of 8.
 template <typename T>
 __device__ __forceinline__ void copy_blocks(const CopyBlocks& jobs, int wg) {
     constexpr int V = 16 / (int)sizeof(T);
@@ -339,15 +340,17 @@ __device__ __forceinline__ void copy_blocks(const CopyBlocks& jobs, int wg) {
     for (int j = 0; j < CopyBlocks::kMax; ++j) {
         if (j >= jobs.n) return;
         const CopyBlock& b = jobs.b[j];
-        const int64_t pieces = (b.cols + V - 1) / V, total = b.rows * pieces;
+        const int64_t pieces = b.wide ? (b.cols + V - 1) / V : b.cols, total = b.rows * pieces;
         if (i < total) {
-            const int64_t r = i / pieces, c = (i % pieces) * V;
+            const int64_t r = i / pieces, c = (i % pieces) * (b.wide ? V : 1);
             const T* src = reinterpret_cast<const T*>(b.src) + r * b.src_ld + c;
             T* dst = reinterpret_cast<T*>(b.dst) + r * b.dst_ld + c;
-            if (b.wide && c + V <= b.cols) {
+            if (!b.wide) {
+                *dst = *src;
+            } else if (c + V <= b.cols) {
                 *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
             } else {
-                for (int u = 0; u < V && c + u < b.cols; ++u) dst[u] = src[u];
+                for (int u = 0; c + u < b.cols; ++u) dst[u] = src[u];
             }
             return;
         }
@@ -567,7 +570,7 @@ void add_copy(int32_t dtype, CopyBlocks& jobs, const void* src, int64_t src_ld, 
 int64_t copy_workgroups(int32_t dtype, const CopyBlocks& jobs) {
     const int64_t v = 16 / (int64_t)dtype_size(dtype);
     int64_t pieces = 0;
-    for (int j = 0; j < jobs.n; ++j) pieces += jobs.b[j].rows * ceil_div(jobs.b[j].cols, v);
+    for (int j = 0; j < jobs.n; ++j) pieces += jobs.b[j].rows * (jobs.b[j].wide ? ceil_div(jobs.b[j].cols, v) : jobs.b[j].cols);
     return ceil_div(pieces, 256);
 }
 int32_t launch_copies(int32_t dtype, const CopyBlocks& jobs, hipStream_t stream) {

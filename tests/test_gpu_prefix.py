@@ -6,7 +6,7 @@ import torch
 
 from oracle import atts_oracle as O
 from synth import WORKLOADS, ModelConfig, make_token_ids, make_weights
-from util import announce, dev, weights_to_numpy, ws
+from util import announce, dev, dirty_ws, weights_to_numpy, ws
 
 pytestmark = pytest.mark.gpu
 
@@ -41,7 +41,7 @@ def _extend(A, pre, ids):
     (WORKLOADS["tiny"].model, 64, 8, 32, (64,)),                                   # fp32, simple attention
     (ModelConfig(2, 96, 4, 1, 24, 200, 515, "fp32"), 19, 4, 23, (7, 1, 11)),        # prefill in three pieces
     (ModelConfig(2, 256, 4, 2, 128, 520, 2003, "bf16"), 70, 3, 45, (70,)),          # MFMA attention, general GEMM
-    (ModelConfig(2, 256, 4, 2, 128, 512, 2048, "bf16"), 72, 5, 40, (40, 32)),       # aligned GEMM + fused RoPE epilogue
+    (ModelConfig(2, 256, 4, 2, 128, 512, 2048, "bf16"), 72, 5, 40, (40, 32)),       # whole columns of tiles, but K below the aligned GEMM's 768
     (ModelConfig(2, 256, 4, 2, 128, 512, 2048, "bf16"), 130, 2, 9, (1, 129)),       # prefix length not a multiple of 4
 ])
 def test_cached_scoring_matches_cold_scoring_and_the_oracle(cfg, P, K, T, chunks):
@@ -72,6 +72,38 @@ def test_cached_scoring_matches_cold_scoring_and_the_oracle(cfg, P, K, T, chunks
     lp_w2, _ = _cached(A, model, pre, drafts, lens)
     assert np.array_equal(lp_w, lp_w2)
     assert A.atts_model_check(model) == 0
+
+
+@pytest.mark.parametrize("P,K,T,chunks", [
+    (72, 2, 7, (72,)), (132, 4, 4, (128, 4)), (8, 1, 16, (4, 4)),                # up to 16 rows: slices of the few-row kernel
+    (72, 5, 20, (40, 32)), (132, 8, 16, (132,)), (136, 1, 17, (120, 9, 7)),      # 17 to 128: slices of the aligned kernel
+    (4, 7, 9, (1, 3)), (260, 3, 40, (64, 131, 65)),
+])
+def test_cached_rows_copied_with_the_finish_of_a_cut_projection(P, K, T, chunks):
+    """Few draft rows on a cached prefix: the QKV projection is cut along K, and the pass that adds its slices also puts the
+    cached keys and transposed values in place, up to the column where the new rows' begin (prefix lengths that are multiples
+    of 8 and of 4 only).  The prefix comes in pieces at odd lengths too, whose values are appended element by element."""
+    import paper_2509_15148_amd as A
+    cfg = ModelConfig(2, 768, 6, 2, 128, 1024, 768, "bf16")
+    announce("prefix cut projection", P, K, T, chunks)
+    route = A.atts_pass_routes(cfg, A.PASS_SCORE_CACHED, P, K, T)
+    assert route.qkv_fused and route.qkv.slices > 1
+    assert route.qkv.kernel == (A.KERNEL_FEW_ROWS if K * T <= 16 else A.KERNEL_ALIGNED)
+    w_dev = make_weights(cfg, seed=P + K, device="cuda")
+    prefix, drafts = [x.numpy() for x in make_token_ids(cfg.vocab, P, K, T, P + 7 * K)]
+    model = A.Model(cfg, w_dev)
+    pre = A.Prefix(model, capacity=P + 3)
+    lo = 0
+    for n in chunks:
+        A.atts_prefix_extend(pre, dev(prefix[lo:lo + n]), dirty_ws(A.atts_prefix_extend_workspace_bytes(pre, n)))
+        lo += n
+    assert A.atts_prefix_length(pre) == P
+    lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_score_drafts_cached(pre, dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
+    lp_c, _ = _cold(A, model, prefix, drafts)
+    ref_lp, ref_s = O.score_drafts(weights_to_numpy(w_dev), cfg, prefix, drafts)
+    assert np.abs(lp.cpu().numpy() - ref_lp).max() <= TOL["bf16"] and np.abs(sc.cpu().numpy() - ref_s).max() <= TOL["bf16"]
+    assert np.abs(lp.cpu().numpy() - lp_c).max() <= TOL["bf16"] / 2
 
 
 def test_extend_with_an_accepted_draft_then_score_the_next_turn():
