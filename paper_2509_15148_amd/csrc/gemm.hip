@@ -1078,14 +1078,24 @@ bool use_big_tile(int32_t M, int32_t N) {
 }
 
 // Products of few tiles go to the kernel with 32 x 32 tiles and K split over a workgroup's wavefronts (small.hip).  Its time
-// grows with its tiles, the general kernel's with its rounds of 128 x 128 tiles; they meet at about 2048 small tiles per
-// round in fp32 (1024 x 2048 x 1024: 86.3 us against 88.4; 300 x 8000 x 512: 58.1 against 49.0) and 768 in bf16, whose
-// matrix instructions take a sixteenth of the time so that the unshared operand reads count (1024 x 1024 x 256: 6.7 us
-// against 8.8; 24 x 32000 x 1000: 21.1 against 20.5; 300 x 8000 x 512: 25.0 against 13.6).
-bool use_small_tile(int32_t dtype, int32_t M, int32_t N) {
-    const int64_t rounds = ceil_div(ceil_div(M, 128) * ceil_div(N, 128), 256);
-    const int64_t tiles = ceil_div(M, 32) * ceil_div(N, 32);
-    return tiles <= rounds * (dtype == ATTS_DTYPE_F32 ? 2048 : 768) && tiles < (1 << 24);      // 2^32 threads a launch
+// grows with its tiles, the general kernel's with its rounds of 128 x 128 tiles, of which a compute unit takes two at a
+// time in 1.64 times the time of one (fp32).  The most small tiles it is taken for, and times around them in us:
+//   fp32, one round    2048 up to K = 256, else 1920:  1024 x 2048 x 128  14.2 (16.7 general); 1000 x 1900 x 2048  165 (168);
+//                      2000 x 1000 (2016 tiles) x 2048  181 (169)
+//   fp32, two rounds   twice that up to K = 256, 1.7 times up to 512, else 1.5:  260 x 11000 (3096 tiles)  71 (75) at K = 512,
+//                      284 (273) at 2048; 129 x 16600 (2595 tiles) x 8192  964 (1090); 300 x 12000 (3750 tiles) x 2048  331 (279)
+//   bf16               768 a round, as its matrix instructions take a sixteenth of the time so that the unshared operand reads
+//                      count:  1000 x 768 x 2048  25 (33); 17 x 49000 (1532 tiles) x 2048  44 (75); 33 x 24000 (1500 tiles of
+//                      one round): general.  Above K = 4096 the weights come from memory once either way and the general kernel's
+//                      second round only counts as it fills: 17 x 33000 (1032 tiles) x 8192  201 (165), 17 x 49000  253 (280)
+bool use_small_tile(int32_t dtype, int32_t M, int32_t N, int32_t Kd) {
+    const int64_t general = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(general, 256), tiles = ceil_div(M, 32) * ceil_div(N, 32);
+    if (tiles >= (1 << 24)) return false;                        // 2^32 threads a launch
+    if (dtype == ATTS_DTYPE_F32) {
+        const double pair = Kd <= 256 ? 2.0 : (Kd <= 512 ? 1.7 : 1.5);
+        return (double)tiles <= (Kd <= 256 ? 2048 : 1920) * ((double)(rounds / 2) * pair + (double)(rounds % 2));
+    }
+    return tiles <= (Kd <= 4096 || general <= 256 ? rounds * 768 : 768 + 7 * (general - 256));
 }
 
 template <typename T, int EPI>
@@ -1227,7 +1237,7 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
         return r;
     }
     const int32_t n_cols = epi == EPI_SWIGLU ? 2 * g.N : g.N;
-    if (use_small_tile(dtype, g.M, n_cols)) {
+    if (use_small_tile(dtype, g.M, n_cols, g.Kd)) {
         r.kernel = ATTS_KERNEL_SMALL; r.n_part = small_lmhead_partials(g.N);
     } else {
         const bool big = use_big_tile(g.M, n_cols);

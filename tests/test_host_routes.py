@@ -58,3 +58,13 @@ def test_route_entry_points_validate_arguments():
     with pytest.raises(A.AttsError) as e:
         A.atts_pass_routes(ModelConfig(1, 66, 4, 2, 16, 128, 100, "bf16"), 0, 1, 1, 1)
     assert e.value.code == A.ERR_SHAPE
+
+
+@pytest.mark.parametrize("dtype,shape,small", [
+    ("fp32", (1024, 2048, 256), True), ("fp32", (2000, 1000, 1024), False), ("fp32", (1000, 1900, 2048), True), ("fp32", (300, 12000, 2048), False),
+    ("fp32", (129, 16600, 8192), True), ("fp32", (260, 11000, 512), True), ("fp32", (260, 11000, 2048), False),
+    ("bf16", (17, 33000, 2048), True), ("bf16", (17, 33000, 8192), False), ("bf16", (17, 49000, 8192), True), ("bf16", (33, 24000, 2048), False),
+    ("fp32", (1 << 30, 32, 8), False)])
+def test_products_of_few_tiles(dtype, shape, small):
+    gemm, _ = A.atts_gemm_routes({"fp32": MODELS["tiny"], "bf16": MODELS["7b"]}[dtype].torch_dtype, *shape)
+    assert (gemm.kernel == A.KERNEL_SMALL) == small
