@@ -1192,6 +1192,11 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 //       1262 against 1441).  Padded rows take the other orientation where its rounds of tiles are fewer by more than the
 //       9 % its epilogue costs at least: 257 to 384 rows (one row of 384 x 256 tiles, 482 against 517; 70B head 748 against 889),
 //       196 rows of the 70B head (540 against 630), 1090 (1953 against 2136).
+//       Small vocabularies leave most of the chip idle, and a tile of 384 x 256 is then the longer chain: exchanged only where its
+//       1.43 (nearly no tile) to 1.69 us (256 tiles) a slab of 64 k elements and 3.5 us are less than the other kernel's time (first
+//       orientation 0.95 to 1.47 and 17, general kernel 0.82 and 15 up to a tile a compute unit, 0.95 to 1.23 and 17.5 up to
+//       two): 300 rows of 9216 entries d 1024 35.4 (general 37.7), 1536 47.3 (44.0), 4096 103.6 (76.6); 256 rows d 768 28.7
+//       (first 36.8), 1536 45 (48), 4096 102 (88).
 //   up to 128: 256 x 128 tiles, vocabulary a multiple of 256.  Bound by the vocabulary matrix streaming by once: three
 //       stages of 48 KB keep 96 KB a CU in flight.  64 rows of 152,064 x 3584 217 us (5.0 TB/s; general kernel
 //       484), 128 rows 226 (unpadded: 496; padded, 128 x 256 tiles the other way round: 248).  128 x 128 tiles, two
@@ -1201,9 +1206,19 @@ static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw
 }
 static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
     if (g.N % 384 != 0 || g.M <= 128 || !lmhead_aligned_k(dtype, g.Kd, g.lda, g.ldw)) return false;
-    if (!g.a_rows_padded || g.N % 256 != 0) return true;              // the other orientation would be the general kernel's
-    const double us = (double)ceil_div(g.N / 384 * ceil_div(g.M, 256), 256) * fast_tile_us(384, false, g.Kd / kWideBK);
-    return us <= 1.09 * direct_plan(EPI_LMHEAD, g).us;
+    const double slabs = (double)(g.Kd / kWideBK);
+    const int64_t tiles = (int64_t)g.N / 384 * ceil_div(g.M, 256);
+    const double light_us = (1.43 + 0.001 * (double)tiles) * slabs + 3.5;     // tiles of a partly filled round
+    if (fast_path_ok(dtype, EPI_LMHEAD, g)) {
+        const TilePlan first = direct_plan(EPI_LMHEAD, g);
+        const double other = (double)(ceil_div(g.M, 256) * (g.N / 256));
+        if (tiles <= 256 && first.rows == 256 && other <= 256) return light_us <= (0.95 + 8e-6 * other * other) * slabs + 17.0;
+        return (double)ceil_div(tiles, 256) * fast_tile_us(384, false, g.Kd / kWideBK) <= 1.09 * first.us;
+    }
+    if (use_small_tile(dtype, g.M, g.N, g.Kd)) return false;
+    const int64_t general = ceil_div(g.M, 128) * ceil_div(g.N, 128);
+    if (use_big_tile(g.M, g.N) || general > 512) return true;
+    return light_us <= (general <= 256 ? 0.82 * slabs + 15.0 : (0.95 + 0.28 * (double)(general - 256) / 256) * slabs + 17.5);
 }
 static bool lmhead_few_ok(int32_t dtype, const GemmArgs& g) {
     return g.N % 256 == 0 && g.M <= 128 && lmhead_aligned_k(dtype, g.Kd, g.lda, g.ldw);

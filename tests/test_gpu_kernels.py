@@ -84,14 +84,21 @@ def test_lmhead_small_products(dtype, shape):
     assert torch.equal(lp, lp2)
 
 
+@pytest.mark.parametrize("V", [2304, 6144])
 @pytest.mark.parametrize("B", [1, 7, 8, 9, 127, 128, 129, 255, 257, 300, 519])
-def test_lmhead_exchanged_takes_any_number_of_rows(B):
+def test_lmhead_exchanged_takes_any_number_of_rows(B, V):
     """Vocabulary entries as tile rows, scoring rows as columns read in place: one to 128 rows (128-column tiles) and more
     (256-column tiles), the last column tile filled by one, seven and eight rows and all but one.  The scoring rows end
-    where their allocation does.  Bound as in test_lmhead_small_products."""
+    where their allocation does.  The smaller vocabulary goes to small tiles from 129 to 320 rows.  Bound as in
+    test_lmhead_small_products."""
     import paper_2509_15148_amd as A
-    d, V = 832, 2304
-    announce("lmhead exchanged rows", B)
+    d = 832
+    announce("lmhead exchanged rows", B, V)
+    _, route = A.atts_gemm_routes(torch.bfloat16, B, V, d)
+    if V == 2304 and 128 < B <= 320:
+        assert route.kernel == A.KERNEL_SMALL
+    else:
+        assert (route.kernel, route.tile_rows) == (A.KERNEL_EXCHANGED, 256 if B <= 128 else 384)
     x, w = _rand((B, d), 71, torch.bfloat16, scale=2.0), _rand((V, d), 72, torch.bfloat16, scale=4.0 / math.sqrt(d))
     tgt = torch.from_numpy(np.random.default_rng(5).integers(0, V, B).astype(np.int32))
     tgt[0], tgt[-1] = 0, V - 1
@@ -106,12 +113,15 @@ def test_lmhead_exchanged_takes_any_number_of_rows(B):
     assert torch.equal(lp[:B], lp2) and torch.isnan(lp[B:]).all()
 
 
-def test_gemm_aligned_last_tile_rows_in_a_second_launch():
-    """27 x 38 tiles of 384 x 256 = 1026 = four rounds of 256 and two tiles over: the aligned bf16 path gives the last
-    tile row to a launch of its own with 128-row tiles (26 x 38 = 988 tiles in four rounds, then 384 rows as 114 small
-    tiles).  Every element against the float64 product."""
+@pytest.mark.parametrize("shape,tail", [((4608, 11008, 768), 128), ((2304, 14592, 1024), 256)])
+def test_gemm_aligned_last_tile_rows_in_a_second_launch(shape, tail):
+    """12 x 43 tiles of 384 x 256 = 516 = two rounds of 256 and four tiles over: the aligned bf16 path gives the last tile row to
+    a launch of its own with 128-row tiles; 6 x 57 = 342: the last two to one with 256-row tiles.  Every element against
+    the float64 product."""
     import paper_2509_15148_amd as A
-    M, N, Kd = 10368, 9728, 768
+    M, N, Kd = shape
+    route, _ = A.atts_gemm_routes(torch.bfloat16, M, N, Kd)
+    assert (route.kernel, route.tile_rows, route.tail_rows) == (A.KERNEL_ALIGNED, 384, tail) and 0 < route.head_rows < M
     announce("gemm tail launch", (M, N, Kd))
     a, w = _rand((M, Kd), 21, torch.bfloat16), _rand((N, Kd), 22, torch.bfloat16)
     c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")

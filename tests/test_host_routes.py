@@ -60,6 +60,16 @@ def test_route_entry_points_validate_arguments():
     assert e.value.code == A.ERR_SHAPE
 
 
+@pytest.mark.parametrize("rows,vocab,d,exchanged", [
+    (300, 768, 4096, False), (300, 9216, 1024, True), (300, 9216, 1536, False), (600, 12288, 4096, False), (1000, 6144, 4096, False),
+    (256, 2304, 768, True), (256, 3072, 4096, False), (160, 32256, 1536, True), (300, 32256, 4096, True), (385, 152064, 3584, True)])
+def test_lm_head_with_few_tiles_keeps_the_faster_kernel(rows, vocab, d, exchanged):
+    """More than 128 unpadded scoring rows: vocabulary entries as rows of 384 x 256 tiles where that was measured faster, and
+    not where a partly filled round of them is the longer chain."""
+    _, head = A.atts_gemm_routes(MODELS["7b"].torch_dtype, rows, vocab, d)
+    assert (head.kernel == A.KERNEL_EXCHANGED) == exchanged
+
+
 @pytest.mark.parametrize("dtype,shape,small", [
     ("fp32", (1024, 2048, 256), True), ("fp32", (2000, 1000, 1024), False), ("fp32", (1000, 1900, 2048), True), ("fp32", (300, 12000, 2048), False),
     ("fp32", (129, 16600, 8192), True), ("fp32", (260, 11000, 512), True), ("fp32", (260, 11000, 2048), False),
