@@ -24,8 +24,8 @@ def _rand(shape, seed, dtype, scale=1.0):
 @pytest.mark.parametrize("shape", [(1, 1, 8), (33, 70, 72), (300, 200, 136), (257, 513, 1000), (128, 128, 64),
                                    (3584, 3600, 264),
                                    # aligned bf16 shapes with more 384-row tiles than compute units: workgroups walk two or
-                                   # three tiles each, some one fewer than others (510 and 700 tiles)
-                                   (1152, 43520, 768), (768, 89600, 832),
+                                   # three tiles each, some one fewer than others (680 and 700 tiles)
+                                   (1536, 43520, 768), (768, 89600, 832),
                                    # at most 16 rows: the weight-streaming kernel (bf16), ragged columns and k-step counts
                                    (1, 1, 32), (4, 100, 96), (7, 4608, 256), (16, 33, 2080), (16, 530, 3584), (3, 48, 18944)])
 def test_gemm_nt_matches_float64_matmul(dtype, shape):
@@ -45,6 +45,7 @@ def test_gemm_nt_matches_float64_matmul(dtype, shape):
     (31, 33, 8), (32, 32, 16), (33, 65, 24), (64, 96, 40), (20, 31, 136),      # edges of 32 x 32 tiles; K from one step to ragged quarters
     (1024, 768, 72), (1024, 769, 72),                                          # bf16: 768 small tiles, and one column of tiles more
     (1024, 2048, 72), (1024, 2049, 72),                                        # fp32: 2048 small tiles, and more: 128 x 128 tiles
+    (1024, 1920, 264), (1024, 1921, 264),                                      # fp32, longer sums: 1920
     (130, 33000, 40), (17, 66000, 24)])                                        # two and three rounds of 128 x 128 tiles
 def test_gemm_small_products(dtype, shape):
     """Shapes at the edges of the kernel for products of few tiles and of the rule that chooses it, against the float64
@@ -132,22 +133,26 @@ def test_gemm_aligned_last_tile_rows_in_a_second_launch(shape, tail):
 
 
 def test_gemm_aligned_shapes_sweep():
-    """Seeded sweep over shapes the aligned bf16 kernel takes (rows a multiple of 256 or 384, columns of 256, inner
+    """Seeded sweep over shapes the aligned bf16 kernel takes (rows a multiple of 256, columns of 256, inner
     dimension of 64 from 768 up): tile counts below and above the number of compute units, partly filled last rounds of
-    the tile walk, both tile heights.  Every element against the float64 product."""
+    the tile walk, all tile heights, second launches.  Every element against the float64 product."""
     import paper_2509_15148_amd as A
-    rng = np.random.default_rng(15148)
+    rng, heights = np.random.default_rng(15148), set()
     for case in range(12):
-        M = int(rng.choice([256, 384, 768, 1152, 1280, 1536, 2304, 3072, 4224]))
+        M = int(rng.choice([256, 512, 768, 1024, 1280, 1536, 2304, 3072, 3840]))
         N = 256 * int(rng.integers(1, 90))
         Kd = 64 * int(rng.choice([12, 13, 16, 24, 31]))
         announce("gemm aligned", case, (M, N, Kd))
+        route, _ = A.atts_gemm_routes(torch.bfloat16, M, N, Kd)
+        assert route.kernel == A.KERNEL_ALIGNED
+        heights |= {route.tile_rows, -route.tail_rows}
         a, w = _rand((M, Kd), 300 + case, torch.bfloat16), _rand((N, Kd), 400 + case, torch.bfloat16)
         c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
         A.atts_gemm_nt(a.cuda(), w.cuda(), c)
         torch.cuda.synchronize()
         ref = a.double().numpy() @ w.double().numpy().T
         assert np.allclose(c.cpu().numpy(), ref, rtol=1e-5, atol=2e-5 * math.sqrt(Kd)), (M, N, Kd)
+    assert heights == {128, 256, 384, 0, -128, -256}
 
 
 def test_gemm_few_rows_random_shapes():

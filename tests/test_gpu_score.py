@@ -76,9 +76,8 @@ def test_small_models_ragged_shapes(cfg, P, K, T):
 
 @pytest.mark.parametrize("P,K,T", [(2, 1, 128), (44, 2, 128), (45, 3, 115), (8, 4, 128), (6, 3, 257), (160, 4, 250), (100, 6, 250)])
 def test_row_counts_between_tiles(P, K, T):
-    """130 to 1600 rows of an aligned bf16 model: the tile height of every projection (128, 256 or 384 rows), the K split of
-    the narrow ones and the orientation of the LM head (128 to 1500 scoring rows) follow from the rounds of tiles, and most
-    of these row counts end in a partly filled tile.  Repeated runs agree bit for bit."""
+    """130 to 1600 rows of an aligned bf16 model, most of them ending in a partly filled tile of 128 or 256 rows, with the narrow
+    projections cut along K and an LM head of 128 to 1500 scoring rows.  Repeated runs agree bit for bit."""
     import paper_2509_15148_amd as A
     cfg = ModelConfig(1, 1024, 8, 2, 128, 4096, 2304, "bf16")
     announce("score rows", P, K, T)
@@ -90,6 +89,46 @@ def test_row_counts_between_tiles(P, K, T):
     assert np.abs(sc - ref_s).max() <= TOL["bf16"]
     _, sc2, _ = _run_gpu(A, cfg, w_dev, prefix, drafts, want_lp=False)
     assert np.array_equal(sc, sc2)
+
+
+ALIGNED, EXCHANGED = 4, 5      # atts.h: ATTS_KERNEL_*
+
+
+@pytest.mark.parametrize("cfg,P,K,T,expected", [
+    # product -> (kernel, rows of a tile, cut along K, rows of a tile of the second launch)
+    (ModelConfig(1, 768, 6, 2, 128, 16384, 768, "bf16"), 8, 96, 16, {"gate_up": (ALIGNED, 384, False, 128), "down": (ALIGNED, 128, True, 0)}),
+    (ModelConfig(1, 1024, 8, 2, 128, 8192, 768, "bf16"), 8, 64, 32, {"gate_up": (ALIGNED, 384, False, 256), "down": (ALIGNED, 256, True, 0)}),
+    (ModelConfig(1, 2048, 16, 4, 128, 8192, 768, "bf16"), 8, 32, 32, {"o": (ALIGNED, 256, True, 0), "gate_up": (ALIGNED, 384, False, 0)}),
+    (ModelConfig(1, 2048, 16, 4, 128, 8192, 768, "bf16"), 8, 64, 40, {"down": (ALIGNED, 384, True, 0), "lm_head": (ALIGNED, 256, False, 0)}),
+    (ModelConfig(1, 8192, 6, 2, 128, 1024, 768, "bf16"), 8, 64, 64, {"o": (ALIGNED, 384, False, 0), "down": (ALIGNED, 384, False, 256)}),
+    (ModelConfig(1, 768, 6, 2, 128, 768, 65536, "bf16"), 8, 49, 16, {"lm_head": (ALIGNED, 384, False, 128)}),
+    (ModelConfig(1, 1024, 8, 2, 128, 768, 44032, "bf16"), 8, 27, 19, {"lm_head": (ALIGNED, 384, False, 256)}),
+    (ModelConfig(1, 768, 6, 2, 128, 768, 98304, "bf16"), 8, 13, 23, {"lm_head": (EXCHANGED, 384, False, 0)}),
+])
+def test_tile_heights_second_launches_and_orientations(cfg, P, K, T, expected):
+    """Every tile height of every product, cut along K and not, the last rows in a second launch of 128- and 256-row tiles
+    (SwiGLU, residual update and LM head, whose targets, partials and logits then start further on) and both orientations of the
+    LM head.  Oracle: the first and the last draft and those on either side of where a second launch begins."""
+    import paper_2509_15148_amd as A
+    announce("score routes", cfg, P, K, T)
+    routes = A.atts_pass_routes(cfg, A.PASS_SCORE, P, K, T)
+    sampled = {0, K - 1}
+    for name, want in expected.items():
+        r = getattr(routes, name)
+        assert (r.kernel, r.tile_rows, r.slices > 1, r.tail_rows) == want, (name, r.kernel, r.tile_rows, r.slices, r.tail_rows)
+        if r.tail_rows:
+            first = r.head_rows if name == "lm_head" else r.head_rows - P
+            sampled |= {(first - 1) // T, first // T, min(first // T + 1, K - 1)}
+    w, prefix, drafts = _case(cfg, P, K, T, seed=K)
+    model = A.Model(cfg, w)
+    lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
+    lp, sc, w_np = lp.cpu().numpy(), sc.cpu().numpy(), weights_to_numpy(w)
+    assert np.isfinite(lp).all() and np.isfinite(sc).all()
+    for k in sorted(sampled):
+        ref = O.token_logprobs(w_np, cfg, prefix, drafts[k])
+        assert np.abs(lp[k] - ref).max() <= TOL["bf16"], (k, np.abs(lp[k] - ref).max())
+        assert abs(sc[k] - O.conformity_score(ref)) <= TOL["bf16"], k
 
 
 @pytest.mark.parametrize("cfg,P,K,T", [
