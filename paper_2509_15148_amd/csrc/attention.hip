@@ -31,7 +31,7 @@ __device__ __forceinline__ int seg_start(int r, int P, int T) { return r < P ? 0
 // ------------------------------------------------------------------------------------------
 template <typename T>
 __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ qkv, T* __restrict__ out, int row0, int P, int Tn,
-                                                         int nq, int nkv, int hd, float scale, bool wide) {
+                                                         int nq, int nkv, int hd, float scale) {
     extern __shared__ float sm[];           // [hd] query, then [n_keys] scores
     float* sq = sm;
     float* sp = sm + hd;
@@ -52,24 +52,7 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
     for (int i = lane; i < n; i += 64) {
         const T* k = kbase + (int64_t)(i < n1 ? i : s0 + (i - n1)) * ld;
         float s = 0.f;
-        if (wide) {             // rows start at multiples of 16 bytes: four 16-byte pieces requested at a time
-            constexpr int kVec = 16 / (int)sizeof(T);
-            for (int c0 = 0; c0 < hd; c0 += 4 * kVec) {
-                uint4 raw[4];
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) raw[q4] = *reinterpret_cast<const uint4*>(k + min(c0 + q4 * kVec, hd - kVec));
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4) {
-                    const T* e = reinterpret_cast<const T*>(&raw[q4]);
-                    const int c = c0 + q4 * kVec;
-                    if (c < hd)
-#pragma unroll
-                        for (int u = 0; u < kVec; ++u) s += sq[c + u] * to_f32<T>(e[u]);
-                }
-            }
-        } else {
-            for (int c = 0; c < hd; ++c) s += sq[c] * to_f32<T>(k[c]);
-        }
+        for (int c = 0; c < hd; ++c) s += sq[c] * to_f32<T>(k[c]);
         sp[i] = s;
         mx = fmaxf(mx, s);
     }
@@ -85,27 +68,46 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     __syncthreads();
     const float inv = 1.f / sum;
-    // output: `width` lanes (a power of two >= hd, at most 64) per key, the 64 / width groups of lanes take every such key,
-    // eight of a group's keys requested at a time (one key at a time, with half the lanes idle at hd 32: 12.7 us for 320
-    // rows x 4 heads over 96 keys, 10.4 now); the groups are added by exchange at the end
+    // output: `width` lanes (a power of two >= hd, at most 64) per key, the 64 / width groups of lanes take every such key; eight
+    // of a group's keys are requested at a time, from the prefix rows and then from the draft's, so that a key costs one
+    // load and one multiply-add; the groups are added by exchange at the end.  320 rows, 4 heads of 32 over up to 96 keys, fp32:
+    // 11.1 us one key at a time, 7.4 now; 3256 rows, 4 heads of 64 over up to 3128, bf16: 838 and 746 (with a clamp and two
+    // selects a key 1044)
     int width = 64;
     while (width / 2 >= hd) width /= 2;
     const int groups = 64 / width, grp = lane / width, sub = lane % width;
+    const int64_t step = (int64_t)groups * ld;
     for (int c = sub; c < align_up_int(hd, width); c += width) {
         const bool ok = c < hd;
-        const T* v = vbase + (ok ? c : 0);
         float acc = 0.f;
-        for (int i0 = grp; i0 < n; i0 += 8 * groups) {
-            float x[8], p[8];
+        auto keys = [&](int i, int end, int row) __attribute__((always_inline)) {      // keys i, i + groups, ... below end; key i is that row
+            const T* v = vbase + (int64_t)row * ld + (ok ? c : 0);
+            for (; i + 7 * groups < end; i += 8 * groups, v += 8 * step) {
+                T x[8];
+                float p[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = i0 + u * groups, ic = min(i, n - 1);
-                x[u] = to_f32<T>(v[(int64_t)(ic < n1 ? ic : s0 + (ic - n1)) * ld]);
-                p[u] = i < n ? sp[ic] : 0.f;
+                for (int u = 0; u < 8; ++u) x[u] = v[u * step];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) p[u] = sp[i + u * groups];
+                __builtin_amdgcn_sched_barrier(0);              // else each 16-bit value is waited for and widened by itself
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc += p[u] * to_f32<T>(x[u]);
             }
+            if (i < end) {                                      // fewer than eight left: the key repeated past the last is not added
+                T x[8];
+                float p[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += i0 + u * groups < n ? p[u] * x[u] : 0.f;
-        }
+                for (int u = 0; u < 8; ++u) x[u] = v[i + u * groups < end ? u * step : 0];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) p[u] = sp[i + u * groups < end ? i + u * groups : i];
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = i + u * groups < end ? acc + p[u] * to_f32<T>(x[u]) : acc;
+            }
+        };
+        keys(grp, n1, grp);
+        const int i2 = n1 + (grp - n1 % groups + groups) % groups;                     // the group's first key of the draft
+        keys(i2, n, s0 + (i2 - n1));
         for (int o = width; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
         if (ok && grp == 0) out[(int64_t)r * nq * hd + head * hd + c] = from_f32<T>(acc * inv);
     }
@@ -442,13 +444,12 @@ int32_t launch_attention(int32_t dtype, const void* qkv, const void* vt, int64_t
     const size_t lds = simple_attention_lds(hd, s.P, s.T);
     if (lds > kSimpleLdsMax) return fail(ATTS_ERR_SHAPE, "attention: context of %d keys is too long for this dtype/head_dim", s.P + s.T);
     dim3 grid(R - row0, nq);
-    const bool wide = (reinterpret_cast<uintptr_t>(qkv) & 15) == 0 && (hd * dtype_size(dtype)) % 16 == 0;
     if (dtype == ATTS_DTYPE_F32)
         hipLaunchKernelGGL(attn_simple_kernel<float>, grid, dim3(64), lds, stream, (const float*)qkv, (float*)out, row0, s.P, s.T,
-                           nq, nkv, hd, scale, wide);
+                           nq, nkv, hd, scale);
     else
         hipLaunchKernelGGL(attn_simple_kernel<bf16>, grid, dim3(64), lds, stream, (const bf16*)qkv, (bf16*)out, row0, s.P, s.T,
-                           nq, nkv, hd, scale, wide);
+                           nq, nkv, hd, scale);
     ATTS_LAUNCH_CHECK("attn_simple_kernel");
     return ATTS_OK;
 }

@@ -258,6 +258,14 @@ def test_general_attention_head_sizes(dtype, tol, hd, offset):
     _attention_case(dtype, (21, 3, 14, 4, 2, hd), tol, offset)
 
 
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.bfloat16, 1.5e-2)])
+@pytest.mark.parametrize("hd", [8, 16, 32, 64, 80, 256])
+@pytest.mark.parametrize("P,K,T", [(1, 2, 9), (131, 2, 77), (64, 1, 200)])
+def test_general_attention_key_counts(dtype, tol, hd, P, K, T):
+    """Whole batches of eight keys a group and every remainder, in the prefix and in the draft, for one to eight groups."""
+    _attention_case(dtype, (P, K, T, 2, 1, hd), tol)
+
+
 def _attention_case(dtype, shape, tol, offset=0):
     import paper_2509_15148_amd as A
     P, K, T, nq, nkv, hd = shape
