@@ -97,7 +97,7 @@ def _check(rc: int) -> None:
 
 # The current stream's handle without building a torch.cuda.Stream object for it: 0.4 us instead of 3.1, which is a third
 # of the host time of a short call (append + verdict of 16 scores: two calls whose kernels take 8 us together).
-_raw_stream = torch._C._cuda_getCurrentRawStream
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # absent from a CPU build, which can still ask for sizes and routes
 
 
 def _stream() -> ctypes.c_void_p:

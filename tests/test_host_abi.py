@@ -3,6 +3,8 @@ and rejects bad arguments on the host before touching a device (no compute is la
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -25,6 +27,12 @@ def test_library_exports_every_declared_symbol():
     for n in names:
         assert hasattr(lib, n), n
     assert set(names) == set(A.EXPORTS)
+
+
+def test_binding_imports_with_a_torch_without_device_streams():
+    code = ("import torch; vars(torch._C).pop('_cuda_getCurrentRawStream', None); import paper_2509_15148_amd as A; "
+            "assert A.atts_gemm_routes(torch.float32, 8, 8, 8)[0].kernel == A.KERNEL_SMALL")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True)
 
 
 def test_error_string_and_status_codes():
