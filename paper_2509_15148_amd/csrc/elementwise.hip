@@ -140,8 +140,8 @@ __device__ __forceinline__ void embed_norm_row(const T* __restrict__ src, int d,
 // Everything a pass needs before its first projection, in one launch (each of these is a few microseconds by itself, most of
 // it the launch): the first row_wgs workgroups embed a row each and apply the first layer's norm; the next rope_wgs fill the
 // rotary table, (cos, sin)(pos(r) theta^(-2 i / hd)) in fp64, rounded once; the last zero columns [R, ldv) of V^T for a
-// producer that writes only the R real ones.  128 rows of the 7B width: 5.7 us for 8.9 + 4.7 + 4.9 in three launches (each
-// with element-wise loads of the embedding); 1152 rows 13.8 for 13.8 + 4.8 + 7.0.
+// producer that writes only the R real ones.  128 rows of the 7B width: 5.9 us for 8.9 + 4.7 + 4.9 in three launches (each
+// with element-wise loads of the embedding); 4608 rows 31.3.
 struct StartDims {
     int32_t vocab, d, P, T, row0, R, half, row_wgs, rope_wgs;
     double log_theta_over_half;

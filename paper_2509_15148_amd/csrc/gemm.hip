@@ -894,10 +894,17 @@ bool fast_path_ok(int32_t dtype, int epi, const GemmArgs& g) {
 // ---- tile shape and K split of an aligned call ----------------------------------------------------------------------
 // Time of one tile of the aligned kernel, in microseconds: a slab of 64 k elements takes 0.86 / 1.53 / 2.05 for 128 / 256 /
 // 384 rows of 256 W rows and 0.58 for 128 x 128, and about 5 go into start, first slabs and epilogue.  Fitted to QKV,
-// gate/up and down projections of the 7B and 70B widths at 200 to 1494 rows (K = 3584, 8192, 18944; within 10 %).  A launch
-// takes its rounds of 256 tiles; so the taller tile wins only where it does not add a partly filled round:
+// gate/up and down projections of the 7B and 70B widths at 200 to 1494 rows (K = 3584, 8192, 18944; within 10 %).  At the 32B
+// widths (K = 5120, 27648) measured times are above it: QKV 83 us for 74 with 128-row tiles and 132 for 127 with 256-row
+// ones, gate/up and down 5 to 15 % from 1094 rows on, and 20 to 40 % at 200 to 516 rows, where the weights' one pass from memory
+// (566 MB of gate/up) shows: 172 for 127, 208 for 169.  The heights compared share that, and the choices stand: 516 rows
+// of gate/up in 384 + 256 rows 374 us, two rounds of 384 rows 371; 774 in 768 + 6 492, in three rounds of 384 540.  A launch
+// takes its rounds of kPlanCus tiles; so the taller tile wins only where it does not add a partly filled round:
 //   7B QKV     774 rows  128-row tiles  57 us (126 tiles), 256-row  90, 384-row 126
 //   7B gate/up 516 rows  128-row tiles 174 us (3 rounds),  256-row 196, 384-row 250;  1094 rows 335, 305, 290
+// Plans and sizes count the whole chip's compute units, whatever device is current or whether there is one: a workspace
+// sized on the host must fit the launch.  (The launch itself asks the device, for the grid that walks the tiles.)
+constexpr int kPlanCus = 256;
 double fast_tile_us(int rows, bool narrow, int64_t slabs) {
     const double a = narrow ? 0.58 : (rows == 128 ? 0.86 : (rows == 256 ? 1.53 : 2.05));
     return a * (double)slabs + 5.0;
@@ -921,7 +928,7 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
     const int n_out = epi == EPI_SWIGLU ? 128 : 256;
     const int64_t nt_n = g.N / n_out, slabs = g.Kd / kWideBK;
     auto rounds_us = [&](int rows, int64_t m) {
-        return (double)ceil_div(ceil_div(m, rows) * nt_n, 256) * fast_tile_us(rows, false, slabs);
+        return (double)ceil_div(ceil_div(m, rows) * nt_n, kPlanCus) * fast_tile_us(rows, false, slabs);
     };
     TilePlan best{};
     for (int rows : {384, 256, 128}) {
@@ -958,14 +965,14 @@ TilePlan partial_plan(const GemmArgs& g) {
         if (!tile_rows_allowed(rows, g)) continue;
         const bool narrow = rows == 128;
         const int64_t tiles = ceil_div(g.M, rows) * (g.N / (narrow ? 128 : 256));
-        int64_t s = 256 / tiles;
+        int64_t s = kPlanCus / tiles;
         if (s > slabs / 6) s = slabs / 6;
         if (s > fitting) s = fitting;
         if (s < 2) continue;
         const double us = fast_tile_us(rows, narrow, ceil_div(slabs, s)) + (double)s * g.M * g.N * 8 / 4.5e6 + 4.0;
         if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0};
     }
-    // without the split the norm that follows is a pass of its own (10 bytes an element less what the sums' pass moves anyway)
+    // without the split the norm that follows is a pass of its own, which reads 4 and writes 2 bytes an element
     const double norm_us = 4.0 + (double)g.M * g.N * 6 / 4.5e6;
     if (best.rows == 0 || (g.M > 128 && direct_plan(EPI_RESID_F32, g).us + norm_us < best.us)) return none;
     return best;
@@ -1089,7 +1096,7 @@ bool use_big_tile(int32_t M, int32_t N) {
 //                      one round): general.  Above K = 4096 the weights come from memory once either way and the general kernel's
 //                      second round only counts as it fills: 17 x 33000 (1032 tiles) x 8192  201 (165), 17 x 49000  253 (280)
 bool use_small_tile(int32_t dtype, int32_t M, int32_t N, int32_t Kd) {
-    const int64_t general = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(general, 256), tiles = ceil_div(M, 32) * ceil_div(N, 32);
+    const int64_t general = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(general, kPlanCus), tiles = ceil_div(M, 32) * ceil_div(N, 32);
     if (tiles >= (1 << 24)) return false;                        // 2^32 threads a launch
     if (dtype == ATTS_DTYPE_F32) {
         const double pair = Kd <= 256 ? 2.0 : (Kd <= 512 ? 1.7 : 1.5);
@@ -1213,7 +1220,7 @@ static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
         const TilePlan first = direct_plan(EPI_LMHEAD, g);
         const double other = (double)(ceil_div(g.M, 256) * (g.N / 256));
         if (tiles <= 256 && first.rows == 256 && other <= 256) return light_us <= (0.95 + 8e-6 * other * other) * slabs + 17.0;
-        return (double)ceil_div(tiles, 256) * fast_tile_us(384, false, g.Kd / kWideBK) <= 1.09 * first.us;
+        return (double)ceil_div(tiles, kPlanCus) * fast_tile_us(384, false, g.Kd / kWideBK) <= 1.09 * first.us;
     }
     if (use_small_tile(dtype, g.M, g.N, g.Kd)) return false;
     const int64_t general = ceil_div(g.M, 128) * ceil_div(g.N, 128);
@@ -1271,7 +1278,7 @@ size_t partial_bytes_bound(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool
     if (max_slices < 2 || !fast_path_ok(dtype, EPI_PARTIAL_F32, g)) return bytes;
     for (int rows : {128, 256, 384}) {
         if (rows > 128 && M <= rows - 128) continue;                 // 256-row tiles from 129 rows on, 384 from 257
-        const size_t by_slices = max_slices * (size_t)M * N * sizeof(float), by_tiles = (size_t)256 * rows * (rows == 128 ? 128 : 256) * sizeof(float);
+        const size_t by_slices = max_slices * (size_t)M * N * sizeof(float), by_tiles = (size_t)kPlanCus * rows * (rows == 128 ? 128 : 256) * sizeof(float);
         const size_t b = by_slices < by_tiles ? by_slices : by_tiles;
         if (b > bytes) bytes = b;
     }
