@@ -1091,16 +1091,20 @@ bool use_big_tile(int32_t M, int32_t N) {
 //                      2000 x 1000 (2016 tiles) x 2048  181 (169)
 //   fp32, two rounds   twice that up to K = 256, 1.7 times up to 512, else 1.5:  260 x 11000 (3096 tiles)  71 (75) at K = 512,
 //                      284 (273) at 2048; 129 x 16600 (2595 tiles) x 8192  964 (1090); 300 x 12000 (3750 tiles) x 2048  331 (279)
+//   fp32, 32 x 64 tiles (SwiGLU, LM head), which read a third fewer operands a product: 2048 a round; above K = 4096 1.7 times that in
+//                      two:  LM head 2000 x 1000 x 2048  147 (187); 300 x 12000 x 2048  273 (298), x 8192  1170 (1121);
+//                      260 x 11000 x 8192  1010 (1104)
 //   bf16               768 a round, as its matrix instructions take a sixteenth of the time so that the unshared operand reads
 //                      count:  1000 x 768 x 2048  25 (33); 17 x 49000 (1532 tiles) x 2048  44 (75); 33 x 24000 (1500 tiles of
 //                      one round): general.  Above K = 4096 the weights come from memory once either way and the general kernel's
 //                      second round only counts as it fills: 17 x 33000 (1032 tiles) x 8192  201 (165), 17 x 49000  253 (280)
-bool use_small_tile(int32_t dtype, int32_t M, int32_t N, int32_t Kd) {
+bool use_small_tile(int32_t dtype, int epi, int32_t M, int32_t N, int32_t Kd) {
     const int64_t general = ceil_div(M, 128) * ceil_div(N, 128), rounds = ceil_div(general, kPlanCus), tiles = ceil_div(M, 32) * ceil_div(N, 32);
     if (tiles >= (1 << 24)) return false;                        // 2^32 threads a launch
     if (dtype == ATTS_DTYPE_F32) {
-        const double pair = Kd <= 256 ? 2.0 : (Kd <= 512 ? 1.7 : 1.5);
-        return (double)tiles <= (Kd <= 256 ? 2048 : 1920) * ((double)(rounds / 2) * pair + (double)(rounds % 2));
+        const bool wide = epi == EPI_SWIGLU || epi == EPI_LMHEAD;
+        const double pair = wide ? (Kd <= 4096 ? 2.0 : 1.7) : (Kd <= 256 ? 2.0 : (Kd <= 512 ? 1.7 : 1.5));
+        return (double)tiles <= (wide || Kd <= 256 ? 2048 : 1920) * ((double)(rounds / 2) * pair + (double)(rounds % 2));
     }
     return tiles <= (Kd <= 4096 || general <= 256 ? rounds * 768 : 768 + 7 * (general - 256));
 }
@@ -1222,7 +1226,7 @@ static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
         if (tiles <= 256 && first.rows == 256 && other <= 256) return light_us <= (0.95 + 8e-6 * other * other) * slabs + 17.0;
         return (double)ceil_div(tiles, kPlanCus) * fast_tile_us(384, false, g.Kd / kWideBK) <= 1.09 * first.us;
     }
-    if (use_small_tile(dtype, g.M, g.N, g.Kd)) return false;
+    if (use_small_tile(dtype, EPI_LMHEAD, g.M, g.N, g.Kd)) return false;
     const int64_t general = ceil_div(g.M, 128) * ceil_div(g.N, 128);
     if (use_big_tile(g.M, g.N) || general > 512) return true;
     return light_us <= (general <= 256 ? 0.82 * slabs + 15.0 : (0.95 + 0.28 * (double)(general - 256) / 256) * slabs + 17.5);
@@ -1259,7 +1263,7 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
         return r;
     }
     const int32_t n_cols = epi == EPI_SWIGLU ? 2 * g.N : g.N;
-    if (use_small_tile(dtype, g.M, n_cols, g.Kd)) {
+    if (use_small_tile(dtype, epi, g.M, n_cols, g.Kd)) {
         r.kernel = ATTS_KERNEL_SMALL; r.n_part = small_lmhead_partials(g.N);
     } else {
         const bool big = use_big_tile(g.M, n_cols);

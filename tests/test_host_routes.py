@@ -78,3 +78,11 @@ def test_lm_head_with_few_tiles_keeps_the_faster_kernel(rows, vocab, d, exchange
 def test_products_of_few_tiles(dtype, shape, small):
     gemm, _ = A.atts_gemm_routes({"fp32": MODELS["tiny"], "bf16": MODELS["7b"]}[dtype].torch_dtype, *shape)
     assert (gemm.kernel == A.KERNEL_SMALL) == small
+
+
+@pytest.mark.parametrize("shape,small", [((2000, 1000, 2048), True), ((300, 12000, 2048), True), ((300, 12000, 8192), False), ((260, 11000, 8192), True),
+                                         ((1024, 2080, 512), False)])
+def test_fp32_lm_head_of_few_tiles(shape, small):
+    """Its 32 x 64 tiles stay ahead of the general kernel for longer than the plain product's 32 x 32."""
+    _, head = A.atts_gemm_routes(MODELS["tiny"].torch_dtype, *shape)
+    assert (head.kernel == A.KERNEL_SMALL) == small
