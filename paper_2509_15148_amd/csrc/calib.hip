@@ -4,8 +4,8 @@
 // an order-preserving image of the fp32 score (-0 folded onto +0, every NaN onto key 0, below
 // -inf), so all comparisons are unsigned-integer comparisons that reproduce the IEEE ones.
 //
-//   append (Online Calibration):  keys of the new scores are sorted (sort.hip: block sort + one-pass
-//       multi-way placement for small batches, radix sort for large ones) and
+//   append (Online Calibration):  keys of the new scores are sorted (sort.hip: sorted runs cut into buckets for
+//       small batches, radix sort for large ones) and
 //       merged with the resident array by a merge-path kernel into the other half of a ping-pong
 //       buffer.  The same pass writes four sampled copies of its output (every 32nd, 1024th, 32768th,
 //       2^20-th key), the levels of a static 32-ary search index: a node is one 128-byte line, the unit the L2
@@ -31,7 +31,7 @@ struct atts_calib {
     uint32_t* index[2][kIndexLevels];   // index[side][k][j] = keys[side][j * 32^(k+1)]
     uint32_t* runs;                     // the batch being appended: two buffers the sort alternates between
     uint32_t* batch;
-    uint32_t* sort_scratch;             // digit histograms of the radix sort
+    uint32_t* sort_scratch;             // samples of the sorted runs, or digit histograms of the radix sort
     int32_t* splits;                    // merge-path splits of one streaming merge launch
     int64_t splits_len;
     int64_t capacity;

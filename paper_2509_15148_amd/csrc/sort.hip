@@ -2,15 +2,14 @@
 // scores of newly pre-sampled outputs join the calibration multiset, which this library keeps sorted).
 //
 // Two regimes:
-//   * up to kSmallSortMax scores (cache-resident, latency-bound): every workgroup sorts one run of kSortChunk keys
-//     in registers + LDS (block_sort_kernel), then ONE pass places every key at its final position
-//     (multiway_place_kernel: own index in its run + its counts in all other runs, searched in windows of the
-//     other runs staged in LDS).  A run is sorted by ONE compute unit, whose instruction issue bounds it; shorter
-//     runs sort faster but make the placement pass (one window per other run) slower: 8192 measured best.
+//   * up to kSmallSortMax scores (cache-resident, latency-bound): every workgroup sorts one run in registers
+//     (block_sort_kernel), and where there are several, ONE further launch cuts them all at sampled keys and sorts the
+//     buckets in between (bucket_sort_kernel).
 //   * larger batches (bandwidth-bound): least-significant-digit radix sort, four passes of 8 bits.  A pass is
 //     three launches: per-tile digit histograms, a scan per digit over the tiles, and a stable scatter (ranks
 //     inside a tile by wavefront-wide digit matching, keys reordered through LDS so that each digit's keys of a
-//     tile leave as one contiguous run).  No inter-workgroup waiting anywhere.
+//     tile leave as one contiguous run).
+// No inter-workgroup waiting anywhere.
 #include "common.h"
 #include "keys.h"
 
@@ -18,15 +17,13 @@ namespace atts {
 namespace {
 
 // ------------------------------------------------------------------------------------------------------------
-// small batches: block sort + multi-way placement
+// one workgroup: a bitonic network over 8 keys per thread
 // ------------------------------------------------------------------------------------------------------------
-constexpr int kSortChunk = 8192;             // keys per block-sort workgroup (one sorted run)
-constexpr int kSortVT = 8;                   // keys per thread
-constexpr int kSortThreads = kSortChunk / kSortVT;
-constexpr int kMaxPlaceRuns = 8;
-constexpr int kSmallSortMax = kMaxPlaceRuns * kSortChunk;   // 65,536: at most 8 runs are placed in one pass
-constexpr int kPlaceThreads = 1024;          // keys per placement workgroup
-constexpr int kWindowCap = 16384;            // LDS keys that hold the other runs' windows of one placement workgroup
+constexpr int kPer = 8;                      // keys per thread
+constexpr int kWaveKeys = 64 * kPer;
+
+// keep the smaller (c = 0) or the larger (c = ~0) of a and b: one three-operand median
+__device__ __forceinline__ uint32_t keep(uint32_t a, uint32_t b, uint32_t c) { return max(min(a, b), min(max(a, b), c)); }
 
 __device__ __forceinline__ void cswap(uint32_t& x, uint32_t& y) {
     const uint32_t lo = min(x, y), hi = max(x, y);
@@ -34,168 +31,296 @@ __device__ __forceinline__ void cswap(uint32_t& x, uint32_t& y) {
     y = hi;
 }
 
-// Each workgroup turns kSortChunk scores into one ascending run of keys: 8 keys per thread sorted in registers
-// (odd-even transposition network), then log2(threads) rounds of pairwise merges of sorted runs through two LDS
-// buffers, one barrier per round.  In a round every thread produces 8 consecutive outputs of its pair of runs: merge
-// path gives the first input of each run, the next 8 keys of both runs are loaded at once (one LDS latency instead
-// of eight dependent ones) and the 8 smallest of the 16 are taken by a bitonic network in registers.
-// The last run is padded with kPadKey up to a multiple of 16 keys.
-// THREADS: a batch of one run takes the smallest workgroup that holds it.  The rounds and their searches are a chain of
-// LDS reads whose length grows with the run, and all wavefronts of a run share one CU: 512 keys take 8.5 us, 1024 10.4,
-// 2048 12.2, 4096 15.2, against 24 - 26 for any of them padded to a run of 8192.
-template <int THREADS>
-__global__ __launch_bounds__(THREADS) void block_sort_kernel(const float* __restrict__ scores, int64_t n,
-                                                             uint32_t* __restrict__ runs) {
-    constexpr int VT = kSortVT, kThreads = THREADS, kChunk = VT * THREADS;
-    static_assert(VT == 8, "register networks below take 8 keys");
-    __shared__ uint32_t buf[2][kChunk];
-    const int64_t base = (int64_t)blockIdx.x * kChunk;
-    const int tid = threadIdx.x;
-    uint32_t k[VT];
+// Compare-exchange of every key with the same register of lane ^ X, the lower lane keeping the smaller key.
+template <int X>
+__device__ __forceinline__ void lane_step(uint32_t (&k)[kPer]) {
+    if constexpr (X <= 8) {
+        const uint32_t c = (threadIdx.x & X) ? ~0u : 0u;
+        int o[kPer];
 #pragma unroll
-    for (int e = 0; e < VT; ++e) {                                 // coalesced: key e of the thread is element e * threads + tid
-        const int64_t i = base + e * kThreads + tid;
-        k[e] = i < n ? score_to_key(scores[i]) : kPadKey;
-    }
+        for (int e = 0; e < kPer; ++e) {
+            if constexpr (X == 1) o[e] = __builtin_amdgcn_mov_dpp((int)k[e], 0xB1, 0xF, 0xF, true);     // lanes (1, 0, 3, 2)
+            if constexpr (X == 2) o[e] = __builtin_amdgcn_mov_dpp((int)k[e], 0x4E, 0xF, 0xF, true);     // lanes (2, 3, 0, 1)
+            if constexpr (X == 4) o[e] = __builtin_amdgcn_mov_dpp((int)k[e], 0x141, 0xF, 0xF, true);    // ^ 7, then ^ 3
+            if constexpr (X == 8) o[e] = __builtin_amdgcn_mov_dpp((int)k[e], 0x128, 0xF, 0xF, true);    // half a row of 16 round
+        }
+        __builtin_amdgcn_sched_barrier(0);                         // a DPP read right behind its register's write costs two idle slots
+        if constexpr (X == 4) {
 #pragma unroll
-    for (int round = 0; round < VT; ++round) {
-#pragma unroll
-        for (int e = round & 1; e + 1 < VT; e += 2) cswap(k[e], k[e + 1]);
-    }
-#pragma unroll
-    for (int e = 0; e < VT; ++e) buf[0][tid * VT + e] = k[e];
-    int cur = 0;
-    for (int width = VT; width < kChunk; width *= 2) {
-        __syncthreads();
-        const uint32_t* src = buf[cur];
-        uint32_t* dst = buf[cur ^ 1];
-        const int o = tid * VT;
-        const int pair = o & ~(2 * width - 1);
-        const uint32_t* a = src + pair;
-        const uint32_t* b = a + width;
-        const int ia = merge_path<int>(a, width, b, width, o - pair);
-        const int ib = o - pair - ia;
-        uint32_t x[VT], y[VT];
-#pragma unroll
-        for (int e = 0; e < VT; ++e) {
-            x[e] = ia + e < width ? a[ia + e] : kPadKey;
-            y[VT - 1 - e] = ib + e < width ? b[ib + e] : kPadKey;  // second run reversed: (x, y) is a bitonic sequence
+            for (int e = 0; e < kPer; ++e) o[e] = __builtin_amdgcn_mov_dpp(o[e], 0x1B, 0xF, 0xF, true);
+            __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int e = 0; e < VT; ++e) k[e] = min(x[e], y[e]);       // the 8 smallest of the 16, as a bitonic sequence
+        for (int e = 0; e < kPer; ++e) k[e] = keep(k[e], (uint32_t)o[e], c);
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        // two registers at a time: the swap puts the lower partners of both into one register and the upper ones into the
+        // other, and a second swap takes them back
 #pragma unroll
-        for (int stride = VT / 2; stride > 0; stride >>= 1)
+        for (int e = 0; e < kPer; e += 2) {
+            auto swap = [](uint32_t x, uint32_t y) {
+                if constexpr (X == 16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+                else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+            };
+            const auto p = swap(k[e], k[e + 1]);
+            const auto q = swap(min(p[0], p[1]), max(p[0], p[1]));
+            k[e] = q[0];
+            k[e + 1] = q[1];
+        }
+    }
+}
+
+// The last steps of a stage: keys S lanes apart down to neighbouring registers.
+template <int S>
+__device__ __forceinline__ void merge_lanes(uint32_t (&k)[kPer]) {
+    if constexpr (S >= 1) {
+        lane_step<S>(k);
+        merge_lanes<S / 2>(k);
+    } else {
 #pragma unroll
-            for (int e = 0; e < VT; ++e)
+        for (int stride = kPer / 2; stride > 0; stride >>= 1)
+#pragma unroll
+            for (int e = 0; e < kPer; ++e)
                 if ((e & stride) == 0) cswap(k[e], k[e + stride]);
-#pragma unroll
-        for (int e = 0; e < VT; ++e) dst[o + e] = k[e];
-        cur ^= 1;
     }
-    __syncthreads();
-    const int64_t n16 = (n + 15) & ~(int64_t)15;
-    for (int i = tid; i < kChunk; i += kThreads)
-        if (base + i < n16) runs[base + i] = buf[cur][i];
 }
 
-// #{keys of the ascending array a[0, len) that are < y}, found by the 64 lanes of a wavefront together: each round
-// the lanes probe 64 evenly spaced keys of the remaining range and a ballot narrows it (three dependent rounds for
-// 8192 keys instead of thirteen).  All lanes return the count.
-__device__ __forceinline__ int wave_count_below(const uint32_t* __restrict__ a, int len, uint32_t y) {
-    const int lane = threadIdx.x & 63;
-    int lo = 0, hi = len;                       // the count lies in [lo, hi]: a[lo - 1] < y (or lo == 0), a[hi] >= y (or hi == len)
-    while (hi > lo) {
-        const int span = hi - lo;
-        const int step = (span + 63) >> 6;      // probes at lo + step - 1, lo + 2 step - 1, ...
-        const int at = lo + (lane + 1) * step - 1;
-        const bool below = at < hi && a[at] < y;
-        const int c = __popcll(__ballot(below));             // the probes below y form a prefix
-        const int new_lo = c > 0 ? lo + c * step : lo;
-        const int new_hi = min(hi, lo + (c + 1) * step - 1); // the first probe not below y (if any) bounds the count
-        lo = min(new_lo, hi);
-        hi = max(new_hi, lo);
+// Keys 8 t .. 8 t + 7 of thread t become the keys of those places in ascending order of the first `size` ones (a power of two
+// from 512 on, at most 8 THREADS; block-uniform).  Everything up to 512 keys happens in the registers of a wavefront
+// (neighbours by DPP, rows and halves by lane swaps); partners in other wavefronts exchange through LDS, one barrier each
+// (two buffers in turn).  A stage's descending groups work on complemented keys, so that the lower place always keeps the smaller.
+// What bounds it is the chain of steps: 512 keys about 620 vector instructions.  A launch that sorts 2048 keys takes 5.2 us and
+// one of 8192 about 12 (16 wavefronts share four SIMDs), against 12.2 and 24 with pairwise merges in LDS, whose binary searches
+// are chains of LDS reads.  buf: 2 x 8 THREADS words if THREADS > 64.
+template <int THREADS>
+__device__ __forceinline__ void sort_in_block(uint32_t (&k)[kPer], int size, uint32_t* buf) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t flip = 0;
+    auto face = [&](bool descending) __attribute__((always_inline)) {
+        const uint32_t now = descending ? ~0u : 0u, change = now ^ flip;
+        flip = now;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) k[e] ^= change;
+    };
+    const bool active = THREADS == 64 || wave * kWaveKeys < size;  // wavefronts past the last place only keep the barriers
+    if (active) {
+        face(lane & 1);
+#pragma unroll
+        for (int round = 0; round < kPer; ++round) {               // eight keys by odd-even transposition
+#pragma unroll
+            for (int e = round & 1; e + 1 < kPer; e += 2) cswap(k[e], k[e + 1]);
+        }
+        face(lane & 2);
+        merge_lanes<1>(k);
+        face(lane & 4);
+        merge_lanes<2>(k);
+        face(lane & 8);
+        merge_lanes<4>(k);
+        face(lane & 16);
+        merge_lanes<8>(k);
+        face(lane & 32);
+        merge_lanes<16>(k);
+        face(size > kWaveKeys && (wave & 1));
+        merge_lanes<32>(k);
     }
-    return lo;
+    if constexpr (THREADS > 64) {
+        int cur = 0;
+        for (int waves = 2; waves * kWaveKeys <= size; waves *= 2) {
+            face(waves * kWaveKeys < size && (wave & waves));
+            for (int s = waves / 2; s > 0; s >>= 1) {
+                uint4* own = reinterpret_cast<uint4*>(buf + cur * (kPer * THREADS));       // two planes of 16 bytes per thread
+                cur ^= 1;
+                if (active) {
+                    own[tid] = make_uint4(k[0], k[1], k[2], k[3]);
+                    own[THREADS + tid] = make_uint4(k[4], k[5], k[6], k[7]);
+                }
+                __syncthreads();
+                if (!active) continue;
+                const uint4 x = own[tid ^ (64 * s)], y = own[THREADS + (tid ^ (64 * s))];
+                const uint32_t c = (wave & s) ? ~0u : 0u;
+                k[0] = keep(k[0], x.x, c);
+                k[1] = keep(k[1], x.y, c);
+                k[2] = keep(k[2], x.z, c);
+                k[3] = keep(k[3], x.w, c);
+                k[4] = keep(k[4], y.x, c);
+                k[5] = keep(k[5], y.y, c);
+                k[6] = keep(k[6], y.z, c);
+                k[7] = keep(k[7], y.w, c);
+            }
+            if (active) merge_lanes<32>(k);
+        }
+    }
 }
 
-// Final position of every key of <= 8 sorted runs of kSortChunk keys (the last one shorter).  Stable: among equal
-// keys, those of earlier runs come first.
-//   position = index in the own run + sum over the other runs q of #{keys of run q that go before x},
-//   "before" = "<= x" for an earlier run, "< x" for a later one = "< x + bias" (x < 2^32 - 1).
-// A workgroup places 1024 consecutive keys of one run.  Their counts in another run lie between the counts of
-// the first and of the last of them (each found by one wavefront): that window of the other run (about 1024 keys
-// when the runs are alike) is copied to LDS with coalesced loads and every key finds its count there by binary
-// search.  Windows that do not fit the LDS budget together (very unlike runs) are searched in global memory instead.
-__global__ __launch_bounds__(kPlaceThreads) void multiway_place_kernel(const uint32_t* __restrict__ runs, int64_t n,
-                                                                       uint32_t* __restrict__ out) {
-    __shared__ uint32_t win[kWindowCap];
-    __shared__ int w_lo[kMaxPlaceRuns], w_hi[kMaxPlaceRuns], w_off[kMaxPlaceRuns + 1];
-    const int n_runs = (int)((n + kSortChunk - 1) / kSortChunk);
-    const int64_t e0 = (int64_t)blockIdx.x * kPlaceThreads;
-    const int cnt = (int)min((int64_t)kPlaceThreads, n - e0);           // >= 1
-    const int my_run = (int)(e0 / kSortChunk);                          // kPlaceThreads divides kSortChunk
-    const int tid = threadIdx.x, wave = tid >> 6;
-    auto run_len = [&](int q) { return (int)min((int64_t)kSortChunk, n - (int64_t)q * kSortChunk); };
-    // wavefront w: one end of the window of run w / 2
-    if (wave < 2 * n_runs) {
-        const int q = wave >> 1;
-        const uint32_t x_end = runs[e0 + ((wave & 1) ? cnt - 1 : 0)];
-        const int c = q == my_run ? 0 : wave_count_below(runs + (int64_t)q * kSortChunk, run_len(q), x_end + (q < my_run ? 1u : 0u));
-        if ((tid & 63) == 0) ((wave & 1) ? w_hi : w_lo)[q] = c;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int total = 0;
-        for (int q = 0; q < n_runs; ++q) {
-            w_off[q] = total;
-            total += w_hi[q] - w_lo[q];                                  // 0 for the own run
-        }
-        w_off[n_runs] = total;
-    }
-    __syncthreads();
-    const bool staged = w_off[n_runs] <= kWindowCap;                     // block-uniform
-    if (staged) {
-        for (int q = 0; q < n_runs; ++q) {
-            const uint32_t* src = runs + (int64_t)q * kSortChunk + w_lo[q];
-            const int len = w_hi[q] - w_lo[q];
-            for (int i = tid; i < len; i += kPlaceThreads) win[w_off[q] + i] = src[i];
-        }
-    }
-    __syncthreads();
-    if (tid >= cnt) return;
-    const uint32_t x = runs[e0 + tid];
-    int pos = (int)((e0 + tid) % kSortChunk);
-    // all windows together, their binary searches in lock step (the probes of one step are independent loads)
-    constexpr int G = kMaxPlaceRuns;
-    const uint32_t* a[G];
-    int lo[G], len[G], longest = 0;
-    uint32_t y[G];
+// ------------------------------------------------------------------------------------------------------------
+// small batches: sorted runs, then buckets between sampled keys
+// ------------------------------------------------------------------------------------------------------------
+constexpr int kRunMax = 8192;                // keys of the longest run: one workgroup of 1024 threads
+constexpr int kSmallSortMax = 1 << 19;       // 64 runs of kRunMax
+constexpr int kMaxRuns = 64;
+constexpr int kSpacing = 64;                 // every 64th key of a run is a sample
+constexpr int kSamplesMin = 16, kSamplesMax = 32;   // samples per bucket: about 1024 or 2048 keys
+constexpr int kBucketThreads = 1024;
+constexpr int kBucketCap = kPer * kBucketThreads;
+// a bucket's keys lie strictly between two splitters with at most q samples between them: at most kSpacing q keys, and from
+// every run fewer than kSpacing more
+static_assert(kSpacing * (kSamplesMax + kMaxRuns) <= kBucketCap && kSmallSortMax / kSpacing <= kBucketCap, "a workgroup holds a bucket, and all samples");
+static_assert(kMaxRuns * kRunMax == kSmallSortMax && kSamplesMin % kPer == 0 && kSmallSortMax / kSpacing / kSamplesMax <= kBucketThreads, "");
+
+// Every workgroup turns 8 THREADS scores into one ascending run; samples != NULL: every kSpacing-th key of it also goes there,
+// run after run.  The last run is padded with kPadKey up to a multiple of 16 keys.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void block_sort_kernel(const float* __restrict__ scores, int64_t n, uint32_t* __restrict__ runs,
+                                                             uint32_t* __restrict__ samples) {
+    constexpr int kRun = kPer * THREADS;
+    __shared__ __attribute__((aligned(16))) uint32_t buf[THREADS > 64 ? 2 * kRun : 4];
+    const int64_t base = (int64_t)blockIdx.x * kRun;
+    const int tid = threadIdx.x;
+    float f[kPer];
 #pragma unroll
-    for (int j = 0; j < G; ++j) {
-        const int q = min(j, n_runs - 1);
-        a[j] = staged ? win + w_off[q] : runs + (int64_t)q * kSortChunk + w_lo[q];
-        len[j] = j < n_runs ? w_hi[q] - w_lo[q] : 0;                      // block-uniform
-        y[j] = x + (q < my_run ? 1u : 0u);
-        lo[j] = 0;
-        longest = max(longest, len[j]);
-        pos += j < n_runs ? w_lo[q] : 0;
-    }
-    // invariant per window: the count (first index with a[idx] >= y) lies in [lo, lo + len]
-    while (longest > 0) {                                                // block-uniform trip count
+    for (int e = 0; e < kPer; ++e) f[e] = scores[min(base + e * THREADS + tid, n - 1)];       // any order will do: coalesced
+    uint32_t k[kPer];
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            if (len[j] > 0) {
-                const int half = len[j] >> 1;
-                const bool below = a[j][lo[j] + half] < y[j];
-                lo[j] = below ? lo[j] + half + 1 : lo[j];
-                len[j] = below ? len[j] - half - 1 : half;
+    for (int e = 0; e < kPer; ++e) k[e] = base + e * THREADS + tid < n ? score_to_key(f[e]) : kPadKey;
+    sort_in_block<THREADS>(k, kRun, buf);
+    const int64_t at = base + tid * kPer, n16 = (n + 15) & ~(int64_t)15;
+    if (at < n16) {                                                // whole groups of eight: n16 is a multiple
+        reinterpret_cast<uint4*>(runs + at)[0] = make_uint4(k[0], k[1], k[2], k[3]);
+        reinterpret_cast<uint4*>(runs + at)[1] = make_uint4(k[4], k[5], k[6], k[7]);
+    }
+    if (samples && at < n && tid % (kSpacing / kPer) == 0) samples[at / kSpacing] = k[0];
+}
+
+// Bucket b of the sorted batch: with S the sorted samples of all runs, the keys strictly between S[b q] and S[(b + 1) q] (no
+// lower limit in the first bucket, no upper one in the last), and its share of the keys equal to S[b q], whose number is
+// known without moving them.  Regular samples bound a bucket whatever the scores are (ties included: equal splitters share
+// their value's range evenly), and no workgroup waits for another: each sorts the samples for itself, finds its limits in every
+// run (the samples lead to one block of 64 keys, read in 16-byte pieces), gathers the segments between them and sorts those.
+// What bounds it is its chain of steps (two sorts, the limits, the gathering), one bucket per CU: 65,536 scores 14 us behind
+// 5.2 for the runs, where runs of 8192 keys merged through LDS and one pass that searched every key's place in the other runs took
+// 25 + 14; 262,144 scores 31 us in all and 524,288 43, by radix sort 76 and 78 (which is why the line to it lies here: its
+// launches are a floor, and 64 runs of one workgroup's keys end at 2^19).
+__global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(const uint32_t* __restrict__ runs, int64_t n, int run_len, int n_runs,
+                                                                     const uint32_t* __restrict__ samples, int n_samples, int q,
+                                                                     uint32_t* __restrict__ out) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+    uint32_t* const buf = lds;                                     // 2 kBucketCap: exchanges; then the gathered keys
+    uint32_t* const smp = lds + 2 * kBucketCap;                    // the samples, run after run
+    __shared__ uint32_t splitter[kBucketCap / kSamplesMin];
+    __shared__ int below[3][kMaxRuns];                             // keys of a run below / not above the lower limit, below the upper one
+    __shared__ int seg_at[kMaxRuns + 1];
+    __shared__ int sum_lo[2];
+    const int tid = threadIdx.x, b = blockIdx.x, n_buckets = gridDim.x;
+    auto size_for = [](int m) {
+        int size = kWaveKeys;
+        while (size < m) size *= 2;
+        return size;
+    };
+    uint32_t k[kPer];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) k[e] = samples[min(e * kBucketThreads + tid, n_samples - 1)];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        const int i = e * kBucketThreads + tid;
+        if (i < n_samples) smp[i] = k[e];
+        else k[e] = kPadKey;
+    }
+    // the network's places are thread-major: keep its first `size` places full when there are fewer samples than places
+    if (n_samples <= kBucketCap / 2) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) k[e] = tid * kPer + e < n_samples ? smp[tid * kPer + e] : kPadKey;
+    }
+    sort_in_block<kBucketThreads>(k, size_for(n_samples), buf);
+    if (tid * kPer % q == 0) splitter[tid * kPer / q] = k[0];
+    __syncthreads();
+    const bool has_lo = b > 0, has_hi = b + 1 < n_buckets;
+    const uint32_t lo = splitter[b], hi = splitter[has_hi ? b + 1 : b];
+    // the splitters equal to lo, and those of them before this one
+    const bool same = tid >= 1 && tid < n_buckets && splitter[tid] == lo;
+    const int n_same = __syncthreads_count(same), my_same = __syncthreads_count(same && tid < b);
+    if (tid < 4 * n_runs && (tid & 3) < 3) {
+        const int r = tid >> 2, kind = tid & 3;
+        const int len = (int)min((int64_t)run_len, n - (int64_t)r * run_len);
+        const uint32_t v = kind < 2 ? lo : hi;
+        const bool equal_too = kind == 1;
+        int count = kind < 2 ? 0 : len;
+        if (kind < 2 ? has_lo : has_hi) {
+            const uint32_t* s = smp + r * (run_len / kSpacing);
+            int x = 0, y = (len + kSpacing - 1) / kSpacing;        // samples below v
+            while (x < y) {
+                const int mid = (x + y) >> 1;
+                if (s[mid] < v || (equal_too && s[mid] == v)) x = mid + 1; else y = mid;
+            }
+            count = 0;
+            if (x > 0) {                                           // the limit lies in the block of the last of them
+                const int first = (x - 1) * kSpacing;
+                const uint4* p = reinterpret_cast<const uint4*>(runs + (int64_t)r * run_len + first);
+                uint4 block[kSpacing / 4];
+#pragma unroll
+                for (int j = 0; j < kSpacing / 4; ++j)
+                    block[j] = p[min(j, (len - 1 - first) >> 2)];
+                auto goes = [&](uint32_t key, int i) { return (first + i < len && (key < v || (equal_too && key == v))) ? 1 : 0; };
+                count = first;
+#pragma unroll
+                for (int j = 0; j < kSpacing / 4; ++j)
+                    count += goes(block[j].x, 4 * j) + goes(block[j].y, 4 * j + 1) + goes(block[j].z, 4 * j + 2) + goes(block[j].w, 4 * j + 3);
             }
         }
-        longest >>= 1;
+        below[kind][r] = count;
     }
+    __syncthreads();
+    if (tid < 64) {                                                // one lane per run: the segments side by side
+        const int from = tid < n_runs ? below[1][tid] : 0;
+        const int len = tid < n_runs ? max(below[2][tid] - from, 0) : 0;
+        int at = len, s0 = tid < n_runs ? below[0][tid] : 0, s1 = from;
 #pragma unroll
-    for (int j = 0; j < G; ++j) pos += lo[j];
-    out[pos] = x;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int up = __shfl_up(at, o);
+            if (tid >= o) at += up;
+            s0 += __shfl_xor(s0, o);
+            s1 += __shfl_xor(s1, o);
+        }
+        seg_at[tid + 1] = at;
+        if (tid == 0) {
+            seg_at[0] = 0;
+            sum_lo[0] = s0;
+            sum_lo[1] = s1;
+        }
+    }
+    __syncthreads();
+    const int m = seg_at[kMaxRuns];                                // at most kBucketCap
+    {
+        const int r = tid >> 4;                                    // sixteen threads per run
+        if (r < n_runs) {
+            const int at = seg_at[r], len = seg_at[r + 1] - at;
+            const uint32_t* src = runs + (int64_t)r * run_len + below[1][r];
+            for (int i0 = tid & 15; i0 < len; i0 += 64) {          // four requested together
+                uint32_t x[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) x[u] = src[min(i0 + 16 * u, len - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i0 + 16 * u < len) buf[at + i0 + 16 * u] = x[u];
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) k[e] = tid * kPer + e < m ? buf[tid * kPer + e] : kPadKey;
+    __syncthreads();
+    sort_in_block<kBucketThreads>(k, size_for(m), buf);
+    __syncthreads();
+    reinterpret_cast<uint4*>(buf)[2 * tid] = make_uint4(k[0], k[1], k[2], k[3]);
+    reinterpret_cast<uint4*>(buf)[2 * tid + 1] = make_uint4(k[4], k[5], k[6], k[7]);
+    __syncthreads();
+    uint32_t* const o = out + sum_lo[1];
+    for (int i = tid; i < m; i += kBucketThreads) o[i] = buf[i];
+    if (has_lo) {
+        const int64_t width = sum_lo[1] - sum_lo[0];
+        const int f0 = sum_lo[0] + (int)(width * my_same / n_same), f1 = sum_lo[0] + (int)(width * (my_same + 1) / n_same);
+        for (int i = f0 + tid; i < f1; i += kBucketThreads) out[i] = lo;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------------------
@@ -365,24 +490,33 @@ int32_t radix_pass(const void* in, int64_t n, int shift, int n_tiles, uint32_t* 
 
 }  // namespace
 
-// radix sort: a digit histogram per tile + the digit totals (the small-batch path needs no scratch)
+// radix sort: a digit histogram per tile + the digit totals; sorted runs: one sample in 64 keys, which is less
 int64_t sort_scratch_words(int64_t n) { return (int64_t)kRadixBins * ceil_div(n > 0 ? n : 1, kRadixTile) + kRadixBins; }
 
 int32_t launch_sort_scores(const float* scores, int64_t n, uint32_t* a, uint32_t* b, uint32_t* scratch, const uint32_t** sorted,
                            hipStream_t stream) {
     if (n <= kSmallSortMax) {
-        const int64_t n_runs = ceil_div(n, kSortChunk);
+        // one run up to kRunMax scores; more: the shortest runs of which kMaxRuns hold the batch
+        const int64_t run = n <= kRunMax ? kRunMax : (n <= 2048 * kMaxRuns ? 2048 : (n <= 4096 * kMaxRuns ? 4096 : 8192));
+        const int n_runs = (int)ceil_div(n, run);
+        uint32_t* samples = n_runs > 1 ? scratch : nullptr;
         const dim3 grid((unsigned)n_runs);
-        if (n <= 512) hipLaunchKernelGGL(block_sort_kernel<64>, grid, dim3(64), 0, stream, scores, n, a);
-        else if (n <= 1024) hipLaunchKernelGGL(block_sort_kernel<128>, grid, dim3(128), 0, stream, scores, n, a);
-        else if (n <= 2048) hipLaunchKernelGGL(block_sort_kernel<256>, grid, dim3(256), 0, stream, scores, n, a);
-        else if (n <= 4096) hipLaunchKernelGGL(block_sort_kernel<512>, grid, dim3(512), 0, stream, scores, n, a);
-        else hipLaunchKernelGGL(block_sort_kernel<kSortThreads>, grid, dim3(kSortThreads), 0, stream, scores, n, a);
+        if (n <= 512) hipLaunchKernelGGL(block_sort_kernel<64>, grid, dim3(64), 0, stream, scores, n, a, samples);
+        else if (n <= 1024) hipLaunchKernelGGL(block_sort_kernel<128>, grid, dim3(128), 0, stream, scores, n, a, samples);
+        else if (n <= 2048 || run == 2048) hipLaunchKernelGGL(block_sort_kernel<256>, grid, dim3(256), 0, stream, scores, n, a, samples);
+        else if (n <= 4096 || run == 4096) hipLaunchKernelGGL(block_sort_kernel<512>, grid, dim3(512), 0, stream, scores, n, a, samples);
+        else hipLaunchKernelGGL(block_sort_kernel<1024>, grid, dim3(1024), 0, stream, scores, n, a, samples);
         ATTS_LAUNCH_CHECK("block_sort_kernel");
         *sorted = a;
         if (n_runs > 1) {
-            hipLaunchKernelGGL(multiway_place_kernel, dim3((unsigned)ceil_div(n, kPlaceThreads)), dim3(kPlaceThreads), 0, stream, a, n, b);
-            ATTS_LAUNCH_CHECK("multiway_place_kernel");
+            const int n_samples = (int)ceil_div(n, kSpacing);
+            const int q = n_samples <= 256 * kSamplesMin ? kSamplesMin : kSamplesMax;      // a bucket takes a CU's LDS: at most 256
+            const size_t lds = (size_t)(2 * kBucketCap + align_up((size_t)n_samples, 4)) * sizeof(uint32_t);
+            int32_t rc = allow_dynamic_lds<bucket_sort_kernel>((size_t)3 * kBucketCap * sizeof(uint32_t));
+            if (rc != ATTS_OK) return rc;
+            hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)ceil_div(n_samples, q)), dim3(kBucketThreads), lds, stream, a, n, (int)run,
+                               n_runs, samples, n_samples, q, b);
+            ATTS_LAUNCH_CHECK("bucket_sort_kernel");
             *sorted = b;
         }
         return ATTS_OK;

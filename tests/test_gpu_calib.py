@@ -75,9 +75,8 @@ def test_small_with_ties_and_special_values():
                                    # set sizes at and around whole index nodes (32, 1024, 32768 keys)
                                    (31, 1, 1, 991, 1, 31743, 1, 1)])
 def test_online_appends_span_sort_chunks_and_merge_paths(sizes):
-    """Batches below / at / above one sort run (8192 keys), the one-pass multi-way placement (up to 8 runs =
-    65,536 keys) and the radix sort (larger batches, ragged last tile); after every append the state must equal
-    the sorted union."""
+    """Batches of one sorted run (up to 8192 keys) and of several, one below, at and above those limits; after every append the
+    state must equal the sorted union."""
     import paper_2509_15148_amd as A
     announce("calib appends", sizes)
     total = sum(sizes)
@@ -125,6 +124,33 @@ def test_small_appends_at_the_edges_of_their_kernels(base, sizes):
         nan = lo - len(finite)
         assert np.isnan(held[:nan]).all() and np.array_equal(held[nan:], np.sort(finite))
         _check_against_oracle(A, c, allv[:lo].astype(np.float64), test, [0.05, 0.2], brute=lo <= 30000)
+
+
+@pytest.mark.parametrize("n", [8193, 10016, 65535, 131072, 131073, 262145, 524288, 524289])
+@pytest.mark.parametrize("kind", ["spread", "one value", "few values", "descending", "clustered"])
+def test_batches_of_several_runs(n, kind):
+    """Batches sorted as runs of 2048 / 4096 / 8192 keys that are cut at sampled keys, at the limits of each run length and of the
+    radix sort above them.  Equal splitters (ties), descending and clustered scores fill the buckets unevenly; zeros of both
+    signs, infinities and NaN among them.  Integer work: the state equals the sorted batch."""
+    import paper_2509_15148_amd as A
+    announce("calib batch", n, kind)
+    x = lognormal_scores(n, seed=n)
+    if kind == "one value":
+        x[:] = 2.5
+    elif kind == "few values":
+        x = np.round(x)
+    elif kind == "descending":
+        x = -np.sort(-x)
+    elif kind == "clustered":
+        x[: n - n // 9] = np.float32(1.0) + np.float32(2.0) ** -23 * (np.arange(n - n // 9) % 700)
+    special = np.array([np.nan, np.inf, -np.inf, -0.0, 0.0, 1e-45, np.nan], dtype=np.float32)
+    x[[0, 1, 2, n // 2, n // 3, n - 2, n - 1]] = special
+    c = A.Calib(n)
+    A.atts_calibrate_online(c, dev(x))
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    A.atts_calib_export(c, out)
+    held, finite = out.cpu().numpy(), x[~np.isnan(x)]
+    assert np.isnan(held[:n - len(finite)]).all() and np.array_equal(held[n - len(finite):], np.sort(finite))
 
 
 def test_capacity_and_argument_errors():
