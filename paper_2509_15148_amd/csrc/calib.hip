@@ -262,42 +262,46 @@ struct SearchIndex {
 
 // One level of the index for the four test keys of a quad of lanes (lane l of the quad owns key x_l and the count
 // t_l of entries of the next coarser level below it).  Result for each lane: the same count for level L, whose
-// candidates are the 32 entries of one aligned 128-byte line (the whole line the L2 fetches is used).  The quad takes
-// its four keys in turn: in round r all four lanes work on lane r's key, each loading and comparing a quarter
+// candidates are the 32 entries of one aligned 128-byte line (the whole line the L2 fetches is used).  The quad
+// shares its four keys: in round r all four lanes work on lane r's key, each loading and comparing a quarter
 // (32 bytes) of its line, so that one load instruction of the wavefront touches 16 lines instead of 64 (the vector
 // cache looks up one line per cycle: a lane-per-line load costs four times the tag look-ups).  Values move inside the
-// quad by DPP, not through LDS.  Every lane of the quad must be active; a lane without work passes t = 0 (nothing is
-// loaded for it).
+// quad by DPP, not through LDS.  Every lane of the quad must be active; a lane without work passes t = 0 and gets 0.
 template <int CTRL>
 __device__ __forceinline__ int quad_perm(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true); }
 
 __device__ __forceinline__ int quad_descend(const uint32_t* __restrict__ L, int64_t len, int t, uint32_t x) {
     const int q = threadIdx.x & 3;
+    // all four lines of the quad are requested together: taken one after the other, each waits out its own latency (16 lines of a
+    // wavefront in flight instead of 64, twelve latencies in a search of three levels instead of three)
+    const int tr[4] = {quad_perm<0x00>(t), quad_perm<0x55>(t), quad_perm<0xAA>(t), quad_perm<0xFF>(t)};
+    const int xr[4] = {quad_perm<0x00>((int)x), quad_perm<0x55>((int)x), quad_perm<0xAA>((int)x), quad_perm<0xFF>((int)x)};
+    uint4 v[4][2];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint4* p = reinterpret_cast<const uint4*>(L + (max(tr[r] - 1, 0) << kFanBits) + 8 * q);      // a lane without work: any line
+        v[r][0] = p[0];
+        v[r][1] = p[1];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     int out = 0;
-    auto round = [&](int xr_, int tr, int r) {
-        const uint32_t xr = (uint32_t)xr_;
-        int c = 0;
-        const int base = (tr - 1) << kFanBits;
-        if (tr > 0) {
-            const uint4 v0 = *reinterpret_cast<const uint4*>(L + base + 8 * q);
-            const uint4 v1 = *reinterpret_cast<const uint4*>(L + base + 8 * q + 4);
-            const int valid = (int)min((int64_t)kFan, len - base) - 8 * q;     // entries of this quarter that exist
-            c = ((valid > 0 && v0.x < xr) ? 1 : 0) + ((valid > 1 && v0.y < xr) ? 1 : 0) + ((valid > 2 && v0.z < xr) ? 1 : 0) +
-                ((valid > 3 && v0.w < xr) ? 1 : 0) + ((valid > 4 && v1.x < xr) ? 1 : 0) + ((valid > 5 && v1.y < xr) ? 1 : 0) +
-                ((valid > 6 && v1.z < xr) ? 1 : 0) + ((valid > 7 && v1.w < xr) ? 1 : 0);
-        }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const uint32_t k = (uint32_t)xr[r];
+        const int base = (tr[r] - 1) << kFanBits;
+        const int valid = (int)min((int64_t)kFan, len - base) - 8 * q;         // entries of this quarter that exist
+        int c = ((valid > 0 && v[r][0].x < k) ? 1 : 0) + ((valid > 1 && v[r][0].y < k) ? 1 : 0) + ((valid > 2 && v[r][0].z < k) ? 1 : 0) +
+                ((valid > 3 && v[r][0].w < k) ? 1 : 0) + ((valid > 4 && v[r][1].x < k) ? 1 : 0) + ((valid > 5 && v[r][1].y < k) ? 1 : 0) +
+                ((valid > 6 && v[r][1].z < k) ? 1 : 0) + ((valid > 7 && v[r][1].w < k) ? 1 : 0);
         c += quad_perm<0xB1>(c);      // lanes (1, 0, 3, 2)
         c += quad_perm<0x4E>(c);      // lanes (2, 3, 0, 1)
-        if (q == r) out = tr > 0 ? base + c : 0;
-    };
-    round(quad_perm<0x00>((int)x), quad_perm<0x00>(t), 0);
-    round(quad_perm<0x55>((int)x), quad_perm<0x55>(t), 1);
-    round(quad_perm<0xAA>((int)x), quad_perm<0xAA>(t), 2);
-    round(quad_perm<0xFF>((int)x), quad_perm<0xFF>(t), 3);
+        if (q == r) out = tr[r] > 0 ? base + c : 0;
+    }
     return out;
 }
 
-__global__ __launch_bounds__(256) void classify_kernel(SearchIndex ix, const float* __restrict__ test, int64_t m,
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const float* __restrict__ test, int64_t m,
                                                        ClassifyLevels lv, int32_t* __restrict__ ranks,
                                                        float* __restrict__ pvalues, uint8_t* __restrict__ classes,
                                                        float* __restrict__ thresholds) {
@@ -306,14 +310,14 @@ __global__ __launch_bounds__(256) void classify_kernel(SearchIndex ix, const flo
     const int64_t top_len = ix.len[ix.top_level], n = ix.len[0];
     const int s = ix.top_shift;
     const int n_top = (int)((top_len + ((int64_t)1 << s) - 1) >> s);
-    for (int i = threadIdx.x; i < n_top; i += 256) top[i] = T[(int64_t)i << s];
+    for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
     __syncthreads();
     if (blockIdx.x == 0 && thresholds && (int)threadIdx.x < lv.n_alpha) {
         const int64_t kth = n + 1 - lv.r[threadIdx.x];     // 1-indexed order statistic
         thresholds[threadIdx.x] = kth > n ? INFINITY : (kth < 1 ? -INFINITY : key_to_score(ix.lvl[0][kth - 1]));
     }
     for (int j = 0; j < ix.per_thread; ++j) {
-        const int64_t i0 = ((int64_t)blockIdx.x * ix.per_thread + j) * 256;      // block-uniform: whole quads stay in the loop
+        const int64_t i0 = ((int64_t)blockIdx.x * ix.per_thread + j) * THREADS;      // block-uniform: whole quads stay in the loop
         if (i0 >= m) break;
         const int64_t i = i0 + threadIdx.x;
         const float sc = i < m ? test[i] : __uint_as_float(0x7FC00000u);
@@ -652,13 +656,23 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
     while (ix.top_level < kIndexLevels && ix.len[ix.top_level] > kTopEntries) ++ix.top_level;
     ix.top_shift = 0;
     while (ceil_div(ix.len[ix.top_level], (int64_t)1 << ix.top_shift) > kTopEntries) ++ix.top_shift;
-    // enough workgroups to fill the chip, few enough that staging the top level stays a small part of the work
-    int64_t per = M / ((int64_t)256 * 2048);
+    // Enough workgroups to fill the chip, few enough that staging the top level stays a small part of the work.  A search is a
+    // chain of memory latencies, so many scores take workgroups of 512 threads: the staged 32 KB leave room for five workgroups on
+    // a CU, which are 20 wavefronts of 32 with 256 threads.  With both changes (quad_descend) 2^24 scores against 2^28 keys take
+    // 713 us for 770 (7 TB/s of lines from beyond the L2: bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
+    // 153 for 174, 2^19 against 2^23 20 for 27; few scores stay spread over more CUs.
+    const bool large = M >= (int64_t)256 * 2048;
+    const int threads = large ? 512 : 256;
+    int64_t per = M / ((int64_t)threads * 1024);
     ix.per_thread = (int32_t)(per < 1 ? 1 : (per > 16 ? 16 : per));
-    const unsigned blocks = (unsigned)(M > 0 ? ceil_div(M, (int64_t)256 * ix.per_thread) : 1);
+    const unsigned blocks = (unsigned)(M > 0 ? ceil_div(M, (int64_t)threads * ix.per_thread) : 1);
     StageTimer t_(ATTS_STAGE_CLASSIFY, static_cast<hipStream_t>(hip_stream));
-    hipLaunchKernelGGL(classify_kernel, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M,
-                       lv, ranks, pvalues, classes, thresholds);
+    if (large)
+        hipLaunchKernelGGL(classify_kernel<512>, dim3(blocks), dim3(512), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M,
+                           lv, ranks, pvalues, classes, thresholds);
+    else
+        hipLaunchKernelGGL(classify_kernel<256>, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M,
+                           lv, ranks, pvalues, classes, thresholds);
     ATTS_LAUNCH_CHECK("classify_kernel");
     return ATTS_OK;
 }

@@ -153,6 +153,25 @@ def test_batches_of_several_runs(n, kind):
     assert np.isnan(held[:n - len(finite)]).all() and np.array_equal(held[n - len(finite):], np.sort(finite))
 
 
+@pytest.mark.parametrize("n", [1, 40, 9000, 300000])
+@pytest.mark.parametrize("m", [(1 << 19) - 1, 1 << 19, (1 << 20) + 513])
+def test_classification_workgroup_sizes(n, m):
+    """Fewer and more test scores than the line between the two workgroup sizes, ragged ends, sets of no, one and two index levels
+    below the staged one; scores outside the set's range, ties and NaN among them.  Integer work: every rank exact."""
+    import paper_2509_15148_amd as A
+    announce("classify", n, m)
+    cal = np.round(lognormal_scores(n, seed=n), 4)
+    test = lognormal_scores(m, seed=m)
+    test[: m // 2] = np.round(test[: m // 2], 4)
+    test[[0, 1, m - 3, m - 2, m - 1]] = np.array([-1.0, np.inf, np.nan, cal[0], -np.inf], dtype=np.float32)
+    c = A.Calib(n)
+    A.atts_calibrate_online(c, dev(cal))
+    ranks, cls, p, q = _classify(A, c, test, [0.05, 0.2])
+    want = O.rank_counts_sorted(cal.astype(np.float64), test)
+    assert np.array_equal(ranks.astype(np.int64), want)
+    assert np.array_equal(cls, O.classify(want, O.reject_ranks([0.05, 0.2], n)))
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
