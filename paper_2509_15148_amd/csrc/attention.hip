@@ -119,6 +119,16 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
 constexpr int kHd = 128;
 constexpr int kKTile = 64;    // keys per LDS tile
 
+// The values of both lanes of the pair (l, l ^ 32), the lower lane's first: the two 32-lane halves exchanged in registers (no
+// LDS round trip in the middle of the softmax).  The results are taken out as integers first: a bit cast applied to an
+// element of the pair reads element 0 whichever is named.
+__device__ __forceinline__ float2 lane_pair(float x) {
+    const unsigned u = __builtin_bit_cast(unsigned, x);
+    const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    const unsigned lower = sw[0], upper = sw[1];
+    return make_float2(__builtin_bit_cast(float, lower), __builtin_bit_cast(float, upper));
+}
+
 // kWaves wavefronts of 32 query rows each share the key / value tiles of one head; kStages tiles of LDS form a ring.
 // kPipe: the scores of tile t + 1 are issued to the matrix cores BEFORE the softmax of tile t, so that the exponentials
 // (vector ALU) of one tile run while the matrix pipe works on the next one; needs the key tile t + 1 next to the value
@@ -282,16 +292,15 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attn_mfma_ke
         float mx = fmaxf(acc_s[0][0], acc_s[1][0]);
 #pragma unroll
         for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, acc_s[0][v]), acc_s[1][v]);    // one three-operand maximum each
-        {   // maximum over the lane pair (l, l ^ 32): the two 32-lane halves exchanged in registers (no LDS round trip
-            // in the middle of the softmax): afterwards one result holds the lower half's values in every lane, the other
-            // the upper half's
-            const unsigned u = __builtin_bit_cast(unsigned, mx);
-            const auto sw = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-            mx = fmaxf(__builtin_bit_cast(float, sw[0]), __builtin_bit_cast(float, sw[1])) * scale_log2e;   // scale > 0: the order is kept
-        }
         // Lazy rescaling: any reference value works in exp2(z - m) as long as it is the same for numerator and
-        // denominator, so the running reference only moves when the new maximum exceeds it by more than 2^6
-        // (p stays <= 64, far inside bf16 / fp32 range); the 64 accumulator multiplies are skipped otherwise.
+        // denominator, so the running reference only moves when a new maximum exceeds it by more than 2^6; the 64
+        // accumulator multiplies are skipped otherwise.  The new maximum is that of the keys in the lower lanes, or of
+        // those in the upper ones where it stands out by more than 2^64 (p stays <= 2^64: far inside the range of bf16 and fp32,
+        // sums of 2^31 keys included).
+        const float2 pair = lane_pair(mx);                                                // scale > 0: the order is kept
+        const float upper = pair.y * scale_log2e;
+        mx = pair.x * scale_log2e;
+        mx = upper > fmaxf(mx, m_run) + 64.f ? upper : mx;
         if (__builtin_amdgcn_ballot_w64(mx > m_run + 6.f) != 0) {
             const float m_new = fmaxf(m_run, mx);
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);

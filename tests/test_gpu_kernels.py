@@ -266,6 +266,30 @@ def test_general_attention_key_counts(dtype, tol, hd, P, K, T):
     _attention_case(dtype, (P, K, T, 2, 1, hd), tol)
 
 
+@pytest.mark.parametrize("nq,rows", [(1, 96), (1, 300), (64, 1100)])
+@pytest.mark.parametrize("key", [3, 8, 21, 30, 47, 61])
+def test_mfma_attention_one_dominant_key(nq, rows, key):
+    """One key whose score stands 181 above all others (exp of the difference overflows fp32): every later row must return its
+    value alone, whichever lane of the score tile holds it, and the rows before it the mean of theirs."""
+    import paper_2509_15148_amd as A
+    announce("attention, dominant key", nq, rows, key)
+    P, T, hd = rows - 40, 40, 128
+    qkv = torch.zeros(rows, (nq + 2) * hd, dtype=torch.bfloat16)
+    qkv[:, :nq * hd] = 4.0
+    qkv[key, nq * hd:(nq + 1) * hd] = 4.0
+    g = torch.Generator().manual_seed(key)
+    v = torch.randn(rows, hd, generator=g).to(torch.bfloat16)
+    qkv[:, (nq + 1) * hd:] = v
+    qkv = qkv.cuda()
+    out = torch.empty(rows, nq * hd, dtype=torch.bfloat16, device="cuda")
+    A.atts_attention_shared_prefix(qkv, out, P, 1, T, nq, 1, hd, ws(A.atts_attention_workspace_bytes(torch.bfloat16, rows, 1, hd)))
+    torch.cuda.synchronize()
+    want = v.double().cumsum(0) / torch.arange(1, rows + 1)[:, None]
+    want[key:] = v[key].double()
+    got = out.cpu().double().view(rows, nq, hd)
+    assert (got - want[:, None]).abs().max().item() <= 1.5e-2
+
+
 def _attention_case(dtype, shape, tol, offset=0):
     import paper_2509_15148_amd as A
     P, K, T, nq, nkv, hd = shape
