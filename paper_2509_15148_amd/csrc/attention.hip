@@ -8,14 +8,16 @@
 // This is exactly K independent causal sequences [prefix ; draft_k], evaluated without
 // recomputing or re-storing the prefix.
 //
-// Two kernels:
-//   * attn_mfma_kernel  bf16, head_dim 128: flash-style, 128 query rows of one head per
-//     workgroup, key/value tiles of 64 rows staged in LDS and shared by the 4 wavefronts.
+// Three kernels:
+//   * attn_mfma_kernel  bf16, head_dim 128: flash-style, 128 or 256 query rows of one head per
+//     workgroup, key/value tiles of 64 rows staged in LDS and shared by its wavefronts.
 //     Works on transposed products so that no register transpose is needed:
 //        S^T = K Q^T   (32 keys x 32 queries per MFMA block; a lane owns ONE query column,
 //                       so the online-softmax statistics are per lane)
 //        O^T = V^T P^T (P^T is fed straight from the S^T accumulator registers; V^T tiles
 //                       come from a [n_kv, hd, rows] copy of V written after the QKV GEMM)
+//   * attn_split_kernel the same products for few query rows: 32 per workgroup, the keys divided among
+//     its wavefronts.
 //   * attn_simple_kernel any dtype / head_dim: one wavefront per (row, head); used by the
 //     fp32 model.
 #include "common.h"
@@ -408,6 +410,167 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attn_mfma_ke
     }
 }
 
+
+// Few query rows: 32 of one head per workgroup, its 32-key tiles dealt to the eight wavefronts.  Each keeps a softmax of its own
+// over every eighth tile and they are merged once, through LDS.  A tile is read in whole rows (the matrix fragments' own layout,
+// one row per lane, takes the address unit four times as long), held in registers while the tile before is worked on, and
+// laid out for the fragments in the wavefront's own part of LDS: no barrier until the merge.
+// What bounds it is the CU's path from the L2: eight tiles (256 keys) of a workgroup take about 2 us, start and merge 5.5.
+constexpr int kSplitWaves = 8;
+constexpr int kSplitPitch = kHd + 4;                    // floats of a merge row in LDS
+constexpr size_t kSplitLds = (size_t)kSplitWaves * 32 * (kSplitPitch + 2) * sizeof(float);
+__global__ __launch_bounds__(64 * kSplitWaves) void attn_split_kernel(const bf16* __restrict__ qkv, const bf16* __restrict__ vt, int64_t ldv,
+                                                                      bf16* __restrict__ out, int row0, int R, int P, int Tn, int nq, int nkv,
+                                                                      int q_tiles, float scale_log2e) {
+    constexpr int kTile = 32;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    float* const part = reinterpret_cast<float*>(smem);                              // [wave][row][kSplitPitch]
+    float2* const stat = reinterpret_cast<float2*>(part + kSplitWaves * 32 * kSplitPitch);   // [wave][row] (maximum, sum)
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    // the workgroups an XCD receives (id mod 8) are consecutive ones of the order heads x query tiles: few key / value heads each
+    const int n_wg = (int)gridDim.x, n8 = n_wg & ~7, pid = (int)blockIdx.x;
+    const int lid = pid < n8 ? (pid & 7) * (n8 >> 3) + (pid >> 3) : pid;
+    const int head = lid / q_tiles, kvh = head / (nq / nkv);
+    const int r0 = row0 + (lid % q_tiles) * 32;
+    const int r_last = min(r0 + 32, R) - 1;
+    const int64_t ld = (int64_t)(nq + 2 * nkv) * kHd;
+    const int r = r0 + l32;
+    const bool r_ok = r < R;
+    const int ss = seg_start(min(r, r_last), P, Tn);
+
+    const int n1 = (min(P, r_last + 1) + kTile - 1) / kTile;
+    const int s2 = max(n1 * kTile, seg_start(r0, P, Tn) / kTile * kTile);
+    const int n_tiles = n1 + (r_last >= s2 ? (r_last - s2) / kTile + 1 : 0);
+    auto tile_start = [&](int t) { return t < n1 ? t * kTile : s2 + (t - n1) * kTile; };
+
+    const int kperm = (l32 & 0x13) | ((l32 & 8) >> 1) | ((l32 & 4) << 1);            // as in attn_mfma_kernel
+    const bf16* const kg = qkv + (nq + kvh) * kHd + 8 * (lane & 15);
+    const bf16* const vg = vt + ((int64_t)kvh * kHd + (lane >> 2)) * ldv + 8 * (lane & 3);
+    char* const own = reinterpret_cast<char*>(part + wave * 32 * kSplitPitch);       // 32 keys x 256 B, then 128 dims x 64 B
+    bf16x8 qf[8], kr[8], vr[8];
+    auto request = [&](int t) __attribute__((always_inline)) {
+        const int j0 = tile_start(t);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) kr[j] = *reinterpret_cast<const bf16x8*>(kg + (int64_t)min(j0 + 4 * j + (lane >> 4), R - 1) * ld);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) vr[j] = *reinterpret_cast<const bf16x8*>(vg + (int64_t)(16 * j) * ldv + j0);
+    };
+    // 16-byte chunks: index XOR (key & 15) in a key's row, XOR (dim / 4) & 3 in a dim's
+    auto stage = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int row = 4 * j + (lane >> 4);
+            *reinterpret_cast<bf16x8*>(own + row * 256 + (((lane & 15) ^ (row & 15)) << 4)) = kr[j];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<bf16x8*>(own + kTile * 256 + (16 * j + (lane >> 2)) * 64 + (((lane & 3) ^ (lane >> 4)) << 4)) = vr[j];
+    };
+    auto load_k = [&](int s) __attribute__((always_inline)) {
+        return *reinterpret_cast<const bf16x8*>(own + kperm * 256 + (((2 * s + g) ^ (kperm & 15)) << 4));
+    };
+    auto load_v = [&](int s, int nb) __attribute__((always_inline)) {
+        return *reinterpret_cast<const bf16x8*>(own + kTile * 256 + (32 * nb + l32) * 64 + (((2 * s + g) ^ ((l32 >> 2) & 3)) << 4));
+    };
+    if (wave < n_tiles) request(wave);
+    {
+        const bf16* qp = qkv + (int64_t)min(r, R - 1) * ld + head * kHd + 8 * g;     // rows past the last: masked
+#pragma unroll
+        for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+    }
+    f32x16 acc_o[4];
+#pragma unroll
+    for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc_o[nb][v] = 0.f;
+    float m_run = -1e30f, l_run = 0.f;
+
+    for (int t = wave; t < n_tiles; t += kSplitWaves) {
+        const int j0 = tile_start(t);
+        stage();
+        if (t + kSplitWaves < n_tiles) request(t + kSplitWaves);
+        f32x16 acc_s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc_s[v] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) acc_s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_k(s), qf[s], acc_s, 0, 0, 0);
+        if (!(j0 + kTile - 1 <= r0 && j0 + kTile <= P && r0 + 31 <= r_last)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int j = j0 + 16 * (v >> 3) + 8 * g + (v & 7);
+                const bool vis = r_ok && j <= r && (j < P || j >= ss);
+                acc_s[v] = vis ? acc_s[v] : -INFINITY;
+            }
+        }
+        float mx = acc_s[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) mx = fmaxf(mx, acc_s[v]);
+        const float2 pair = lane_pair(mx);
+        mx = fmaxf(pair.x, pair.y) * scale_log2e;
+        if (__builtin_amdgcn_ballot_w64(mx > m_run + 6.f) != 0) {
+            const float m_new = fmaxf(m_run, mx);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            m_run = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc_o[nb][v] *= alpha;
+        }
+        bf16x8 pf[2];
+        float psum = 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(acc_s[v], scale_log2e, -m_run));
+            psum += p;
+            pf[v >> 3][v & 7] = (bf16)p;
+        }
+        l_run += psum;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int nb = 0; nb < 4; ++nb) acc_o[nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load_v(s, nb), pf[s], acc_o[nb], 0, 0, 0);
+    }
+
+    // merge: the wavefronts that had a tile leave their sums, every thread weighs eight output columns of a row
+    const int used = min(kSplitWaves, n_tiles);
+    if (wave < used) {
+        const float l_tot = l_run + __shfl_xor(l_run, 32);
+        float* const mine = part + (wave * 32 + l32) * kSplitPitch + 4 * g;
+#pragma unroll
+        for (int nb = 0; nb < 4; ++nb)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                *reinterpret_cast<f32x4*>(mine + 32 * nb + 8 * a) = f32x4{acc_o[nb][4 * a], acc_o[nb][4 * a + 1], acc_o[nb][4 * a + 2], acc_o[nb][4 * a + 3]};
+        if (g == 0) stat[wave * 32 + l32] = make_float2(m_run, l_tot);
+    }
+    __syncthreads();
+    const int row = tid >> 4, col = (tid & 15) * 8;
+    if (r0 + row > r_last) return;
+    float m_all = -1e30f;
+    for (int w = 0; w < used; ++w) m_all = fmaxf(m_all, stat[w * 32 + row].x);
+    f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = {0.f, 0.f, 0.f, 0.f};
+    float sum = 0.f;
+    for (int w = 0; w < used; ++w) {
+        const float2 st = stat[w * 32 + row];
+        const float e = __builtin_amdgcn_exp2f(st.x - m_all);
+        const f32x4* p = reinterpret_cast<const f32x4*>(part + (w * 32 + row) * kSplitPitch + col);
+        sum += e * st.y;
+        o0 += e * p[0];
+        o1 += e * p[1];
+    }
+    const float inv = 1.f / sum;
+    bf16x8 o;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        o[c] = (bf16)(o0[c] * inv);
+        o[4 + c] = (bf16)(o1[c] * inv);
+    }
+    *reinterpret_cast<bf16x8*>(out + (int64_t)(r0 + row) * nq * kHd + head * kHd + col) = o;
+}
+
 }  // namespace
 
 bool attention_uses_vt(int32_t dtype, int32_t hd) { return dtype == ATTS_DTYPE_BF16 && hd == kHd; }
@@ -429,12 +592,24 @@ int32_t launch_attention(int32_t dtype, const void* qkv, const void* vt, int64_t
     if (attention_uses_vt(dtype, hd)) {
         if (!vt || ldv < (int64_t)align_up(R, kKTile) || ldv % 8)
             return fail(ATTS_ERR_WORKSPACE, "attention: transposed-V buffer missing or too narrow");
+        // 32 query rows per workgroup, its keys dealt to eight wavefronts, while one workgroup per CU holds them all: the other
+        // forms then are few workgroups that walk their keys one tile after the other (7B widths, 128 rows against a prefix of 512:
+        // 10.2 us for 18.3, of 2048: 20.7 for 44.8; 8 rows 12.1 for 21.2 and 22.5 for 67.6; 70B, 256 workgroups: 9.2 for 13.7 at
+        // 256 keys, 24.4 for 45.5 at 2048).  A second round of them still wins for long contexts (448 to 512 workgroups:
+        // 16.0 - 20.8 for 13.9 - 18.4 up to 512 keys, 28 - 30 for 27 - 28 at 1024, 40 - 44 for 46 - 47 at 2048).
         // 256 query rows per workgroup (8 wavefronts, one workgroup per CU, four LDS stages, scores of the next tile issued
         // ahead of the softmax) once the call has enough rows to fill the chip that way; 128 rows (4 wavefronts, two
-        // workgroups per CU) for smaller calls
+        // workgroups per CU) for calls in between
         constexpr int kStage = 2 * kKTile * kHd * 2;
         const float sc2 = scale * 1.4426950408889634f;
-        if ((int64_t)ceil_div(R - row0, 256) * nq >= 256) {
+        const int q_tiles = (int)ceil_div(R - row0, 32);
+        const int64_t split_wgs = (int64_t)q_tiles * nq;
+        if (split_wgs <= 256 || (split_wgs <= 512 && s.P + s.T >= 1536)) {
+            int32_t rc = allow_dynamic_lds<attn_split_kernel>(kSplitLds);
+            if (rc != ATTS_OK) return rc;
+            hipLaunchKernelGGL(attn_split_kernel, dim3((unsigned)(q_tiles * nq)), dim3(64 * kSplitWaves), kSplitLds, stream, (const bf16*)qkv,
+                               (const bf16*)vt, ldv, (bf16*)out, row0, R, s.P, s.T, nq, nkv, q_tiles, sc2);
+        } else if ((int64_t)ceil_div(R - row0, 256) * nq >= 256) {
             constexpr size_t lds = 4 * kStage;
             int32_t rc = allow_dynamic_lds<attn_mfma_kernel<8, 4, true>>(lds);
             if (rc != ATTS_OK) return rc;

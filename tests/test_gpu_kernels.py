@@ -266,6 +266,18 @@ def test_general_attention_key_counts(dtype, tol, hd, P, K, T):
     _attention_case(dtype, (P, K, T, 2, 1, hd), tol)
 
 
+@pytest.mark.parametrize("P,K,T,nq,nkv", [
+    (1, 1, 1, 1, 1), (5, 1, 26, 2, 1), (5, 1, 27, 2, 1), (5, 1, 28, 2, 2),            # 7 rows below .. above one query tile of 32
+    (224, 1, 32, 3, 1), (225, 2, 16, 3, 1), (250, 3, 8, 4, 4),                         # eight key tiles, one more, drafts inside a tile
+    (480, 1, 32, 16, 2), (480, 1, 33, 16, 2),                                           # 256 workgroups, and one row more (128-row tiles)
+    (1500, 1, 36, 8, 1), (1400, 3, 100, 9, 3),                                          # 384 and 486 workgroups with a long context
+    (1400, 3, 100, 10, 5),                                                              # 540: too many
+])
+def test_attention_with_few_query_rows(P, K, T, nq, nkv):
+    """Edges of the kernel for few query rows (keys divided among the wavefronts) and of the rule that takes it."""
+    _attention_case(torch.bfloat16, (P, K, T, nq, nkv, 128), 1.5e-2)
+
+
 @pytest.mark.parametrize("nq,rows", [(1, 96), (1, 300), (64, 1100)])
 @pytest.mark.parametrize("key", [3, 8, 21, 30, 47, 61])
 def test_mfma_attention_one_dominant_key(nq, rows, key):
