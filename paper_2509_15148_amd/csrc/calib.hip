@@ -18,6 +18,7 @@
 //       that input's own calibration scores.
 #include "common.h"
 #include "keys.h"
+#include "block_sort.h"
 
 #include <math.h>
 #include <new>
@@ -46,13 +47,15 @@ constexpr int kMergeThreads = 256;
 constexpr int kMergeSegSmall = 2048;   // outputs per merge workgroup: cache-resident sizes (more workgroups)
 constexpr int kMergeSegLarge = 4096;   // ... and streaming sizes (split search amortised over more keys; 8 workgroups per CU)
 constexpr int64_t kMergeLargeFrom = (int64_t)1 << 22;
-// Appends of up to kInlineMax scores into sets of up to kInlineTotal keys are sorted by the merge workgroups themselves
-// (every workgroup ranks the whole batch in LDS, one key per thread against all others): 16 scores into 1000 then take one
-// launch of 4.7 us instead of 23.9 + 4.2 for a sort and a merge.  The ranking grows with the square of the batch (256
-// scores: 13.6 us against 8.5 + 6.2 for the two launches, the break-even), and every workgroup repeats it, so a
-// set whose merge takes more than one workgroup per CU keeps the separate sort.
-constexpr int kInlineMax = 256;
-constexpr int64_t kInlineTotal = (int64_t)kMergeSegSmall * 256;    // one workgroup per CU
+// Appends of up to kInlineMax scores into sets of up to kInlineTotal keys are sorted by the merge workgroups themselves, each for
+// itself: one launch instead of two.  Up to kRankMax scores every thread ranks one against all others (its time grows with the
+// square: 1000 + 16 scores 5.6 us, 64 7.2, 256 13.4), more go through the register network of one wavefront (16: 6.3, 64: 6.8,
+// 256: 8.1, 512: 8.4), a sort of its own ahead of the merge costs a launch (8.2, 8.3, 9.2, 9.7).  Every workgroup repeats the
+// sort, so sets whose merge has more than four workgroups a CU keep it apart (2,000,000 + 256: 9.7 inside, 10.7 apart; 4,000,000:
+// 15.8 and 13.7).
+constexpr int kInlineMax = kWaveKeys;
+constexpr int kRankMax = 48;
+constexpr int64_t kInlineTotal = (int64_t)kMergeSegSmall * 1024;
 
 // first index in [0, n) with a[idx] >= x  (n if none)
 __device__ __forceinline__ int64_t lower_bound(const uint32_t* __restrict__ a, int64_t n, uint32_t x) {
@@ -117,20 +120,31 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
     __shared__ __attribute__((aligned(16))) uint32_t buf[SEG + SEG / 32];
     __shared__ uint32_t batch[INLINE_SORT ? kInlineMax : 1];
     if constexpr (INLINE_SORT) {
-        // rank of every key among the batch (equal keys in batch order), then the key goes to its rank
-        static_assert(kInlineMax == kMergeThreads, "one key per thread");
-        const int t = (int)threadIdx.x, m = (int)nb;
-        const uint32_t mine = t < m ? score_to_key(job.scores[t]) : kPadKey;
-        buf[t] = mine;
-        __syncthreads();
-        int rank = 0;
+        if (nb <= kRankMax) {
+            // rank of every key among the batch (equal keys in batch order), then the key goes to its rank
+            const int t = (int)threadIdx.x, m = (int)nb;
+            const uint32_t mine = t < m ? score_to_key(job.scores[t]) : kPadKey;
+            buf[t] = mine;
+            __syncthreads();
+            int rank = 0;
 #pragma unroll 4
-        for (int j = 0; j < m; j += 4) {                            // past the end: kPadKey, never below a key
-            const uint4 q = *reinterpret_cast<const uint4*>(buf + j);
-            rank += (q.x < mine || (q.x == mine && j < t) ? 1 : 0) + (q.y < mine || (q.y == mine && j + 1 < t) ? 1 : 0) +
-                    (q.z < mine || (q.z == mine && j + 2 < t) ? 1 : 0) + (q.w < mine || (q.w == mine && j + 3 < t) ? 1 : 0);
+            for (int j = 0; j < m; j += 4) {                        // past the end: kPadKey, never below a key
+                const uint4 q = *reinterpret_cast<const uint4*>(buf + j);
+                rank += (q.x < mine || (q.x == mine && j < t) ? 1 : 0) + (q.y < mine || (q.y == mine && j + 1 < t) ? 1 : 0) +
+                        (q.z < mine || (q.z == mine && j + 2 < t) ? 1 : 0) + (q.w < mine || (q.w == mine && j + 3 < t) ? 1 : 0);
+            }
+            if (t < m) batch[rank] = mine;
+        } else if (threadIdx.x < 64) {
+            float f[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) f[e] = job.scores[min((int64_t)(e * 64 + threadIdx.x), nb - 1)];
+            uint32_t k[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) k[e] = e * 64 + threadIdx.x < nb ? score_to_key(f[e]) : kPadKey;
+            sort_in_block<64>(k, kWaveKeys, nullptr);
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) batch[kPer * threadIdx.x + e] = k[e];
         }
-        if (t < m) batch[rank] = mine;
         __syncthreads();
     }
     auto batch_key = [&](int64_t i) { return INLINE_SORT ? batch[i] : b[i]; };

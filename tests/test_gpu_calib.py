@@ -94,6 +94,29 @@ def test_online_appends_span_sort_chunks_and_merge_paths(sizes):
         _check_against_oracle(A, c, allv[:lo].astype(np.float64), test, [0.05, 0.2], brute=lo <= 30000)
 
 
+@pytest.mark.parametrize("base,sizes", [(0, (48,)), (0, (49,)), (700, (47, 48, 49, 50)), (0, (512,)), (3, (510, 511, 512, 513)),
+                                        ((1 << 21) - 1000, (512, 48, 440, 1, 30))])
+def test_appends_sorted_inside_the_merge(base, sizes):
+    """One below, at and above the sizes of the batches that the merge workgroups rank or sort themselves, and of the set that lets
+    them; ties, NaN and both infinities in the batch.  The state equals the sorted union after every append."""
+    import paper_2509_15148_amd as A
+    announce("calib inline sort", base, sizes)
+    allv = np.round(lognormal_scores(base + sum(sizes), seed=base % 1000 + 3), 2)
+    allv[base:base + 3] = [np.nan, np.inf, -np.inf]
+    c = A.Calib(base + sum(sizes))
+    if base:
+        A.atts_calibrate_online(c, dev(allv[:base]))
+    lo = base
+    for n in sizes:
+        A.atts_calibrate_online(c, dev(allv[lo:lo + n]))
+        lo += n
+        out = torch.empty(lo, dtype=torch.float32, device="cuda")
+        A.atts_calib_export(c, out)
+        held, finite = out.cpu().numpy(), allv[:lo][~np.isnan(allv[:lo])]
+        nan = lo - len(finite)
+        assert np.isnan(held[:nan]).all() and np.array_equal(held[nan:], np.sort(finite))
+
+
 @pytest.mark.parametrize("base,sizes", [(0, (1, 3, 4, 5)), (1000, (16, 63, 64, 65)), (5000, (255, 256, 257)), (37, (511, 512, 513, 1024, 1025)),
                                         (2047, (1, 2049, 4096, 4097)), ((1 << 19) - 300, (100, 200, 1, 17))])
 def test_small_appends_at_the_edges_of_their_kernels(base, sizes):
