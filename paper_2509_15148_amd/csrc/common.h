@@ -129,6 +129,7 @@ struct GemmArgs {
     float2* partials;        // [M, n_part] (running max, sum of exp) per column slab
     float* target_logit;     // [M]
     int32_t n_part;          // number of column slabs = gemm_route(...).n_part of this call
+    int32_t v0;              // set by launch_gemm: first vocabulary entry of a launch that covers the last ones only
     // EPI_QKV_ROPE only:
     const float2* rope;      // [M, 64] (cos, sin) per row and rotation pair
     void* vt;                // [n_kv, 128, ldv] transposed V
@@ -145,7 +146,8 @@ struct GemmRoute {
     int32_t kernel;          // ATTS_KERNEL_*
     int32_t tile_rows;       // aligned kernels: rows of a tile (of the vocabulary where the operands are exchanged)
     int32_t slices;          // EPI_PARTIAL_F32: K slices; 1: cutting would not help, the caller takes the direct epilogue
-    int32_t head_rows, tail_rows;   // tail_rows != 0: rows [0, head_rows) in tiles of tile_rows, the rest in a second launch of tail_rows
+    int32_t head_rows, tail_rows;   // tail_rows != 0: rows (exchanged operands: vocabulary entries) [0, head_rows) in tiles of
+                                    // tile_rows, the rest in a second launch of tail_rows
     int32_t n_part;          // EPI_LMHEAD: column slabs (partials per row)
 };
 GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);

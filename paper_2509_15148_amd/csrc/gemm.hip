@@ -98,6 +98,7 @@ struct GemmDims {
     int32_t n_rot_heads;    // EPI_QKV_ROPE: heads (128 columns each) that get rotated; later heads are V
     int32_t k_slices;       // EPI_PARTIAL_F32: the K range is split over this many workgroups per tile, slice s stores
     int64_t slice_pitch;    // its partial sums at out + s slice_pitch (floats); 1 for every other epilogue
+    int32_t v0;             // EPI_LMHEAD_T: vocabulary entry of row 0
 };
 
 
@@ -363,7 +364,7 @@ __device__ __forceinline__ void gemm_epilogue_impl(f32x16 (&acc)[MI][NI], int m0
         // the other orientation needs ten), the two lane halves are merged with one exchange, and the wave's partial goes to
         // slot (tile row, wave row).  The target logit is stored by the lane that holds the target's vocabulary entry.
         const int part = (m0 / (4 * WM)) * 4 + wm;
-        const int vrow0 = m0 + wm * WM + 4 * half;     // every vocabulary row of the tile exists (whole tiles, checked on the host)
+        const int vrow0 = g.v0 + m0 + wm * WM + 4 * half;     // every vocabulary row of the tile exists (whole tiles, checked on the host)
 #pragma unroll
         for (int j = 0; j < NI; ++j) {
             const int col = n0 + wn * WN + 32 * j + l32;              // scoring row; < g.N unless kRaggedB
@@ -409,7 +410,7 @@ __device__ __forceinline__ void lmhead_tile_epilogue(f32x16 (&acc)[MI][NI], int 
                                                      const GemmDims& g) {
     constexpr int WM = 32 * MI, WN = 32 * NI, BN = 2 * WN, kWm = 4;
     float2* red = reinterpret_cast<float2*>(smem);                    // [kWm][BN] (max, sum of exponentials)
-    const int vrow0 = m0 + wm * WM + 4 * half;
+    const int vrow0 = g.v0 + m0 + wm * WM + 4 * half;
     block_barrier();                                                  // every wave is through with the last slab
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -1009,6 +1010,7 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
     d.nt_n = (int)ceil_div(g.N, n_out);     // whole tiles, except the columns of the exchanged LM head
     d.k_slices = EPI == EPI_PARTIAL_F32 ? g.n_slices : 1;
     d.slice_pitch = (int64_t)g.M * g.ldc;
+    d.v0 = g.v0;
     const size_t lds = 160 * 1024;
     ATTS_TRY_RC((allow_dynamic_lds<gemm_bf16_wide_kernel<EPI, kWavesM, MI, NI, kRaggedB>>(lds)));
     // 384-row tiles without a K split: one workgroup per CU (a workgroup takes a CU's whole LDS), each walking
@@ -1198,11 +1200,12 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 // place without padding) their columns; the epilogue reduces inside the lanes.
 //   more than 128 scoring rows: 384 x 256 tiles, vocabulary a multiple of 384.  No row of padding is computed in the
 //       long direction (4096 scoring rows are 10.67 tiles of 384 in the other orientation) and the tile count drops (7B: 6336
-//       instead of 6534, 25 rounds instead of 26).  Rows that the caller has not padded (385 of 152,064 x 3584): 503 us
-//       against 825 with the general kernel; padded ones 519 against 558 with 256 x 256 tiles the other way round (1397:
-//       1262 against 1441).  Padded rows take the other orientation where its rounds of tiles are fewer by more than the
-//       9 % its epilogue costs at least: 257 to 384 rows (one row of 384 x 256 tiles, 482 against 517; 70B head 748 against 889),
-//       196 rows of the 70B head (540 against 630), 1090 (1953 against 2136).
+//       instead of 6534, 25 rounds instead of 26).  Rows that the caller has not padded (385 of 152,064 x 3584): 447 us
+//       against 825 with the general kernel.  Padded rows take the other orientation where the model's time for it is shorter by
+//       more than it leaves out: the epilogue that reduces across lanes, the less the longer K is, and the vocabulary matrix that
+//       a single row of tiles streams by alone.  Short passes with the head, other orientation and exchanged (model's
+//       ratio): 7B 300 rows 620 and 577 us (1.16), 1090 rows 1219 and 1167 (1.14), 800 rows 1141 and 961 (1.02); 32B 300 rows 845 and
+//       805 (1.15); 70B 300 rows 893 and 1000 (1.38), 1090 rows 2108 and 2186 (1.13), 800 rows 1920 and 1771 (1.12).
 //       Small vocabularies leave most of the chip idle, and a tile of 384 x 256 is then the longer chain: exchanged only where its
 //       1.43 (nearly no tile) to 1.69 us (256 tiles) a slab of 64 k elements and 3.5 us are less than the other kernel's time (first
 //       orientation 0.95 to 1.47 and 17, general kernel 0.82 and 15 up to a tile a compute unit, 0.95 to 1.23 and 17.5 up to
@@ -1215,6 +1218,26 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw) {
     return dtype == ATTS_DTYPE_BF16 && Kd % kWideBK == 0 && Kd >= kMinSlabs * kWideBK && lda * 2 * 17 < (1ll << 31) && ldw * 2 * 17 < (1ll << 31);
 }
+// 384 x 256 tiles of g.N vocabulary entries and g.M scoring rows: whole rounds of them, and where the last round would leave
+// many CUs idle, the vocabulary's last entries in a second launch of smaller tiles (one partial per row and tile there).  7B head,
+// the call alone: 256 rows (396 tiles) 315 -> 293 us, 385 rows (792 tiles: three rounds and 24) 495 -> 447, 800 rows 855 ->
+// 818; 70B head 200 rows 580 -> 491, 1000 rows 1650 -> 1620.
+static TilePlan lmhead_exchanged_plan(const GemmArgs& g) {
+    const int64_t nt_m = g.N / 384, nt_n = ceil_div(g.M, 256), slabs = g.Kd / kWideBK, full = nt_m * nt_n / kPlanCus;
+    TilePlan best{384, 1, (double)ceil_div(nt_m * nt_n, kPlanCus) * fast_tile_us(384, false, slabs), 0, 0};
+    if (full == 0 || nt_m * nt_n % kPlanCus == 0) return best;
+    const double base = best.us;
+    for (int rows : {256, 128}) {
+        int64_t head = full * kPlanCus / nt_n;
+        if (rows == 256 && (nt_m - head) % 2) --head;               // whole tiles in the second launch
+        if (head < 1) continue;
+        const int64_t tail_tiles = (nt_m - head) * 384 / rows * nt_n;
+        const double us = (double)ceil_div(head * nt_n, kPlanCus) * fast_tile_us(384, false, slabs) +
+                          (double)ceil_div(tail_tiles, kPlanCus) * fast_tile_us(rows, false, slabs) + 4.0;
+        if (us < best.us && us < 0.95 * base) best = TilePlan{384, 1, us, (int)(head * 384), rows};
+    }
+    return best;
+}
 static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
     if (g.N % 384 != 0 || g.M <= 128 || !lmhead_aligned_k(dtype, g.Kd, g.lda, g.ldw)) return false;
     const double slabs = (double)(g.Kd / kWideBK);
@@ -1224,7 +1247,7 @@ static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
         const TilePlan first = direct_plan(EPI_LMHEAD, g);
         const double other = (double)(ceil_div(g.M, 256) * (g.N / 256));
         if (tiles <= 256 && first.rows == 256 && other <= 256) return light_us <= (0.95 + 8e-6 * other * other) * slabs + 17.0;
-        return (double)ceil_div(tiles, kPlanCus) * fast_tile_us(384, false, g.Kd / kWideBK) <= 1.09 * first.us;
+        return lmhead_exchanged_plan(g).us <= (1.06 + 8.0 / slabs) * first.us;
     }
     if (use_small_tile(dtype, EPI_LMHEAD, g.M, g.N, g.Kd)) return false;
     const int64_t general = ceil_div(g.M, 128) * ceil_div(g.N, 128);
@@ -1242,7 +1265,12 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
         return r;
     }
     if (epi == EPI_LMHEAD && lmhead_exchanged_ok(dtype, g)) {
+        const TilePlan plan = lmhead_exchanged_plan(g);
         r.kernel = ATTS_KERNEL_EXCHANGED; r.tile_rows = 384; r.n_part = g.N / 384 * 4;
+        if (plan.tail_rows) {
+            r.head_rows = plan.head_m; r.tail_rows = plan.tail_rows;
+            r.n_part = r.head_rows / 384 * 4 + (g.N - r.head_rows) / r.tail_rows;
+        }
         return r;
     }
     // The aligned bf16 kernel serves every call it can (its DMA ring also streams weights well when the tiles are few).  A
@@ -1321,7 +1349,15 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
         x.w = g.a; x.ldw = g.lda; x.N = g.M;
         x.a_rows_padded = false;
         if (r.tile_rows == 256) return launch_wide_tile<EPI_LMHEAD_T, 2, 2, true>(x, stream);
-        return x.N % 256 ? launch_wide_tile<EPI_LMHEAD_T, 3, 4, true>(x, stream) : launch_wide_tile<EPI_LMHEAD_T, 3>(x, stream);
+        GemmArgs tail = x;
+        if (r.tail_rows) x.M = r.head_rows;
+        ATTS_TRY_RC((x.N % 256 ? launch_wide_tile<EPI_LMHEAD_T, 3, 4, true>(x, stream) : launch_wide_tile<EPI_LMHEAD_T, 3>(x, stream)));
+        if (!r.tail_rows) return ATTS_OK;
+        tail.a = static_cast<const char*>(x.a) + (int64_t)r.head_rows * x.lda * 2;
+        tail.M -= r.head_rows;
+        tail.v0 = r.head_rows;
+        tail.partials = g.partials + r.head_rows / 384 * 4;
+        return r.tail_rows == 128 ? launch_wide_tile<EPI_LMHEAD_T, 1, 4, true>(tail, stream) : launch_wide_tile<EPI_LMHEAD_T, 2, 4, true>(tail, stream);
     }
     if (epi == EPI_QKV_ROPE) {
         if (!qkv_rope_fusable(dtype, g.M, g.N, g.Kd, 128, g.a_rows_padded) || !g.rope || !g.vt || g.ldv < g.M || g.ldv % 4 ||

@@ -208,6 +208,30 @@ def test_lmhead_logprobs_matches_log_softmax_gather(dtype, tol, shape):
     assert np.all(got <= 1e-6)
 
 
+@pytest.mark.parametrize("B,d,V,tail", [(129, 3584, 384 * 396, 256), (256, 3584, 384 * 396, 256), (385, 768, 384 * 396, 128),
+                                        (513, 768, 384 * 262, 128), (1025, 768, 384 * 64, 128)])
+def test_lmhead_with_a_second_launch(B, d, V, tail):
+    """The vocabulary's last entries in smaller tiles (ragged and whole column tiles of scoring rows); targets on both sides of the
+    seam, at both ends and inside.  bf16 products summed in fp32, the reference in float64: 1e-3 as above."""
+    import paper_2509_15148_amd as A
+    announce("lmhead, second launch", B, d, V, tail)
+    _, route = A.atts_gemm_routes(torch.bfloat16, B, V, d)
+    assert route.kernel == A.KERNEL_EXCHANGED and route.tail_rows == tail
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = (torch.randn(B, d, device="cuda", generator=g) * 2).to(torch.bfloat16)
+    w = (torch.randn(V, d, device="cuda", generator=g) * (2 / math.sqrt(d))).to(torch.bfloat16)
+    tgt = torch.randint(0, V, (B,), dtype=torch.int32, device="cuda", generator=g)
+    seam = route.head_rows
+    tgt[:6] = torch.tensor([0, V - 1, seam - 1, seam, seam + tail - 1, min(seam + tail, V - 1)])
+    tgt[-1] = seam
+    lp = torch.full((B,), float("nan"), dtype=torch.float32, device="cuda")
+    A.atts_lmhead_logprobs(x, w, tgt, lp, ws(A.atts_lmhead_workspace_bytes(B, V)))
+    torch.cuda.synchronize()
+    z = x.double() @ w.double().t()
+    ref = torch.log_softmax(z, dim=1).gather(1, tgt[:, None].long())[:, 0]
+    assert (lp.double() - ref).abs().max().item() <= 1e-3
+
+
 # ------------------------------------------------------------------------------------ attention
 def _tree_attention_reference(qkv, P, K, T, nq, nkv, hd):
     """K independent causal sequences [prefix ; draft k] through torch's float64 SDPA."""

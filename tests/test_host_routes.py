@@ -70,6 +70,15 @@ def test_lm_head_with_few_tiles_keeps_the_faster_kernel(rows, vocab, d, exchange
     assert (head.kernel == A.KERNEL_EXCHANGED) == exchanged
 
 
+@pytest.mark.parametrize("rows,vocab,d,head,tail", [
+    (256, 152064, 3584, 256 * 384, 256), (385, 152064, 3584, 384 * 384, 128), (800, 152064, 3584, 384 * 384, 128),
+    (300, 24576, 3584, 0, 0), (4096, 152064, 3584, 0, 0), (128, 152064, 3584, 0, 0)])
+def test_lm_head_second_launch(rows, vocab, d, head, tail):
+    """A last round of 384 x 256 tiles that would leave most compute units idle goes to smaller tiles of the last vocabulary entries."""
+    _, r = A.atts_gemm_routes(MODELS["7b"].torch_dtype, rows, vocab, d)
+    assert (r.head_rows, r.tail_rows) == (head, tail)
+
+
 @pytest.mark.parametrize("dtype,shape,small", [
     ("fp32", (1024, 2048, 256), True), ("fp32", (2000, 1000, 1024), False), ("fp32", (1000, 1900, 2048), True), ("fp32", (300, 12000, 2048), False),
     ("fp32", (129, 16600, 8192), True), ("fp32", (260, 11000, 512), True), ("fp32", (260, 11000, 2048), False),
