@@ -129,7 +129,9 @@ struct GemmArgs {
     float2* partials;        // [M, n_part] (running max, sum of exp) per column slab
     float* target_logit;     // [M]
     int32_t n_part;          // number of column slabs = gemm_route(...).n_part of this call
-    int32_t v0;              // set by launch_gemm: first vocabulary entry of a launch that covers the last ones only
+    // set by launch_gemm where a call takes two launches:
+    int32_t v0;              // first vocabulary entry of the one that covers the last ones
+    int32_t n_cols;          // columns of the launch (0: all N)
     // EPI_QKV_ROPE only:
     const float2* rope;      // [M, 64] (cos, sin) per row and rotation pair
     void* vt;                // [n_kv, 128, ldv] transposed V
@@ -148,6 +150,7 @@ struct GemmRoute {
     int32_t slices;          // EPI_PARTIAL_F32: K slices; 1: cutting would not help, the caller takes the direct epilogue
     int32_t head_rows, tail_rows;   // tail_rows != 0: rows (exchanged operands: vocabulary entries) [0, head_rows) in tiles of
                                     // tile_rows, the rest in a second launch of tail_rows
+    int32_t head_cols;       // != 0 (then head_rows is 0): columns [0, head_cols) in tiles of tile_rows, the rest in a second launch of tail_rows
     int32_t n_part;          // EPI_LMHEAD: column slabs (partials per row)
 };
 GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);

@@ -920,11 +920,17 @@ struct TilePlan {
     int rows, slices;        // slices > 1: partial sums per K slice (EPI_PARTIAL_F32; 128-row tiles are 128 columns wide there)
     double us;
     int head_m, tail_rows;   // tail_rows != 0: rows [0, head_m) in tiles of `rows`, the rest in a second launch of this height
+    int head_n;              // ... or, != 0: columns [0, head_n) of all rows, and the rest
 };
 
 // Tile height of a call without a K split.  A last round of 384-row tiles that would leave most CUs idle (32B-class O and
 // down projections: 1820 tiles = 7.1 rounds of 256) is avoided by giving the last tile rows to a second launch of smaller
-// tiles: 89 tile rows in 7 full rounds, then 640 rows as 100 tiles of 128 rows; 5 % faster there.
+// tiles: 89 tile rows in 7 full rounds, then 640 rows as 100 tiles of 128 rows; 5 % faster there.  With few tile rows the cut
+// goes through the columns: whole rounds of tall tiles over the first columns, lower tiles over the last (776 rows of the 7B
+// gate/up projection: 444 tiles of 384 rows are two rounds; 85 columns of them and 63 of 256-row tiles, 252, are one of each).
+// Gate/up, us: 7B 776 rows 222 -> 209, 1300 330 -> 298, 1500 353 -> 310, 4096 846 -> 823; 32B 900 500 -> 456, 1024 498 -> 467,
+// 4096 1737 -> 1673; 70B 1024 765 -> 722, 8192 5543 -> 5419; 70B 4608 rows, O 541 -> 490 and down 1844 -> 1598.  The residual epilogue,
+// whose tiles wait for their old values, wants more than the model's 3 % (7B 8192 rows: O 199 -> 205 at 0.97).
 TilePlan direct_plan(int epi, const GemmArgs& g) {
     const int n_out = epi == EPI_SWIGLU ? 128 : 256;
     const int64_t nt_n = g.N / n_out, slabs = g.Kd / kWideBK;
@@ -937,17 +943,29 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
         // the LM head's epilogue reduces every row across lanes: with 128-row tiles it would take a third of the time
         if (rows == 128 && g.M > 128 && epi == EPI_LMHEAD) continue;
         const double us = rounds_us(rows, g.M);
-        if (best.rows == 0 || us < best.us * 0.98) best = TilePlan{rows, 1, us, 0, 0};
+        if (best.rows == 0 || us < best.us * 0.98) best = TilePlan{rows, 1, us, 0, 0, 0};
     }
-    if (epi == EPI_QKV_ROPE || g.M <= 384 || !tile_rows_allowed(384, g)) return best;     // its V^T output is not addressed by row alone
+    if (epi == EPI_QKV_ROPE) return best;                        // its V^T output is not addressed by row or column alone
     const int64_t nt_m = ceil_div(g.M, 384);
-    for (int drop = 1; drop <= 3 && drop < nt_m; ++drop)
+    for (int drop = 1; drop <= 3 && drop < nt_m && tile_rows_allowed(384, g); ++drop)
         for (int tail : {256, 128}) {
             const int head_m = (int)(nt_m - drop) * 384;
             // readable rows: the caller's, or up to the next multiple of 768
             if (head_m + ceil_div(g.M - head_m, tail) * tail > (int64_t)(g.a_rows_padded ? align_up((size_t)g.M, 768) : (size_t)g.M)) continue;
             const double us = rounds_us(384, head_m) + rounds_us(tail, g.M - head_m) + 4.0;     // a launch more
-            if (us < best.us * 0.96) best = TilePlan{384, 1, us, head_m, tail};
+            if (us < best.us * 0.96) best = TilePlan{384, 1, us, head_m, tail, 0};
+        }
+    if (epi != EPI_LMHEAD)                                       // whose partials are counted in tiles of one width
+        for (int rows : {384, 256}) {
+            if (!tile_rows_allowed(rows, g)) continue;
+            const int64_t tall = ceil_div(g.M, rows), full = tall * nt_n / kPlanCus, head = full * kPlanCus / tall;
+            if (full == 0 || head >= nt_n) continue;
+            for (int tail : {256, 128}) {
+                if (tail >= rows || !tile_rows_allowed(tail, g)) continue;
+                const double us = (double)full * fast_tile_us(rows, false, slabs) +
+                                  (double)ceil_div(ceil_div(g.M, tail) * (nt_n - head), kPlanCus) * fast_tile_us(tail, false, slabs) + 4.0;
+                if (us < best.us * (epi == EPI_SWIGLU ? 0.985 : 0.96)) best = TilePlan{rows, 1, us, 0, tail, (int)head * n_out};
+            }
         }
     return best;
 }
@@ -960,7 +978,7 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
 // for the same 128 tiles unsplit.
 TilePlan partial_plan(const GemmArgs& g) {
     const int64_t slabs = g.Kd / kWideBK, fitting = (int64_t)(g.room / ((size_t)g.M * g.N * sizeof(float)));
-    const TilePlan none{0, 1, 0.0, 0, 0};
+    const TilePlan none{0, 1, 0.0, 0, 0, 0};
     TilePlan best = none;
     for (int rows : {384, 256, 128}) {
         if (!tile_rows_allowed(rows, g)) continue;
@@ -971,7 +989,7 @@ TilePlan partial_plan(const GemmArgs& g) {
         if (s > fitting) s = fitting;
         if (s < 2) continue;
         const double us = fast_tile_us(rows, narrow, ceil_div(slabs, s)) + (double)s * g.M * g.N * 8 / 4.5e6 + 4.0;
-        if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0};
+        if (best.rows == 0 || us < best.us) best = TilePlan{rows, (int)s, us, 0, 0, 0};
     }
     // without the split the norm that follows is a pass of its own, which reads 4 and writes 2 bytes an element
     const double norm_us = 4.0 + (double)g.M * g.N * 6 / 4.5e6;
@@ -1007,7 +1025,7 @@ int32_t launch_wide_tile(const GemmArgs& g, hipStream_t stream) {
     d.ldv = g.ldv;
     d.n_rot_heads = g.n_rot_heads;
     d.nt_m = (int)ceil_div(g.M, BM);
-    d.nt_n = (int)ceil_div(g.N, n_out);     // whole tiles, except the columns of the exchanged LM head
+    d.nt_n = (int)ceil_div(g.n_cols ? g.n_cols : g.N, n_out);     // whole tiles, except the columns of the exchanged LM head
     d.k_slices = EPI == EPI_PARTIAL_F32 ? g.n_slices : 1;
     d.slice_pitch = (int64_t)g.M * g.ldc;
     d.v0 = g.v0;
@@ -1044,6 +1062,15 @@ int32_t launch_fast(const GemmRoute& r, const GemmArgs& g, hipStream_t stream) {
     } else {
         if (r.tail_rows == 0) return launch_tile_rows<EPI>(r.tile_rows, g, stream);
         GemmArgs head = g, tail = g;
+        if (r.head_cols) {
+            // the columns from head_cols on: weights (SwiGLU: gate and up rows, N apart as before) and output further on
+            head.n_cols = r.head_cols;
+            ATTS_TRY_RC(launch_tile_rows<EPI>(r.tile_rows, head, stream));
+            tail.n_cols = g.N - r.head_cols;
+            tail.w = static_cast<const char*>(g.w) + (int64_t)r.head_cols * g.ldw * 2;
+            tail.out = static_cast<char*>(g.out) + (int64_t)r.head_cols * ((EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32) ? 4 : 2);
+            return launch_tile_rows<EPI>(r.tail_rows, tail, stream);
+        }
         head.M = r.head_rows;
         ATTS_TRY_RC((launch_wide_tile<EPI, 3>(head, stream)));
         const int64_t r0 = head.M;
@@ -1224,7 +1251,7 @@ static bool lmhead_aligned_k(int32_t dtype, int32_t Kd, int64_t lda, int64_t ldw
 // 818; 70B head 200 rows 580 -> 491, 1000 rows 1650 -> 1620.
 static TilePlan lmhead_exchanged_plan(const GemmArgs& g) {
     const int64_t nt_m = g.N / 384, nt_n = ceil_div(g.M, 256), slabs = g.Kd / kWideBK, full = nt_m * nt_n / kPlanCus;
-    TilePlan best{384, 1, (double)ceil_div(nt_m * nt_n, kPlanCus) * fast_tile_us(384, false, slabs), 0, 0};
+    TilePlan best{384, 1, (double)ceil_div(nt_m * nt_n, kPlanCus) * fast_tile_us(384, false, slabs), 0, 0, 0};
     if (full == 0 || nt_m * nt_n % kPlanCus == 0) return best;
     const double base = best.us;
     for (int rows : {256, 128}) {
@@ -1234,7 +1261,7 @@ static TilePlan lmhead_exchanged_plan(const GemmArgs& g) {
         const int64_t tail_tiles = (nt_m - head) * 384 / rows * nt_n;
         const double us = (double)ceil_div(head * nt_n, kPlanCus) * fast_tile_us(384, false, slabs) +
                           (double)ceil_div(tail_tiles, kPlanCus) * fast_tile_us(rows, false, slabs) + 4.0;
-        if (us < best.us && us < 0.95 * base) best = TilePlan{384, 1, us, (int)(head * 384), rows};
+        if (us < best.us && us < 0.95 * base) best = TilePlan{384, 1, us, (int)(head * 384), rows, 0};
     }
     return best;
 }
@@ -1259,7 +1286,7 @@ static bool lmhead_few_ok(int32_t dtype, const GemmArgs& g) {
 }
 
 GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
-    GemmRoute r{ATTS_KERNEL_GENERAL_128, 0, 1, 0, 0, 0};
+    GemmRoute r{ATTS_KERNEL_GENERAL_128, 0, 1, 0, 0, 0, 0};
     if (epi == EPI_LMHEAD && lmhead_few_ok(dtype, g)) {
         r.kernel = ATTS_KERNEL_EXCHANGED; r.tile_rows = 256; r.n_part = g.N / 256;
         return r;
@@ -1286,7 +1313,7 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
     if (fast) {
         const TilePlan plan = epi == EPI_PARTIAL_F32 ? partial_plan(g) : direct_plan(epi, g);
         r.kernel = ATTS_KERNEL_ALIGNED; r.tile_rows = plan.rows; r.slices = plan.slices;
-        r.head_rows = plan.head_m; r.tail_rows = plan.tail_rows;
+        r.head_rows = plan.head_m; r.tail_rows = plan.tail_rows; r.head_cols = plan.head_n;
         r.n_part = g.N / 256 * 2;
         return r;
     }

@@ -94,6 +94,29 @@ def test_row_counts_between_tiles(P, K, T):
 ALIGNED, EXCHANGED = 4, 5      # atts.h: ATTS_KERNEL_*
 
 
+@pytest.mark.parametrize("cfg,P,K,T,product,tile,tail", [
+    (ModelConfig(1, 1024, 8, 2, 128, 12288, 768, "bf16"), 7, 24, 32, "gate_up", 256, 128),
+    (ModelConfig(1, 768, 6, 2, 128, 16384, 768, "bf16"), 8, 50, 37, "gate_up", 384, 256),
+    (ModelConfig(1, 8192, 6, 2, 128, 1024, 768, "bf16"), 8, 150, 32, "down", 384, 256),
+])
+def test_last_columns_in_a_second_launch(cfg, P, K, T, product, tile, tail):
+    """Tall tiles over the first columns, lower ones over the last (SwiGLU, whose gate and up rows lie apart, and the residual
+    update): a wrong column shows in every row.  Oracle: the first, a middle and the last draft."""
+    import paper_2509_15148_amd as A
+    announce("last columns", cfg, P, K, T)
+    r = getattr(A.atts_pass_routes(cfg, A.PASS_SCORE, P, K, T), product)
+    assert (r.kernel, r.tile_rows, r.head_rows, r.tail_rows) == (ALIGNED, tile, 0, tail)
+    w, prefix, drafts = _case(cfg, P, K, T, seed=K)
+    model = A.Model(cfg, w)
+    lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
+    lp, sc, w_np = lp.cpu().numpy(), sc.cpu().numpy(), weights_to_numpy(w)
+    assert np.isfinite(lp).all() and np.isfinite(sc).all()
+    for k in (0, K // 2, K - 1):
+        ref = O.token_logprobs(w_np, cfg, prefix, drafts[k])
+        assert np.abs(lp[k] - ref).max() <= TOL["bf16"], (k, np.abs(lp[k] - ref).max())
+
+
 @pytest.mark.parametrize("cfg,P,K,T,expected", [
     # product -> (kernel, rows of a tile, cut along K, rows of a tile of the second launch)
     (ModelConfig(1, 768, 6, 2, 128, 16384, 768, "bf16"), 8, 96, 16, {"gate_up": (ALIGNED, 384, False, 128), "down": (ALIGNED, 128, True, 0)}),

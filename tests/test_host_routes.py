@@ -79,6 +79,15 @@ def test_lm_head_second_launch(rows, vocab, d, head, tail):
     assert (r.head_rows, r.tail_rows) == (head, tail)
 
 
+@pytest.mark.parametrize("name,rows,product,tile,tail", [
+    ("7b", 776, "gate_up", 384, 256), ("7b", 385, "gate_up", 256, 128), ("7b", 1500, "gate_up", 384, 128), ("7b", 4608, "gate_up", 384, 0),
+    ("70b", 4608, "down", 384, 256), ("7b", 8192, "o", 256, 0)])
+def test_last_columns_of_a_projection(name, rows, product, tile, tail):
+    """Whole rounds of tall tiles over the first columns, lower ones over the last, where the last round would be partly filled."""
+    r = getattr(A.atts_pass_routes(MODELS[name], A.PASS_SCORE, 4, 1, rows - 4), product)
+    assert (r.kernel, r.tile_rows, r.head_rows, r.tail_rows) == (A.KERNEL_ALIGNED, tile, 0, tail)
+
+
 @pytest.mark.parametrize("dtype,shape,small", [
     ("fp32", (1024, 2048, 256), True), ("fp32", (2000, 1000, 1024), False), ("fp32", (1000, 1900, 2048), True), ("fp32", (300, 12000, 2048), False),
     ("fp32", (129, 16600, 8192), True), ("fp32", (260, 11000, 512), True), ("fp32", (260, 11000, 2048), False),
