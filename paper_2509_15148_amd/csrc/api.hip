@@ -347,9 +347,15 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
                                    fuse_rope ? vt : nullptr, (int64_t)kvd, ws.ldv, m->err_flag, st));
     }
     char* xn0 = xn + (size_t)row0 * d.d_model * es;
+    // a small fp32 model: the norms ride in the projections that read them, the rotation in the QKV projection
+    const bool fp32 = d.dtype == ATTS_DTYPE_F32;
+    const bool rope_in_small = fp32 && vt == nullptr && d.head_dim <= 32 && (d.head_dim & (d.head_dim - 1)) == 0 &&
+                               gemm_route(d.dtype, EPI_STORE_ACT, gemm_shape(d, M, qkv_out, d.d_model)).kernel == ATTS_KERNEL_SMALL;
+    const bool norm_in_gate_up = fp32 && gemm_route(d.dtype, EPI_SWIGLU, gemm_shape(d, M, d.d_ffn, d.d_model)).kernel == ATTS_KERNEL_SMALL;
     bool xn_ready = true;       // xn already holds the attention norm of this layer (written with the embedding or the previous residual update)
     for (int l = 0; l < d.n_layers; ++l) {
-        if (!xn_ready) {
+        const bool norm_in_qkv = !xn_ready && rope_in_small;
+        if (!xn_ready && !norm_in_qkv) {
             StageTimer t_(ATTS_STAGE_NORM, st);
             ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->attn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
         }
@@ -379,6 +385,11 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             g.n_rot_heads = d.n_q_heads + d.n_kv_heads;
             StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
             ATTS_TRY(launch_gemm(d.dtype, EPI_QKV_ROPE, g, st));
+        } else if (rope_in_small) {
+            g.rope = rope + (size_t)row0 * (d.head_dim / 2); g.n_rot_heads = d.n_q_heads + d.n_kv_heads; g.head_dim = d.head_dim;
+            if (norm_in_qkv) { g.a = h0; g.norm_gain = m->attn_norm[l]; g.norm_eps = d.rms_eps; }
+            StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
+            ATTS_TRY(launch_gemm_small_fused(EPI_QKV_ROPE, g, st));
         } else {
             {
                 StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
@@ -438,8 +449,10 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
                 StageTimer t_(ATTS_STAGE_GEMM_O, st);
                 ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
             }
-            StageTimer t_(ATTS_STAGE_NORM, st);
-            ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
+            if (!norm_in_gate_up) {
+                StageTimer t_(ATTS_STAGE_NORM, st);
+                ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
+            }
         }
         g = GemmArgs{};
         g.a = xn0; g.w = m->w_gate_up[l]; g.out = act;             // act: the M rows of this pass from its start on
@@ -447,7 +460,12 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
         g.lda = d.d_model; g.ldw = d.d_model; g.ldc = d.d_ffn; g.a_rows_padded = padded;
         {
             StageTimer t_(ATTS_STAGE_GEMM_GATE_UP, st);
-            ATTS_TRY(launch_gemm(d.dtype, EPI_SWIGLU, g, st));
+            if (norm_in_gate_up) {
+                g.a = h0; g.norm_gain = m->ffn_norm[l]; g.norm_eps = d.rms_eps;
+                ATTS_TRY(launch_gemm_small_fused(EPI_SWIGLU, g, st));
+            } else {
+                ATTS_TRY(launch_gemm(d.dtype, EPI_SWIGLU, g, st));
+            }
         }
         g = GemmArgs{};
         g.a = act; g.w = m->w_down[l]; g.out = h0; g.M = M; g.N = d.d_model; g.Kd = d.d_ffn;

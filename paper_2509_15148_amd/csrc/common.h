@@ -137,6 +137,10 @@ struct GemmArgs {
     void* vt;                // [n_kv, 128, ldv] transposed V
     int64_t ldv;
     int32_t n_rot_heads;     // n_q + n_kv: heads (of 128 columns) that are rotated; the rest are V heads
+    // launch_gemm_small_fused only:
+    int32_t head_dim;        // EPI_QKV_ROPE: columns of a head
+    const float* norm_gain;  // != NULL: a is the fp32 residual stream, normalised row by row with this gain
+    float norm_eps;
     // EPI_PARTIAL_F32 only:
     int32_t n_slices;        // slices stored = gemm_route(...).slices
     size_t room;             // bytes `out` has for them: no more slices than fit
@@ -169,6 +173,10 @@ size_t skinny_partial_bound(int32_t M, int32_t N, int32_t Kd);    // bytes of it
 // The kernel for products of few tiles (small.hip), any shape; launch_gemm hands it the calls that leave the chip idle otherwise.
 int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
+// The same for an fp32 model with passes around the product fused in (no transposed values): EPI_QKV_ROPE for heads of a power
+// of two of at most 32 columns, with or without the norm, and EPI_SWIGLU with the norm.  For calls whose plain form
+// (EPI_STORE_ACT, EPI_SWIGLU) gemm_route gives to the small kernel.
+int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 // true if the EPI_QKV_ROPE epilogue can serve this QKV projection (else: EPI_STORE_ACT + launch_rope_split)
 bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t head_dim, bool a_rows_padded);
 

@@ -12,6 +12,12 @@
 // Against 128 x 128 tiles: fp32 320 x 128 x 512 45.3 -> 7.1 us, 320 x 512 x 128 15.3 -> 3.7, 1024 x 512 x 512 45.6 -> 13.4,
 // 64 x 4096 x 4096 330 -> 35; bf16 320 x 512 x 512 11.7 -> 4.4.  The scoring pass of the fp32 model (2 layers, 320 rows):
 // 267 -> 104 us.
+// A launch of such a product is itself a third of its time, so in fp32 the passes around it ride along (2 layers,
+// 320 rows: 20 launches and 90.5 us -> 15 and 80.0, the old residual values requested with the operands included):
+//   kNorm  A is the residual stream: its rows are multiplied by the norm's gain as they are read, their sums of squares are taken
+//          on the way, and the finished sums are scaled by 1 / rms;
+//   EPI_QKV_ROPE  heads of at most 32 columns lie inside one tile: rotated with the partner column's value from the lane that
+//          holds it (values stay rows of the output, there is no transposed copy here).
 #include "common.h"
 
 namespace atts {
@@ -24,6 +30,8 @@ struct SmallDims {
     int32_t M, N, Kd;
     int64_t lda, ldw, ldc;
     int32_t n_part, nt_m;
+    float eps;                              // kNorm
+    int32_t rot_cols, half_hd, cs_ld;       // EPI_QKV_ROPE: columns that are rotated, half a head's columns (a power of two), pitch of the table
 };
 
 // One step: lane (row = l % 32, half = l / 32) holds 16 bytes of its row, at byte 32 step + 16 half.  bf16: the operand of
@@ -43,14 +51,17 @@ template <> struct SmallMma<float> {
     }
 };
 
-template <typename T, int EPI, int NI>
+template <typename T, int EPI, int NI, bool kNorm = false>
 __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char* __restrict__ gA, const char* __restrict__ gW,
                                                                       void* __restrict__ g_out, const int32_t* __restrict__ g_targets,
                                                                       float2* __restrict__ g_partials, float* __restrict__ g_target_logit,
+                                                                      const float* __restrict__ g_gain, const float2* __restrict__ g_rope,
                                                                       const SmallDims d) {
+    static_assert(!kNorm || sizeof(T) == 4, "the residual stream is fp32");
     constexpr int ES = (int)sizeof(T), N_OUT = EPI == EPI_SWIGLU ? 32 : 32 * NI;
     static_assert((EPI == EPI_SWIGLU || EPI == EPI_LMHEAD) == (NI == 2), "tile width");
     __shared__ float part[kSmallWaves][NI][16][64];
+    __shared__ float squares[kNorm ? kSmallWaves : 1][32];
     const int lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));    // scalar: the K loop's branches must be too
     const int tm = (int)blockIdx.x % d.nt_m, tn = (int)blockIdx.x / d.nt_m;
@@ -68,7 +79,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
     const int n_steps = (k_bytes + 31) / 32;
     const int s0 = wave * n_steps / kSmallWaves, s1 = (wave + 1) * n_steps / kSmallWaves;
     struct Frags {
-        uint4 a[kSmallUnroll], w[NI][kSmallUnroll];
+        uint4 a[kSmallUnroll], w[NI][kSmallUnroll], gain[kNorm ? kSmallUnroll : 1];
     };
     auto load = [&](Frags& f, int s) __attribute__((always_inline)) {
 #pragma unroll
@@ -76,20 +87,43 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
             const int64_t off = (int64_t)(s + u) * 32;
             const bool ok = s + u < s1 && off + 16 * half < k_bytes;
             f.a[u] = ok ? *reinterpret_cast<const uint4*>(ap + off) : make_uint4(0, 0, 0, 0);
+            if constexpr (kNorm)
+                f.gain[u] = ok ? *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(g_gain) + off + 16 * half) : make_uint4(0, 0, 0, 0);
 #pragma unroll
             for (int j = 0; j < NI; ++j) f.w[j][u] = ok ? *reinterpret_cast<const uint4*>(wp[j] + off) : make_uint4(0, 0, 0, 0);
         }
     };
+    // residual update: the old values are on their way with the operands, not waited for behind the sums
+    const int row0 = m0 + 8 * wave + 4 * half, col = n0 + l32;
+    float old[EPI == EPI_RESID_F32 ? 4 : 1];
+    if constexpr (EPI == EPI_RESID_F32) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+            old[b] = reinterpret_cast<const float*>(g_out)[(int64_t)min(row0 + b, d.M - 1) * d.ldc + min(col, d.N - 1)];
+    }
     f32x16 acc[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+    float sq = 0.f;
     auto mma = [&](const Frags& f) __attribute__((always_inline)) {      // steps past the end multiply zeros
 #pragma unroll
-        for (int u = 0; u < kSmallUnroll; ++u)
+        for (int u = 0; u < kSmallUnroll; ++u) {
+            uint4 a = f.a[u];
+            if constexpr (kNorm) {
+                f32x4 x = __builtin_bit_cast(f32x4, a);
+                const f32x4 gain = __builtin_bit_cast(f32x4, f.gain[u]);
 #pragma unroll
-            for (int j = 0; j < NI; ++j) SmallMma<T>::mma(f.a[u], f.w[j][u], acc[j]);
+                for (int e = 0; e < 4; ++e) {
+                    sq += x[e] * x[e];
+                    x[e] *= gain[e];
+                }
+                a = __builtin_bit_cast(uint4, x);
+            }
+#pragma unroll
+            for (int j = 0; j < NI; ++j) SmallMma<T>::mma(a, f.w[j][u], acc[j]);
+        }
     };
     Frags fa, fb;
     load(fa, s0);
@@ -105,6 +139,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
     for (int j = 0; j < NI; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) part[wave][j][v][lane] = acc[j][v];
+    if constexpr (kNorm) {
+        sq += __shfl_xor(sq, 32);
+        if (half == 0) squares[wave][l32] = sq;
+    }
     __syncthreads();
 
     // wavefront w finishes entries v = 4 w .. 4 w + 3 of every block: rows m0 + 8 w + 4 half + (v & 3), column l32
@@ -116,9 +154,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
             float s = part[0][j][4 * wave + b][lane];
 #pragma unroll
             for (int w = 1; w < kSmallWaves; ++w) s += part[w][j][4 * wave + b][lane];
+            if constexpr (kNorm) {
+                float sum = 0.f;
+#pragma unroll
+                for (int w = 0; w < kSmallWaves; ++w) sum += squares[w][8 * wave + 4 * half + b];
+                s *= rsqrtf(sum / (float)d.Kd + d.eps);
+            }
             z[j][b] = s;
         }
-    const int row0 = m0 + 8 * wave + 4 * half, col = n0 + l32;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
         const int row = row0 + b;
@@ -143,17 +186,25 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
             for (int o = 1; o < 32; o <<= 1) sum += __shfl_xor(sum, o);
             if (row_ok && l32 == 0) g_partials[(int64_t)row * d.n_part + tn] = make_float2(mx, sum);
         } else {
+            float rotated = 0.f;
+            if constexpr (EPI == EPI_QKV_ROPE) {                            // every lane of the wavefront takes part in the exchange
+                const float other = __shfl_xor(z[0][b], d.half_hd);
+                const float2 cs = g_rope[(int64_t)min(row, d.M - 1) * d.cs_ld + (col & (d.half_hd - 1))];
+                rotated = (col & d.half_hd) ? z[0][b] * cs.x + other * cs.y : z[0][b] * cs.x - other * cs.y;
+                if (col >= d.rot_cols) rotated = z[0][b];
+            }
             if (row >= d.M || col >= d.N) continue;
             const int64_t idx = (int64_t)row * d.ldc + col;
             if constexpr (EPI == EPI_SWIGLU) {
                 const float gate = z[0][b], up = z[1][b];
                 // hardware reciprocal, as in the tiled kernels
                 reinterpret_cast<T*>(g_out)[idx] = from_f32<T>(gate * __builtin_amdgcn_rcpf(1.f + __expf(-gate)) * up);
+            } else if constexpr (EPI == EPI_QKV_ROPE) {
+                reinterpret_cast<T*>(g_out)[idx] = from_f32<T>(rotated);
             } else if constexpr (EPI == EPI_STORE_ACT) {
                 reinterpret_cast<T*>(g_out)[idx] = from_f32<T>(z[0][b]);
             } else if constexpr (EPI == EPI_RESID_F32) {
-                float* p = reinterpret_cast<float*>(g_out) + idx;
-                *p = *p + z[0][b];
+                reinterpret_cast<float*>(g_out)[idx] = old[b] + z[0][b];
             } else {
                 reinterpret_cast<float*>(g_out)[idx] = z[0][b];
             }
@@ -161,12 +212,13 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
     }
 }
 
-template <typename T, int EPI>
+template <typename T, int EPI, bool kNorm = false>
 int32_t launch_small_epi(const GemmArgs& g, hipStream_t stream) {
     constexpr int NI = EPI == EPI_SWIGLU || EPI == EPI_LMHEAD ? 2 : 1, N_OUT = EPI == EPI_LMHEAD ? 64 : 32;
-    SmallDims d{g.M, g.N, g.Kd, g.lda, g.ldw, g.ldc, g.n_part, (int32_t)ceil_div(g.M, 32)};
-    hipLaunchKernelGGL((gemm_small_kernel<T, EPI, NI>), dim3((unsigned)(d.nt_m * ceil_div(g.N, N_OUT))), dim3(64 * kSmallWaves), 0, stream,
-                       reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), g.out, g.targets, g.partials, g.target_logit, d);
+    SmallDims d{g.M, g.N, g.Kd, g.lda, g.ldw, g.ldc, g.n_part, (int32_t)ceil_div(g.M, 32), g.norm_eps,
+                g.n_rot_heads * g.head_dim, g.head_dim / 2, g.head_dim / 2};
+    hipLaunchKernelGGL((gemm_small_kernel<T, EPI, NI, kNorm>), dim3((unsigned)(d.nt_m * ceil_div(g.N, N_OUT))), dim3(64 * kSmallWaves), 0, stream,
+                       reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), g.out, g.targets, g.partials, g.target_logit, g.norm_gain, g.rope, d);
     ATTS_LAUNCH_CHECK("gemm_small_kernel");
     return ATTS_OK;
 }
@@ -185,6 +237,12 @@ int32_t launch_small_t(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) 
 }
 
 }  // namespace
+
+int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
+    if (epi == EPI_QKV_ROPE) return g.norm_gain ? launch_small_epi<float, EPI_QKV_ROPE, true>(g, stream) : launch_small_epi<float, EPI_QKV_ROPE>(g, stream);
+    if (epi == EPI_SWIGLU && g.norm_gain) return launch_small_epi<float, EPI_SWIGLU, true>(g, stream);
+    return fail(ATTS_ERR_INVALID_ARG, "gemm (small product): epilogue %d is not fused", (int)epi);
+}
 
 int32_t small_lmhead_partials(int32_t N) { return (int32_t)ceil_div(N, 64); }
 
