@@ -27,9 +27,12 @@ constexpr int kSpacing = 64;                 // every 64th key of a run is a sam
 constexpr int kSamplesMin = 16, kSamplesMax = 32;   // samples per bucket: about 1024 or 2048 keys
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketCap = kPer * kBucketThreads;
+constexpr int kFewThreads = 512;             // ... and for few runs (of 2048 keys)
+constexpr int kFewRuns = 32;
 // a bucket's keys lie strictly between two splitters with at most q samples between them: at most kSpacing q keys, and from
 // every run fewer than kSpacing more
 static_assert(kSpacing * (kSamplesMax + kMaxRuns) <= kBucketCap && kSmallSortMax / kSpacing <= kBucketCap, "a workgroup holds a bucket, and all samples");
+static_assert(kSpacing * (kSamplesMin + kFewRuns) <= kPer * kFewThreads && kFewRuns * 16 <= kFewThreads && kMaxRuns * 16 <= kBucketThreads, "");
 static_assert(kMaxRuns * kRunMax == kSmallSortMax && kSamplesMin % kPer == 0 && kSmallSortMax / kSpacing / kSamplesMax <= kBucketThreads, "");
 
 // Every workgroup turns 8 THREADS scores into one ascending run; samples != NULL: every kSpacing-th key of it also goes there,
@@ -64,16 +67,18 @@ __global__ __launch_bounds__(THREADS) void block_sort_kernel(const float* __rest
 // What bounds it is its chain of steps (two sorts, the limits, the gathering), one bucket per CU: 65,536 scores 14 us behind
 // 5.2 for the runs, where runs of 8192 keys merged through LDS and one pass that searched every key's place in the other runs took
 // 25 + 14; 262,144 scores 31 us in all and 524,288 43, by radix sort 76 and 78 (which is why the line to it lies here: its
-// launches are a floor, and 64 runs of one workgroup's keys end at 2^19).
-__global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(const uint32_t* __restrict__ runs, int64_t n, int run_len, int n_runs,
-                                                                     const uint32_t* __restrict__ samples, int n_samples, int q,
-                                                                     uint32_t* __restrict__ out) {
+// launches are a floor, and 64 runs of one workgroup's keys end at 2^19).  Up to 32 runs by workgroups of 512 threads: 0.6 us less.
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void bucket_sort_kernel(const uint32_t* __restrict__ runs, int64_t n, int run_len, int n_runs,
+                                                              const uint32_t* __restrict__ samples, int n_samples, int q,
+                                                              uint32_t* __restrict__ out) {
+    constexpr int kCap = kPer * THREADS, kRuns = THREADS / 16;
     extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-    uint32_t* const buf = lds;                                     // 2 kBucketCap: exchanges; then the gathered keys
-    uint32_t* const smp = lds + 2 * kBucketCap;                    // the samples, run after run
-    __shared__ uint32_t splitter[kBucketCap / kSamplesMin];
-    __shared__ int below[3][kMaxRuns];                             // keys of a run below / not above the lower limit, below the upper one
-    __shared__ int seg_at[kMaxRuns + 1];
+    uint32_t* const buf = lds;                                     // 2 kCap: exchanges; then the gathered keys
+    uint32_t* const smp = lds + 2 * kCap;                          // the samples, run after run
+    __shared__ uint32_t splitter[kCap / kSamplesMin];
+    __shared__ int below[3][kRuns];                                // keys of a run below / not above the lower limit, below the upper one
+    __shared__ int seg_at[64 + 1];
     __shared__ int sum_lo[2];
     const int tid = threadIdx.x, b = blockIdx.x, n_buckets = gridDim.x;
     auto size_for = [](int m) {
@@ -83,20 +88,20 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(const uint3
     };
     uint32_t k[kPer];
 #pragma unroll
-    for (int e = 0; e < kPer; ++e) k[e] = samples[min(e * kBucketThreads + tid, n_samples - 1)];
+    for (int e = 0; e < kPer; ++e) k[e] = samples[min(e * THREADS + tid, n_samples - 1)];
 #pragma unroll
     for (int e = 0; e < kPer; ++e) {
-        const int i = e * kBucketThreads + tid;
+        const int i = e * THREADS + tid;
         if (i < n_samples) smp[i] = k[e];
         else k[e] = kPadKey;
     }
     // the network's places are thread-major: keep its first `size` places full when there are fewer samples than places
-    if (n_samples <= kBucketCap / 2) {
+    if (n_samples <= kCap / 2) {
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < kPer; ++e) k[e] = tid * kPer + e < n_samples ? smp[tid * kPer + e] : kPadKey;
     }
-    sort_in_block<kBucketThreads>(k, size_for(n_samples), buf);
+    sort_in_block<THREADS>(k, size_for(n_samples), buf);
     if (tid * kPer % q == 0) splitter[tid * kPer / q] = k[0];
     __syncthreads();
     const bool has_lo = b > 0, has_hi = b + 1 < n_buckets;
@@ -154,7 +159,7 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(const uint3
         }
     }
     __syncthreads();
-    const int m = seg_at[kMaxRuns];                                // at most kBucketCap
+    const int m = seg_at[64];                                // at most kCap
     {
         const int r = tid >> 4;                                    // sixteen threads per run
         if (r < n_runs) {
@@ -174,17 +179,17 @@ __global__ __launch_bounds__(kBucketThreads) void bucket_sort_kernel(const uint3
 #pragma unroll
     for (int e = 0; e < kPer; ++e) k[e] = tid * kPer + e < m ? buf[tid * kPer + e] : kPadKey;
     __syncthreads();
-    sort_in_block<kBucketThreads>(k, size_for(m), buf);
+    sort_in_block<THREADS>(k, size_for(m), buf);
     __syncthreads();
     reinterpret_cast<uint4*>(buf)[2 * tid] = make_uint4(k[0], k[1], k[2], k[3]);
     reinterpret_cast<uint4*>(buf)[2 * tid + 1] = make_uint4(k[4], k[5], k[6], k[7]);
     __syncthreads();
     uint32_t* const o = out + sum_lo[1];
-    for (int i = tid; i < m; i += kBucketThreads) o[i] = buf[i];
+    for (int i = tid; i < m; i += THREADS) o[i] = buf[i];
     if (has_lo) {
         const int64_t width = sum_lo[1] - sum_lo[0];
         const int f0 = sum_lo[0] + (int)(width * my_same / n_same), f1 = sum_lo[0] + (int)(width * (my_same + 1) / n_same);
-        for (int i = f0 + tid; i < f1; i += kBucketThreads) out[i] = lo;
+        for (int i = f0 + tid; i < f1; i += THREADS) out[i] = lo;
     }
 }
 
@@ -376,11 +381,16 @@ int32_t launch_sort_scores(const float* scores, int64_t n, uint32_t* a, uint32_t
         if (n_runs > 1) {
             const int n_samples = (int)ceil_div(n, kSpacing);
             const int q = n_samples <= 256 * kSamplesMin ? kSamplesMin : kSamplesMax;      // a bucket takes a CU's LDS: at most 256
-            const size_t lds = (size_t)(2 * kBucketCap + align_up((size_t)n_samples, 4)) * sizeof(uint32_t);
-            int32_t rc = allow_dynamic_lds<bucket_sort_kernel>((size_t)3 * kBucketCap * sizeof(uint32_t));
-            if (rc != ATTS_OK) return rc;
-            hipLaunchKernelGGL(bucket_sort_kernel, dim3((unsigned)ceil_div(n_samples, q)), dim3(kBucketThreads), lds, stream, a, n, (int)run,
-                               n_runs, samples, n_samples, q, b);
+            const int threads = n_runs <= kFewRuns ? kFewThreads : kBucketThreads;
+            const size_t lds = (size_t)(2 * kPer * threads + align_up((size_t)n_samples, 4)) * sizeof(uint32_t);
+            const dim3 buckets((unsigned)ceil_div(n_samples, q));
+            if (threads == kFewThreads) {
+                hipLaunchKernelGGL(bucket_sort_kernel<kFewThreads>, buckets, dim3(kFewThreads), lds, stream, a, n, (int)run, n_runs, samples, n_samples, q, b);
+            } else {
+                int32_t rc = allow_dynamic_lds<bucket_sort_kernel<kBucketThreads>>((size_t)3 * kBucketCap * sizeof(uint32_t));
+                if (rc != ATTS_OK) return rc;
+                hipLaunchKernelGGL(bucket_sort_kernel<kBucketThreads>, buckets, dim3(kBucketThreads), lds, stream, a, n, (int)run, n_runs, samples, n_samples, q, b);
+            }
             ATTS_LAUNCH_CHECK("bucket_sort_kernel");
             *sorted = b;
         }
