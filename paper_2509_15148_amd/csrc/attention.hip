@@ -263,6 +263,7 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attn_mfma_ke
         for (int v = 0; v < 16; ++v) acc_o[nb][v] = 0.f;
     float m_run = -1e30f;   // reference max (scaled, log2 domain), shared by the lane pair (l, l ^ 32)
     float l_run = 0.f;      // this lane's share of the running denominator
+    const float move_from = g ? 64.f : 6.f;     // how far above the reference a key of this lane may stand
 
     // Wave-uniform visibility of tile t for the wave's rows rw0 .. rw1:
     //   nothing visible: the tile starts after the last row, or lies in drafts before the wave's first row's
@@ -335,17 +336,16 @@ __global__ __launch_bounds__(64 * kWaves, 512 / (64 * kWaves)) void attn_mfma_ke
 #pragma unroll
         for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, acc_s[0][v]), acc_s[1][v]);    // one three-operand maximum each
         // Lazy rescaling: any reference value works in exp2(z - m) as long as it is the same for numerator and
-        // denominator, so the running reference only moves when a new maximum exceeds it by more than 2^6; the 64
-        // accumulator multiplies are skipped otherwise.  The new maximum is that of the keys in the lower lanes, or of
-        // those in the upper ones where it stands out by more than 2^64 (p stays <= 2^64: far inside the range of bf16 and fp32,
-        // sums of 2^31 keys included).  Measured: 1720 us over 40 query and 8 key heads, 2048 + 64 x 512 rows, against 1704 for the lower
-        // lanes alone, which gives NaN once a key of the upper ones stands out by more than 2^127.
-        const float2 pair = lane_pair(mx);                                                // scale > 0: the order is kept
-        const float upper = pair.y * scale_log2e;
-        mx = pair.x * scale_log2e;
-        mx = upper > fmaxf(mx, m_run) + 64.f ? upper : mx;
-        if (__builtin_amdgcn_ballot_w64(mx > m_run + 6.f) != 0) {
-            const float m_new = fmaxf(m_run, mx);
+        // denominator, so the running reference only moves when a key of the lower lanes exceeds it by more than 2^6 or one of the
+        // upper lanes by more than 2^64, which every lane sees from its own keys; the exchange and the 64 accumulator
+        // multiplies are skipped otherwise.  p stays <= 2^64: sums of 2^20 keys are finite up to values of 2^43.  40 query and 8 key
+        // heads, 2048 + 64 x 512 rows: 1682 us; 1714 with the exchange and the test of both halves in every tile, 1698 with the
+        // reference of the lower lanes alone, which gives NaN once a key of the upper ones stands out by more than 2^127.
+        const float own = mx * scale_log2e;                                               // scale > 0: the order is kept
+        if (__builtin_amdgcn_ballot_w64(own > m_run + move_from) != 0) {
+            const float2 pair = lane_pair(own);
+            float m_new = fmaxf(m_run, pair.x);
+            m_new = pair.y > m_new + 64.f ? pair.y : m_new;
             const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
             m_run = m_new;
             l_run *= alpha;

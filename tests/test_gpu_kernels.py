@@ -318,28 +318,71 @@ def test_attention_with_few_query_rows(P, K, T, nq, nkv):
     _attention_case(torch.bfloat16, (P, K, T, nq, nkv, 128), 1.5e-2)
 
 
-@pytest.mark.parametrize("nq,rows", [(1, 96), (1, 300), (64, 1100)])
+# (query heads, rows): 3 and 10 workgroups of 32 rows with the keys divided; 128 rows a workgroup; 256 rows a workgroup
+DOMINANT_SHAPES = [(1, 96), (1, 300), (32, 300), (8, 1100), (64, 1100)]
+
+
+def _uniform_queries(nq, rows, key_values, v):
+    """qkv for one key head: every query element 4, key j's elements key_values[j] (scores 45.25 times that), values v."""
+    hd = v.shape[1]
+    qkv = torch.zeros(rows, (nq + 2) * hd, dtype=torch.bfloat16)
+    qkv[:, :nq * hd] = 4.0
+    for j, x in key_values.items():
+        qkv[j, nq * hd:(nq + 1) * hd] = x
+    qkv[:, (nq + 1) * hd:] = v
+    return qkv.cuda()
+
+
+def _run_attention(qkv, nq, rows):
+    import paper_2509_15148_amd as A
+    out = torch.empty(rows, nq * 128, dtype=torch.bfloat16, device="cuda")
+    A.atts_attention_shared_prefix(qkv, out, rows - 40, 1, 40, nq, 1, 128, ws(A.atts_attention_workspace_bytes(torch.bfloat16, rows, 1, 128)))
+    torch.cuda.synchronize()
+    return out.cpu().double().view(rows, nq, 128)
+
+
+@pytest.mark.parametrize("nq,rows", DOMINANT_SHAPES)
 @pytest.mark.parametrize("key", [3, 8, 21, 30, 47, 61])
 def test_mfma_attention_one_dominant_key(nq, rows, key):
     """One key whose score stands 181 above all others (exp of the difference overflows fp32): every later row must return its
     value alone, whichever lane of the score tile holds it, and the rows before it the mean of theirs."""
-    import paper_2509_15148_amd as A
     announce("attention, dominant key", nq, rows, key)
-    P, T, hd = rows - 40, 40, 128
-    qkv = torch.zeros(rows, (nq + 2) * hd, dtype=torch.bfloat16)
-    qkv[:, :nq * hd] = 4.0
-    qkv[key, nq * hd:(nq + 1) * hd] = 4.0
-    g = torch.Generator().manual_seed(key)
-    v = torch.randn(rows, hd, generator=g).to(torch.bfloat16)
-    qkv[:, (nq + 1) * hd:] = v
-    qkv = qkv.cuda()
-    out = torch.empty(rows, nq * hd, dtype=torch.bfloat16, device="cuda")
-    A.atts_attention_shared_prefix(qkv, out, P, 1, T, nq, 1, hd, ws(A.atts_attention_workspace_bytes(torch.bfloat16, rows, 1, hd)))
-    torch.cuda.synchronize()
+    v = torch.randn(rows, 128, generator=torch.Generator().manual_seed(key)).to(torch.bfloat16)
+    got = _run_attention(_uniform_queries(nq, rows, {key: 4.0}, v), nq, rows)
     want = v.double().cumsum(0) / torch.arange(1, rows + 1)[:, None]
     want[key:] = v[key].double()
-    got = out.cpu().double().view(rows, nq, hd)
     assert (got - want[:, None]).abs().max().item() <= 1.5e-2
+
+
+@pytest.mark.parametrize("nq,rows", DOMINANT_SHAPES)
+@pytest.mark.parametrize("key", [5, 12, 70, 78])          # lower and upper half of the lanes, first and second tile
+@pytest.mark.parametrize("x", [0.09375, 0.6640625, 0.97265625, 0.984375, 1.109375])
+def test_mfma_attention_reference_left_behind(nq, rows, key, x):
+    """One key 4.2 (2^6.1), 30, 44.0 (2^63.5), 44.5 (2^64.3) and 50 above all others: where the softmax reference just stays
+    and just moves, for either half of the lanes.  Against the weighted mean in float64: the probabilities and the output are
+    rounded to bf16, 2^-8 of a value each."""
+    announce("attention, reference", nq, rows, key, x)
+    v = torch.randn(rows, 128, generator=torch.Generator().manual_seed(key)).to(torch.bfloat16)
+    got = _run_attention(_uniform_queries(nq, rows, {key: x}, v), nq, rows)
+    w = torch.ones(rows, dtype=torch.float64)
+    w[key] = math.exp(128 * 4 * x / math.sqrt(128))
+    want = (w[:, None] * v.double()).cumsum(0) / w.cumsum(0)[:, None]
+    assert (got - want[:, None]).abs().max().item() <= 2.0 ** -7 * v.double().abs().max().item()
+
+
+@pytest.mark.parametrize("nq,rows", DOMINANT_SHAPES)
+def test_mfma_attention_probabilities_stay_bounded(nq, rows):
+    """Values of 2^60 with a key of the lower lanes 2^5.9 and one of the upper lanes 2^69 above the keys of the tile before.  With
+    probabilities of at most 2^64 the sums are finite (2^124).  Tolerance as above."""
+    announce("attention, bounded", nq, rows)
+    v = torch.randn(rows, 128, generator=torch.Generator().manual_seed(nq)).clamp(-2, 2).to(torch.bfloat16)
+    x = {66: 0.09033203125, 75: 1.0546875}                 # scores 4.088 (2^5.9) and 47.73 (2^68.9)
+    got = _run_attention(_uniform_queries(nq, rows, x, v * 2.0 ** 60), nq, rows) / 2.0 ** 60
+    w = torch.ones(rows, dtype=torch.float64)
+    for j, c in x.items():
+        w[j] = math.exp(128 * 4 * c / math.sqrt(128))
+    want = (w[:, None] * v.double()).cumsum(0) / w.cumsum(0)[:, None]
+    assert (got - want[:, None]).abs().max().item() <= 2.0 ** -7 * v.double().abs().max().item()
 
 
 def _attention_case(dtype, shape, tol, offset=0):
