@@ -71,12 +71,13 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
     __syncthreads();
     const float inv = 1.f / sum;
     // Heads of 128 bytes, or 64 in 16 bits, whose rows start at 16 bytes: a lane takes a 16-byte piece, four or eight lanes a key's
-    // row, so that the wavefront's 16 or 8 groups walk the keys in fewer batches.  bf16, hd 64, 1224 rows: 67.8 -> 57.7 us, hd 32
-    // 36.8 -> 33.2; fp32, hd 32, 320 rows 7.1 -> 6.7.  Not for fewer bytes, where the sums over the groups outweigh it (bf16, hd 8:
-    // 5.6 against 7.1; fp32, hd 16: 28.8 and 29.2).
+    // row, so that the wavefront's 16 or 8 groups walk the keys in fewer batches (8 query and 2 key heads, 300 + 4 x 200 rows: bf16,
+    // hd 64 94.8 -> 82.1 us, hd 32 54.2 -> 49.5; fp32, hd 32 63.8 -> 62.2; 4 heads, 64 + 8 x 32 rows 9.7 -> 8.7, 6.9 -> 6.2, 7.2 -> 6.1).
+    // Not for fewer bytes, where the sums over the groups outweigh it (bf16, hd 8: 5.6 against 7.1; fp32, hd 16: 28.8 and 29.2), nor
+    // in bf16, hd 64, for fewer than 16 keys, which fill a quarter of a batch (8 heads, 8 + 8 x 4 rows 5.2 against 4.9).
     constexpr int kPiece = 16 / (int)sizeof(T);
     const int pieces = hd / kPiece;
-    if (hd % kPiece == 0 && (pieces == 8 || (pieces == 4 && sizeof(T) == 2)) &&
+    if (hd % kPiece == 0 && (pieces == 8 ? kPiece == 4 || n >= 16 : pieces == 4 && kPiece == 8) &&
         ((reinterpret_cast<uintptr_t>(vbase) | (uintptr_t)(ld * (int64_t)sizeof(T))) & 15) == 0) {
         const int groups = 64 / pieces, grp = lane / pieces, piece = lane % pieces;
         float acc[kPiece];
@@ -100,13 +101,31 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
                 }
             }
         }
+        T* const to = out + (int64_t)r * nq * hd + head * hd + piece * kPiece;
+        if constexpr (kPiece == 8) {
+            // every exchange halves the elements a lane still adds up, until each has one to store: adding all eight in all lanes
+            // outweighs the loop up to 44 keys (heads of 32: 170)
+            int o = pieces, first = 0;
 #pragma unroll
-        for (int e = 0; e < kPiece; ++e)
-            for (int o = pieces; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
-        if (grp == 0) {
-            T* to = out + (int64_t)r * nq * hd + head * hd + piece * kPiece;
+            for (int half = kPiece / 2; half > 0; half >>= 1, o <<= 1) {
+                const bool upper = lane & o;
 #pragma unroll
-            for (int e = 0; e < kPiece; ++e) to[e] = from_f32<T>(acc[e] * inv);
+                for (int e = 0; e < half; ++e) {
+                    const float other = __shfl_xor(upper ? acc[e] : acc[half + e], o);
+                    acc[e] = (upper ? acc[half + e] : acc[e]) + other;
+                }
+                first += upper ? half : 0;
+            }
+            for (; o < 64; o <<= 1) acc[0] += __shfl_xor(acc[0], o);
+            if (lane < pieces * kPiece) to[first] = from_f32<T>(acc[0] * inv);
+        } else {
+#pragma unroll
+            for (int e = 0; e < kPiece; ++e)
+                for (int o = pieces; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+            if (grp == 0) {
+#pragma unroll
+                for (int e = 0; e < kPiece; ++e) to[e] = from_f32<T>(acc[e] * inv);
+            }
         }
         return;
     }
