@@ -1229,10 +1229,13 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
 //       long direction (4096 scoring rows are 10.67 tiles of 384 in the other orientation) and the tile count drops (7B: 6336
 //       instead of 6534, 25 rounds instead of 26).  Rows that the caller has not padded (385 of 152,064 x 3584): 447 us
 //       against 825 with the general kernel.  Padded rows take the other orientation where the model's time for it is shorter by
-//       more than it leaves out: the epilogue that reduces across lanes, the less the longer K is, and the vocabulary matrix that
-//       a single row of tiles streams by alone.  Short passes with the head, other orientation and exchanged (model's
-//       ratio): 7B 300 rows 620 and 577 us (1.16), 1090 rows 1219 and 1167 (1.14), 800 rows 1141 and 961 (1.02); 32B 300 rows 845 and
-//       805 (1.15); 70B 300 rows 893 and 1000 (1.38), 1090 rows 2108 and 2186 (1.13), 800 rows 1920 and 1771 (1.12).
+//       more than it leaves out: the epilogue that reduces across lanes (the less the longer K is), and the vocabulary matrix that a
+//       single row of tiles, or a second launch for the last rows, streams by alone (lmhead_exchanged_ok).  Of 504 heads of 16 models
+//       (K 1024 to 16384, 129 to 3900 rows) timed both ways the rule takes none that is more than 0.3 % slower than the other way
+//       round.  Short passes with the head, other orientation and exchanged (model's ratio): one row of tiles 7B 300 rows 474 and 434 us
+//       (1.16), 32B 300 643 and 631 (1.15), 70B 300 698 and 815 (1.38), K 8192 with 152,064 entries 320 957 and 986 (1.15); second
+//       launch 70B 600 1225 and 1173 (1.14), K 16384 520 2391 and 2298 (1.14); whole rows 7B 1090 1063 and 1027 (1.14), 32B
+//       1425 and 1458 (1.14), 70B 1800 2980 and 3047 (1.10).
 //       Small vocabularies leave most of the chip idle, and a tile of 384 x 256 is then the longer chain: exchanged only where its
 //       1.43 (nearly no tile) to 1.69 us (256 tiles) a slab of 64 k elements and 3.5 us are less than the other kernel's time (first
 //       orientation 0.95 to 1.47 and 17, general kernel 0.82 and 15 up to a tile a compute unit, 0.95 to 1.23 and 17.5 up to
@@ -1274,7 +1277,8 @@ static bool lmhead_exchanged_ok(int32_t dtype, const GemmArgs& g) {
         const TilePlan first = direct_plan(EPI_LMHEAD, g);
         const double other = (double)(ceil_div(g.M, 256) * (g.N / 256));
         if (tiles <= 256 && first.rows == 256 && other <= 256) return light_us <= (0.95 + 8e-6 * other * other) * slabs + 17.0;
-        return lmhead_exchanged_plan(g).us <= (1.06 + 8.0 / slabs) * first.us;
+        const double alone = first.tail_rows != 0 ? 1.14 : (g.M <= first.rows ? 1.05 : 1.0);
+        return lmhead_exchanged_plan(g).us <= (0.98 + 12.0 / slabs) * alone * first.us;
     }
     if (use_small_tile(dtype, EPI_LMHEAD, g.M, g.N, g.Kd)) return false;
     const int64_t general = ceil_div(g.M, 128) * ceil_div(g.N, 128);
