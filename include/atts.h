@@ -280,7 +280,9 @@ typedef struct {
     int32_t kernel;                 /* ATTS_KERNEL_*                                                           */
     int32_t tile_rows;              /* rows of a tile of the aligned kernels, else 0                           */
     int32_t slices;                 /* slices the inner dimension is cut into over workgroups (1: not)         */
-    int32_t head_rows, tail_rows;   /* tail_rows != 0: the rows (exchanged operands: vocabulary entries) from head_rows on take a second launch with tiles of tail_rows; head_rows == 0: the last columns do, of all rows */
+    int32_t head_rows, tail_rows;   /* tail_rows != 0: the rows (exchanged operands: vocabulary entries) from head_rows on take a
+                                       second launch with tiles of tail_rows, or, head_rows == 0, the columns from head_cols on */
+    int32_t head_cols;
 } atts_gemm_route;
 
 typedef struct {

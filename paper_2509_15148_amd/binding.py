@@ -66,7 +66,7 @@ PASS_SCORE, PASS_SCORE_CACHED, PASS_CONTINUE = range(3)
 
 
 class GemmRoute(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "tile_rows", "slices", "head_rows", "tail_rows")]
+    _fields_ = [(n, ctypes.c_int32) for n in ("kernel", "tile_rows", "slices", "head_rows", "tail_rows", "head_cols")]
 
 
 class PassRoute(ctypes.Structure):

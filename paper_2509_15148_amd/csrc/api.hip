@@ -846,7 +846,7 @@ int32_t atts_model_check(const atts_model* m, void* hip_stream, int32_t* host_fl
 namespace {
 void show_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, atts_gemm_route* out) {
     const GemmRoute r = gemm_route(dtype, epi, g);
-    *out = atts_gemm_route{r.kernel, r.tile_rows, r.slices, r.head_rows, r.tail_rows};
+    *out = atts_gemm_route{r.kernel, r.tile_rows, r.slices, r.head_rows, r.tail_rows, r.head_cols};
 }
 }  // namespace
 

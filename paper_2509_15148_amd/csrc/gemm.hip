@@ -959,7 +959,7 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
         for (int rows : {384, 256}) {
             if (!tile_rows_allowed(rows, g)) continue;
             const int64_t tall = ceil_div(g.M, rows), full = tall * nt_n / kPlanCus, head = full * kPlanCus / tall;
-            if (full == 0 || head >= nt_n) continue;
+            if (full == 0 || head == 0 || head >= nt_n) continue;    // both launches have columns
             for (int tail : {256, 128}) {
                 if (tail >= rows || !tile_rows_allowed(tail, g)) continue;
                 const double us = (double)full * fast_tile_us(rows, false, slabs) +

@@ -132,13 +132,13 @@ def test_gemm_aligned_last_tile_rows_in_a_second_launch(shape, tail):
     assert np.allclose(c.cpu().numpy(), ref, rtol=1e-5, atol=2e-5 * math.sqrt(Kd))
 
 
-@pytest.mark.parametrize("shape,tile,tail", [((1280, 14336, 832), 256, 128), ((3072, 12544, 832), 384, 256)])
-def test_gemm_aligned_last_columns_in_a_second_launch(shape, tile, tail):
+@pytest.mark.parametrize("shape,tile,tail,seam", [((1280, 14336, 832), 256, 128, 51 * 256), ((3072, 12544, 832), 384, 256, 32 * 256)])
+def test_gemm_aligned_last_columns_in_a_second_launch(shape, tile, tail, seam):
     """Tall tiles over the first columns, lower ones over the last.  Every element against the float64 product."""
     import paper_2509_15148_amd as A
     M, N, Kd = shape
     route, _ = A.atts_gemm_routes(torch.bfloat16, M, N, Kd)
-    assert (route.kernel, route.tile_rows, route.head_rows, route.tail_rows) == (A.KERNEL_ALIGNED, tile, 0, tail)
+    assert (route.kernel, route.tile_rows, route.head_rows, route.tail_rows, route.head_cols) == (A.KERNEL_ALIGNED, tile, 0, tail, seam)
     announce("gemm last columns", shape)
     a, w = _rand((M, Kd), 31, torch.bfloat16), _rand((N, Kd), 32, torch.bfloat16)
     c = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")

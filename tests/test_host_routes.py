@@ -89,13 +89,29 @@ def test_lm_head_second_launch(rows, vocab, d, head, tail):
     assert (r.head_rows, r.tail_rows) == (head, tail)
 
 
-@pytest.mark.parametrize("name,rows,product,tile,tail", [
-    ("7b", 776, "gate_up", 384, 256), ("7b", 385, "gate_up", 256, 128), ("7b", 1500, "gate_up", 384, 128), ("7b", 4608, "gate_up", 384, 0),
-    ("70b", 4608, "down", 384, 256), ("7b", 8192, "o", 256, 0)])
-def test_last_columns_of_a_projection(name, rows, product, tile, tail):
+@pytest.mark.parametrize("name,rows,product,tile,tail,seam", [
+    ("7b", 776, "gate_up", 384, 256, 85 * 128), ("7b", 385, "gate_up", 256, 128, 128 * 128), ("7b", 1500, "gate_up", 384, 128, 128 * 128),
+    ("7b", 4608, "gate_up", 384, 0, 0), ("70b", 4608, "down", 384, 256, 21 * 256), ("7b", 8192, "o", 256, 0, 0)])
+def test_last_columns_of_a_projection(name, rows, product, tile, tail, seam):
     """Whole rounds of tall tiles over the first columns, lower ones over the last, where the last round would be partly filled."""
     r = getattr(A.atts_pass_routes(MODELS[name], A.PASS_SCORE, 4, 1, rows - 4), product)
-    assert (r.kernel, r.tile_rows, r.head_rows, r.tail_rows) == (A.KERNEL_ALIGNED, tile, 0, tail)
+    assert (r.kernel, r.tile_rows, r.head_rows, r.tail_rows, r.head_cols) == (A.KERNEL_ALIGNED, tile, 0, tail, seam)
+
+
+def test_second_launches_and_first_ones_have_work():
+    """A call in two launches is cut either by rows or by columns, inside them: neither launch is empty.  Shapes around whole rounds
+    of tiles, down to one column of tiles, long and short inner dimensions."""
+    cut = set()
+    bf16 = MODELS["7b"].torch_dtype
+    for K in (768, 4096, 28672):
+        for N in [256 * n for n in (1, 2, 3, 5, 8, 14, 21, 32, 55, 85, 112, 148, 257)]:
+            for M in [128 * m for m in (2, 3, 4, 6, 7, 9, 12, 18, 20, 36, 64, 90, 129, 258, 600, 771, 774, 1538)]:
+                for r in A.atts_gemm_routes(bf16, M, N, K):
+                    assert (r.head_rows != 0) + (r.head_cols != 0) == (r.tail_rows != 0), (M, N, K)
+                    assert 0 <= r.head_rows < (N if r.kernel == A.KERNEL_EXCHANGED else M) and 0 <= r.head_cols < N
+                    if r.tail_rows:
+                        cut.add((r.kernel, r.head_cols != 0))
+    assert cut == {(A.KERNEL_ALIGNED, False), (A.KERNEL_ALIGNED, True), (A.KERNEL_EXCHANGED, False)}
 
 
 @pytest.mark.parametrize("dtype,shape,small", [
