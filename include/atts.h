@@ -288,6 +288,8 @@ typedef struct {
 typedef struct {
     atts_gemm_route qkv, o, gate_up, down, lm_head;
     int32_t qkv_fused;              /* rotary embedding and transposed values in the projection's epilogue or finish */
+    int32_t rope_in_qkv;            /* small fp32 passes: rotary embedding, and from the second layer on the norm, in the projection */
+    int32_t norm_in_gate_up;        /* ... the feed-forward norm in the gate/up projection                     */
     size_t workspace_bytes;
 } atts_pass_route;
 

@@ -71,7 +71,7 @@ class GemmRoute(ctypes.Structure):
 
 class PassRoute(ctypes.Structure):
     _fields_ = [(n, GemmRoute) for n in ("qkv", "o", "gate_up", "down", "lm_head")] + \
-        [("qkv_fused", ctypes.c_int32), ("workspace_bytes", ctypes.c_size_t)]
+        [(n, ctypes.c_int32) for n in ("qkv_fused", "rope_in_qkv", "norm_in_gate_up")] + [("workspace_bytes", ctypes.c_size_t)]
 
 
 def load_library(path: str = LIB_PATH) -> ctypes.CDLL:

@@ -140,6 +140,18 @@ SplitPlan split_plan(const atts_model_desc& d, int64_t M, const SumsRoom& room) 
                      slices(d.d_model, d.d_ffn, room.down)};
 }
 
+// Passes that ride in the small products of an fp32 pass of M rows: the rotation, and from the second layer on the norm, in the
+// QKV projection; the feed-forward norm in the gate/up projection.
+struct SmallFusion {
+    bool qkv, gate_up;
+};
+SmallFusion small_fusion(const atts_model_desc& d, int64_t M) {
+    if (d.dtype != ATTS_DTYPE_F32) return SmallFusion{false, false};
+    const int32_t qkv_out = (d.n_q_heads + 2 * d.n_kv_heads) * d.head_dim;
+    auto small = [&](GemmEpilogue epi, int32_t N) { return gemm_route(d.dtype, epi, gemm_shape(d, M, N, d.d_model)).kernel == ATTS_KERNEL_SMALL; };
+    return SmallFusion{small_rope_fusable(d.head_dim) && small(EPI_STORE_ACT, qkv_out), small(EPI_SWIGLU, d.d_ffn)};
+}
+
 Workspace carve(const atts_model_desc& d, ScoreShape s) {
     const size_t es = dtype_size(d.dtype);
     const size_t R = (size_t)s.R(), B = (size_t)s.B();
@@ -347,14 +359,10 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
                                    fuse_rope ? vt : nullptr, (int64_t)kvd, ws.ldv, m->err_flag, st));
     }
     char* xn0 = xn + (size_t)row0 * d.d_model * es;
-    // a small fp32 model: the norms ride in the projections that read them, the rotation in the QKV projection
-    const bool fp32 = d.dtype == ATTS_DTYPE_F32;
-    const bool rope_in_small = fp32 && vt == nullptr && d.head_dim <= 32 && (d.head_dim & (d.head_dim - 1)) == 0 &&
-                               gemm_route(d.dtype, EPI_STORE_ACT, gemm_shape(d, M, qkv_out, d.d_model)).kernel == ATTS_KERNEL_SMALL;
-    const bool norm_in_gate_up = fp32 && gemm_route(d.dtype, EPI_SWIGLU, gemm_shape(d, M, d.d_ffn, d.d_model)).kernel == ATTS_KERNEL_SMALL;
+    const SmallFusion small = small_fusion(d, M);
     bool xn_ready = true;       // xn already holds the attention norm of this layer (written with the embedding or the previous residual update)
     for (int l = 0; l < d.n_layers; ++l) {
-        const bool norm_in_qkv = !xn_ready && rope_in_small;
+        const bool norm_in_qkv = !xn_ready && small.qkv;
         if (!xn_ready && !norm_in_qkv) {
             StageTimer t_(ATTS_STAGE_NORM, st);
             ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->attn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
@@ -385,7 +393,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
             g.n_rot_heads = d.n_q_heads + d.n_kv_heads;
             StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
             ATTS_TRY(launch_gemm(d.dtype, EPI_QKV_ROPE, g, st));
-        } else if (rope_in_small) {
+        } else if (small.qkv) {
             g.rope = rope + (size_t)row0 * (d.head_dim / 2); g.n_rot_heads = d.n_q_heads + d.n_kv_heads; g.head_dim = d.head_dim;
             if (norm_in_qkv) { g.a = h0; g.norm_gain = m->attn_norm[l]; g.norm_eps = d.rms_eps; }
             StageTimer t_(ATTS_STAGE_GEMM_QKV, st);
@@ -449,7 +457,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
                 StageTimer t_(ATTS_STAGE_GEMM_O, st);
                 ATTS_TRY(launch_gemm(d.dtype, EPI_RESID_F32, g, st));
             }
-            if (!norm_in_gate_up) {
+            if (!small.gate_up) {
                 StageTimer t_(ATTS_STAGE_NORM, st);
                 ATTS_TRY(launch_rmsnorm(d.dtype, h0, m->ffn_norm[l], d.rms_eps, M, d.d_model, xn0, st));
             }
@@ -460,7 +468,7 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
         g.lda = d.d_model; g.ldw = d.d_model; g.ldc = d.d_ffn; g.a_rows_padded = padded;
         {
             StageTimer t_(ATTS_STAGE_GEMM_GATE_UP, st);
-            if (norm_in_gate_up) {
+            if (small.gate_up) {
                 g.a = h0; g.norm_gain = m->ffn_norm[l]; g.norm_eps = d.rms_eps;
                 ATTS_TRY(launch_gemm_small_fused(EPI_SWIGLU, g, st));
             } else {
@@ -885,6 +893,9 @@ int32_t atts_pass_routes(const atts_model_desc* desc, int32_t pass, int32_t P, i
         // as forward_tree: only the fused form of the projection is split
         out->qkv_fused = attention_uses_vt(d.dtype, d.head_dim) && row0 % 4 == 0 && qkv_rope_fusable(d.dtype, M, qkv_out, d.d_model, d.head_dim, pads_rows(d));
         if (!out->qkv_fused) plan.qkv = 1;
+        const SmallFusion small = small_fusion(d, M);
+        out->rope_in_qkv = small.qkv;
+        out->norm_in_gate_up = small.gate_up;
         out->workspace_bytes = ws.total;
     }
     const GemmEpilogue qkv_direct = pass == ATTS_PASS_CONTINUE ? EPI_STORE_F32 : (out->qkv_fused ? EPI_QKV_ROPE : EPI_STORE_ACT);

@@ -173,9 +173,10 @@ size_t skinny_partial_bound(int32_t M, int32_t N, int32_t Kd);    // bytes of it
 // The kernel for products of few tiles (small.hip), any shape; launch_gemm hands it the calls that leave the chip idle otherwise.
 int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
-// The same for an fp32 model with passes around the product fused in (no transposed values): EPI_QKV_ROPE for heads of a power
-// of two of at most 32 columns, with or without the norm, and EPI_SWIGLU with the norm.  For calls whose plain form
-// (EPI_STORE_ACT, EPI_SWIGLU) gemm_route gives to the small kernel.
+// The same for an fp32 model with passes around the product fused in (no transposed values): EPI_QKV_ROPE for the heads of
+// small_rope_fusable, with or without the norm, and EPI_SWIGLU with the norm.  For calls whose plain form (EPI_STORE_ACT,
+// EPI_SWIGLU) gemm_route gives to the small kernel; others are refused.
+inline bool small_rope_fusable(int32_t head_dim) { return head_dim >= 2 && head_dim <= 32 && (head_dim & (head_dim - 1)) == 0; }
 int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 // true if the EPI_QKV_ROPE epilogue can serve this QKV projection (else: EPI_STORE_ACT + launch_rope_split)
 bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t head_dim, bool a_rows_padded);

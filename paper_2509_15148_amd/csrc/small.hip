@@ -239,6 +239,12 @@ int32_t launch_small_t(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) 
 }  // namespace
 
 int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream) {
+    if ((g.Kd % 4) || (g.lda % 4) || (g.ldw % 4) || (((uintptr_t)g.a | (uintptr_t)g.w | (uintptr_t)g.norm_gain) & 15))
+        return fail(ATTS_ERR_SHAPE, "gemm (small product): rows and gain must be multiples of 16 bytes at 16-byte addresses");
+    if (gemm_route(ATTS_DTYPE_F32, epi == EPI_QKV_ROPE ? EPI_STORE_ACT : epi, g).kernel != ATTS_KERNEL_SMALL)
+        return fail(ATTS_ERR_SHAPE, "gemm (small product): %d x %d x %d is not one", g.M, g.N, g.Kd);
+    if (epi == EPI_QKV_ROPE && (!small_rope_fusable(g.head_dim) || !g.rope || g.N % g.head_dim || g.n_rot_heads < 1 || g.n_rot_heads * g.head_dim > g.N))
+        return fail(ATTS_ERR_SHAPE, "gemm (small product): the rotation of %d heads of %d columns does not fit", g.n_rot_heads, g.head_dim);
     if (epi == EPI_QKV_ROPE) return g.norm_gain ? launch_small_epi<float, EPI_QKV_ROPE, true>(g, stream) : launch_small_epi<float, EPI_QKV_ROPE>(g, stream);
     if (epi == EPI_SWIGLU && g.norm_gain) return launch_small_epi<float, EPI_SWIGLU, true>(g, stream);
     return fail(ATTS_ERR_INVALID_ARG, "gemm (small product): epilogue %d is not fused", (int)epi);

@@ -94,18 +94,23 @@ def test_row_counts_between_tiles(P, K, T):
 ALIGNED, EXCHANGED = 4, 5      # atts.h: ATTS_KERNEL_*
 
 
-@pytest.mark.parametrize("cfg,P,K,T", [
-    (ModelConfig(3, 64, 3, 1, 4, 36, 100, "fp32"), 5, 2, 3),        # heads of 4 columns, 20 of a tile's 32
-    (ModelConfig(2, 100, 5, 1, 8, 44, 130, "fp32"), 33, 3, 10),     # inner dimension of 100: the last step of K half filled
-    (ModelConfig(2, 36, 3, 3, 16, 260, 70, "fp32"), 31, 1, 2),      # 33 rows: one past a tile
-    (ModelConfig(2, 128, 4, 2, 32, 512, 1024, "fp32"), 1, 1, 31),   # 32 rows
-    (ModelConfig(2, 132, 2, 1, 64, 72, 90, "fp32"), 17, 2, 9),      # heads of two tiles: the rotation stays a pass of its own
-    (ModelConfig(2, 60, 5, 5, 12, 40, 100, "fp32"), 9, 2, 7),       # ... and heads that are no power of two
+@pytest.mark.parametrize("cfg,P,K,T,rope", [
+    (ModelConfig(3, 64, 3, 1, 4, 36, 100, "fp32"), 5, 2, 3, 1),     # heads of 4 columns, 20 of a tile's 32
+    (ModelConfig(2, 100, 5, 1, 8, 44, 130, "fp32"), 33, 3, 10, 1),  # inner dimension of 100: the last step of K half filled
+    (ModelConfig(2, 36, 3, 3, 16, 260, 70, "fp32"), 31, 1, 2, 1),   # 33 rows: one past a tile
+    (ModelConfig(2, 128, 4, 2, 32, 512, 1024, "fp32"), 1, 1, 31, 1),    # 32 rows
+    (ModelConfig(2, 132, 2, 1, 64, 72, 90, "fp32"), 17, 2, 9, 0),   # heads of two tiles: the rotation stays a pass of its own
+    (ModelConfig(2, 60, 5, 5, 12, 40, 100, "fp32"), 9, 2, 7, 0),    # ... and heads that are no power of two
 ])
-def test_small_fp32_models_norms_and_rotation_in_the_products(cfg, P, K, T):
+def test_small_fp32_models_norms_and_rotation_in_the_products(cfg, P, K, T, rope):
     """Norms inside the projections that read them and rotary embedding inside the QKV projection, at the edges of their tiles.
-    Cold scoring, and through a prefix handle (rows that do not start at 0); residual stream scaled to rows of unlike size."""
+    Cold scoring, and through a prefix handle (rows that do not start at 0); residual stream scaled to rows of unlike size.  The routes
+    say which passes ride along, and the launches of the stages bear it out."""
     import paper_2509_15148_amd as A
+    L = cfg.n_layers
+    for kind in (A.PASS_SCORE, A.PASS_SCORE_CACHED):
+        r = A.atts_pass_routes(cfg, kind, P, K, T)
+        assert (r.rope_in_qkv, r.norm_in_gate_up, r.qkv_fused) == (rope, 1, 0)
     announce("small fp32", cfg, P, K, T)
     w, prefix, drafts = _case(cfg, P, K, T, seed=7)
     scale = torch.logspace(-3, 3, cfg.vocab, device="cuda")[:, None]
@@ -113,7 +118,11 @@ def test_small_fp32_models_norms_and_rotation_in_the_products(cfg, P, K, T):
     ref, _ = O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)
     model = A.Model(cfg, w)
     lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+    A.atts_profile_enable(True)
     A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, dirty_ws(A.atts_workspace_bytes(model, P, K, T)))
+    launches = {n: A.atts_profile_read(A.STAGES.index(n))[1] for n in ("norm", "rope")}
+    A.atts_profile_enable(False)
+    assert launches == ({"norm": 0, "rope": 0} if rope else {"norm": L - 1, "rope": L})
     assert np.abs(lp.cpu().numpy() - ref).max() <= TOL["fp32"]
     pre = A.Prefix(model, P)
     A.atts_prefix_extend(pre, dev(prefix), dirty_ws(A.atts_prefix_extend_workspace_bytes(pre, P)))

@@ -114,6 +114,17 @@ def test_second_launches_and_first_ones_have_work():
     assert cut == {(A.KERNEL_ALIGNED, False), (A.KERNEL_ALIGNED, True), (A.KERNEL_EXCHANGED, False)}
 
 
+@pytest.mark.parametrize("cfg,rows,rope,norm", [
+    (MODELS["tiny"], 320, 1, 1), (MODELS["7b"], 320, 0, 0),
+    (ModelConfig(2, 2048, 64, 16, 32, 8192, 8000, "fp32"), 16, 1, 1), (ModelConfig(2, 2048, 64, 16, 32, 8192, 8000, "fp32"), 1500, 0, 0),
+    (ModelConfig(2, 512, 8, 8, 64, 1536, 4000, "fp32"), 100, 0, 1), (ModelConfig(2, 60, 5, 5, 12, 40, 100, "fp32"), 20, 0, 1)])
+def test_passes_inside_small_products(cfg, rows, rope, norm):
+    """fp32 passes whose products are small: rotation (heads of a power of two of at most 32 columns) and norms ride in them."""
+    r = A.atts_pass_routes(cfg, A.PASS_SCORE, 4, 1, rows - 4)
+    assert (r.rope_in_qkv, r.norm_in_gate_up) == (rope, norm)
+    assert A.atts_pass_routes(cfg, A.PASS_CONTINUE, 4, 4, rows - 4).norm_in_gate_up == 0
+
+
 @pytest.mark.parametrize("dtype,shape,small", [
     ("fp32", (1024, 2048, 256), True), ("fp32", (2000, 1000, 1024), False), ("fp32", (1000, 1900, 2048), True), ("fp32", (300, 12000, 2048), False),
     ("fp32", (129, 16600, 8192), True), ("fp32", (260, 11000, 512), True), ("fp32", (260, 11000, 2048), False),
