@@ -195,6 +195,25 @@ def test_classification_workgroup_sizes(n, m):
     assert np.array_equal(cls, O.classify(want, O.reject_ranks([0.05, 0.2], n)))
 
 
+@pytest.mark.parametrize("n", [9000, 300000, 9000000])
+@pytest.mark.parametrize("m", [1, 2, 3, 4, 5, 6, 65, 257, 258])
+def test_classification_of_a_few_scores(n, m):
+    """Quads of lanes with work for one, two or more of them, in every wavefront and in the last one only; one to three index
+    levels below the staged one.  The first scores are in turn a NaN and below all of the set: lanes without work ahead of others."""
+    import paper_2509_15148_amd as A
+    announce("classify few", n, m)
+    cal = np.round(lognormal_scores(n, seed=n % 1000), 4)
+    c = A.Calib(n)
+    A.atts_calibrate_online(c, dev(cal))
+    for first in ([], [np.nan], [-1.0, np.nan]):
+        test = np.round(lognormal_scores(m, seed=m), 4)
+        test[:len(first)] = first[:m]
+        ranks, cls, _, _ = _classify(A, c, test, [0.05, 0.2])
+        want = O.rank_counts_sorted(cal.astype(np.float64), test)
+        assert np.array_equal(ranks.astype(np.int64), want)
+        assert np.array_equal(cls, O.classify(want, O.reject_ranks([0.05, 0.2], n)))
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
