@@ -930,7 +930,13 @@ struct TilePlan {
 // gate/up projection: 444 tiles of 384 rows are two rounds; 85 columns of them and 63 of 256-row tiles, 252, are one of each).
 // Gate/up, us: 7B 776 rows 222 -> 209, 1300 330 -> 298, 1500 353 -> 310, 4096 846 -> 823; 32B 900 500 -> 456, 1024 498 -> 467,
 // 4096 1737 -> 1673; 70B 1024 765 -> 722, 8192 5543 -> 5419; 70B 4608 rows, O 541 -> 490 and down 1844 -> 1598.  The residual epilogue,
-// whose tiles wait for their old values, wants more than the model's 3 % (7B 8192 rows: O 199 -> 205 at 0.97).
+// whose tiles wait for their old values, wants more than the model's 3 % (7B 8192 rows: O 199 -> 205 at 0.97).  384-row tiles with
+// the rest in 128-row ones are up to 5 % slower than the model has them, so they want more: 5 % against 256-row tiles, whose partly
+// filled last round is faster than its model, or rows cut already, and 7 % where the 128-row tiles take two rounds (us without and
+// with them, model's ratio): against 256 rows 7B gate/up 644 - 740 rows 171 - 176 and 179 - 183 (0.976), 7B down 8068 - 8804 894 - 911
+// and 901 - 920 (0.956), 32B down 5764 - 6372 1314 - 1393 and 1319 - 1347 (0.954), 70B gate/up 2436 1752 and 1762 (0.953), 32B down
+// 15748 3390 and 3179 (0.918); two rounds 70B gate/up 1124 788 - 855 and 787 - 869 on two boxes (0.959), 70B 4868 O 545 and 551
+// (0.938), down 1912 and 1840 (0.925).
 TilePlan direct_plan(int epi, const GemmArgs& g) {
     const int n_out = epi == EPI_SWIGLU ? 128 : 256;
     const int64_t nt_n = g.N / n_out, slabs = g.Kd / kWideBK;
@@ -962,9 +968,12 @@ TilePlan direct_plan(int epi, const GemmArgs& g) {
             if (full == 0 || head == 0 || head >= nt_n) continue;    // both launches have columns
             for (int tail : {256, 128}) {
                 if (tail >= rows || !tile_rows_allowed(tail, g)) continue;
+                const int64_t tail_tiles = ceil_div(g.M, tail) * (nt_n - head);
                 const double us = (double)full * fast_tile_us(rows, false, slabs) +
-                                  (double)ceil_div(ceil_div(g.M, tail) * (nt_n - head), kPlanCus) * fast_tile_us(tail, false, slabs) + 4.0;
-                if (us < best.us * (epi == EPI_SWIGLU ? 0.985 : 0.96)) best = TilePlan{rows, 1, us, 0, tail, (int)head * n_out};
+                                  (double)ceil_div(tail_tiles, kPlanCus) * fast_tile_us(tail, false, slabs) + 4.0;
+                double need = epi == EPI_SWIGLU ? 0.985 : 0.96;
+                if (rows == 384 && tail == 128) need = best.rows == 256 || best.head_m != 0 ? 0.95 : (tail_tiles > kPlanCus ? 0.93 : need);
+                if (us < best.us * need) best = TilePlan{rows, 1, us, 0, tail, (int)head * n_out};
             }
         }
     return best;

@@ -91,7 +91,10 @@ def test_lm_head_second_launch(rows, vocab, d, head, tail):
 
 @pytest.mark.parametrize("name,rows,product,tile,tail,seam", [
     ("7b", 776, "gate_up", 384, 256, 85 * 128), ("7b", 385, "gate_up", 256, 128, 128 * 128), ("7b", 1500, "gate_up", 384, 128, 128 * 128),
-    ("7b", 4608, "gate_up", 384, 0, 0), ("70b", 4608, "down", 384, 256, 21 * 256), ("7b", 8192, "o", 256, 0, 0)])
+    ("7b", 4608, "gate_up", 384, 0, 0), ("70b", 4608, "down", 384, 256, 21 * 256), ("7b", 8192, "o", 256, 0, 0),
+    # 384-row tiles and 128-row ones for the rest: not where the model has them only little faster
+    ("7b", 700, "gate_up", 256, 0, 0), ("7b", 8192, "down", 256, 0, 0), ("70b", 1100, "gate_up", 384, 0, 0), ("70b", 4900, "o", 384, 0, 0),
+    ("32b", 15800, "down", 384, 128, 18 * 256), ("70b", 4900, "down", 384, 128, 19 * 256)])
 def test_last_columns_of_a_projection(name, rows, product, tile, tail, seam):
     """Whole rounds of tall tiles over the first columns, lower ones over the last, where the last round would be partly filled."""
     r = getattr(A.atts_pass_routes(MODELS[name], A.PASS_SCORE, 4, 1, rows - 4), product)
