@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # (FETCH_SIZE, then WRITE_SIZE), each scaled by what the same counter reads for a plain device copy of known
 # size (--traffic-probe); see profiles/traffic_gemm_gate_up_7b.txt.  Valid only for the kernel source it was
 # taken with: reported as null when the hash of csrc/gemm.hip differs.
-MEASURED_TRAFFIC = {"gemm_sha256": "bc6282a3bf4d69d0dda49f9c33a4aecbac0bd1a5af1515aaf475a294824bda10",
+MEASURED_TRAFFIC = {"gemm_sha256": "22eceb798b52fe624534db6e3dcbb0afd8e6fe30555c29ea11fbd8316b163bc7",
                     "workload": "7b", "bytes_per_launch": 1.753e9}
 
 

@@ -544,7 +544,8 @@ int32_t atts_calib_create(int64_t capacity, atts_calib** out) {
     c->n = 0;
     c->cur = 0;
     // Every array is rounded up to whole 128-byte lines plus one: the index search reads whole lines (entries
-    // past the fill are masked, not avoided).  Sorted runs are padded to whole chunks only in LDS.
+    // past the fill are masked, not avoided), and the sort writes a batch's last run padded to 16 keys and reads the padding, in
+    // `runs` and `batch`.
     uint32_t** bufs[5 + 2 * kIndexLevels] = {&c->keys[0], &c->keys[1], &c->runs, &c->batch, &c->sort_scratch};
     int64_t sizes[5 + 2 * kIndexLevels];
     for (int i = 0; i < 4; ++i) sizes[i] = capacity;
@@ -687,7 +688,7 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
     // Enough workgroups to fill the chip, few enough that staging the top level stays a small part of the work.  A search is a
     // chain of memory latencies, so many scores take workgroups of 512 threads: the staged 32 KB leave room for five workgroups on
     // a CU, which are 20 wavefronts of 32 with 256 threads.  With both changes (quad_rounds) 2^24 scores against 2^28 keys take
-    // 713 us for 770 (7 TB/s of lines from beyond the L2: bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
+    // 713 us for 770 (5.0 GB of lines from beyond the L2 by the counters: 7 TB/s, bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
     // 153 for 174, 2^19 against 2^23 20 for 27; few scores stay spread over more CUs.
     const bool large = M >= (int64_t)256 * 2048;
     const int threads = large ? 512 : 256;
