@@ -22,6 +22,7 @@
 
 #include <math.h>
 #include <new>
+#include <type_traits>
 
 constexpr int kIndexLevels = 4;
 constexpr int kFanBits = 5;                 // 32 keys per index node (one 128-byte line)
@@ -425,56 +426,87 @@ struct ConditionalLevels {
     int32_t n_alpha;
 };
 
-// The work of an input is a few hundred instructions; what takes the time is its chain of loads (offsets, then scores).  So
-// the first kHeld blocks of calibration scores and the first candidates are requested together as soon as the offsets are
-// there, and the calibration keys stay in registers for every block of candidates.  4096 inputs of about 64 scores and 64
-// candidates: 15.4 -> 10.0 us; 8192 of about 400 and 100: 78 -> 60.
+// (rank + 1) / (N + 1) as the binary64 quotient rounded once to fp32.  Whole numbers below 2^24 are exact in fp32 and its division
+// is correctly rounded; the binary64 quotient has more than 2 x 24 + 2 bits, so rounding through it gives the same bits, and
+// the fp32 sequence takes a fraction of the binary64 one.
+__device__ __forceinline__ float p_value(int64_t c1, int64_t n1) {
+    if (n1 < ((int64_t)1 << 24)) return (float)(int32_t)c1 / (float)(int32_t)n1;
+    return (float)((double)c1 / (double)n1);
+}
+
+// The work of an input is a few hundred instructions; what takes the time is its chain of loads (offsets, then scores), so both
+// offset pairs are requested at once, then up to kCondHeld blocks of calibration scores and the first candidates.  The
+// calibration scores go to the wavefront's own LDS and come back four to a read, the same for every lane, and are compared as
+// they are (an IEEE comparison, sub-normals kept by the kernel's float mode, is what the rank counts): two vector instructions a
+// pair, where a key passing by through a lane read made three, and no conversions.  What bounds it: the chain of loads, and from
+// about 200 scores on those two instructions.  8192 inputs of about 400 and 100 scores 58.8 -> 32.2 us, of 200 and 32 17.2 -> 10.6;
+// 4096 of 64 and 64 9.1 -> 7.5, where the host side of a call begins to bound it.
+constexpr int kCondHeld = 8;                                     // blocks of 64 calibration scores a wavefront holds
 __global__ __launch_bounds__(256) void conditional_kernel(const float* __restrict__ cal, const int64_t* __restrict__ cal_off,
                                                           const float* __restrict__ test, const int64_t* __restrict__ test_off,
-                                                          int64_t n_inputs, ConditionalLevels lv, int32_t* __restrict__ ranks,
-                                                          float* __restrict__ pvalues, uint8_t* __restrict__ classes) {
-    constexpr int kHeld = 4;
-    const int lane = threadIdx.x & 63;
-    const int64_t x = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    if (x >= n_inputs) return;                                   // whole wavefronts leave together
-    const int64_t c0 = cal_off[x], c1 = cal_off[x + 1], t0 = test_off[x], t1 = test_off[x + 1];
+                                                          int64_t n_inputs, int32_t* __restrict__ ranks, float* __restrict__ pvalues,
+                                                          uint8_t* __restrict__ classes, ConditionalLevels lv) {
+    constexpr int kChunk = 64 * kCondHeld;
+    __shared__ __attribute__((aligned(16))) float lds[4][kChunk];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t x = (int64_t)blockIdx.x * 4 + wave, xl = min(x, n_inputs - 1);
+    const int64_t c0 = cal_off[xl], c1 = cal_off[xl + 1], t0 = test_off[xl], t1 = test_off[xl + 1];
+    // everything the wavefront reads as scalars is requested here, not one piece behind each branch
+    asm volatile("" ::"s"(c0), "s"(c1), "s"(t0), "s"(t1), "s"(cal), "s"(test), "s"(ranks), "s"(pvalues), "s"(classes), "s"(lv.n_alpha));
     const int64_t m = max((int64_t)0, c1 - c0), k = max((int64_t)0, t1 - t0);
-    if (k == 0) return;
-    float held_score[kHeld];
+    if (x >= n_inputs || k == 0) return;                         // whole wavefronts leave together
+    float* const set = lds[wave];
+    const float none = __uint_as_float(0x7FC00000u);             // an absent score: never >= anything
+    // calibration scores [at, at + kChunk) into LDS, whole blocks
+    auto load_blocks = [&](const float* p, int here, auto count) __attribute__((always_inline)) {
+        constexpr int kBlocks = decltype(count)::value;
+        float f[kBlocks];
 #pragma unroll
-    for (int h = 0; h < kHeld; ++h) held_score[h] = 64 * h + lane < m ? cal[c0 + 64 * h + lane] : __uint_as_float(0x7FC00000u);
+        for (int h = 0; h < kBlocks; ++h) f[h] = 64 * h + lane < here ? p[64 * h + lane] : none;
+#pragma unroll
+        for (int h = 0; h < kBlocks; ++h) set[64 * h + lane] = f[h];
+    };
+    auto load_chunk = [&](int64_t at) __attribute__((always_inline)) {
+        const int here = (int)min(m - at, (int64_t)kChunk);
+        if (here <= 128) load_blocks(cal + c0 + at, here, std::integral_constant<int, 2>{});
+        else load_blocks(cal + c0 + at, here, std::integral_constant<int, kCondHeld>{});
+    };
     float s = lane < k ? test[t0 + lane] : 0.f;
-    uint32_t held[kHeld];                                        // an absent score is key 0 (NaN): it never counts
-#pragma unroll
-    for (int h = 0; h < kHeld; ++h) held[h] = score_to_key(held_score[h]);
+    if (m > 0) load_chunk(0);
     const double n1 = (double)(m + 1);
-    const int n_blocks = (int)((m + 63) >> 6);
     for (int64_t tb = 0; tb < k; tb += 64) {
         const float next = tb + 64 + lane < k ? test[t0 + tb + 64 + lane] : 0.f;     // the next block's, in flight meanwhile
-        const uint32_t xk = max(score_to_key(s), 1u);            // a NaN candidate's key is 0: its count is dropped below
         int64_t c = 0;
-#pragma unroll 1
-        for (int q = 0; q < n_blocks; ++q) {                     // one copy of the steps: every launch fetches its code cold
-            uint32_t mine = held[0];
-#pragma unroll
-            for (int h = 1; h < kHeld; ++h) mine = q == h ? held[h] : mine;
-            const int64_t at = (int64_t)64 * q;
-            if (q >= kHeld) mine = at + lane < m ? score_to_key(cal[c0 + at + lane]) : 0u;
-            const int nb = (int)min((int64_t)64, m - at);
+        for (int64_t at = 0; at < m; at += kChunk) {
+            if (m > kChunk && (at > 0 || tb > 0)) {              // every lane has read the chunk before: one wavefront, in order
+                __builtin_amdgcn_wave_barrier();
+                load_chunk(at);
+            }
+            __builtin_amdgcn_wave_barrier();
+            const int pieces = (int)((min(m - at, (int64_t)kChunk) + 15) >> 4);
             int cnt = 0;
 #pragma unroll 1
-            for (int j0 = 0; j0 < nb; j0 += 16)                  // in sixteens: a block is often partly filled (64 at once: 11.3 us)
+            for (int j = 0; j < pieces; ++j) {                   // in sixteens: a block is often partly filled
+                float4 q[4];
 #pragma unroll
-                for (int j = 0; j < 16; ++j)                     // lane j's key passes by through a scalar register
-                    cnt += (uint32_t)__builtin_amdgcn_readlane((int)mine, j0 + j) >= xk ? 1 : 0;
-            c += cnt;
+                for (int e = 0; e < 4; ++e) q[e] = reinterpret_cast<const float4*>(set)[4 * j + e];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float y[4] = {q[e].x, q[e].y, q[e].z, q[e].w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        cnt += y[i] >= s ? 1 : 0;
+                        asm volatile("" : "+v"(cnt));            // added one by one, each as a comparison's carry
+                    }
+                }
+            }
+            c += cnt;                                            // a NaN candidate counts nothing
         }
         if (tb + lane < k) {
-            if (score_is_nan(s)) c = 0;
             const int64_t t = t0 + tb + lane;
             const double c1p = (double)(c + 1);
             ranks[t] = (int32_t)c;
-            if (pvalues) pvalues[t] = (float)(c1p / n1);
+            if (pvalues) pvalues[t] = p_value(c + 1, m + 1);
             int cls = 0;
             for (int l = 0; l < lv.n_alpha; ++l) cls += c1p <= floor(lv.alpha[l] * n1) ? 1 : 0;     // whole numbers below 2^53
             classes[t] = (uint8_t)cls;
@@ -731,7 +763,7 @@ int32_t atts_classify_conditional(const float* cal_scores, const int64_t* cal_of
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     StageTimer t_(ATTS_STAGE_CLASSIFY, stream);
     hipLaunchKernelGGL(conditional_kernel, dim3((unsigned)ceil_div(n_inputs, 4)), dim3(256), 0, stream, cal_scores, cal_offsets,
-                       test_scores, test_offsets, n_inputs, lv, ranks, pvalues, classes);
+                       test_scores, test_offsets, n_inputs, ranks, pvalues, classes, lv);
     ATTS_LAUNCH_CHECK("conditional_kernel");
     return ATTS_OK;
 }

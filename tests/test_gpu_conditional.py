@@ -88,6 +88,23 @@ def test_set_sizes_around_the_held_blocks():
         _check(A, [scores(m) for m in m_sizes], [scores(k) for k in k_sizes], alphas)
 
 
+@pytest.mark.parametrize("m_sizes", [[1, 127, 128, 129, 130], [511, 512, 513, 528, 1024, 1025], [640, 3, 0, 2048]])
+def test_set_sizes_around_the_blocks_in_lds(m_sizes):
+    """Calibration sets at the edges of the two and the eight blocks that are loaded together and of a second load, several blocks of
+    candidates each; sub-normal scores of both signs, zeros, infinities and NaN are compared as they are."""
+    import paper_2509_15148_amd as A
+    announce("conditional blocks in LDS", m_sizes)
+    rng = np.random.default_rng(len(m_sizes))
+    special = np.array([np.nan, np.inf, -np.inf, -0.0, 0.0, 1e-45, -1e-45, 3e-45, 1e-38], np.float32)
+
+    def scores(n):
+        v = np.concatenate([special, rng.choice(np.arange(0, 40), size=n).astype(np.float32) * np.float32(1e-45),
+                            np.round(rng.lognormal(size=n), 1).astype(np.float32)])
+        return rng.permutation(v)[:n]
+    k_sizes = [64, 129, 65, 1, 200, 63][:len(m_sizes)]
+    _check(A, [scores(m) for m in m_sizes], [scores(k) for k in k_sizes], [0.05, 0.2, 0.6])
+
+
 def test_many_small_inputs():
     """4096 inputs x 64 own calibration scores x 64 candidates (the batch shape bench.py times); the reject
     fraction per level is close to alpha (budget control per input, Sec. "Budget Prediction")."""
