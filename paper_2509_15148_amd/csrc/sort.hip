@@ -24,7 +24,7 @@ constexpr int kRunMax = 8192;                // keys of the longest run: one wor
 constexpr int kSmallSortMax = 1 << 19;       // 64 runs of kRunMax
 constexpr int kMaxRuns = 64;
 constexpr int kSpacing = 64;                 // every 64th key of a run is a sample
-constexpr int kSamplesMin = 16, kSamplesMax = 32;   // samples per bucket: about 1024 or 2048 keys
+constexpr int kSamplesMin = 8, kSamplesMax = 32;    // samples per bucket: about 512, 1024 or 2048 keys
 constexpr int kBucketThreads = 1024;
 constexpr int kBucketCap = kPer * kBucketThreads;
 constexpr int kFewThreads = 512;             // ... and for few runs (of 2048 keys)
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(THREADS) void block_sort_kernel(const float* __rest
 // known without moving them.  Regular samples bound a bucket whatever the scores are (ties included: equal splitters share
 // their value's range evenly), and no workgroup waits for another: each sorts the samples for itself, finds its limits in every
 // run (the samples lead to one block of 64 keys, read in 16-byte pieces), gathers the segments between them and sorts those.
-// What bounds it is its chain of steps (two sorts, the limits, the gathering), one bucket per CU: 65,536 scores 14 us behind
+// What bounds it is its chain of steps (two sorts, the limits, the gathering), one bucket per CU: 65,536 scores 12 us behind
 // 5.2 for the runs, where runs of 8192 keys merged through LDS and one pass that searched every key's place in the other runs took
 // 25 + 14; 262,144 scores 31 us in all and 524,288 43, by radix sort 76 and 78 (which is why the line to it lies here: its
 // launches are a floor, and 64 runs of one workgroup's keys end at 2^19).  Up to 32 runs by workgroups of 512 threads: 0.6 us less.
@@ -109,35 +109,42 @@ __global__ __launch_bounds__(THREADS) void bucket_sort_kernel(const uint32_t* __
     // the splitters equal to lo, and those of them before this one
     const bool same = tid >= 1 && tid < n_buckets && splitter[tid] == lo;
     const int n_same = __syncthreads_count(same), my_same = __syncthreads_count(same && tid < b);
-    if (tid < 4 * n_runs && (tid & 3) < 3) {
-        const int r = tid >> 2, kind = tid & 3;
-        const int len = (int)min((int64_t)run_len, n - (int64_t)r * run_len);
-        const uint32_t v = kind < 2 ? lo : hi;
-        const bool equal_too = kind == 1;
-        int count = kind < 2 ? 0 : len;
-        if (kind < 2 ? has_lo : has_hi) {
+    {
+        // Sixteen threads a run: the samples lead to one block of 64 keys for each of the three limits, of which every thread takes
+        // 16 bytes; all three are requested before the first is counted (one thread a limit, with sixteen loads of its own: 3.2 us
+        // of a workgroup's 11 at 65,536 scores, now 1.9).
+        const int r = tid >> 4, l16 = tid & 15;
+        if (r < n_runs) {
+            const int len = (int)min((int64_t)run_len, n - (int64_t)r * run_len);
             const uint32_t* s = smp + r * (run_len / kSpacing);
-            int x = 0, y = (len + kSpacing - 1) / kSpacing;        // samples below v
-            while (x < y) {
-                const int mid = (x + y) >> 1;
-                if (s[mid] < v || (equal_too && s[mid] == v)) x = mid + 1; else y = mid;
+            const uint32_t* run = runs + (int64_t)r * run_len;
+            int first[3];                                          // -1: no sample lies below the limit, so no key does
+            uint4 piece[3];
+#pragma unroll
+            for (int kind = 0; kind < 3; ++kind) {
+                const uint32_t v = kind < 2 ? lo : hi;
+                int x = 0, y = (len + kSpacing - 1) / kSpacing;    // samples below v
+                while (x < y) {
+                    const int mid = (x + y) >> 1;
+                    if (s[mid] < v || (kind == 1 && s[mid] == v)) x = mid + 1; else y = mid;
+                }
+                first[kind] = (x - 1) * kSpacing;                  // the limit lies in the block of the last of them
+                const int at = max(first[kind], 0) + 4 * l16;
+                piece[kind] = reinterpret_cast<const uint4*>(run)[min(at, len - 1) >> 2];
             }
-            count = 0;
-            if (x > 0) {                                           // the limit lies in the block of the last of them
-                const int first = (x - 1) * kSpacing;
-                const uint4* p = reinterpret_cast<const uint4*>(runs + (int64_t)r * run_len + first);
-                uint4 block[kSpacing / 4];
 #pragma unroll
-                for (int j = 0; j < kSpacing / 4; ++j)
-                    block[j] = p[min(j, (len - 1 - first) >> 2)];
-                auto goes = [&](uint32_t key, int i) { return (first + i < len && (key < v || (equal_too && key == v))) ? 1 : 0; };
-                count = first;
+            for (int kind = 0; kind < 3; ++kind) {
+                const uint32_t v = kind < 2 ? lo : hi;
+                const int at = first[kind] + 4 * l16;
+                auto goes = [&](uint32_t key, int i) { return (at + i < len && (key < v || (kind == 1 && key == v))) ? 1 : 0; };
+                int count = goes(piece[kind].x, 0) + goes(piece[kind].y, 1) + goes(piece[kind].z, 2) + goes(piece[kind].w, 3);
 #pragma unroll
-                for (int j = 0; j < kSpacing / 4; ++j)
-                    count += goes(block[j].x, 4 * j) + goes(block[j].y, 4 * j + 1) + goes(block[j].z, 4 * j + 2) + goes(block[j].w, 4 * j + 3);
+                for (int o = 1; o < 16; o <<= 1) count += __shfl_xor(count, o);
+                count = first[kind] < 0 ? 0 : first[kind] + count;
+                if (kind < 2 ? !has_lo : !has_hi) count = kind < 2 ? 0 : len;
+                if (l16 == 0) below[kind][r] = count;
             }
         }
-        below[kind][r] = count;
     }
     __syncthreads();
     if (tid < 64) {                                                // one lane per run: the segments side by side
@@ -380,7 +387,9 @@ int32_t launch_sort_scores(const float* scores, int64_t n, uint32_t* a, uint32_t
         *sorted = a;
         if (n_runs > 1) {
             const int n_samples = (int)ceil_div(n, kSpacing);
-            const int q = n_samples <= 256 * kSamplesMin ? kSamplesMin : kSamplesMax;      // a bucket takes a CU's LDS: at most 256
+            // a bucket takes a CU's LDS: at most 256.  Shorter ones while they are few: 20,000 scores 1.3 us less with 8 samples than
+            // with 16, 65,536 the same
+            const int q = n_samples <= 128 * kSamplesMin ? kSamplesMin : (n_samples <= 256 * 16 ? 16 : kSamplesMax);
             const int threads = n_runs <= kFewRuns ? kFewThreads : kBucketThreads;
             const size_t lds = (size_t)(2 * kPer * threads + align_up((size_t)n_samples, 4)) * sizeof(uint32_t);
             const dim3 buckets((unsigned)ceil_div(n_samples, q));

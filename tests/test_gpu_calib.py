@@ -214,6 +214,28 @@ def test_classification_of_a_few_scores(n, m):
         assert np.array_equal(cls, O.classify(want, O.reject_ranks([0.05, 0.2], n)))
 
 
+@pytest.mark.parametrize("n", [20000, 32768, 32769, 65536, 65537])
+def test_bucket_sizes_and_limits(n):
+    """Batches around the line between buckets of 8 and of 16 samples.  Whole blocks of 64 equal keys, one key above a block, runs that
+    end inside a block of 64 and inside a 16-byte piece: the limits of a bucket fall on and beside block edges in every run."""
+    import paper_2509_15148_amd as A
+    announce("bucket limits", n)
+    rng = np.random.default_rng(n)
+    for m in (n, n - 1, n - 61):
+        v = np.concatenate([np.repeat(rng.lognormal(size=m // 128 + 1), 64), rng.lognormal(size=m // 3), np.repeat(rng.lognormal(size=m // 300 + 1), 65),
+                            [np.nan, np.inf, -np.inf, 0.0, -0.0], rng.lognormal(size=m)]).astype(np.float32)[:m]
+        v = rng.permutation(v) if m % 2 else np.sort(v)
+        c = A.Calib(m)
+        A.atts_calibrate_online(c, dev(v))
+        out = torch.empty(m, dtype=torch.float32, device="cuda")
+        A.atts_calib_export(c, out)
+        torch.cuda.synchronize()
+        got, ref = out.cpu().numpy(), np.sort(v)                       # NaN last there, first here
+        k = int(np.isnan(v).sum())
+        assert np.isnan(got[:k]).all() and np.array_equal(got[k:], ref[:m - k] if k else ref), m
+        c.close()
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
