@@ -45,7 +45,11 @@ namespace atts {
 namespace {
 
 constexpr int kMergeThreads = 256;
-constexpr int kMergeSegSmall = 2048;   // outputs per merge workgroup: cache-resident sizes (more workgroups)
+// outputs per merge workgroup: the shorter chain of 1024 while a workgroup a CU covers them (100,000 + 2000 keys 15.4 -> 14.7 us
+// with their ranks, 3,000,000 + 100 16.8 and 17.4)
+constexpr int kMergeSegTiny = 1024;
+constexpr int64_t kMergeTinyTo = (int64_t)kMergeSegTiny * 256;
+constexpr int kMergeSegSmall = 2048;   // ... cache-resident sizes (more workgroups)
 constexpr int kMergeSegLarge = 4096;   // ... and streaming sizes (split search amortised over more keys; 8 workgroups per CU)
 constexpr int64_t kMergeLargeFrom = (int64_t)1 << 22;
 // Appends of up to kInlineMax scores into sets of up to kInlineTotal keys are sorted by the merge workgroups themselves, each for
@@ -152,37 +156,33 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
     if constexpr (PRESPLIT) {
         if (threadIdx.x < 2) split[threadIdx.x] = splits[blockIdx.x + threadIdx.x];
     } else
-    // Merge-path split of both segment ends at once: threads 0..127 search the diagonal o0, threads 128..255 the
-    // diagonal o1.  Each round probes 128 evenly spaced candidates of the current range in parallel (one load
-    // latency per round instead of one per halving step); "a[i] <= b[diag - 1 - i]" is true below the split.
-    {
-        __shared__ int64_t s_lo[2], s_hi[2];
-        __shared__ int s_cnt[2];
-        const int h = threadIdx.x >> 7, t = threadIdx.x & 127;
+    // Merge-path split of both segment ends at once, one wavefront each: "a[i] <= b[diag - 1 - i]" is true below the split, and
+    // every round probes 512 evenly spaced candidates of the range that is left, eight a lane requested together.  One load
+    // latency a round, two rounds up to 2^18 candidates, and nothing to wait for but the wavefront's own loads (128 candidates a
+    // round with counts and limits through LDS and three barriers: 3.6 us of a workgroup's 6 at 2^20 + 65,536 keys).
+    if (threadIdx.x < 128) {
+        constexpr int kProbes = 1;
+        const int h = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
         const int64_t diag = h ? o1 : o0;
-        if (t == 0) {
-            s_lo[h] = diag > nb ? diag - nb : 0;
-            s_hi[h] = diag < na ? diag : na;
-        }
-        __syncthreads();
-        while (s_lo[0] != s_hi[0] || s_lo[1] != s_hi[1]) {      // block-uniform
-            const int64_t lo = s_lo[h], hi = s_hi[h], range = hi - lo;
-            if (t == 0) s_cnt[h] = 0;
-            __syncthreads();
-            const int64_t step = (range + 127) / 128;
-            const int64_t i = lo + t * step;
-            const bool pred = range > 0 && i < hi && a[i] <= batch_key(diag - 1 - i);
-            const int c_wave = __popcll(__ballot(pred));
-            if ((threadIdx.x & 63) == 0 && c_wave) atomicAdd(&s_cnt[h], c_wave);
-            __syncthreads();
-            if (t == 0 && range > 0) {
-                const int64_t c = s_cnt[h], n_probe = (range + step - 1) / step;
-                s_lo[h] = c > 0 ? lo + (c - 1) * step + 1 : lo;
-                s_hi[h] = c == 0 ? lo : (c < n_probe ? lo + c * step : hi);
+        int64_t lo = diag > nb ? diag - nb : 0, hi = diag < na ? diag : na;
+        while (lo < hi) {
+            const int64_t step = (hi - lo + 64 * kProbes - 1) / (64 * kProbes);
+            uint32_t x[kProbes], y[kProbes];
+#pragma unroll
+            for (int u = 0; u < kProbes; ++u) {
+                const int64_t i = min(lo + (int64_t)(64 * u + lane) * step, hi - 1);
+                x[u] = a[i];
+                y[u] = batch_key(diag - 1 - i);
             }
-            __syncthreads();
+            int64_t below = 0;
+#pragma unroll
+            for (int u = 0; u < kProbes; ++u)
+                below += __popcll(__ballot(lo + (int64_t)(64 * u + lane) * step < hi && x[u] <= y[u]));
+            // the last true candidate and the one behind it (or the end) enclose the split
+            hi = min(lo + below * step, hi);
+            lo = below > 0 ? lo + (below - 1) * step + 1 : lo;
         }
-        if (t == 0) split[h] = s_lo[h];
+        if (lane == 0) split[h] = lo;
     }
     __syncthreads();
     const int64_t i0 = split[0], i1 = split[1];
@@ -202,9 +202,10 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
     for (int e = 0; e < PER; ++e) buf[lds_pad((int)threadIdx.x + e * kMergeThreads)] = k[e];
     __syncthreads();
 
-    // every thread merges PER consecutive outputs into registers
+    // every thread merges PER consecutive outputs (its split by halving: three probes a step, with twice the reads, took 1.3 us
+    // for 0.6 where several workgroups share a CU)
     const int d0 = min((int)threadIdx.x * PER, len);
-    int ia, ib;
+    int ia;
     {
         int lo = d0 > lb ? d0 - lb : 0, hi = d0 < la ? d0 : la;
         while (lo < hi) {
@@ -212,27 +213,51 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
             if (buf[lds_pad(mid)] <= buf[lds_pad(la + d0 - 1 - mid)]) lo = mid + 1; else hi = mid;
         }
         ia = lo;
-        ib = d0 - lo;
     }
-    uint32_t ka = ia < la ? buf[lds_pad(ia)] : kPadKey, kb = ib < lb ? buf[lds_pad(la + ib)] : kPadKey;
+    const int ib = d0 - ia;
+    // The PER smallest of the next PER keys of both sides, all read together: min(a[e], b[PER - 1 - e]) is a bitonic sequence of
+    // them, sorted by the last stages of a network (equal keys are alike, so which side one comes from does not matter).  Taken
+    // one by one, each key waits for the LDS read that the choice before it made: 1.2 us a workgroup instead of 0.4.
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
-        const bool take_a = ib >= lb || (ia < la && ka <= kb);
-        k[e] = take_a ? ka : kb;
-        if (take_a) {
-            ++ia;
-            ka = ia < la ? buf[lds_pad(ia)] : kPadKey;
+        const uint32_t x = ia + e < la ? buf[lds_pad(ia + e)] : kPadKey;
+        const int f = PER - 1 - e;
+        const uint32_t y = ib + f < lb ? buf[lds_pad(la + ib + f)] : kPadKey;
+        k[e] = min(x, y);
+    }
+#pragma unroll
+    for (int stride = PER / 2; stride > 0; stride >>= 1)
+#pragma unroll
+        for (int e = 0; e < PER; ++e)
+            if ((e & stride) == 0) cswap(k[e], k[e + stride]);
+    uint32_t* o = out + o0;
+    if constexpr (PER <= 8) {
+        // straight from the registers: 16 or 32 bytes a lane
+        if (d0 + PER <= len) {
+#pragma unroll
+            for (int e = 0; e < PER; e += 4) *reinterpret_cast<uint4*>(o + d0 + e) = make_uint4(k[e], k[e + 1], k[e + 2], k[e + 3]);
         } else {
-            ++ib;
-            kb = ib < lb ? buf[lds_pad(la + ib)] : kPadKey;
+#pragma unroll
+            for (int e = 0; e < PER; ++e)
+                if (d0 + e < len) o[d0 + e] = k[e];
         }
+        if constexpr (EMIT) {                                    // an index entry is the first key of a thread
+            if (d0 < len) {
+#pragma unroll
+                for (int lvl = 0; lvl < kIndexLevels; ++lvl) {
+                    const int shift = kFanBits * (lvl + 1);
+                    const int64_t at = o0 + d0;
+                    if ((at & (((int64_t)1 << shift) - 1)) == 0) job.index[lvl][at >> shift] = k[0];
+                }
+            }
+        }
+        return;
     }
     __syncthreads();
     // through LDS again, so that the segment leaves in whole 16-byte pieces per lane
 #pragma unroll
     for (int e = 0; e < PER; ++e) buf[lds_pad((int)threadIdx.x * PER + e)] = k[e];
     __syncthreads();
-    uint32_t* o = out + o0;
     for (int i = (int)threadIdx.x * 4; i < len; i += kMergeThreads * 4) {
         if (i + 4 <= len) {
             uint4 v;
@@ -550,6 +575,9 @@ int32_t launch_merge(atts_calib* c, const MergeJob& job, int64_t total, bool str
         } else {
             hipLaunchKernelGGL((merge_kernel<kMergeSegLarge, EMIT, false>), dim3((unsigned)segs), dim3(kMergeThreads), 0, stream, job, nullptr);
         }
+    } else if (total <= kMergeTinyTo) {
+        hipLaunchKernelGGL((merge_kernel<kMergeSegTiny, EMIT, false>), dim3((unsigned)ceil_div(total, kMergeSegTiny)), dim3(kMergeThreads), 0,
+                           stream, job, nullptr);
     } else {
         hipLaunchKernelGGL((merge_kernel<kMergeSegSmall, EMIT, false>), dim3((unsigned)ceil_div(total, kMergeSegSmall)), dim3(kMergeThreads), 0,
                            stream, job, nullptr);
@@ -662,8 +690,12 @@ int32_t atts_calibrate_online(atts_calib* c, const float* new_scores, int64_t n_
     for (int k = 0; k < kIndexLevels; ++k) job.index[k] = c->index[to][k];
     StageTimer t_(ATTS_STAGE_CALIB_MERGE, stream);
     if (inline_sort) {
-        hipLaunchKernelGGL((merge_kernel<kMergeSegSmall, true, false, true>), dim3((unsigned)ceil_div(total, kMergeSegSmall)), dim3(kMergeThreads),
-                           0, stream, job, nullptr);
+        if (total <= kMergeTinyTo)
+            hipLaunchKernelGGL((merge_kernel<kMergeSegTiny, true, false, true>), dim3((unsigned)ceil_div(total, kMergeSegTiny)), dim3(kMergeThreads),
+                               0, stream, job, nullptr);
+        else
+            hipLaunchKernelGGL((merge_kernel<kMergeSegSmall, true, false, true>), dim3((unsigned)ceil_div(total, kMergeSegSmall)),
+                               dim3(kMergeThreads), 0, stream, job, nullptr);
         ATTS_LAUNCH_CHECK("merge_kernel");
     } else {
         int32_t rc = launch_merge<true>(c, job, total, total >= kMergeLargeFrom, stream);

@@ -236,6 +236,36 @@ def test_bucket_sizes_and_limits(n):
         c.close()
 
 
+@pytest.mark.parametrize("base,sizes", [(0, (1023, 1, 1, 1022, 1, 1)), (900, (60, 64, 65)), ((1 << 18) - 513, (512, 1, 1, 600)),
+                                        ((1 << 18) - 5000, (4096, 4097)), (300000, (700, 65536, 262145)), (5, (20000,)), (40000, (9,))])
+@pytest.mark.parametrize("where", ["spread", "one place", "below", "above", "ties"])
+def test_merge_segments_and_splits(base, sizes, where):
+    """Totals around whole segments of 1024 and 2048 keys and around the line between them, batches one below, at and above 64, 64^2
+    and 64^3 keys (rounds of the split search), larger and smaller than the set; the batch spread over the set, in one place of it, outside
+    it on either side, or all ties with it."""
+    import paper_2509_15148_amd as A
+    announce("merge segments", base, sizes, where)
+    rng = np.random.default_rng(base + len(sizes))
+    total = base + sum(sizes)
+    c = A.Calib(total)
+    have = np.round(rng.lognormal(size=base), 3).astype(np.float32)
+    if base:
+        A.atts_calibrate_online(c, dev(have))
+    for n in sizes:
+        v = {"spread": lambda: np.round(rng.lognormal(size=n), 3), "one place": lambda: 1.0 + 1e-6 * rng.random(n), "below": lambda: -rng.random(n),
+             "above": lambda: 1e6 + rng.random(n), "ties": lambda: np.full(n, have[base // 2] if base else 1.0)}[where]().astype(np.float32)
+        A.atts_calibrate_online(c, dev(v))
+        have = np.concatenate([have, v])
+        out = torch.empty(len(have), dtype=torch.float32, device="cuda")
+        A.atts_calib_export(c, out)
+        torch.cuda.synchronize()
+        assert np.array_equal(out.cpu().numpy(), np.sort(have)), n
+        probe = np.concatenate([rng.choice(have, 300), [0.0, 2e6, -2.0]]).astype(np.float32)         # the index levels written with it
+        ranks = _classify(A, c, probe, [0.1])[0]
+        assert np.array_equal(ranks.astype(np.int64), O.rank_counts_sorted(have, probe))
+    c.close()
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
