@@ -284,6 +284,14 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
     }
 }
 
+// (rank + 1) / (N + 1) as the binary64 quotient rounded once to fp32.  Whole numbers below 2^24 are exact in fp32 and its division
+// is correctly rounded; the binary64 quotient has more than 2 x 24 + 2 bits, so rounding through it gives the same bits, and
+// the fp32 sequence takes a fraction of the binary64 one.
+__device__ __forceinline__ float p_value(int64_t c1, int64_t n1) {
+    if (n1 < ((int64_t)1 << 24)) return (float)(int32_t)c1 / (float)(int32_t)n1;
+    return (float)((double)c1 / (double)n1);
+}
+
 // ---- classification ----------------------------------------------------------------------------------
 struct ClassifyLevels {
     int64_t r[ATTS_MAX_ALPHAS];   // reject ranks floor(alpha_l (N + 1))
@@ -356,30 +364,66 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
                                                        ClassifyLevels lv, int32_t* __restrict__ ranks,
                                                        float* __restrict__ pvalues, uint8_t* __restrict__ classes,
                                                        float* __restrict__ thresholds) {
-    __shared__ uint32_t top[kTopEntries];
+    __shared__ __attribute__((aligned(16))) uint32_t top[kTopEntries + 4];
     const uint32_t* __restrict__ T = ix.lvl[ix.top_level];
     const int64_t top_len = ix.len[ix.top_level], n = ix.len[0];
     const int s = ix.top_shift;
     const int n_top = (int)((top_len + ((int64_t)1 << s) - 1) >> s);
-    for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
-    __syncthreads();
-    if (blockIdx.x == 0 && thresholds && (int)threadIdx.x < lv.n_alpha) {
-        const int64_t kth = n + 1 - lv.r[threadIdx.x];     // 1-indexed order statistic
-        thresholds[threadIdx.x] = kth > n ? INFINITY : (kth < 1 ? -INFINITY : key_to_score(ix.lvl[0][kth - 1]));
+    // the first scores and the thresholds are requested ahead of the staged level, which comes in 16-byte pieces (its array is
+    // padded to whole lines): a small call is nothing but this chain of latencies
+    const float none = __uint_as_float(0x7FC00000u);
+    const int64_t first = (int64_t)blockIdx.x * ix.per_thread * THREADS + threadIdx.x;
+    float next = first < m ? test[first] : none;
+    const bool quantile = blockIdx.x == 0 && thresholds && (int)threadIdx.x < lv.n_alpha;
+    const int64_t kth = quantile ? n + 1 - lv.r[threadIdx.x] : 0;                  // 1-indexed order statistic
+    const uint32_t kth_key = quantile && kth >= 1 && kth <= n ? ix.lvl[0][kth - 1] : 0u;
+    if (s == 0) {
+        const int n4 = (n_top + 3) >> 2;
+        for (int i0 = 0; i0 < n4; i0 += 4 * THREADS) {
+            uint4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * THREADS + (int)threadIdx.x < n4) reinterpret_cast<uint4*>(top)[i0 + u * THREADS + threadIdx.x] = v[u];
+        }
+    } else {
+        for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
     }
+    if (THREADS == 256) {                                        // what the search below finds behind the last entry
+        __syncthreads();
+        if (threadIdx.x == 0) top[n_top] = kPadKey;
+    }
+    __syncthreads();
+    if (quantile) thresholds[threadIdx.x] = kth > n ? INFINITY : (kth < 1 ? -INFINITY : key_to_score(kth_key));
     for (int j = 0; j < ix.per_thread; ++j) {
         const int64_t i0 = ((int64_t)blockIdx.x * ix.per_thread + j) * THREADS;      // block-uniform: whole quads stay in the loop
         if (i0 >= m) break;
         const int64_t i = i0 + threadIdx.x;
-        const float sc = i < m ? test[i] : __uint_as_float(0x7FC00000u);
+        const float sc = next;
+        next = j + 1 < ix.per_thread && i + THREADS < m ? test[i + THREADS] : none;
         const bool searching = !score_is_nan(sc);
         const uint32_t x = score_to_key(sc);
         int t = 0;                                             // number of entries of the current level below x
         if (searching) {
-            int lo = 0, hi = n_top;                            // number of staged entries < x
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (top[mid] < x) lo = mid + 1; else hi = mid;
+            int lo = 0;                                        // number of staged entries < x
+            if constexpr (THREADS == 256) {
+                // three probes a step, read together: half the steps of a chain of LDS latencies (1024 entries 1.2 -> 0.7 us);
+                // many scores want fewer reads instead
+                for (int range = n_top + 1; range > 1;) {
+                    const int q = (range + 3) >> 2;
+                    int below = 0;
+#pragma unroll
+                    for (int u = 1; u <= 3; ++u) below += top[min(lo + u * q - 1, n_top)] < x ? 1 : 0;
+                    lo += below * q;
+                    range = q;
+                }
+            } else {
+                int hi = n_top;
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (top[mid] < x) lo = mid + 1; else hi = mid;
+                }
             }
             t = lo;
             if (s > 0 && lo > 0) {
@@ -397,7 +441,7 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
         if (i >= m) continue;
         const int64_t c = searching ? n - t : 0;
         ranks[i] = (int32_t)c;
-        if (pvalues) pvalues[i] = (float)((double)(c + 1) / (double)(n + 1));
+        if (pvalues) pvalues[i] = p_value(c + 1, n + 1);
         int cls = 0;
         for (int l = 0; l < lv.n_alpha; ++l) cls += (c + 1 <= lv.r[l]) ? 1 : 0;
         classes[i] = (uint8_t)cls;
@@ -450,14 +494,6 @@ struct ConditionalLevels {
     double alpha[ATTS_MAX_ALPHAS];
     int32_t n_alpha;
 };
-
-// (rank + 1) / (N + 1) as the binary64 quotient rounded once to fp32.  Whole numbers below 2^24 are exact in fp32 and its division
-// is correctly rounded; the binary64 quotient has more than 2 x 24 + 2 bits, so rounding through it gives the same bits, and
-// the fp32 sequence takes a fraction of the binary64 one.
-__device__ __forceinline__ float p_value(int64_t c1, int64_t n1) {
-    if (n1 < ((int64_t)1 << 24)) return (float)(int32_t)c1 / (float)(int32_t)n1;
-    return (float)((double)c1 / (double)n1);
-}
 
 // The work of an input is a few hundred instructions; what takes the time is its chain of loads (offsets, then scores), so both
 // offset pairs are requested at once, then up to kCondHeld blocks of calibration scores and the first candidates.  The

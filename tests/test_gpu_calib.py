@@ -266,6 +266,22 @@ def test_merge_segments_and_splits(base, sizes, where):
     c.close()
 
 
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 255, 1021, 1024, 4099, 8191, 8192, 8193, 262144, 262145])
+@pytest.mark.parametrize("m", [1, 255, 256, 700])
+def test_staged_levels_of_every_length(n, m):
+    """The staged level read in 16-byte pieces and searched by three probes a step: lengths around whole pieces, whole batches of
+    them and the most that is staged; scores below, in and above the set, NaN and ties; thresholds inside and outside the set."""
+    import paper_2509_15148_amd as A
+    announce("staged level", n, m)
+    rng = np.random.default_rng(n * 7 + m)
+    cal = np.round(rng.lognormal(size=n), 4).astype(np.float32)
+    test = np.concatenate([rng.choice(cal, m), [np.nan, -1.0, np.inf, cal.max(), cal.min()], np.round(rng.lognormal(size=m), 4)]).astype(np.float32)[-m:]
+    c = A.Calib(n)
+    A.atts_calibrate_online(c, dev(cal))
+    _check_against_oracle(A, c, cal, test, [0.001, 0.05, 0.2, 0.999], brute=n < 5000)
+    c.close()
+
+
 def test_capacity_and_argument_errors():
     import paper_2509_15148_amd as A
     announce("calib errors")
