@@ -1,4 +1,4 @@
-"""ctypes binding of libatts.so: argument marshalling only.
+"""Binding of libatts.so (ctypes, and native code for the short calls): argument marshalling only.
 
 Every function here has the name of the C entry point it calls (include/atts.h) and does
 nothing but convert torch tensors to device pointers, check dtypes/contiguity, pick the
@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import Dict, Optional, Sequence
 
 import torch
@@ -23,19 +24,24 @@ DTYPE_F32, DTYPE_BF16 = 0, 1
 SCORE_MEAN_NLL, SCORE_SUM_NLL = 0, 1
 MAX_ALPHAS = 8
 
-EXPORTS = (
-    "atts_last_error_string", "atts_model_create", "atts_model_destroy", "atts_workspace_bytes",
-    "atts_score_drafts", "atts_model_check", "atts_prefix_create", "atts_prefix_destroy", "atts_prefix_length",
-    "atts_prefix_reset", "atts_prefix_extend_workspace_bytes", "atts_prefix_extend", "atts_score_drafts_cached",
-    "atts_continue_workspace_bytes", "atts_continue_greedy", "atts_continue_sample", "atts_lmhead_workspace_bytes", "atts_lmhead_logprobs",
-    "atts_lmhead_logprobs_static",
-    "atts_gemm_nt", "atts_attention_workspace_bytes", "atts_attention_shared_prefix",
-    "atts_calib_create", "atts_calib_destroy", "atts_calib_size", "atts_calib_reset",
-    "atts_calibrate_online", "atts_classify_ordinal", "atts_classify_conditional", "atts_calib_export",
-    "atts_calib_import", "atts_classic_workspace_bytes", "atts_classic_normalize", "atts_classic_threshold",
-    "atts_classic_prediction_sets",
-    "atts_gemm_routes", "atts_pass_routes", "atts_profile_enable", "atts_profile_read",
-)
+# The C entry points and their arguments (p pointer, i int32_t, l int64_t, z size_t, f float, d double).  Declared once, they take
+# plain Python numbers and None: an argument object built for each of a short call's eleven arguments took longer than its kernels.
+_ARGUMENTS = {
+    "atts_last_error_string": "", "atts_model_create": "ppp", "atts_model_destroy": "p", "atts_workspace_bytes": "piiip",
+    "atts_score_drafts": "ppippiiipppzp", "atts_model_check": "ppp", "atts_prefix_create": "pip", "atts_prefix_destroy": "p",
+    "atts_prefix_length": "pp", "atts_prefix_reset": "p", "atts_prefix_extend_workspace_bytes": "pip", "atts_prefix_extend": "ppipzp",
+    "atts_score_drafts_cached": "pppiiipppzp", "atts_continue_workspace_bytes": "piiip", "atts_continue_greedy": "pppiiiippzp",
+    "atts_continue_sample": "pppiiiifpppzp", "atts_lmhead_workspace_bytes": "iip", "atts_lmhead_logprobs": "ipppiiippzp",
+    "atts_lmhead_logprobs_static": "ipppiiipp", "atts_gemm_nt": "ipppiiip", "atts_attention_workspace_bytes": "iiiip",
+    "atts_attention_shared_prefix": "ippiiiiiipzp", "atts_calib_create": "lp", "atts_calib_destroy": "p", "atts_calib_size": "pp",
+    "atts_calib_reset": "p", "atts_calibrate_online": "pplp", "atts_classify_ordinal": "pplpippppp",
+    "atts_classify_conditional": "pppplpipppp", "atts_calib_export": "ppp", "atts_calib_import": "pplp",
+    "atts_classic_workspace_bytes": "lp", "atts_classic_normalize": "plipp", "atts_classic_threshold": "pldppzp",
+    "atts_classic_prediction_sets": "plppp", "atts_gemm_routes": "iiiipp", "atts_pass_routes": "piiiiip", "atts_profile_enable": "i",
+    "atts_profile_read": "ipp",
+}
+_C_TYPES = {"p": ctypes.c_void_p, "i": ctypes.c_int32, "l": ctypes.c_int64, "z": ctypes.c_size_t, "f": ctypes.c_float, "d": ctypes.c_double}
+EXPORTS = tuple(_ARGUMENTS)
 
 STAGES = ("embed", "norm", "gemm_qkv", "rope", "attention", "gemm_o", "gemm_gate_up", "gemm_down", "gather_norm",
           "lmhead", "reduce", "calib_sort", "calib_merge", "classify")
@@ -79,15 +85,19 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
         raise ImportError(f"{path} is missing: build it with `python -m paper_2509_15148_amd.build` "
                           "(there is no CPU fallback)")
     lib = ctypes.CDLL(path)
-    lib.atts_last_error_string.restype = ctypes.c_char_p
-    for name in EXPORTS:
+    for name, arguments in _ARGUMENTS.items():
         fn = getattr(lib, name)            # AttributeError if a declared symbol is not exported
-        if name != "atts_last_error_string":
-            fn.restype = ctypes.c_int32
+        fn.restype = ctypes.c_int32
+        fn.argtypes = [_C_TYPES[a] for a in arguments]
+    lib.atts_last_error_string.restype = ctypes.c_char_p
     return lib
 
 
 _lib = load_library()
+try:
+    from . import _marshal                 # the short calls' arguments in native code; see marshal.cpp
+except ImportError as e:
+    raise ImportError(f"{os.path.join(_HERE, '_marshal.so')} cannot be loaded ({e}): build it with `python -m paper_2509_15148_amd.build`") from e
 
 
 def _check(rc: int) -> None:
@@ -95,25 +105,34 @@ def _check(rc: int) -> None:
         raise AttsError(rc, _lib.atts_last_error_string().decode())
 
 
-# The current stream's handle without building a torch.cuda.Stream object for it: 0.4 us instead of 3.1, which is a third
-# of the host time of a short call (append + verdict of 16 scores: two calls whose kernels take 8 us together).
+# The current stream's handle without building a torch.cuda.Stream object for it, and the current device without the check that
+# the runtime is up (the tensors of the call have seen to that): 0.2 us instead of 3.1, which is a third of the host time of a
+# short call (append + verdict of 16 scores: two calls whose kernels take 6 us together).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)     # absent from a CPU build, which can still ask for sizes and routes
+_device = getattr(torch._C, "_cuda_getDevice", None)
+if _raw_stream is not None and _device is not None:
+    _marshal.setup(_device, _raw_stream)
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(_raw_stream(torch.cuda.current_device()))
+def _stream() -> int:
+    return _raw_stream(_device())
 
 
-def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> ctypes.c_void_p:
+def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> Optional[int]:
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     if not t.is_cuda:
         raise AttsError(ERR_INVALID_ARG, f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise AttsError(ERR_INVALID_ARG, f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise AttsError(ERR_INVALID_ARG, f"{name} must have dtype {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _levels(alphas: Sequence[float]) -> bytes:
+    """The levels as an array of C doubles."""
+    return struct.pack("%dd" % len(alphas), *map(float, alphas))
 
 
 def _dtype_code(dt: torch.dtype) -> int:
@@ -175,11 +194,11 @@ def atts_score_drafts(model: Model, prefix_ids: torch.Tensor, draft_ids: torch.T
     if scores.numel() != K or (draft_lens is not None and draft_lens.numel() != K):
         raise AttsError(ERR_INVALID_ARG, "scores / draft_lens must have K elements")
     _check(_lib.atts_score_drafts(
-        model.handle, _ptr(prefix_ids, torch.int32, "prefix_ids"), ctypes.c_int32(prefix_ids.numel()),
+        model.handle, _ptr(prefix_ids, torch.int32, "prefix_ids"), prefix_ids.numel(),
         _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-        ctypes.c_int32(K), ctypes.c_int32(T_max), ctypes.c_int32(score_mode),
+        K, T_max, score_mode,
         _ptr(token_logprobs, torch.float32, "token_logprobs"), _ptr(scores, torch.float32, "scores"),
-        _ptr(workspace, torch.uint8, "workspace"), ctypes.c_size_t(workspace.numel()), _stream()))
+        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
 
 class Prefix:
@@ -188,7 +207,7 @@ class Prefix:
     def __init__(self, model: Model, capacity: int):
         self.model = model
         self.handle = ctypes.c_void_p()
-        _check(_lib.atts_prefix_create(model.handle, ctypes.c_int32(capacity), ctypes.byref(self.handle)))
+        _check(_lib.atts_prefix_create(model.handle, capacity, ctypes.byref(self.handle)))
 
     def close(self) -> None:
         if self.handle:
@@ -214,13 +233,13 @@ def atts_prefix_reset(prefix: Prefix) -> None:
 
 def atts_prefix_extend_workspace_bytes(prefix: Prefix, n: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_prefix_extend_workspace_bytes(prefix.handle, ctypes.c_int32(n), ctypes.byref(out)))
+    _check(_lib.atts_prefix_extend_workspace_bytes(prefix.handle, n, ctypes.byref(out)))
     return out.value
 
 
 def atts_prefix_extend(prefix: Prefix, ids: torch.Tensor, workspace: torch.Tensor) -> None:
-    _check(_lib.atts_prefix_extend(prefix.handle, _ptr(ids, torch.int32, "ids"), ctypes.c_int32(ids.numel()),
-                                   _ptr(workspace, torch.uint8, "workspace"), ctypes.c_size_t(workspace.numel()),
+    _check(_lib.atts_prefix_extend(prefix.handle, _ptr(ids, torch.int32, "ids"), ids.numel(),
+                                   _ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
                                    _stream()))
 
 
@@ -234,14 +253,14 @@ def atts_score_drafts_cached(prefix: Prefix, draft_ids: torch.Tensor, draft_lens
         raise AttsError(ERR_INVALID_ARG, "scores / draft_lens must have K elements")
     _check(_lib.atts_score_drafts_cached(
         prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-        ctypes.c_int32(K), ctypes.c_int32(T_max), ctypes.c_int32(score_mode),
+        K, T_max, score_mode,
         _ptr(token_logprobs, torch.float32, "token_logprobs"), _ptr(scores, torch.float32, "scores"),
-        _ptr(workspace, torch.uint8, "workspace"), ctypes.c_size_t(workspace.numel()), _stream()))
+        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
 
 def atts_continue_workspace_bytes(prefix: Prefix, K: int, T: int, n_new: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_continue_workspace_bytes(prefix.handle, ctypes.c_int32(K), ctypes.c_int32(T), ctypes.c_int32(n_new),
+    _check(_lib.atts_continue_workspace_bytes(prefix.handle, K, T, n_new,
                                               ctypes.byref(out)))
     return out.value
 
@@ -252,9 +271,9 @@ def atts_continue_greedy(prefix: Prefix, draft_ids: torch.Tensor, out_ids: torch
     if out_ids.dim() != 2 or out_ids.shape[0] != K or (draft_lens is not None and draft_lens.numel() != K):
         raise AttsError(ERR_INVALID_ARG, "out_ids must be [K, n_new], draft_lens [K]")
     _check(_lib.atts_continue_greedy(prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-                                     ctypes.c_int32(K), ctypes.c_int32(T), ctypes.c_int32(out_ids.shape[1]), ctypes.c_int32(eos_id),
+                                     K, T, out_ids.shape[1], eos_id,
                                      _ptr(out_ids, torch.int32, "out_ids"), _ptr(workspace, torch.uint8, "workspace"),
-                                     ctypes.c_size_t(workspace.numel()), _stream()))
+                                     workspace.numel(), _stream()))
 
 
 def atts_continue_sample(prefix: Prefix, draft_ids: torch.Tensor, temperature: float, uniforms: torch.Tensor,
@@ -266,10 +285,10 @@ def atts_continue_sample(prefix: Prefix, draft_ids: torch.Tensor, temperature: f
     if draft_lens is not None and draft_lens.numel() != K:
         raise AttsError(ERR_INVALID_ARG, "draft_lens must have K elements")
     _check(_lib.atts_continue_sample(prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-                                     ctypes.c_int32(K), ctypes.c_int32(T), ctypes.c_int32(out_ids.shape[1]), ctypes.c_int32(eos_id),
-                                     ctypes.c_float(temperature), _ptr(uniforms, torch.float32, "uniforms"),
+                                     K, T, out_ids.shape[1], eos_id,
+                                     temperature, _ptr(uniforms, torch.float32, "uniforms"),
                                      _ptr(out_ids, torch.int32, "out_ids"), _ptr(workspace, torch.uint8, "workspace"),
-                                     ctypes.c_size_t(workspace.numel()), _stream()))
+                                     workspace.numel(), _stream()))
 
 
 def atts_model_check(model: Model) -> int:
@@ -293,7 +312,7 @@ def atts_lmhead_logprobs(x: torch.Tensor, w: torch.Tensor, targets: torch.Tensor
     _check(_lib.atts_lmhead_logprobs(_dtype_code(x.dtype), _ptr(x, None, "x"), _ptr(w, x.dtype, "w"),
                                      _ptr(targets, torch.int32, "targets"), B, d, V,
                                      _ptr(logprobs, torch.float32, "logprobs"),
-                                     _ptr(workspace, torch.uint8, "workspace"), ctypes.c_size_t(workspace.numel()),
+                                     _ptr(workspace, torch.uint8, "workspace"), workspace.numel(),
                                      _stream()))
 
 
@@ -330,7 +349,7 @@ def atts_attention_shared_prefix(qkv: torch.Tensor, out: torch.Tensor, P: int, K
     _check(_lib.atts_attention_shared_prefix(
         _dtype_code(qkv.dtype), _ptr(qkv, None, "qkv"), _ptr(out, qkv.dtype, "out"), P, K, T, n_q, n_kv, hd,
         _ptr(workspace, torch.uint8, "workspace"),
-        ctypes.c_size_t(0 if workspace is None else workspace.numel()), _stream()))
+        0 if workspace is None else workspace.numel(), _stream()))
 
 
 class Calib:
@@ -338,7 +357,7 @@ class Calib:
 
     def __init__(self, capacity: int):
         self.handle = ctypes.c_void_p()
-        _check(_lib.atts_calib_create(ctypes.c_int64(capacity), ctypes.byref(self.handle)))
+        _check(_lib.atts_calib_create(capacity, ctypes.byref(self.handle)))
 
     def close(self) -> None:
         if self.handle:
@@ -363,21 +382,26 @@ def atts_calib_reset(calib: Calib) -> None:
 
 
 def atts_calibrate_online(calib: Calib, new_scores: torch.Tensor) -> None:
+    rc = _marshal.calibrate_online(calib.handle.value, new_scores)
+    if rc != _marshal.OTHER:
+        return _check(rc)
     _check(_lib.atts_calibrate_online(calib.handle, _ptr(new_scores, torch.float32, "new_scores"),
-                                      ctypes.c_int64(new_scores.numel()), _stream()))
+                                      new_scores.numel(), _stream()))
 
 
 def atts_classify_ordinal(calib: Calib, test_scores: torch.Tensor, alphas: Sequence[float],
                           ranks: Optional[torch.Tensor], pvalues: Optional[torch.Tensor], classes: torch.Tensor,
                           thresholds: Optional[torch.Tensor]) -> None:
+    rc = _marshal.classify_ordinal(calib.handle.value, test_scores, alphas, ranks, pvalues, classes, thresholds)
+    if rc != _marshal.OTHER:
+        return _check(rc)
     M = test_scores.numel()
     if (ranks is not None and ranks.numel() != M) or classes.numel() != M or (pvalues is not None and pvalues.numel() != M):
         raise AttsError(ERR_INVALID_ARG, "ranks / pvalues / classes must have M elements")
     if thresholds is not None and thresholds.numel() != len(alphas):
         raise AttsError(ERR_INVALID_ARG, "thresholds must have n_alpha elements")
-    arr = (ctypes.c_double * max(len(alphas), 1))(*[float(a) for a in alphas])
     _check(_lib.atts_classify_ordinal(calib.handle, _ptr(test_scores, torch.float32, "test_scores"),
-                                      ctypes.c_int64(M), arr, ctypes.c_int32(len(alphas)),
+                                      M, _levels(alphas), len(alphas),
                                       _ptr(ranks, torch.int32, "ranks"), _ptr(pvalues, torch.float32, "pvalues"),
                                       _ptr(classes, torch.uint8, "classes"),
                                       _ptr(thresholds, torch.float32, "thresholds"), _stream()))
@@ -386,13 +410,15 @@ def atts_classify_ordinal(calib: Calib, test_scores: torch.Tensor, alphas: Seque
 def atts_classify_conditional(cal_scores: torch.Tensor, cal_offsets: torch.Tensor, test_scores: torch.Tensor,
                               test_offsets: torch.Tensor, alphas: Sequence[float], ranks: torch.Tensor,
                               pvalues: Optional[torch.Tensor], classes: torch.Tensor) -> None:
+    rc = _marshal.classify_conditional(cal_scores, cal_offsets, test_scores, test_offsets, alphas, ranks, pvalues, classes)
+    if rc != _marshal.OTHER:
+        return _check(rc)
     n_inputs = cal_offsets.numel() - 1
     if n_inputs < 0 or test_offsets.numel() != n_inputs + 1:
         raise AttsError(ERR_INVALID_ARG, "cal_offsets and test_offsets must both have n_inputs + 1 elements")
     M = test_scores.numel()
     if ranks.numel() != M or classes.numel() != M or (pvalues is not None and pvalues.numel() != M):
         raise AttsError(ERR_INVALID_ARG, "ranks / pvalues / classes must have one element per test score")
-    arr = (ctypes.c_double * max(len(alphas), 1))(*[float(a) for a in alphas])
     if n_inputs > 0 and (M == 0 or cal_scores.numel() == 0):    # the library wants non-NULL arrays; an empty tensor has no address
         spare = torch.zeros(1, dtype=torch.float32, device=cal_offsets.device)
         cal_scores = cal_scores if cal_scores.numel() else spare
@@ -402,8 +428,8 @@ def atts_classify_conditional(cal_scores: torch.Tensor, cal_offsets: torch.Tenso
     _check(_lib.atts_classify_conditional(_ptr(cal_scores, torch.float32, "cal_scores"),
                                           _ptr(cal_offsets, torch.int64, "cal_offsets"),
                                           _ptr(test_scores, torch.float32, "test_scores"),
-                                          _ptr(test_offsets, torch.int64, "test_offsets"), ctypes.c_int64(n_inputs),
-                                          arr, ctypes.c_int32(len(alphas)), _ptr(ranks, torch.int32, "ranks"),
+                                          _ptr(test_offsets, torch.int64, "test_offsets"), n_inputs,
+                                          _levels(alphas), len(alphas), _ptr(ranks, torch.int32, "ranks"),
                                           _ptr(pvalues, torch.float32, "pvalues"), _ptr(classes, torch.uint8, "classes"),
                                           _stream()))
 
@@ -413,35 +439,35 @@ def atts_calib_export(calib: Calib, out: torch.Tensor) -> None:
 
 
 def atts_calib_import(calib: Calib, scores: torch.Tensor) -> None:
-    _check(_lib.atts_calib_import(calib.handle, _ptr(scores, torch.float32, "scores") if scores.numel() else ctypes.c_void_p(0),
-                                  ctypes.c_int64(scores.numel()), _stream()))
+    _check(_lib.atts_calib_import(calib.handle, _ptr(scores, torch.float32, "scores") if scores.numel() else None,
+                                  scores.numel(), _stream()))
 
 
 def atts_classic_workspace_bytes(n_scores: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_classic_workspace_bytes(ctypes.c_int64(n_scores), ctypes.byref(out)))
+    _check(_lib.atts_classic_workspace_bytes(n_scores, ctypes.byref(out)))
     return out.value
 
 
 def atts_classic_normalize(nll: torch.Tensor, scores: torch.Tensor) -> None:
     if nll.dim() != 2 or tuple(scores.shape) != tuple(nll.shape):
         raise AttsError(ERR_INVALID_ARG, "nll and scores must both be [n_inputs, m]")
-    _check(_lib.atts_classic_normalize(_ptr(nll, torch.float32, "nll"), ctypes.c_int64(nll.shape[0]), ctypes.c_int32(nll.shape[1]),
+    _check(_lib.atts_classic_normalize(_ptr(nll, torch.float32, "nll"), nll.shape[0], nll.shape[1],
                                        _ptr(scores, torch.float32, "scores"), _stream()))
 
 
 def atts_classic_threshold(cal_scores: torch.Tensor, alpha: float, tau: torch.Tensor, workspace: torch.Tensor) -> None:
     if tau.numel() != 1:
         raise AttsError(ERR_INVALID_ARG, "tau must have one element")
-    _check(_lib.atts_classic_threshold(_ptr(cal_scores, torch.float32, "cal_scores"), ctypes.c_int64(cal_scores.numel()),
-                                       ctypes.c_double(alpha), _ptr(tau, torch.float32, "tau"),
-                                       _ptr(workspace, torch.uint8, "workspace"), ctypes.c_size_t(workspace.numel()), _stream()))
+    _check(_lib.atts_classic_threshold(_ptr(cal_scores, torch.float32, "cal_scores"), cal_scores.numel(),
+                                       alpha, _ptr(tau, torch.float32, "tau"),
+                                       _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
 
 def atts_classic_prediction_sets(scores: torch.Tensor, tau: torch.Tensor, member: torch.Tensor) -> None:
     if member.numel() != scores.numel() or tau.numel() != 1:
         raise AttsError(ERR_INVALID_ARG, "member must have one element per score, tau one element")
-    _check(_lib.atts_classic_prediction_sets(_ptr(scores, torch.float32, "scores"), ctypes.c_int64(scores.numel()),
+    _check(_lib.atts_classic_prediction_sets(_ptr(scores, torch.float32, "scores"), scores.numel(),
                                              _ptr(tau, torch.float32, "tau"), _ptr(member, torch.uint8, "member"), _stream()))
 
 
@@ -463,11 +489,11 @@ def atts_pass_routes(cfg, pass_kind: int, P: int, K: int, T_max: int, n_new: int
 
 
 def atts_profile_enable(on: bool) -> None:
-    _check(_lib.atts_profile_enable(ctypes.c_int32(1 if on else 0)))
+    _check(_lib.atts_profile_enable(1 if on else 0))
 
 
 def atts_profile_read(stage: int):
     """-> (total device milliseconds, launches) of one stage since atts_profile_enable(True)."""
     ms, n = ctypes.c_double(), ctypes.c_int64()
-    _check(_lib.atts_profile_read(ctypes.c_int32(stage), ctypes.byref(ms), ctypes.byref(n)))
+    _check(_lib.atts_profile_read(stage, ctypes.byref(ms), ctypes.byref(n)))
     return ms.value, n.value

@@ -1,4 +1,5 @@
-"""Builds libatts.so (the C-ABI HIP library) in-tree for gfx950 with hipcc.
+"""Builds libatts.so (the C-ABI HIP library) in-tree for gfx950 with hipcc, and _marshal.so (the short calls' argument marshalling,
+host code over torch's C++ headers) with g++.
 
     python -m paper_2509_15148_amd.build
 """
@@ -7,12 +8,14 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libatts.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 SOURCES = ["api.hip", "gemm.hip", "attention.hip", "elementwise.hip", "calib.hip", "sort.hip", "decode.hip", "skinny.hip", "small.hip", "classic.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -37,13 +40,38 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_marshal() -> str:
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    obj = os.path.join(HERE, "_build", "marshal.o")
+    os.makedirs(os.path.dirname(obj), exist_ok=True)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for path in include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", path]
+    r = subprocess.run([*cmd, "-I", os.path.join(ROOT, "include"), "-c", os.path.join(CSRC, "marshal.cpp"), "-o", obj], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on marshal.cpp:\n{r.stderr[-8000:]}")
+    return obj
+
+
+def _link_marshal(obj: str) -> None:
+    import torch
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-shared", "-o", MARSHAL, obj, "-L", HERE, "-latts", "-Wl,-rpath,$ORIGIN", "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"link of _marshal.so failed:\n{r.stderr[-8000:]}")
+
+
 def build(verbose: bool = True) -> str:
-    with ThreadPoolExecutor(max_workers=min(len(SOURCES), 8)) as ex:
+    with ThreadPoolExecutor(max_workers=min(len(SOURCES) + 1, 8)) as ex:
+        marshal = ex.submit(_compile_marshal)
         objs = list(ex.map(_compile, SOURCES))
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"link failed:\n{r.stderr[-8000:]}")
+    _link_marshal(marshal.result())
     if verbose:
         print(f"[build] wrote {LIB}")
     return LIB
