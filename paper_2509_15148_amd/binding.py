@@ -67,7 +67,7 @@ class _Weights(ctypes.Structure):
                 ("w_gate_up", ctypes.POINTER(ctypes.c_void_p)), ("w_down", ctypes.POINTER(ctypes.c_void_p))]
 
 
-KERNEL_GENERAL_128, KERNEL_GENERAL_256, KERNEL_SMALL, KERNEL_FEW_ROWS, KERNEL_ALIGNED, KERNEL_EXCHANGED = range(6)
+KERNEL_GENERAL_128, KERNEL_GENERAL_256, KERNEL_SMALL, KERNEL_FEW_ROWS, KERNEL_ALIGNED, KERNEL_EXCHANGED, KERNEL_STREAMED = range(7)
 PASS_SCORE, PASS_SCORE_CACHED, PASS_CONTINUE = range(3)
 
 

@@ -16,7 +16,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libatts.so")
 MARSHAL = os.path.join(HERE, "_marshal.so")
-SOURCES = ["api.hip", "gemm.hip", "attention.hip", "elementwise.hip", "calib.hip", "sort.hip", "decode.hip", "skinny.hip", "small.hip", "classic.hip"]
+SOURCES = ["api.hip", "gemm.hip", "attention.hip", "elementwise.hip", "calib.hip", "sort.hip", "decode.hip", "skinny.hip", "streamed.hip", "small.hip", "classic.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",

@@ -1323,6 +1323,10 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
         if (epi == EPI_PARTIAL_F32) r.slices = skinny_partial_slices(g);
         return r;
     }
+    if (gemm_streamed_ok(dtype, epi, g)) {
+        r.kernel = ATTS_KERNEL_STREAMED;
+        return r;
+    }
     if (fast) {
         const TilePlan plan = epi == EPI_PARTIAL_F32 ? partial_plan(g) : direct_plan(epi, g);
         r.kernel = ATTS_KERNEL_ALIGNED; r.tile_rows = plan.rows; r.slices = plan.slices;
@@ -1406,6 +1410,7 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
         return launch_fast<EPI_QKV_ROPE>(r, g, stream);
     }
     if (r.kernel == ATTS_KERNEL_FEW_ROWS) return launch_gemm_skinny(epi, g, stream);
+    if (r.kernel == ATTS_KERNEL_STREAMED) return launch_gemm_streamed(g, stream);
     return dtype == ATTS_DTYPE_F32 ? launch_t<float>(r, epi, g, stream) : launch_t<bf16>(r, epi, g, stream);
 }
 

@@ -1,0 +1,50 @@
+"""The SwiGLU projection of at most 128 rows with weights streamed by about a tile a compute unit, inside a one-layer pass against the
+oracle.  The down projection picks single features, one of every block of 16 in turn, so that each block reaches the logits by itself."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2509_15148_amd as A
+from oracle import atts_oracle as O
+from synth import ModelConfig, make_token_ids, make_weights
+from util import announce, dev, dirty_ws, weights_to_numpy
+
+D = 768
+
+
+@pytest.mark.parametrize("d_ffn,streamed", [(8192, False), (8320, True), (12288, True), (12416, True), (18944, True), (22016, True), (27648, True),
+                                            (28672, False)])
+def test_route_of_a_few_rows(d_ffn, streamed):
+    """From F = 8193 on (96 weight rows a tile, three quarters of a tile's traffic with few rows), and while the aligned kernel's tiles
+    of 128 features leave more than an eighth of the compute units without work."""
+    cfg = ModelConfig(1, 3584, 28, 4, 128, d_ffn, 2304, "bf16")
+    for rows in (2, 16, 17, 128, 129):
+        r = A.atts_pass_routes(cfg, A.PASS_SCORE, 1, 1, rows - 1).gate_up
+        assert (r.kernel == A.KERNEL_STREAMED) == (streamed and rows <= 128), rows
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d_ffn,rows", [(8320, 2), (8320, 33), (8320, 128), (12416, 16), (12416, 64), (12416, 65), (18944, 4), (18944, 32), (18944, 63),
+                                        (18944, 100), (22016, 17), (22016, 48), (22016, 127), (27648, 31), (27648, 64), (27648, 128)])
+def test_every_block_of_features(d_ffn, rows):
+    """3 to 7 blocks a tile with a partly filled last tile (and a whole one), 1, 2 and 4 blocks of rows, whole and not."""
+    cfg = ModelConfig(1, D, 6, 2, 128, d_ffn, 768, "bf16")
+    P, K, T = 1, 1, rows - 1
+    assert A.atts_pass_routes(cfg, A.PASS_SCORE, P, K, T).gate_up.kernel == A.KERNEL_STREAMED
+    w = make_weights(cfg, seed=rows, device="cuda")
+    prefix, drafts = [x.numpy() for x in make_token_ids(cfg.vocab, P, K, T, seed=d_ffn)]
+    blocks = d_ffn // 16
+    space = dirty_ws(A.atts_pass_routes(cfg, A.PASS_SCORE, P, K, T).workspace_bytes)
+    for first in range(0, blocks, D):
+        announce("streamed swiglu", d_ffn, rows, first)
+        pick = torch.zeros(D, d_ffn)
+        for i, b in enumerate(range(first, min(first + D, blocks))):
+            pick[i, 16 * b + (5 * b + first // D) % 16] = 2.0
+        w["w_down"][0].copy_(pick)
+        model = A.Model(cfg, w)
+        lp, sc = torch.full((K, T), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+        A.atts_score_drafts(model, dev(prefix), dev(drafts), None, 0, lp, sc, space)
+        ref_lp, ref_s = O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)
+        # bf16 log-probabilities (2e-2); a block taken from another place moves its logits by about 2 x 0.5 / sqrt(768) each
+        assert np.abs(lp.cpu().numpy() - ref_lp).max() <= 2e-2
+        model.close()
