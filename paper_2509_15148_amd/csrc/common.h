@@ -170,9 +170,12 @@ bool gemm_skinny_ok(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);
 int32_t launch_gemm_skinny(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t skinny_partial_slices(const GemmArgs& g);         // K slices of its EPI_PARTIAL_F32 form, at most as many as g.room holds
 size_t skinny_partial_bound(int32_t M, int32_t N, int32_t Kd);    // bytes of its sums, for any call with at most M rows
-// The kernel for the SwiGLU projection of at most 128 rows (streamed.hip): launch_gemm hands it the calls it serves.
+// The kernel for the SwiGLU projection of at most 128 rows and the partial sums of at most 64 (streamed.hip): launch_gemm hands it the
+// calls it serves.
 bool gemm_streamed_ok(int32_t dtype, GemmEpilogue epi, const GemmArgs& g);
-int32_t launch_gemm_streamed(const GemmArgs& g, hipStream_t stream);
+int32_t launch_gemm_streamed(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
+int32_t streamed_partial_slices(int32_t dtype, const GemmArgs& g);     // K slices of its EPI_PARTIAL_F32 form; 0: not served
+size_t streamed_partial_bound(int32_t M, int32_t N, int32_t Kd);       // bytes of its sums, for any call with at most M rows
 // The kernel for products of few tiles (small.hip), any shape; launch_gemm hands it the calls that leave the chip idle otherwise.
 int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes

@@ -1313,18 +1313,19 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
         }
         return r;
     }
-    // The aligned bf16 kernel serves every call it can (its DMA ring also streams weights well when the tiles are few).  A
-    // decoding step (at most 16 rows) streams the weights once: narrow outputs (partial-sum epilogue) go to the kernel that
-    // cuts K over single wavefronts; wide outputs (SwiGLU, logits) already give the aligned kernel enough tiles, and it
-    // streams them as fast, so they only go there when it cannot serve the shape.
+    // A decoding step or a batch of short drafts streams the weights once: the kernel built for that takes the SwiGLU and the narrow
+    // projections (partial-sum epilogue) of few rows whose tiles fill the chip.  At most 16 rows of other narrow outputs go to the kernel
+    // that cuts K over single wavefronts; wide outputs (logits) give the aligned kernel enough tiles and it streams them as fast,
+    // so they only go there when it cannot serve the shape.
     const bool fast = fast_path_ok(dtype, epi, g);
+    if (gemm_streamed_ok(dtype, epi, g)) {
+        r.kernel = ATTS_KERNEL_STREAMED;
+        if (epi == EPI_PARTIAL_F32) r.slices = streamed_partial_slices(dtype, g);
+        return r;
+    }
     if (gemm_skinny_ok(dtype, epi, g) && (epi == EPI_PARTIAL_F32 || !fast)) {
         r.kernel = ATTS_KERNEL_FEW_ROWS;
         if (epi == EPI_PARTIAL_F32) r.slices = skinny_partial_slices(g);
-        return r;
-    }
-    if (gemm_streamed_ok(dtype, epi, g)) {
-        r.kernel = ATTS_KERNEL_STREAMED;
         return r;
     }
     if (fast) {
@@ -1347,7 +1348,8 @@ GemmRoute gemm_route(int32_t dtype, GemmEpilogue epi, const GemmArgs& g) {
 
 size_t partial_bytes_bound(int32_t dtype, int32_t M, int32_t N, int32_t Kd, bool a_rows_padded) {
     if (dtype != ATTS_DTYPE_BF16) return 0;
-    size_t bytes = skinny_partial_bound(M, N, Kd);
+    const size_t few = skinny_partial_bound(M, N, Kd), streamed = streamed_partial_bound(M, N, Kd);
+    size_t bytes = few > streamed ? few : streamed;
     GemmArgs g{};
     g.M = M; g.N = N; g.Kd = Kd; g.lda = Kd; g.ldw = Kd; g.a_rows_padded = a_rows_padded;
     const size_t max_slices = (size_t)Kd / kWideBK / 6;              // as partial_plan: and at most one round of tiles
@@ -1410,7 +1412,7 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
         return launch_fast<EPI_QKV_ROPE>(r, g, stream);
     }
     if (r.kernel == ATTS_KERNEL_FEW_ROWS) return launch_gemm_skinny(epi, g, stream);
-    if (r.kernel == ATTS_KERNEL_STREAMED) return launch_gemm_streamed(g, stream);
+    if (r.kernel == ATTS_KERNEL_STREAMED) return launch_gemm_streamed(epi, g, stream);
     return dtype == ATTS_DTYPE_F32 ? launch_t<float>(r, epi, g, stream) : launch_t<bf16>(r, epi, g, stream);
 }
 

@@ -1,4 +1,4 @@
-"""The SwiGLU projection of at most 128 rows with weights streamed by about a tile a compute unit, inside a one-layer pass against the
+"""Projections of a few rows with weights streamed by about a tile a compute unit (SwiGLU up to 128 rows, narrow ones up to 64), inside a one-layer pass against the
 oracle.  The down projection picks single features, one of every block of 16 in turn, so that each block reaches the logits by itself."""
 import numpy as np
 import pytest
@@ -21,6 +21,44 @@ def test_route_of_a_few_rows(d_ffn, streamed):
     for rows in (2, 16, 17, 128, 129):
         r = A.atts_pass_routes(cfg, A.PASS_SCORE, 1, 1, rows - 1).gate_up
         assert (r.kernel == A.KERNEL_STREAMED) == (streamed and rows <= 128), rows
+
+
+NARROW = ModelConfig(1, 3584, 28, 4, 128, 9216, 768, "bf16")       # tiles of 64 columns; of 128 for down from 33 rows on
+WIDE = ModelConfig(1, 5568, 42, 2, 128, 4096, 768, "bf16")         # tiles of 128 columns, the last half filled
+
+
+@pytest.mark.parametrize("cfg,rows,slices", [(NARROW, 16, (3, 4, 4)), (NARROW, 33, (3, 4, 9)), (WIDE, 17, (5, 5, 5)), (WIDE, 64, (5, 5, 5)),
+                                             (ModelConfig(1, 8192, 64, 8, 128, 28672, 768, "bf16"), 20, (None, 4, 4)),
+                                             (ModelConfig(1, 768, 6, 2, 128, 1024, 768, "bf16"), 20, (None, None, None))])
+def test_route_of_narrow_projections(cfg, rows, slices):
+    """QKV, O and down up to 64 rows where the tiles and slices fill three quarters of the chip; the bound of their sums holds for fewer rows."""
+    r = A.atts_pass_routes(cfg, A.PASS_SCORE, 1, 1, rows - 1)
+    for product, s in zip((r.qkv, r.o, r.down), slices):
+        assert (product.kernel == A.KERNEL_STREAMED) == (s is not None) and (s is None or product.slices == s)
+    r = A.atts_pass_routes(cfg, A.PASS_SCORE, 1, 1, 64)
+    assert A.KERNEL_STREAMED not in (r.qkv.kernel, r.o.kernel, r.down.kernel)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("cfg,rows", [(NARROW, 2), (NARROW, 16), (NARROW, 17), (NARROW, 32), (NARROW, 33), (NARROW, 64), (WIDE, 5), (WIDE, 32), (WIDE, 50), (WIDE, 64)])
+def test_partial_sums_of_a_few_rows(cfg, rows):
+    """One and two blocks of rows, whole and not, slices of unequal length, a partly filled last tile; against the oracle, and against the same
+    draft scored several times in one call of more than 64 rows, which other kernels serve."""
+    announce("streamed partial sums", cfg.d_model, rows)
+    w = make_weights(cfg, seed=rows, device="cuda")
+    prefix, drafts = [x.numpy() for x in make_token_ids(cfg.vocab, 1, 1, rows - 1, seed=rows)]
+    model = A.Model(cfg, w)
+
+    def score(K):
+        lp, sc = torch.full((K, rows - 1), float("nan"), device="cuda"), torch.full((K,), float("nan"), device="cuda")
+        space = dirty_ws(A.atts_workspace_bytes(model, 1, K, rows - 1))
+        A.atts_score_drafts(model, dev(prefix), dev(np.repeat(drafts, K, axis=0)), None, 0, lp, sc, space)
+        return lp.cpu().numpy()
+    lp, ref = score(1), O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)[0]
+    assert np.abs(lp - ref).max() <= 2e-2                             # bf16 log-probabilities
+    more = score(max(2, 64 // (rows - 1) + 1))                        # other orders of sums and attention tiles: half the tolerance
+    assert np.abs(more - lp).max() <= 1e-2
+    model.close()
 
 
 @pytest.mark.gpu
