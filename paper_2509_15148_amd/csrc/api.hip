@@ -498,22 +498,30 @@ int32_t forward_tree(const atts_model* m, ScoreShape s, int32_t row0, atts_prefi
     if (save) ATTS_HIP_TRY(hipMemcpyAsync(pre->h_last, h + (size_t)(R - 1) * d.d_model, d.d_model * sizeof(float), hipMemcpyDeviceToDevice, st));
     if (!score) return ATTS_OK;
     // the first token of every draft is predicted from the last prefix row
-    if (pre && row0 > 0) ATTS_HIP_TRY(hipMemcpyAsync(h + (size_t)(s.P - 1) * d.d_model, pre->h_last, d.d_model * sizeof(float), hipMemcpyDeviceToDevice, st));
-    {
-        StageTimer t_(ATTS_STAGE_GATHER_NORM, st);
-        ATTS_TRY(launch_gather_norm(d.dtype, h, m->final_norm, d.rms_eps, d.d_model, draft_ids, draft_lens, d.vocab, s, xs,
-                                    targets, valid, st));
-    }
+    const float* first = pre && row0 > 0 ? pre->h_last : h + (size_t)(s.P - 1) * d.d_model;
     GemmArgs g{};
     g.a = xs; g.w = m->lm_head; g.out = nullptr; g.M = B; g.N = d.vocab; g.Kd = d.d_model;
     g.lda = d.d_model; g.ldw = d.d_model; g.ldc = 0; g.a_rows_padded = padded;
     g.targets = targets; g.partials = partials; g.target_logit = zt; g.n_part = ws.n_part;
-    {
+    if (d.dtype == ATTS_DTYPE_F32 && gemm_route(d.dtype, EPI_LMHEAD, g).kernel == ATTS_KERNEL_SMALL) {
+        // a small fp32 model: the final norm on the scoring rows rides in the product too
+        g.a = h; g.norm_gain = m->final_norm; g.norm_eps = d.rms_eps;
+        g.first = first; g.tree_P = s.P; g.tree_T = s.T; g.targets = draft_ids;
+        valid = nullptr;                                   // the score reduction leaves out what lies past a draft's length
+        StageTimer t_(ATTS_STAGE_LMHEAD, st);
+        ATTS_TRY(launch_gemm_small_fused(EPI_LMHEAD, g, st));
+    } else {
+        {
+            StageTimer t_(ATTS_STAGE_GATHER_NORM, st);
+            ATTS_TRY(launch_gather_norm(d.dtype, h, first, m->final_norm, d.rms_eps, d.d_model, draft_ids, draft_lens, d.vocab, s, xs,
+                                        targets, valid, st));
+        }
         StageTimer t_(ATTS_STAGE_LMHEAD, st);
         ATTS_TRY(launch_gemm(d.dtype, EPI_LMHEAD, g, st));
     }
     {
         StageTimer t_(ATTS_STAGE_REDUCE, st);
+        if (lmhead_score_ok(s.T, ws.n_part)) return launch_lmhead_score(partials, zt, s.K, s.T, ws.n_part, draft_lens, score_mode, token_logprobs, scores, st);
         ATTS_TRY(launch_lmhead_combine(partials, zt, B, ws.n_part, valid, lp, st));
         ATTS_TRY(launch_score_reduce(lp, draft_lens, s.K, s.T, score_mode, token_logprobs, scores, st));
     }

@@ -141,6 +141,8 @@ struct GemmArgs {
     int32_t head_dim;        // EPI_QKV_ROPE: columns of a head
     const float* norm_gain;  // != NULL: a is the fp32 residual stream, normalised row by row with this gain
     float norm_eps;
+    const float* first;      // EPI_LMHEAD: a is the residual stream of the token tree [P | K x T]; scoring row k T + t reads row P + k T + t - 1 of it,
+    int32_t tree_P, tree_T;  // and `first` for t = 0; `targets` are the draft ids (one outside the vocabulary is read as 0)
     // EPI_PARTIAL_F32 only:
     int32_t n_slices;        // slices stored = gemm_route(...).slices
     size_t room;             // bytes `out` has for them: no more slices than fit
@@ -180,8 +182,8 @@ size_t streamed_partial_bound(int32_t M, int32_t N, int32_t Kd);       // bytes 
 int32_t launch_gemm_small(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 int32_t small_lmhead_partials(int32_t N);                 // partials per row its LM-head epilogue writes
 // The same for an fp32 model with passes around the product fused in (no transposed values): EPI_QKV_ROPE for the heads of
-// small_rope_fusable, with or without the norm, and EPI_SWIGLU with the norm.  For calls whose plain form (EPI_STORE_ACT,
-// EPI_SWIGLU) gemm_route gives to the small kernel; others are refused.
+// small_rope_fusable, with or without the norm, EPI_SWIGLU with the norm, and EPI_LMHEAD with the scoring rows gathered and the norm.  For
+// calls whose plain form (EPI_STORE_ACT, EPI_SWIGLU, EPI_LMHEAD) gemm_route gives to the small kernel; others are refused.
 inline bool small_rope_fusable(int32_t head_dim) { return head_dim >= 2 && head_dim <= 32 && (head_dim & (head_dim - 1)) == 0; }
 int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t stream);
 // true if the EPI_QKV_ROPE epilogue can serve this QKV projection (else: EPI_STORE_ACT + launch_rope_split)
@@ -191,6 +193,11 @@ bool qkv_rope_fusable(int32_t dtype, int32_t M, int32_t N, int32_t Kd, int32_t h
 // (or b beyond) get 0.  valid may be NULL.
 int32_t launch_lmhead_combine(const float2* partials, const float* target_logit, int32_t B, int32_t n_part,
                               const uint8_t* valid, float* lp, hipStream_t stream);
+
+// Both the combine and launch_score_reduce for K short drafts (lmhead_score_ok), in one launch.
+bool lmhead_score_ok(int32_t T, int32_t n_part);
+int32_t launch_lmhead_score(const float2* partials, const float* target_logit, int32_t K, int32_t T, int32_t n_part, const int32_t* draft_lens,
+                            int32_t mode, float* token_logprobs, float* scores, hipStream_t stream);
 
 struct ScoreShape {
     int32_t P, K, T;        // prefix length, drafts, padded draft length
@@ -242,8 +249,9 @@ int32_t launch_qkv_finish(int32_t dtype, const float* acc, int32_t n_slices, int
 // gain != NULL: then xn[r] = rmsnorm(h[r]; gain) in the model dtype (residual update and the next norm in one pass)
 int32_t launch_resid_norm(int32_t dtype, float* h, const float* partials, int32_t n_slices, int64_t slice_pitch, const float* gain,
                           float eps, int32_t rows, int32_t d, void* xn, hipStream_t stream);
-// xs[b] = rmsnorm(h[row(b)]) for the B = K T scoring rows; targets[b] / valid[b] from the draft ids.
-int32_t launch_gather_norm(int32_t dtype, const float* h, const float* gain, float eps, int32_t d,
+// xs[b] = rmsnorm(h[row(b)]) for the B = K T scoring rows, where row(b) of a draft's first token is `first`; targets[b] / valid[b]
+// from the draft ids.
+int32_t launch_gather_norm(int32_t dtype, const float* h, const float* first, const float* gain, float eps, int32_t d,
                            const int32_t* draft_ids, const int32_t* draft_lens, int32_t vocab, ScoreShape s,
                            void* xs, int32_t* targets, uint8_t* valid, hipStream_t stream);
 int32_t launch_score_reduce(const float* lp, const int32_t* draft_lens, int32_t K, int32_t T, int32_t mode,

@@ -412,10 +412,10 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(const float* __restrict
 }
 
 // ---- S6: gather the scoring rows, final RMSNorm, targets -----------------------------------------
-// Scoring row b = k T + t reads the hidden state that predicts y^k_t: the last prefix row for
-// t = 0, else the row of y^k_{t-1}.
+// Scoring row b = k T + t reads the hidden state that predicts y^k_t: the last prefix row (`first`: in the tree, or kept with a cached
+// prefix) for t = 0, else the row of y^k_{t-1}.
 template <typename T>
-__global__ __launch_bounds__(256) void gather_norm_kernel(const float* __restrict__ h, const float* __restrict__ gain,
+__global__ __launch_bounds__(256) void gather_norm_kernel(const float* __restrict__ h, const float* __restrict__ first, const float* __restrict__ gain,
                                                           float eps, int d, const int32_t* __restrict__ draft_ids,
                                                           const int32_t* __restrict__ draft_lens, int vocab, int P,
                                                           int Tn, T* __restrict__ xs, int32_t* __restrict__ targets,
@@ -423,8 +423,7 @@ __global__ __launch_bounds__(256) void gather_norm_kernel(const float* __restric
     __shared__ float red[4];
     const int b = blockIdx.x;
     const int k = b / Tn, t = b % Tn;
-    const int src_row = t == 0 ? P - 1 : P + k * Tn + t - 1;
-    rmsnorm_row<T>(h + (int64_t)src_row * d, gain, eps, d, xs + (int64_t)b * d, red);
+    rmsnorm_row<T>(t == 0 ? first : h + (int64_t)(P + k * Tn + t - 1) * d, gain, eps, d, xs + (int64_t)b * d, red);
     if (threadIdx.x == 0) {
         int id = draft_ids[b];
         bool ok = !(draft_lens && t >= draft_lens[k]);
@@ -580,10 +579,10 @@ int32_t launch_copies(int32_t dtype, const CopyBlocks& jobs, hipStream_t stream)
     return ATTS_OK;
 }
 
-int32_t launch_gather_norm(int32_t dtype, const float* h, const float* gain, float eps, int32_t d,
+int32_t launch_gather_norm(int32_t dtype, const float* h, const float* first, const float* gain, float eps, int32_t d,
                            const int32_t* draft_ids, const int32_t* draft_lens, int32_t vocab, ScoreShape s, void* xs,
                            int32_t* targets, uint8_t* valid, hipStream_t stream) {
-    DISPATCH_T(dtype, hipLaunchKernelGGL(gather_norm_kernel<T>, dim3(s.B()), dim3(256), 0, stream, h, gain, eps, d,
+    DISPATCH_T(dtype, hipLaunchKernelGGL(gather_norm_kernel<T>, dim3(s.B()), dim3(256), 0, stream, h, first, gain, eps, d,
                                          draft_ids, draft_lens, vocab, s.P, s.T, (T*)xs, targets, valid);)
     ATTS_LAUNCH_CHECK("gather_norm_kernel");
     return ATTS_OK;

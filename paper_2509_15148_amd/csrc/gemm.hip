@@ -1179,22 +1179,13 @@ int32_t launch_t(const GemmRoute& r, GemmEpilogue epi, const GemmArgs& g, hipStr
     return fail(ATTS_ERR_INVALID_ARG, "unknown GEMM epilogue %d", (int)epi);
 }
 
+// log of the sum of exponentials of a row's logits from its n_part (maximum, sum) partials; one wavefront.
 template <int kHeld>
-__global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const float* __restrict__ target_logit, int B, int n_part,
-                                      const uint8_t* __restrict__ valid, float* __restrict__ lp) {
-    // one wavefront per row
-    const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (row >= B) return;
-    if (valid && !valid[row]) {
-        if (lane == 0) lp[row] = 0.f;
-        return;
-    }
+__device__ __forceinline__ float row_logsumexp(const float2* __restrict__ p, int n_part, int lane) {
     // Two passes over the row's partials, the sum against the row's final maximum and in the order of the columns.  The first
     // 64 kHeld are requested at once and held in registers in between, the rest eight at a time (one load at a time was a
     // chain of fifty load latencies: 4096 rows of 1584 partials 31.4 -> 12.1 us, 385 rows 11.8 -> 5.2; one pass with a running
     // maximum per lane 11.3 and 5.3, for other roundings of the sum).
-    const float2* p = partials + (int64_t)row * n_part;
     const float2 none = make_float2(-INFINITY, 0.f);
     float2 held[kHeld];
     float mx = -INFINITY;
@@ -1227,7 +1218,51 @@ __global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const
     }
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) lp[row] = target_logit[row] - (mx + __logf(sum));
+    return mx + __logf(sum);
+}
+
+template <int kHeld>
+__global__ void lmhead_combine_kernel(const float2* __restrict__ partials, const float* __restrict__ target_logit, int B, int n_part,
+                                      const uint8_t* __restrict__ valid, float* __restrict__ lp) {
+    // one wavefront per row
+    const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= B) return;
+    if (valid && !valid[row]) {
+        if (lane == 0) lp[row] = 0.f;
+        return;
+    }
+    const float z = row_logsumexp<kHeld>(partials + (int64_t)row * n_part, n_part, lane);
+    if (lane == 0) lp[row] = target_logit[row] - z;
+}
+
+// Log-probabilities and score of one draft of at most kScoreTokens tokens by one workgroup, a wavefront a token and round: what the
+// combine and the score reduction would do in a launch each, where a draft's partials are what one compute unit reads in less than a
+// launch takes (16 drafts of 8 tokens and 594 partials: a pass 832 -> 826 us; 10 of 32 and 1584, 400 KB a draft: 8 us slower, so not).  The
+// sums are the score reduction's.
+constexpr int kScoreTokens = 32, kScorePartials = 10000;
+template <int kHeld>
+__global__ __launch_bounds__(1024) void lmhead_score_kernel(const float2* __restrict__ partials, const float* __restrict__ target_logit, int Tn, int n_part,
+                                                            const int32_t* __restrict__ draft_lens, int mode, float* __restrict__ token_logprobs,
+                                                            float* __restrict__ scores) {
+    __shared__ float lp[kScoreTokens];
+    const int k = blockIdx.x, lane = threadIdx.x & 63;
+    const int len = draft_lens ? min(max(draft_lens[k], 0), Tn) : Tn;
+    for (int t = threadIdx.x >> 6; t < Tn; t += 16) {
+        const int64_t row = (int64_t)k * Tn + t;
+        float v = 0.f;
+        if (t < len) v = target_logit[row] - row_logsumexp<kHeld>(partials + row * n_part, n_part, lane);
+        if (lane == 0) {
+            lp[t] = v;
+            if (token_logprobs) token_logprobs[row] = v;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    float s = lane < Tn ? lp[lane] : 0.f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o);
+    if (lane == 0) scores[k] = mode == ATTS_SCORE_MEAN_NLL ? -s / (float)max(len, 1) : -s;
 }
 
 }  // namespace
@@ -1414,6 +1449,19 @@ int32_t launch_gemm(int32_t dtype, GemmEpilogue epi, const GemmArgs& g, hipStrea
     if (r.kernel == ATTS_KERNEL_FEW_ROWS) return launch_gemm_skinny(epi, g, stream);
     if (r.kernel == ATTS_KERNEL_STREAMED) return launch_gemm_streamed(epi, g, stream);
     return dtype == ATTS_DTYPE_F32 ? launch_t<float>(r, epi, g, stream) : launch_t<bf16>(r, epi, g, stream);
+}
+
+bool lmhead_score_ok(int32_t T, int32_t n_part) { return T <= kScoreTokens && (int64_t)T * n_part <= kScorePartials; }
+int32_t launch_lmhead_score(const float2* partials, const float* target_logit, int32_t K, int32_t T, int32_t n_part, const int32_t* draft_lens,
+                            int32_t mode, float* token_logprobs, float* scores, hipStream_t stream) {
+    if (!lmhead_score_ok(T, n_part)) return fail(ATTS_ERR_SHAPE, "score: drafts of %d tokens and %d partials take two launches", T, n_part);
+    const dim3 grid((unsigned)K), block(1024);
+    if (n_part <= 64 * 8)
+        hipLaunchKernelGGL(lmhead_score_kernel<8>, grid, block, 0, stream, partials, target_logit, T, n_part, draft_lens, mode, token_logprobs, scores);
+    else
+        hipLaunchKernelGGL(lmhead_score_kernel<16>, grid, block, 0, stream, partials, target_logit, T, n_part, draft_lens, mode, token_logprobs, scores);
+    ATTS_LAUNCH_CHECK("lmhead_score_kernel");
+    return ATTS_OK;
 }
 
 int32_t launch_lmhead_combine(const float2* partials, const float* target_logit, int32_t B, int32_t n_part,

@@ -16,6 +16,7 @@
 // 320 rows: 20 launches and 90.5 us -> 15 and 80.0, the old residual values requested with the operands included):
 //   kNorm  A is the residual stream: its rows are multiplied by the norm's gain as they are read, their sums of squares are taken
 //          on the way, and the finished sums are scaled by 1 / rms;
+//          (LM head: the rows are the scoring rows, gathered from the token tree; the targets are the draft ids.)
 //   EPI_QKV_ROPE  heads of at most 32 columns lie inside one tile: rotated with the partner column's value from the lane that
 //          holds it (values stay rows of the output, there is no transposed copy here).
 #include "common.h"
@@ -32,6 +33,8 @@ struct SmallDims {
     int32_t n_part, nt_m;
     float eps;                              // kNorm
     int32_t rot_cols, half_hd, cs_ld;       // EPI_QKV_ROPE: columns that are rotated, half a head's columns (a power of two), pitch of the table
+    const float* first;                     // EPI_LMHEAD with kNorm: see GemmArgs
+    int32_t tree_P, tree_T;
 };
 
 // One step: lane (row = l % 32, half = l / 32) holds 16 bytes of its row, at byte 32 step + 16 half.  bf16: the operand of
@@ -68,7 +71,12 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
     const int m0 = tm * 32, n0 = tn * N_OUT;
 
     // rows and columns past the end repeat the last one (their results are dropped); 16-byte pieces past the end are zero
-    const char* ap = gA + (int64_t)min(m0 + l32, d.M - 1) * d.lda * ES + 16 * half;
+    const int a_row = min(m0 + l32, d.M - 1);
+    const char* ap = gA + (int64_t)a_row * d.lda * ES + 16 * half;
+    if constexpr (EPI == EPI_LMHEAD && kNorm) {                             // the hidden state that predicts token a_row % T of its draft
+        ap = gA + (int64_t)(d.tree_P + a_row - 1) * d.lda * ES + 16 * half;
+        if (a_row % d.tree_T == 0) ap = reinterpret_cast<const char*>(d.first) + 16 * half;
+    }
     const char* wp[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
@@ -167,7 +175,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
         const int row = row0 + b;
         if constexpr (EPI == EPI_LMHEAD) {
             const bool row_ok = row < d.M;                                  // uniform over the 32 lanes that share `half`
-            const int tcol = row_ok ? g_targets[row] - n0 : -1;
+            int target = row_ok ? g_targets[row] : -1;
+            if constexpr (kNorm)
+                if (target < 0 || target >= d.N) target = row_ok ? 0 : -1;  // flagged by the embedding kernel already
+            const int tcol = row_ok ? target - n0 : -1;
             float mx = -INFINITY;
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
@@ -216,7 +227,7 @@ template <typename T, int EPI, bool kNorm = false>
 int32_t launch_small_epi(const GemmArgs& g, hipStream_t stream) {
     constexpr int NI = EPI == EPI_SWIGLU || EPI == EPI_LMHEAD ? 2 : 1, N_OUT = EPI == EPI_LMHEAD ? 64 : 32;
     SmallDims d{g.M, g.N, g.Kd, g.lda, g.ldw, g.ldc, g.n_part, (int32_t)ceil_div(g.M, 32), g.norm_eps,
-                g.n_rot_heads * g.head_dim, g.head_dim / 2, g.head_dim / 2};
+                g.n_rot_heads * g.head_dim, g.head_dim / 2, g.head_dim / 2, g.first, g.tree_P, g.tree_T};
     hipLaunchKernelGGL((gemm_small_kernel<T, EPI, NI, kNorm>), dim3((unsigned)(d.nt_m * ceil_div(g.N, N_OUT))), dim3(64 * kSmallWaves), 0, stream,
                        reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), g.out, g.targets, g.partials, g.target_logit, g.norm_gain, g.rope, d);
     ATTS_LAUNCH_CHECK("gemm_small_kernel");
@@ -247,6 +258,12 @@ int32_t launch_gemm_small_fused(GemmEpilogue epi, const GemmArgs& g, hipStream_t
         return fail(ATTS_ERR_SHAPE, "gemm (small product): the rotation of %d heads of %d columns does not fit", g.n_rot_heads, g.head_dim);
     if (epi == EPI_QKV_ROPE) return g.norm_gain ? launch_small_epi<float, EPI_QKV_ROPE, true>(g, stream) : launch_small_epi<float, EPI_QKV_ROPE>(g, stream);
     if (epi == EPI_SWIGLU && g.norm_gain) return launch_small_epi<float, EPI_SWIGLU, true>(g, stream);
+    if (epi == EPI_LMHEAD && g.norm_gain) {
+        if (!g.first || ((uintptr_t)g.first & 15) || g.tree_T < 1 || g.M % g.tree_T || !g.targets || !g.partials || !g.target_logit ||
+            g.n_part != small_lmhead_partials(g.N))
+            return fail(ATTS_ERR_INVALID_ARG, "gemm (small product): LM head without its rows or buffers");
+        return launch_small_epi<float, EPI_LMHEAD, true>(g, stream);
+    }
     return fail(ATTS_ERR_INVALID_ARG, "gemm (small product): epilogue %d is not fused", (int)epi);
 }
 
