@@ -18,9 +18,11 @@
 //                       come from a [n_kv, hd, rows] copy of V written after the QKV GEMM)
 //   * attn_split_kernel the same products for few query rows: 32 per workgroup, the keys divided among
 //     its wavefronts.
-//   * attn_simple_kernel any dtype / head_dim: one wavefront per (row, head); used by the
-//     fp32 model.
+//   * attn_rows_kernel  heads of 4 to 32 16-byte pieces: one wavefront per (row, head), in registers; used by the fp32 model.
+//   * attn_simple_kernel any dtype / head_dim: one wavefront per (row, head).
 #include "common.h"
+
+#include <type_traits>
 
 namespace atts {
 namespace {
@@ -70,65 +72,6 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
     __syncthreads();
     const float inv = 1.f / sum;
-    // Heads of 128 bytes, or 64 in 16 bits, whose rows start at 16 bytes: a lane takes a 16-byte piece, four or eight lanes a key's
-    // row, so that the wavefront's 16 or 8 groups walk the keys in fewer batches (8 query and 2 key heads, 300 + 4 x 200 rows: bf16,
-    // hd 64 94.8 -> 82.1 us, hd 32 54.2 -> 49.5; fp32, hd 32 63.8 -> 62.2; 4 heads, 64 + 8 x 32 rows 9.7 -> 8.7, 6.9 -> 6.2, 7.2 -> 6.1).
-    // Not for fewer bytes, where the sums over the groups outweigh it (bf16, hd 8: 5.6 against 7.1; fp32, hd 16: 28.8 and 29.2), nor
-    // in bf16, hd 64, for fewer than 16 keys, which fill a quarter of a batch (8 heads, 8 + 8 x 4 rows 5.2 against 4.9).
-    constexpr int kPiece = 16 / (int)sizeof(T);
-    const int pieces = hd / kPiece;
-    if (hd % kPiece == 0 && (pieces == 8 ? kPiece == 4 || n >= 16 : pieces == 4 && kPiece == 8) &&
-        ((reinterpret_cast<uintptr_t>(vbase) | (uintptr_t)(ld * (int64_t)sizeof(T))) & 15) == 0) {
-        const int groups = 64 / pieces, grp = lane / pieces, piece = lane % pieces;
-        float acc[kPiece];
-#pragma unroll
-        for (int e = 0; e < kPiece; ++e) acc[e] = 0.f;
-        for (int i0 = grp; i0 < n; i0 += 8 * groups) {                                // eight of a group's keys requested together
-            uint4 x[8];
-            float p[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int i = min(i0 + u * groups, n - 1);
-                x[u] = *reinterpret_cast<const uint4*>(vbase + (int64_t)(i < n1 ? i : s0 + (i - n1)) * ld + piece * kPiece);
-                p[u] = sp[i];
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (i0 + u * groups < n) {                                            // a row past the last is not added
-                    const T* v = reinterpret_cast<const T*>(&x[u]);
-#pragma unroll
-                    for (int e = 0; e < kPiece; ++e) acc[e] += p[u] * to_f32<T>(v[e]);
-                }
-            }
-        }
-        T* const to = out + (int64_t)r * nq * hd + head * hd + piece * kPiece;
-        if constexpr (kPiece == 8) {
-            // every exchange halves the elements a lane still adds up, until each has one to store: adding all eight in all lanes
-            // outweighs the loop up to 44 keys (heads of 32: 170)
-            int o = pieces, first = 0;
-#pragma unroll
-            for (int half = kPiece / 2; half > 0; half >>= 1, o <<= 1) {
-                const bool upper = lane & o;
-#pragma unroll
-                for (int e = 0; e < half; ++e) {
-                    const float other = __shfl_xor(upper ? acc[e] : acc[half + e], o);
-                    acc[e] = (upper ? acc[half + e] : acc[e]) + other;
-                }
-                first += upper ? half : 0;
-            }
-            for (; o < 64; o <<= 1) acc[0] += __shfl_xor(acc[0], o);
-            if (lane < pieces * kPiece) to[first] = from_f32<T>(acc[0] * inv);
-        } else {
-#pragma unroll
-            for (int e = 0; e < kPiece; ++e)
-                for (int o = pieces; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
-            if (grp == 0) {
-#pragma unroll
-                for (int e = 0; e < kPiece; ++e) to[e] = from_f32<T>(acc[e] * inv);
-            }
-        }
-        return;
-    }
     // output: `width` lanes (a power of two >= hd, at most 64) per key, the 64 / width groups of lanes take every such key; eight
     // of a group's keys are requested at a time, from the prefix rows and then from the draft's, so that a key costs one
     // load and one multiply-add; the groups are added by exchange at the end.  320 rows, 4 heads of 32 over up to 96 keys, fp32:
@@ -172,6 +115,136 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
         for (int o = width; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
         if (ok && grp == 0) out[(int64_t)r * nq * hd + head * hd + c] = from_f32<T>(acc * inv);
     }
+}
+
+// The same for heads of 4 to 32 16-byte pieces at 16-byte addresses: one wavefront per (row, head) again, but everything in registers.
+// PIECES lanes hold a key's row; 16 loads of keys and 16 of values (32 to 256 rows) are requested before the query is there, scores stay in
+// the lanes that summed them, and the groups meet only in the maximum, the sum and the output; longer contexts go on in batches with a
+// running maximum.  What bounds it is a memory latency and a chain of about 300 vector instructions a batch; the kernel above, a lane a
+// key and scores through LDS, waits for five latencies and reads 64 rows with every load.  us before and now: fp32, hd 32: 4 heads, 64 + 8 x 32
+// rows 6.2 -> 5.5 alone and 8 -> 4.6 inside a pass; 4 heads, 400 + 16 x 64 45.7 -> 25.3; 32 query and 8 key heads, 500 + 4 x 500 963 -> 453;
+// bf16, hd 64: 8.5 -> 5.3, 58.5 -> 32.9, 1534 -> 589; 30 + 2 x 20 rows the same.
+template <typename T, int PIECES>
+__global__ __launch_bounds__(64) void attn_rows_kernel(const T* __restrict__ qkv, T* __restrict__ out, int row0, int P, int Tn, int nq, int nkv,
+                                                      float scale) {
+    constexpr int kPiece = 16 / (int)sizeof(T), hd = PIECES * kPiece, kGroups = 64 / PIECES, kLoads = 16;
+    const int r = row0 + blockIdx.x, head = blockIdx.y, lane = threadIdx.x;
+    const int kvh = head / (nq / nkv), grp = lane / PIECES, piece = lane % PIECES;
+    const int64_t ld = (int64_t)(nq + 2 * nkv) * hd;
+    const T* const kbase = qkv + (nq + kvh) * hd + piece * kPiece;
+    const T* const vbase = kbase + nkv * hd;
+    const int n1 = r < P ? r + 1 : P;                 // visible prefix keys
+    const int s0 = seg_start(r, P, Tn);
+    const int n = n1 + (r < P ? 0 : r - s0 + 1);      // ... and those of the own draft
+    uint4 kx[kLoads], vx[kLoads];
+    auto load = [&](const T* base, int first, uint4 (&x)[kLoads]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            const int i = min(first + u * kGroups + grp, n - 1);
+            x[u] = *reinterpret_cast<const uint4*>(base + (int64_t)(i < n1 ? i : s0 + (i - n1)) * ld);
+        }
+    };
+    const uint4 qx = *reinterpret_cast<const uint4*>(qkv + (int64_t)r * ld + head * hd + piece * kPiece);
+    load(kbase, 0, kx);
+    load(vbase, 0, vx);
+    float q[kPiece], acc[kPiece], mx = -INFINITY, sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < kPiece; ++e) {
+        q[e] = to_f32<T>(reinterpret_cast<const T*>(&qx)[e]) * scale;
+        acc[e] = 0.f;
+    }
+    auto across = [&](float v, auto op) __attribute__((always_inline)) {     // over the groups
+#pragma unroll
+        for (int o = PIECES; o < 64; o <<= 1) v = op(v, __shfl_xor(v, o));
+        return v;
+    };
+    auto add_dpp = [&](float v, auto ctrl) __attribute__((always_inline)) {
+        return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    for (int first = 0;;) {
+        float s[kLoads];
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            s[u] = 0.f;
+#pragma unroll
+            for (int e = 0; e < kPiece; ++e) s[u] += q[e] * to_f32<T>(reinterpret_cast<const T*>(&kx[u])[e]);
+        }
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) s[u] = add_dpp(s[u], std::integral_constant<int, 0xB1>{});         // lane ^ 1
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) s[u] = add_dpp(s[u], std::integral_constant<int, 0x4E>{});         // lane ^ 2
+        if constexpr (PIECES >= 8) {
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) s[u] = add_dpp(s[u], std::integral_constant<int, 0x141>{});    // the other quad of eight
+        }
+        if constexpr (PIECES >= 16) {
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) s[u] = add_dpp(s[u], std::integral_constant<int, 0x140>{});    // the other eight of sixteen
+        }
+        if constexpr (PIECES >= 32) {
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) s[u] += __shfl_xor(s[u], 16);
+        }
+        float here = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            if (first + u * kGroups + grp >= n) s[u] = -INFINITY;
+            here = fmaxf(here, s[u]);
+        }
+        const float m = fmaxf(mx, across(here, [](float a, float b) { return fmaxf(a, b); }));
+        const float base = m == -INFINITY ? 0.f : m;
+        const float old = first == 0 ? 0.f : __expf(mx - base);
+        float part = 0.f;
+#pragma unroll
+        for (int u = 0; u < kLoads; ++u) {
+            s[u] = __expf(s[u] - base);
+            part += s[u];
+        }
+        sum = sum * old + part;                                     // this group's
+#pragma unroll
+        for (int e = 0; e < kPiece; ++e) {
+            acc[e] *= old;
+#pragma unroll
+            for (int u = 0; u < kLoads; ++u) {
+                // a row past the last is a repeat with probability zero
+                acc[e] += s[u] * to_f32<T>(reinterpret_cast<const T*>(&vx[u])[e]);
+            }
+        }
+        mx = m;
+        first += kLoads * kGroups;
+        if (first >= n) break;                                      // wave-uniform
+        load(kbase, first, kx);
+        load(vbase, first, vx);
+    }
+    auto plus = [](float a, float b) { return a + b; };
+    const float inv = 1.f / across(sum, plus);
+#pragma unroll
+    for (int e = 0; e < kPiece; ++e) acc[e] = across(acc[e], plus) * inv;
+    if (grp == 0) {
+        T y[kPiece];
+#pragma unroll
+        for (int e = 0; e < kPiece; ++e) y[e] = from_f32<T>(acc[e]);
+        *reinterpret_cast<uint4*>(out + (int64_t)r * nq * hd + head * hd + piece * kPiece) = *reinterpret_cast<const uint4*>(y);
+    }
+}
+
+// Takes the call if the kernel serves its heads and addresses.
+template <typename T>
+bool launch_attn_rows(const void* qkv, void* out, ScoreShape s, int32_t row0, int32_t nq, int32_t nkv, int32_t hd, float scale, hipStream_t stream) {
+    const int bytes = hd * (int)sizeof(T);
+    if (bytes % 16 || ((reinterpret_cast<uintptr_t>(qkv) | reinterpret_cast<uintptr_t>(out)) & 15)) return false;
+    auto launch = [&](auto pieces) {
+        hipLaunchKernelGGL((attn_rows_kernel<T, decltype(pieces)::value>), dim3(s.R() - row0, nq), dim3(64), 0, stream,
+                           static_cast<const T*>(qkv), static_cast<T*>(out), row0, s.P, s.T, nq, nkv, scale);
+        return true;
+    };
+    switch (bytes / 16) {
+        case 4: return launch(std::integral_constant<int, 4>{});
+        case 8: return launch(std::integral_constant<int, 8>{});
+        case 16: return launch(std::integral_constant<int, 16>{});
+        case 32: return launch(std::integral_constant<int, 32>{});
+    }
+    return false;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -688,6 +761,11 @@ int32_t launch_attention(int32_t dtype, const void* qkv, const void* vt, int64_t
     const size_t lds = simple_attention_lds(hd, s.P, s.T);
     if (lds > kSimpleLdsMax) return fail(ATTS_ERR_SHAPE, "attention: context of %d keys is too long for this dtype/head_dim", s.P + s.T);
     dim3 grid(R - row0, nq);
+    if (dtype == ATTS_DTYPE_F32 ? launch_attn_rows<float>(qkv, out, s, row0, nq, nkv, hd, scale, stream)
+                                : launch_attn_rows<bf16>(qkv, out, s, row0, nq, nkv, hd, scale, stream)) {
+        ATTS_LAUNCH_CHECK("attn_rows_kernel");
+        return ATTS_OK;
+    }
     if (dtype == ATTS_DTYPE_F32)
         hipLaunchKernelGGL(attn_simple_kernel<float>, grid, dim3(64), lds, stream, (const float*)qkv, (float*)out, row0, s.P, s.T,
                            nq, nkv, hd, scale);
