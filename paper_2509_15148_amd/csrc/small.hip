@@ -109,6 +109,17 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
         for (int b = 0; b < 4; ++b)
             old[b] = reinterpret_cast<const float*>(g_out)[(int64_t)min(row0 + b, d.M - 1) * d.ldc + min(col, d.N - 1)];
     }
+    // ... and the rotation's table and the targets likewise
+    float2 cs[EPI == EPI_QKV_ROPE ? 4 : 1];
+    if constexpr (EPI == EPI_QKV_ROPE) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) cs[b] = g_rope[(int64_t)min(row0 + b, d.M - 1) * d.cs_ld + (col & (d.half_hd - 1))];
+    }
+    int target[EPI == EPI_LMHEAD ? 4 : 1];
+    if constexpr (EPI == EPI_LMHEAD) {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) target[b] = g_targets[min(row0 + b, d.M - 1)];
+    }
     f32x16 acc[NI];
 #pragma unroll
     for (int j = 0; j < NI; ++j)
@@ -175,10 +186,10 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
         const int row = row0 + b;
         if constexpr (EPI == EPI_LMHEAD) {
             const bool row_ok = row < d.M;                                  // uniform over the 32 lanes that share `half`
-            int target = row_ok ? g_targets[row] : -1;
+            int tcol = target[b];
             if constexpr (kNorm)
-                if (target < 0 || target >= d.N) target = row_ok ? 0 : -1;  // flagged by the embedding kernel already
-            const int tcol = row_ok ? target - n0 : -1;
+                if (tcol < 0 || tcol >= d.N) tcol = 0;                      // flagged by the embedding kernel already
+            tcol = row_ok ? tcol - n0 : -1;
             float mx = -INFINITY;
 #pragma unroll
             for (int j = 0; j < NI; ++j) {
@@ -200,8 +211,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
             float rotated = 0.f;
             if constexpr (EPI == EPI_QKV_ROPE) {                            // every lane of the wavefront takes part in the exchange
                 const float other = __shfl_xor(z[0][b], d.half_hd);
-                const float2 cs = g_rope[(int64_t)min(row, d.M - 1) * d.cs_ld + (col & (d.half_hd - 1))];
-                rotated = (col & d.half_hd) ? z[0][b] * cs.x + other * cs.y : z[0][b] * cs.x - other * cs.y;
+                rotated = (col & d.half_hd) ? z[0][b] * cs[b].x + other * cs[b].y : z[0][b] * cs[b].x - other * cs[b].y;
                 if (col >= d.rot_cols) rotated = z[0][b];
             }
             if (row >= d.M || col >= d.N) continue;
