@@ -233,9 +233,89 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
     }
 }
 
+// fp32 products of so few 32 x 32 tiles that most compute units would idle: 16 x 16 tiles, four times as many workgroups, each wavefront's
+// chain of matrix instructions a quarter as long.  A step is 64 bytes of K a row: lane (r = l % 16, q = l / 16) holds floats 4 q .. 4 q + 3 of
+// its row, the operand of four 16 x 16 x 4 products (the k order inside a step is permuted alike for both operands).  Eight steps are
+// requested at once, so that K up to 512 waits for one latency.  us, 32 x 32 and 16 x 16 tiles: 320 x 128 x 512 (40 tiles) 6.9 and 4.9,
+// 100 x 256 x 1024 (32) 10.4 and 6.2, 64 x 1024 x 4096 (64) 33.2 and 21.8, 1000 x 128 x 512 (128) 7.0 and 6.3, 100 x 768 x 768 (96) 8.6 both;
+// 320 x 512 x 512 (160) 7.0 and 8.4, 300 x 768 x 3072 (240) 27.8 and 50.1: the operands are read twice as often.
+constexpr int kSmall16Unroll = 8;
+// 32 x 32 tiles up to which the smaller ones are taken: 128 up to K = 1024, 80 above (80 x 800 x 4096, 75 tiles, 33.6 and 18.4; 96 x 1024 x 2048, 96
+// tiles, 17.5 and 18.3; 64 x 2048 x 4096, 128 tiles, 33.6 and 37.4)
+static bool use_tiles_of_16(const GemmArgs& g) { return ceil_div(g.M, 32) * ceil_div(g.N, 32) <= (g.Kd <= 1024 ? 128 : 80); }
+template <int EPI>
+__global__ __launch_bounds__(64 * kSmallWaves) void gemm_small16_kernel(const char* __restrict__ gA, const char* __restrict__ gW, float* __restrict__ g_out,
+                                                                        const SmallDims d) {
+    __shared__ float part[kSmallWaves][4][64];
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));    // scalar: the K loop's branches must be too
+    const int m0 = (int)blockIdx.x % d.nt_m * 16, n0 = (int)blockIdx.x / d.nt_m * 16;
+    // rows and columns past the end repeat the last one (their results are dropped); 16-byte pieces past the end are zero
+    const char* const ap = gA + (int64_t)min(m0 + l16, d.M - 1) * d.lda * 4 + 16 * q;
+    const char* const wp = gW + (int64_t)min(n0 + l16, d.N - 1) * d.ldw * 4 + 16 * q;
+    const int k_bytes = d.Kd * 4, n_steps = (k_bytes + 63) / 64;
+    const int s0 = wave * n_steps / kSmallWaves, s1 = (wave + 1) * n_steps / kSmallWaves;
+    struct Frags {
+        uint4 a[kSmall16Unroll], w[kSmall16Unroll];
+    };
+    auto load = [&](Frags& f, int s) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kSmall16Unroll; ++u) {
+            const int64_t off = (int64_t)(s + u) * 64;
+            const bool ok = s + u < s1 && off + 16 * q < k_bytes;
+            f.a[u] = ok ? *reinterpret_cast<const uint4*>(ap + off) : make_uint4(0, 0, 0, 0);
+            f.w[u] = ok ? *reinterpret_cast<const uint4*>(wp + off) : make_uint4(0, 0, 0, 0);
+        }
+    };
+    const int row = m0 + 4 * q + wave, col = n0 + l16;                 // the element this lane finishes
+    const bool mine = row < d.M && col < d.N;
+    float old = 0.f;
+    if constexpr (EPI == EPI_RESID_F32) old = g_out[(int64_t)min(row, d.M - 1) * d.ldc + min(col, d.N - 1)];
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](const Frags& f) __attribute__((always_inline)) {   // steps past the end multiply zeros
+#pragma unroll
+        for (int u = 0; u < kSmall16Unroll; ++u) {
+            const f32x4 x = __builtin_bit_cast(f32x4, f.a[u]), y = __builtin_bit_cast(f32x4, f.w[u]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
+        }
+    };
+    Frags fa, fb;
+    load(fa, s0);
+    for (int s = s0; s < s1; s += 2 * kSmall16Unroll) {
+        if (s + kSmall16Unroll < s1) {                                  // scalar
+            load(fb, s + kSmall16Unroll);
+            mma(fa);
+            if (s + 2 * kSmall16Unroll < s1) load(fa, s + 2 * kSmall16Unroll);
+            mma(fb);
+        } else {
+            mma(fa);
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) part[wave][v][lane] = acc[v];
+    __syncthreads();
+    float z = part[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < kSmallWaves; ++w) z += part[w][wave][lane];
+    if (mine) g_out[(int64_t)row * d.ldc + col] = old + z;
+}
+
 template <typename T, int EPI, bool kNorm = false>
 int32_t launch_small_epi(const GemmArgs& g, hipStream_t stream) {
     constexpr int NI = EPI == EPI_SWIGLU || EPI == EPI_LMHEAD ? 2 : 1, N_OUT = EPI == EPI_LMHEAD ? 64 : 32;
+    if constexpr (sizeof(T) == 4 && (EPI == EPI_STORE_ACT || EPI == EPI_STORE_F32 || EPI == EPI_RESID_F32)) {
+        if (use_tiles_of_16(g)) {
+            SmallDims d{};
+            d.M = g.M; d.N = g.N; d.Kd = g.Kd;
+            d.lda = g.lda; d.ldw = g.ldw; d.ldc = g.ldc;
+            d.nt_m = (int32_t)ceil_div(g.M, 16);
+            hipLaunchKernelGGL(gemm_small16_kernel<EPI>, dim3((unsigned)(d.nt_m * ceil_div(g.N, 16))), dim3(64 * kSmallWaves), 0, stream,
+                               reinterpret_cast<const char*>(g.a), reinterpret_cast<const char*>(g.w), reinterpret_cast<float*>(g.out), d);
+            ATTS_LAUNCH_CHECK("gemm_small16_kernel");
+            return ATTS_OK;
+        }
+    }
     SmallDims d{g.M, g.N, g.Kd, g.lda, g.ldw, g.ldc, g.n_part, (int32_t)ceil_div(g.M, 32), g.norm_eps,
                 g.n_rot_heads * g.head_dim, g.head_dim / 2, g.head_dim / 2, g.first, g.tree_P, g.tree_T};
     hipLaunchKernelGGL((gemm_small_kernel<T, EPI, NI, kNorm>), dim3((unsigned)(d.nt_m * ceil_div(g.N, N_OUT))), dim3(64 * kSmallWaves), 0, stream,
