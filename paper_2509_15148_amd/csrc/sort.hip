@@ -6,7 +6,7 @@
 //     (block_sort_kernel), and where there are several, ONE further launch cuts them all at sampled keys and sorts the
 //     buckets in between (bucket_sort_kernel).
 //   * larger batches (bandwidth-bound): least-significant-digit radix sort, four passes of 8 bits.  A pass is
-//     three launches: per-tile digit histograms, a scan per digit over the tiles, and a stable scatter (ranks
+//     three launches: digit histograms of groups of tiles, a scan per digit over the groups, and a stable scatter (ranks
 //     inside a tile by wavefront-wide digit matching, keys reordered through LDS so that each digit's keys of a
 //     tile leave as one contiguous run).
 // No inter-workgroup waiting anywhere.
@@ -238,38 +238,57 @@ __device__ __forceinline__ uint32_t load_key(const void* __restrict__ in, int64_
     else return reinterpret_cast<const uint32_t*>(in)[idx];
 }
 
-// counts[d n_tiles + tile] = number of keys of the tile whose digit (key >> shift) & 255 is d
+// Digit counts, [tile][digit].  A workgroup walks a group of `per_group` consecutive tiles and keeps one running histogram: the row of
+// the group's first tile gets the group's totals (the scan turns them into the group's offsets), every other row the counts of the tiles
+// before it in the group.  So the scan has at most 256 groups to add up, and all rows are written and read whole: a histogram per tile stored
+// digit by digit cost a 4-byte access to 256 lines a tile here and in the scatter, and a scan over all tiles (2^24 keys, four passes:
+// histograms 96 -> 59 us, scans 46 -> 20; the sort 350 -> 284, of one value 473 -> 294).  Four copies of the bins, 16 banks apart, lanes in turn: neighbouring keys often
+// share a high digit, and an LDS atomic takes the lanes of one address one by one.
+constexpr int kHistThreads = 1024, kHistCopies = 4, kHistPitch = kRadixBins + 16;
 template <bool FIRST>
-__global__ __launch_bounds__(kRadixThreads) void radix_hist_kernel(const void* __restrict__ in, int64_t n, int shift,
-                                                                   int n_tiles, uint32_t* __restrict__ counts) {
-    __shared__ uint32_t h[kRadixBins];
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    const int64_t base = (int64_t)blockIdx.x * kRadixTile;
-#pragma unroll 8
-    for (int i = 0; i < kRadixItems; ++i) {
-        const int64_t idx = base + i * kRadixThreads + threadIdx.x;
-        if (idx < n) atomicAdd(&h[(load_key<FIRST>(in, idx) >> shift) & 255u], 1u);
+__global__ __launch_bounds__(kHistThreads) void radix_hist_kernel(const void* __restrict__ in, int64_t n, int shift, int n_tiles, int per_group,
+                                                                  uint32_t* __restrict__ counts) {
+    constexpr int kKeys = kRadixTile / kHistThreads;
+    __shared__ uint32_t h[kHistCopies][kHistPitch];
+    const int tid = threadIdx.x, first = blockIdx.x * per_group, last = min(first + per_group, n_tiles);
+    if (tid < kRadixBins) {
+#pragma unroll
+        for (int c = 0; c < kHistCopies; ++c) h[c][tid] = 0;
+    }
+    auto sum = [&]() __attribute__((always_inline)) { return h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid]; };
+    auto load = [&](int tile, uint32_t (&k)[kKeys]) __attribute__((always_inline)) {
+        const int64_t base = (int64_t)tile * kRadixTile;
+#pragma unroll
+        for (int i = 0; i < kKeys; ++i) k[i] = load_key<FIRST>(in, min(base + i * kHistThreads + tid, n - 1));
+    };
+    uint32_t key[kKeys], next[kKeys];
+    load(first, key);
+    for (int tile = first; tile < last; ++tile) {
+        load(min(tile + 1, last - 1), next);
+        __syncthreads();                                     // the tile before is counted (or the bins are clear)
+        if (tile > first && tid < kRadixBins) counts[(int64_t)tile * kRadixBins + tid] = sum();
+        __syncthreads();
+        const int64_t base = (int64_t)tile * kRadixTile;
+#pragma unroll
+        for (int i = 0; i < kKeys; ++i) {
+            if (base + i * kHistThreads + tid < n) atomicAdd(&h[tid & (kHistCopies - 1)][(key[i] >> shift) & 255u], 1u);
+            key[i] = next[i];
+        }
     }
     __syncthreads();
-    counts[(int64_t)threadIdx.x * n_tiles + blockIdx.x] = h[threadIdx.x];
+    if (tid < kRadixBins) counts[(int64_t)first * kRadixBins + tid] = sum();
 }
 
-// One workgroup per digit d: counts[d][*] becomes its exclusive prefix over the tiles, digit_tot[d] the digit's total.
-__global__ __launch_bounds__(kRadixThreads) void radix_scan_kernel(uint32_t* __restrict__ counts, int n_tiles,
+// One workgroup per digit d: the groups' totals become their exclusive prefix over the groups (at most 256), digit_tot[d] the digit's total.
+__global__ __launch_bounds__(kRadixThreads) void radix_scan_kernel(uint32_t* __restrict__ counts, int n_groups, int per_group,
                                                                    uint32_t* __restrict__ digit_tot) {
     __shared__ uint32_t red[4];
-    uint32_t* p = counts + (int64_t)blockIdx.x * n_tiles;
-    uint32_t carry = 0;
-    for (int t0 = 0; t0 < n_tiles; t0 += kRadixThreads) {
-        const int t = t0 + threadIdx.x;
-        const uint32_t v = t < n_tiles ? p[t] : 0u;
-        uint32_t total;
-        const uint32_t ex = block_excl_scan(v, red, total);
-        if (t < n_tiles) p[t] = carry + ex;
-        carry += total;
-    }
-    if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
+    uint32_t* const p = counts + (int64_t)threadIdx.x * per_group * kRadixBins + blockIdx.x;
+    const uint32_t v = (int)threadIdx.x < n_groups ? *p : 0u;
+    uint32_t total;
+    const uint32_t ex = block_excl_scan(v, red, total);
+    if ((int)threadIdx.x < n_groups) *p = ex;
+    if (threadIdx.x == 0) digit_tot[blockIdx.x] = total;
 }
 
 // Stable scatter of one tile.  Order inside the tile: wavefront w owns a quarter of the tile (consecutive keys) and walks
@@ -280,7 +299,7 @@ __global__ __launch_bounds__(kRadixThreads) void radix_scan_kernel(uint32_t* __r
 // keys go to that place in LDS and leave in tile order, so each digit's keys are written as one contiguous run.
 template <bool FIRST>
 __global__ __launch_bounds__(kRadixThreads) void radix_scatter_kernel(const void* __restrict__ in, int64_t n, int shift,
-                                                                      int n_tiles, const uint32_t* __restrict__ tile_ofs,
+                                                                      int per_group, const uint32_t* __restrict__ counts,
                                                                       const uint32_t* __restrict__ digit_tot,
                                                                       uint32_t* __restrict__ out) {
     constexpr int kWaves = kRadixThreads / 64;
@@ -291,6 +310,10 @@ __global__ __launch_bounds__(kRadixThreads) void radix_scatter_kernel(const void
     __shared__ uint32_t red[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t base = (int64_t)blockIdx.x * kRadixTile + (int64_t)wave * (64 * kRadixItems);
+    // keys of digit tid in the tiles before this one: its group's offset, and the tiles before it in the group
+    const int group_first = (int)blockIdx.x / per_group * per_group;
+    uint32_t before = counts[(int64_t)group_first * kRadixBins + tid];
+    if ((int)blockIdx.x != group_first) before += counts[(int64_t)blockIdx.x * kRadixBins + tid];
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) wcnt[w][tid] = 0;
     uint32_t key[kRadixItems];
@@ -336,7 +359,7 @@ __global__ __launch_bounds__(kRadixThreads) void radix_scatter_kernel(const void
     const uint32_t first = block_excl_scan(cnt, red, tile_total);
     const uint32_t digit_base = block_excl_scan(digit_tot[tid], red, all);
     lstart[tid] = first;
-    gdelta[tid] = digit_base + tile_ofs[(int64_t)tid * n_tiles + blockIdx.x] - first;
+    gdelta[tid] = digit_base + before - first;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < kRadixItems; ++i) {
@@ -355,11 +378,12 @@ __global__ __launch_bounds__(kRadixThreads) void radix_scatter_kernel(const void
 template <bool FIRST>
 int32_t radix_pass(const void* in, int64_t n, int shift, int n_tiles, uint32_t* counts, uint32_t* out, hipStream_t stream) {
     uint32_t* digit_tot = counts + (int64_t)kRadixBins * n_tiles;
-    hipLaunchKernelGGL(radix_hist_kernel<FIRST>, dim3((unsigned)n_tiles), dim3(kRadixThreads), 0, stream, in, n, shift, n_tiles, counts);
+    const int per_group = (int)ceil_div(n_tiles, kRadixBins), n_groups = (int)ceil_div(n_tiles, per_group);
+    hipLaunchKernelGGL(radix_hist_kernel<FIRST>, dim3((unsigned)n_groups), dim3(kHistThreads), 0, stream, in, n, shift, n_tiles, per_group, counts);
     ATTS_LAUNCH_CHECK("radix_hist_kernel");
-    hipLaunchKernelGGL(radix_scan_kernel, dim3(kRadixBins), dim3(kRadixThreads), 0, stream, counts, n_tiles, digit_tot);
+    hipLaunchKernelGGL(radix_scan_kernel, dim3(kRadixBins), dim3(kRadixThreads), 0, stream, counts, n_groups, per_group, digit_tot);
     ATTS_LAUNCH_CHECK("radix_scan_kernel");
-    hipLaunchKernelGGL(radix_scatter_kernel<FIRST>, dim3((unsigned)n_tiles), dim3(kRadixThreads), 0, stream, in, n, shift, n_tiles,
+    hipLaunchKernelGGL(radix_scatter_kernel<FIRST>, dim3((unsigned)n_tiles), dim3(kRadixThreads), 0, stream, in, n, shift, per_group,
                        counts, digit_tot, out);
     ATTS_LAUNCH_CHECK("radix_scatter_kernel");
     return ATTS_OK;

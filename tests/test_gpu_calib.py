@@ -266,6 +266,26 @@ def test_merge_segments_and_splits(base, sizes, where):
     c.close()
 
 
+@pytest.mark.parametrize("n", [(1 << 19) + 1, 4096 * 256, 4096 * 256 + 1, 4096 * 257 - 1, 4096 * 512, 4096 * 513 + 77, 5000003])
+@pytest.mark.parametrize("kind", ["spread", "one value", "high digits", "bits"])
+def test_radix_sort_groups_of_tiles(n, kind):
+    """Tiles around one, two and more a group, partly filled last tiles and groups; one digit only, few high digits, all bit patterns
+    (NaN, infinities and zeros of both signs among them)."""
+    import paper_2509_15148_amd as A
+    announce("radix groups", n, kind)
+    rng = np.random.default_rng(n)
+    v = {"spread": lambda: rng.lognormal(size=n), "one value": lambda: np.full(n, 0.75), "high digits": lambda: 1.0 + 1e-3 * rng.random(n),
+         "bits": lambda: rng.integers(0, 1 << 32, n, dtype=np.uint64).astype(np.uint32).view(np.float32)}[kind]().astype(np.float32)
+    c = A.Calib(n)
+    A.atts_calibrate_online(c, dev(v))
+    out = torch.empty(n, dtype=torch.float32, device="cuda")
+    A.atts_calib_export(c, out)
+    torch.cuda.synchronize()
+    got, k = out.cpu().numpy(), int(np.isnan(v).sum())
+    assert np.isnan(got[:k]).all() and np.array_equal(got[k:], np.sort(v)[:n - k])
+    c.close()
+
+
 @pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 63, 255, 1021, 1024, 4099, 8191, 8192, 8193, 262144, 262145])
 @pytest.mark.parametrize("m", [1, 255, 256, 700])
 def test_staged_levels_of_every_length(n, m):
