@@ -500,8 +500,8 @@ struct ConditionalLevels {
 // calibration scores go to the wavefront's own LDS and come back four to a read, the same for every lane, and are compared as
 // they are (an IEEE comparison, sub-normals kept by the kernel's float mode, is what the rank counts): two vector instructions a
 // pair, where a key passing by through a lane read made three, and no conversions.  What bounds it: the chain of loads, and from
-// about 200 scores on those two instructions.  8192 inputs of about 400 and 100 scores 58.8 -> 32.2 us, of 200 and 32 17.2 -> 10.6;
-// 4096 of 64 and 64 9.1 -> 7.5, where the host side of a call begins to bound it.
+// about 200 scores on those two instructions.  8192 inputs of about 400 and 100 scores 58.8 -> 30.7 us, of 200 and 32 17.2 -> 10.1;
+// 4096 of 64 and 64 9.1 -> 5.9.
 constexpr int kCondHeld = 8;                                     // blocks of 64 calibration scores a wavefront holds
 __global__ __launch_bounds__(256) void conditional_kernel(const float* __restrict__ cal, const int64_t* __restrict__ cal_off,
                                                           const float* __restrict__ test, const int64_t* __restrict__ test_off,
@@ -553,12 +553,19 @@ __global__ __launch_bounds__(256) void conditional_kernel(const float* __restric
                 for (int e = 0; e < 4; ++e) q[e] = reinterpret_cast<const float4*>(set)[4 * j + e];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    const float y[4] = {q[e].x, q[e].y, q[e].z, q[e].w};
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        cnt += y[i] >= s ? 1 : 0;
-                        asm volatile("" : "+v"(cnt));            // added one by one, each as a comparison's carry
-                    }
+                    // A comparison's result is added as a carry: four comparisons ahead of their additions, which may read a
+                    // mask no sooner than two instructions behind its write (the compiler's pairs wait two slots each: 32.2 us for 30.7).
+                    uint64_t b0, b1, b2, b3;
+                    asm("v_cmp_ge_f32_e64 %1, %5, %9\n\t"
+                        "v_cmp_ge_f32_e64 %2, %6, %9\n\t"
+                        "v_cmp_ge_f32_e64 %3, %7, %9\n\t"
+                        "v_cmp_ge_f32_e64 %4, %8, %9\n\t"
+                        "v_addc_co_u32_e64 %0, %1, 0, %0, %1\n\t"
+                        "v_addc_co_u32_e64 %0, %2, 0, %0, %2\n\t"
+                        "v_addc_co_u32_e64 %0, %3, 0, %0, %3\n\t"
+                        "v_addc_co_u32_e64 %0, %4, 0, %0, %4"
+                        : "+v"(cnt), "=&s"(b0), "=&s"(b1), "=&s"(b2), "=&s"(b3)
+                        : "v"(q[e].x), "v"(q[e].y), "v"(q[e].z), "v"(q[e].w), "v"(s));
                 }
             }
             c += cnt;                                            // a NaN candidate counts nothing
