@@ -298,6 +298,8 @@ struct ClassifyLevels {
     int32_t n_alpha;
 };
 
+constexpr int64_t kFewScores = (int64_t)1 << 17;     // test scores up to which a call is a chain of latencies (65,536 in 2^20 6.5 -> 5.2 us, 524,287 in 500,000
+                                                    // 10.9 -> 11.3 with that form)
 constexpr int kTopEntries = 8192;   // LDS copy of the coarsest level (or of every 2^top_shift-th entry of it): 32 KB
 
 struct SearchIndex {
@@ -359,7 +361,9 @@ __device__ __forceinline__ int quad_descend(const uint32_t* __restrict__ L, int6
     return quad_rounds<4>(L, len, t, x);
 }
 
-template <int THREADS>
+// kFew: the few scores of a small call, for which the chain of latencies counts; many want fewer LDS reads and no clamped loads instead (524,288
+// scores in 5000 keys 8.3 us, with the other form 10.5).
+template <int THREADS, bool kFew>
 __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const float* __restrict__ test, int64_t m,
                                                        ClassifyLevels lv, int32_t* __restrict__ ranks,
                                                        float* __restrict__ pvalues, uint8_t* __restrict__ classes,
@@ -377,12 +381,13 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
     const bool quantile = blockIdx.x == 0 && thresholds && (int)threadIdx.x < lv.n_alpha;
     const int64_t kth = quantile ? n + 1 - lv.r[threadIdx.x] : 0;                  // 1-indexed order statistic
     const uint32_t kth_key = quantile && kth >= 1 && kth <= n ? ix.lvl[0][kth - 1] : 0u;
-    if (s == 0) {
+    if (kFew && s == 0) {
         const int n4 = (n_top + 3) >> 2;
         for (int i0 = 0; i0 < n4; i0 += 4 * THREADS) {
             uint4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u * THREADS < n4) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];   // block-uniform
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (i0 + u * THREADS + (int)threadIdx.x < n4) reinterpret_cast<uint4*>(top)[i0 + u * THREADS + threadIdx.x] = v[u];
@@ -390,7 +395,7 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
     } else {
         for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
     }
-    if (THREADS == 256) {                                        // what the search below finds behind the last entry
+    if (kFew) {                                                  // what the search below finds behind the last entry
         __syncthreads();
         if (threadIdx.x == 0) top[n_top] = kPadKey;
     }
@@ -407,9 +412,8 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
         int t = 0;                                             // number of entries of the current level below x
         if (searching) {
             int lo = 0;                                        // number of staged entries < x
-            if constexpr (THREADS == 256) {
-                // three probes a step, read together: half the steps of a chain of LDS latencies (1024 entries 1.2 -> 0.7 us);
-                // many scores want fewer reads instead
+            if constexpr (kFew) {
+                // three probes a step, read together: half the steps of a chain of LDS latencies (1024 entries 1.2 -> 0.9 us)
                 for (int range = n_top + 1; range > 1;) {
                     const int q = (range + 3) >> 2;
                     int below = 0;
@@ -441,7 +445,7 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
         if (i >= m) continue;
         const int64_t c = searching ? n - t : 0;
         ranks[i] = (int32_t)c;
-        if (pvalues) pvalues[i] = p_value(c + 1, n + 1);
+        if (pvalues) pvalues[i] = kFew ? p_value(c + 1, n + 1) : (float)((double)(c + 1) / (double)(n + 1));     // alike; many scores hide the longer one
         int cls = 0;
         for (int l = 0; l < lv.n_alpha; ++l) cls += (c + 1 <= lv.r[l]) ? 1 : 0;
         classes[i] = (uint8_t)cls;
@@ -798,17 +802,19 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
     // 713 us for 770 (5.0 GB of lines from beyond the L2 by the counters: 7 TB/s, bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
     // 153 for 174, 2^19 against 2^23 20 for 27; few scores stay spread over more CUs.
     const bool large = M >= (int64_t)256 * 2048;
+    const bool few = M < kFewScores;
     const int threads = large ? 512 : 256;
     int64_t per = M / ((int64_t)threads * 1024);
     ix.per_thread = (int32_t)(per < 1 ? 1 : (per > 16 ? 16 : per));
     const unsigned blocks = (unsigned)(M > 0 ? ceil_div(M, (int64_t)threads * ix.per_thread) : 1);
     StageTimer t_(ATTS_STAGE_CLASSIFY, static_cast<hipStream_t>(hip_stream));
-    if (large)
-        hipLaunchKernelGGL(classify_kernel<512>, dim3(blocks), dim3(512), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M,
-                           lv, ranks, pvalues, classes, thresholds);
-    else
-        hipLaunchKernelGGL(classify_kernel<256>, dim3(blocks), dim3(256), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M,
-                           lv, ranks, pvalues, classes, thresholds);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3((unsigned)threads), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M, lv, ranks,
+                           pvalues, classes, thresholds);
+    };
+    if (large) launch(classify_kernel<512, false>);
+    else if (few) launch(classify_kernel<256, true>);
+    else launch(classify_kernel<256, false>);
     ATTS_LAUNCH_CHECK("classify_kernel");
     return ATTS_OK;
 }
