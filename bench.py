@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # (FETCH_SIZE, then WRITE_SIZE), each scaled by what the same counter reads for a plain device copy of known
 # size (--traffic-probe); see profiles/traffic_gemm_gate_up_7b.txt.  Valid only for the kernel source it was
 # taken with: reported as null when the hash of csrc/gemm.hip differs.
-MEASURED_TRAFFIC = {"gemm_sha256": "22eceb798b52fe624534db6e3dcbb0afd8e6fe30555c29ea11fbd8316b163bc7",
+MEASURED_TRAFFIC = {"gemm_sha256": "bf6aa43d8b6c3d6a5addeb2ee4743f928009be8b38416b6c593e1b2b2093275a",
                     "workload": "7b", "bytes_per_launch": 1.753e9}
 
 

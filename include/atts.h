@@ -271,7 +271,7 @@ int32_t atts_attention_shared_prefix(int32_t dtype, const void* qkv, void* out,
 #define ATTS_KERNEL_FEW_ROWS    3   /* at most 16 rows                                                         */
 #define ATTS_KERNEL_ALIGNED     4   /* aligned bf16 shapes                                                     */
 #define ATTS_KERNEL_EXCHANGED   5   /* aligned bf16 LM head, vocabulary entries as tile rows                   */
-#define ATTS_KERNEL_STREAMED    6   /* SwiGLU projection of at most 128 rows, about a tile a compute unit      */
+#define ATTS_KERNEL_STREAMED    6   /* SwiGLU of at most 128 rows, narrow projections of at most 64            */
 
 #define ATTS_PASS_SCORE        0
 #define ATTS_PASS_SCORE_CACHED 1

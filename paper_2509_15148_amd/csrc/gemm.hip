@@ -4,9 +4,10 @@
 // goes through one of the kernels below; scoring the drafts is the compute-bound part of the
 // method (Sec. "Q1"), so this is where the time goes.
 //
-//   gemm_bf16_wide_kernel   aligned bf16 shapes (every projection of the bf16 models): 8 wavefronts,
+//   gemm_bf16_wide_kernel   aligned bf16 shapes (the bf16 models' projections of more rows): 8 wavefronts,
 //                           384 x 256, 256 x 256 or 128 x 256 output tiles, operand slabs of 128 bytes
 //                           per row DMA-ed global -> LDS in whole 128-byte lines, explicit waits.
+//   gemm_streamed_kernel    (streamed.hip) SwiGLU of at most 128 rows, narrow projections of at most 64 (bf16)
 //   gemm_small_kernel       (small.hip) products of few tiles, any shape and dtype
 //   gemm_nt_kernel          any shape, bf16 or fp32 (v_mfma_f32_32x32x2_f32): 4 wavefronts (2 x 2),
 //                           tile BM x BN, 128-byte slabs through registers with bounds checks,
