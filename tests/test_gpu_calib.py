@@ -497,3 +497,18 @@ def test_export_import_round_trip():
         assert A.atts_calib_size(b) == 0
         a.close()
         b.close()
+
+
+@pytest.mark.parametrize("n", [1, 1000, 20001])
+@pytest.mark.parametrize("m", [(1 << 17) - 1, 1 << 17, (1 << 19) - 1, 1 << 19])
+def test_rank_search_on_both_sides_of_its_sizes(n, m):
+    """The three forms of the rank search, on each side of the numbers of scores where one follows the other: ranks,
+    classes, thresholds and p-values exactly the oracle's.  Half of the scores tie with the set's."""
+    import paper_2509_15148_amd as A
+    announce("calib rank search sizes", n, m)
+    cal = lognormal_scores(n, seed=31)
+    test = lognormal_scores(m, seed=32)
+    test[::2] = cal[np.arange(len(test[::2])) % n]
+    calib = A.Calib(n)
+    A.atts_calibrate_online(calib, dev(cal))
+    _check_against_oracle(A, calib, cal, test, [0.05, 0.2, 0.5], brute=False)
