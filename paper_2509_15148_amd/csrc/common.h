@@ -90,9 +90,10 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 __device__ __forceinline__ void block_barrier() {
-    // bare s_barrier (no fence): ordering against our own LDS traffic is done with the explicit
-    // waits around it; the asm statements keep the compiler from moving memory operations across.
-    asm volatile("" ::: "memory");
+    // s_barrier without a fence: DMA stays in flight across it (wait_vmcnt).  A wavefront's own LDS accesses are waited for, since what
+    // follows may overwrite what they read, and the compiler moves the wait for a read's value to where the value is used, behind
+    // the barrier too.  The asm statements keep it from moving memory operations across.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
