@@ -71,6 +71,27 @@ def test_running_maximum(dtype, hd, order):
     assert torch.isfinite(got).all() and err <= (1e-2 if dtype == torch.float32 else 3e-2), err
 
 
+@pytest.mark.parametrize("dtype,hd", HEADS)
+@pytest.mark.parametrize("P,K,T", [(1, 1, 1), (7, 2, 3), (64, 1, 5), (300, 2, 40)])
+def test_infinite_values(dtype, hd, P, K, T):
+    """An infinite value reaches the rows that see its key, the key's own row (whose last key it is) among them, and no others."""
+    announce("attention rows infinities", dtype, hd, P, K, T)
+    nq, nkv, R = 4, 2, P + K * T
+    qkv = torch.randn(R, (nq + 2 * nkv) * hd, generator=torch.Generator().manual_seed(hd + R)).to(dtype)
+    ref = _reference(qkv, P, K, T, nq, nkv, hd)                       # with finite values
+    row = torch.arange(R)
+    seg = torch.where(row < P, torch.zeros_like(row), P + (row - P) // T * T)
+    for i, key in enumerate(sorted({0, P // 2, P - 1, P, P + T - 1, R - 1})):
+        sees = (row >= key) & ((key < P) | (seg <= key))
+        qkv[key, (nq + nkv) * hd + i] = qkv[key, (nq + 2 * nkv - 1) * hd + i] = -math.inf if i % 2 else math.inf
+        for h in range(nq):
+            ref[sees, h * hd + i] = -math.inf if i % 2 else math.inf
+    got = _run(qkv.cuda(), P, K, T, nq, nkv, hd)
+    infinite = torch.isinf(ref)
+    assert torch.equal(got[infinite], ref[infinite])
+    assert (got[~infinite] - ref[~infinite]).abs().max().item() <= (2e-5 if dtype == torch.float32 else 1.5e-2)
+
+
 @pytest.mark.parametrize("dtype,hd", [(torch.float32, 32), (torch.bfloat16, 64), (torch.float32, 20), (torch.float32, 8), (torch.bfloat16, 24), (torch.bfloat16, 16)])
 def test_other_heads_and_addresses(dtype, hd):
     """Heads of other sizes, and rows or outputs that do not start at 16 bytes, stay with the general kernel."""
