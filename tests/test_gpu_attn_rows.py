@@ -94,7 +94,7 @@ def test_infinite_values(dtype, hd, P, K, T):
 
 @pytest.mark.parametrize("dtype,hd", [(torch.float32, 32), (torch.bfloat16, 64), (torch.float32, 20), (torch.float32, 8), (torch.bfloat16, 24), (torch.bfloat16, 16)])
 def test_other_heads_and_addresses(dtype, hd):
-    """Heads of other sizes, and rows or outputs that do not start at 16 bytes, stay with the general kernel."""
+    """Heads of other sizes, and rows that do not start at 16 bytes, stay with the general kernel; outputs may start anywhere."""
     announce("attention rows others", dtype, hd)
     P, K, T, nq, nkv = 70, 2, 20, 4, 2
     R, cols = P + K * T, (nq + 2 * nkv) * hd
@@ -110,3 +110,17 @@ def test_other_heads_and_addresses(dtype, hd):
         ref = _reference(qkv, P, K, T, nq, nkv, hd)
         err = (_run(qkv, P, K, T, nq, nkv, hd, room[to:to + R * nq * hd].view(R, nq * hd)) - ref).abs().max().item()
         assert err <= (2e-5 if dtype == torch.float32 else 1.5e-2), (at, to, err)
+
+
+@pytest.mark.parametrize("dtype,hd", HEADS)
+def test_output_at_any_address(dtype, hd):
+    """An output that does not start at 16 bytes is served by the same kernel: the same bits, and nothing beside it is written."""
+    announce("attention rows output address", dtype, hd)
+    P, K, T, nq, nkv = 70, 2, 20, 4, 2
+    R, size = P + K * T, (P + K * T) * nq * hd
+    qkv = torch.randn(R, (nq + 2 * nkv) * hd, generator=torch.Generator().manual_seed(hd)).to(dtype).cuda()
+    ref = _run(qkv, P, K, T, nq, nkv, hd)
+    for to in (1, 3, 4):
+        room = torch.full((size + 8,), 7.0, dtype=dtype, device="cuda")
+        assert torch.equal(_run(qkv, P, K, T, nq, nkv, hd, room[to:to + size].view(R, nq * hd)), ref)
+        assert (room[:to] == 7).all() and (room[to + size:] == 7).all()
