@@ -386,8 +386,10 @@ __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const
         for (int i0 = 0; i0 < n4; i0 += 4 * THREADS) {
             uint4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 4; ++u) {
+                v[u] = make_uint4(0, 0, 0, 0);                     // (left undefined, the pieces go through scratch memory one by one)
                 if (i0 + u * THREADS < n4) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];   // block-uniform
+            }
 #pragma unroll
             for (int u = 0; u < 4; ++u)
                 if (i0 + u * THREADS + (int)threadIdx.x < n4) reinterpret_cast<uint4*>(top)[i0 + u * THREADS + threadIdx.x] = v[u];

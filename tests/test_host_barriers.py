@@ -1,13 +1,11 @@
 """Barriers of the kernels that order their LDS traffic themselves (block_barrier): no wavefront arrives at one with an LDS access of its own
 still under way, since another may write the same bytes behind it.  Read from the assembly of the build's own flags; no GPU."""
-import os
 import re
-import subprocess
 from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
-from paper_2509_15148_amd import build as B
+from util import device_assembly
 
 SOURCES = ("streamed.hip", "gemm.hip", "attention.hip")
 
@@ -50,13 +48,8 @@ def test_the_walk_itself():
 @pytest.fixture(scope="module")
 def assembly(tmp_path_factory):
     out = tmp_path_factory.mktemp("asm")
-
-    def compile_one(src):
-        path = str(out / (src + ".s"))
-        subprocess.run([B.HIPCC, *B.FLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, src), "-o", path], check=True, capture_output=True)
-        return open(path).read()
     with ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
-        return dict(zip(SOURCES, ex.map(compile_one, SOURCES)))
+        return dict(zip(SOURCES, ex.map(lambda src: device_assembly(src, out), SOURCES)))
 
 
 @pytest.mark.parametrize("src", SOURCES)

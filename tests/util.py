@@ -1,6 +1,11 @@
 """Helpers shared by the GPU parity tests (no method arithmetic here)."""
+import os
+import subprocess
+
 import numpy as np
 import torch
+
+from paper_2509_15148_amd import build as B
 
 
 def weights_to_numpy(w):
@@ -37,3 +42,11 @@ def tight_ws(nbytes):
 def announce(*what):
     """Name the case before the GPU step runs, flushed, so a lost box still tells which case it was."""
     print("[case]", *what, flush=True)
+
+
+def device_assembly(src, folder):
+    """The assembly of one source file by the build's own flags."""
+    path = os.path.join(str(folder), src + ".s")
+    subprocess.run([B.HIPCC, *B.FLAGS, "--cuda-device-only", "-S", os.path.join(B.CSRC, src), "-o", path], check=True, capture_output=True)
+    with open(path) as f:
+        return f.read()
