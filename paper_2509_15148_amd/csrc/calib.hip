@@ -362,53 +362,68 @@ __device__ __forceinline__ int quad_descend(const uint32_t* __restrict__ L, int6
 }
 
 // kFew: the few scores of a small call, for which the chain of latencies counts; many want fewer LDS reads and no clamped loads instead (524,288
-// scores in 5000 keys 8.3 us, with the other form 10.5).
-template <int THREADS, bool kFew>
+// scores in 5000 keys 8.3 us, with the other form 10.5), and LDS and registers for 32 wavefronts a CU.  kOne: every thread has one score, which
+// it requests ahead of the staged level (524,288 in 5000 keys 8.3 -> 6.0 us, in 2^23 25.9 -> 22.5, 200,000 in 5000 5.7 -> 5.4); carried from round to
+// round of a loop it costs the register that makes it 24 wavefronts.
+template <int THREADS, bool kFew, bool kOne>
 __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const float* __restrict__ test, int64_t m,
                                                        ClassifyLevels lv, int32_t* __restrict__ ranks,
                                                        float* __restrict__ pvalues, uint8_t* __restrict__ classes,
                                                        float* __restrict__ thresholds) {
-    __shared__ __attribute__((aligned(16))) uint32_t top[kTopEntries + 4];
+    __shared__ __attribute__((aligned(16))) uint32_t top[kTopEntries + (kFew ? 4 : 0)];
     const uint32_t* __restrict__ T = ix.lvl[ix.top_level];
     const int64_t top_len = ix.len[ix.top_level], n = ix.len[0];
     const int s = ix.top_shift;
     const int n_top = (int)((top_len + ((int64_t)1 << s) - 1) >> s);
-    // the first scores and the thresholds are requested ahead of the staged level, which comes in 16-byte pieces (its array is
-    // padded to whole lines): a small call is nothing but this chain of latencies
     const float none = __uint_as_float(0x7FC00000u);
-    const int64_t first = (int64_t)blockIdx.x * ix.per_thread * THREADS + threadIdx.x;
-    float next = first < m ? test[first] : none;
     const bool quantile = blockIdx.x == 0 && thresholds && (int)threadIdx.x < lv.n_alpha;
-    const int64_t kth = quantile ? n + 1 - lv.r[threadIdx.x] : 0;                  // 1-indexed order statistic
-    const uint32_t kth_key = quantile && kth >= 1 && kth <= n ? ix.lvl[0][kth - 1] : 0u;
-    if (kFew && s == 0) {
-        const int n4 = (n_top + 3) >> 2;
-        for (int i0 = 0; i0 < n4; i0 += 4 * THREADS) {
-            uint4 v[4];
+    auto order_statistic = [&](int64_t kth) { return kth >= 1 && kth <= n ? ix.lvl[0][kth - 1] : 0u; };      // 1-indexed
+    auto threshold = [&](int64_t kth, uint32_t key) { return kth > n ? INFINITY : (kth < 1 ? -INFINITY : key_to_score(key)); };
+    float first = none;
+    if constexpr (kOne) {
+        const int64_t i = (int64_t)blockIdx.x * THREADS + threadIdx.x;
+        if (i < m) first = test[i];
+    }
+    if constexpr (kFew) {
+        // The thresholds are requested ahead of the staged level too, which comes in 16-byte pieces (its array is padded to whole lines): a small
+        // call is nothing but this chain of latencies.  The first workgroup waits for the levels' ranks, read by index, in between; taken
+        // from scalars by selects they cost every call 0.05 to 0.1 us.
+        const int64_t kth = quantile ? n + 1 - lv.r[threadIdx.x] : 0;
+        const uint32_t kth_key = quantile ? order_statistic(kth) : 0u;
+        if (s == 0) {
+            const int n4 = (n_top + 3) >> 2;
+            for (int i0 = 0; i0 < n4; i0 += 4 * THREADS) {
+                uint4 v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                v[u] = make_uint4(0, 0, 0, 0);                     // (left undefined, the pieces go through scratch memory one by one)
-                if (i0 + u * THREADS < n4) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];   // block-uniform
+                for (int u = 0; u < 4; ++u) {
+                    v[u] = make_uint4(0, 0, 0, 0);               // (left undefined, the pieces go through scratch memory one by one)
+                    if (i0 + u * THREADS < n4) v[u] = reinterpret_cast<const uint4*>(T)[min(i0 + u * THREADS + (int)threadIdx.x, n4 - 1)];   // block-uniform
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i0 + u * THREADS + (int)threadIdx.x < n4) reinterpret_cast<uint4*>(top)[i0 + u * THREADS + threadIdx.x] = v[u];
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (i0 + u * THREADS + (int)threadIdx.x < n4) reinterpret_cast<uint4*>(top)[i0 + u * THREADS + threadIdx.x] = v[u];
+        } else {
+            for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
         }
+        __syncthreads();
+        if (threadIdx.x == 0) top[n_top] = kPadKey;              // what the search below finds behind the last entry
+        __syncthreads();
+        if (quantile) thresholds[threadIdx.x] = threshold(kth, kth_key);
     } else {
         for (int i = threadIdx.x; i < n_top; i += THREADS) top[i] = T[(int64_t)i << s];
-    }
-    if (kFew) {                                                  // what the search below finds behind the last entry
         __syncthreads();
-        if (threadIdx.x == 0) top[n_top] = kPadKey;
+        if (quantile) {
+            const int64_t kth = n + 1 - lv.r[threadIdx.x];
+            thresholds[threadIdx.x] = threshold(kth, order_statistic(kth));
+        }
     }
-    __syncthreads();
-    if (quantile) thresholds[threadIdx.x] = kth > n ? INFINITY : (kth < 1 ? -INFINITY : key_to_score(kth_key));
-    for (int j = 0; j < ix.per_thread; ++j) {
-        const int64_t i0 = ((int64_t)blockIdx.x * ix.per_thread + j) * THREADS;      // block-uniform: whole quads stay in the loop
+    const int per_thread = kOne ? 1 : ix.per_thread;
+    for (int j = 0; j < per_thread; ++j) {
+        const int64_t i0 = ((int64_t)blockIdx.x * per_thread + j) * THREADS;      // block-uniform: whole quads stay in the loop
         if (i0 >= m) break;
         const int64_t i = i0 + threadIdx.x;
-        const float sc = next;
-        next = j + 1 < ix.per_thread && i + THREADS < m ? test[i + THREADS] : none;
+        const float sc = kOne ? first : (i < m ? test[i] : none);
         const bool searching = !score_is_nan(sc);
         const uint32_t x = score_to_key(sc);
         int t = 0;                                             // number of entries of the current level below x
@@ -800,7 +815,7 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
     while (ceil_div(ix.len[ix.top_level], (int64_t)1 << ix.top_shift) > kTopEntries) ++ix.top_shift;
     // Enough workgroups to fill the chip, few enough that staging the top level stays a small part of the work.  A search is a
     // chain of memory latencies, so many scores take workgroups of 512 threads: the staged 32 KB leave room for five workgroups on
-    // a CU, which are 20 wavefronts of 32 with 256 threads.  With both changes (quad_rounds) 2^24 scores against 2^28 keys take
+    // a CU (four with kFew's spare entries, which two fill), which are 20 wavefronts of 32 with 256 threads.  With both changes (quad_rounds) 2^24 scores against 2^28 keys take
     // 713 us for 770 (5.0 GB of lines from beyond the L2 by the counters: 7 TB/s, bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
     // 153 for 174, 2^19 against 2^23 20 for 27; few scores stay spread over more CUs.
     const bool large = M >= (int64_t)256 * 2048;
@@ -814,9 +829,10 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3((unsigned)threads), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M, lv, ranks,
                            pvalues, classes, thresholds);
     };
-    if (large) launch(classify_kernel<512, false>);
-    else if (few) launch(classify_kernel<256, true>);
-    else launch(classify_kernel<256, false>);
+    if (large && ix.per_thread > 1) launch(classify_kernel<512, false, false>);
+    else if (large) launch(classify_kernel<512, false, true>);
+    else if (few) launch(classify_kernel<256, true, true>);
+    else launch(classify_kernel<256, false, true>);
     ATTS_LAUNCH_CHECK("classify_kernel");
     return ATTS_OK;
 }

@@ -177,9 +177,9 @@ def test_batches_of_several_runs(n, kind):
 
 
 @pytest.mark.parametrize("n", [1, 40, 9000, 300000])
-@pytest.mark.parametrize("m", [(1 << 19) - 1, 1 << 19, (1 << 20) + 513])
+@pytest.mark.parametrize("m", [(1 << 19) - 1, 1 << 19, (1 << 20) - 1, 1 << 20, (1 << 20) + 513])
 def test_classification_workgroup_sizes(n, m):
-    """Fewer and more test scores than the line between the two workgroup sizes, ragged ends, sets of no, one and two index levels
+    """Fewer and more test scores than the lines between the two workgroup sizes and one score a thread or several, ragged ends, sets of no, one and two index levels
     below the staged one; scores outside the set's range, ties and NaN among them.  Integer work: every rank exact."""
     import paper_2509_15148_amd as A
     announce("classify", n, m)
