@@ -1,5 +1,10 @@
 """The short calls' native marshalling takes plain device tensors only; everything else goes the general way, which converts it or
 words its error.  Both ways make the same call."""
+import os
+import shutil
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -12,6 +17,7 @@ from util import announce, dev
 
 def test_what_is_not_plain_is_left_to_the_general_way():
     m, other = B._marshal, B._marshal.OTHER
+    assert m.__file__.endswith("_marshal.so")                     # the native one
     host, off = torch.zeros(4), torch.zeros(2, dtype=torch.int64)
     assert other not in (A.OK, A.ERR_INVALID_ARG, A.ERR_SHAPE, A.ERR_WORKSPACE, A.ERR_CAPACITY, A.ERR_HIP)
     for handle in (None, 0, "x", 1.5):
@@ -22,6 +28,22 @@ def test_what_is_not_plain_is_left_to_the_general_way():
         assert m.classify_conditional(host, off, host, off, alphas, host.int(), None, host.to(torch.uint8)) == other
     fake = torch.empty(4, device="meta")
     assert m.calibrate_online(1 << 20, fake) == other
+
+
+@pytest.mark.parametrize("native", ["absent", "not loadable"])
+def test_import_without_the_native_module(tmp_path, native):
+    """libatts.so is all that the package needs: the short calls then take the general way, with its wording of errors."""
+    where = os.path.dirname(B.__file__)
+    shutil.copytree(where, tmp_path / "paper_2509_15148_amd", ignore=shutil.ignore_patterns("_marshal.so", "_build", "csrc", "__pycache__"))
+    if native == "not loadable":
+        (tmp_path / "paper_2509_15148_amd" / "_marshal.so").write_bytes(b"no library")
+    code = ("import torch, paper_2509_15148_amd as A\nassert A.__file__.startswith(%r), A.__file__\nprint(A.atts_classic_workspace_bytes(100))\n"
+            "c = A.Calib.__new__(A.Calib); c.handle = A.binding.ctypes.c_void_p()\n"
+            "for call in (lambda: A.atts_calibrate_online(c, torch.zeros(4)), lambda: A.atts_classify_ordinal(c, torch.zeros(4), [0.1], None, None, "
+            "torch.zeros(4, dtype=torch.uint8), None)):\n"
+            "    try: call()\n    except A.AttsError as e: assert 'device tensor' in str(e), e\n    else: raise AssertionError\n" % str(tmp_path))
+    r = subprocess.run([sys.executable, "-c", code], cwd=tmp_path, capture_output=True, text=True, env={**os.environ, "PYTHONPATH": str(tmp_path)})
+    assert r.returncode == 0 and int(r.stdout) == A.atts_classic_workspace_bytes(100), r.stderr
 
 
 @pytest.mark.gpu
