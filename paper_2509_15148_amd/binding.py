@@ -26,6 +26,7 @@ MAX_ALPHAS = 8
 
 # The C entry points and their arguments (p pointer, i int32_t, l int64_t, z size_t, f float, d double).  Declared once, they take
 # plain Python numbers and None: an argument object built for each of a short call's eleven arguments took longer than its kernels.
+# Numbers that come from the caller are still converted one by one, so that one of a wrong type is a TypeError that says so.
 _ARGUMENTS = {
     "atts_last_error_string": "", "atts_model_create": "ppp", "atts_model_destroy": "p", "atts_workspace_bytes": "piiip",
     "atts_score_drafts": "ppippiiipppzp", "atts_model_check": "ppp", "atts_prefix_create": "pip", "atts_prefix_destroy": "p",
@@ -207,7 +208,7 @@ def atts_score_drafts(model: Model, prefix_ids: torch.Tensor, draft_ids: torch.T
     _check(_lib.atts_score_drafts(
         model.handle, _ptr(prefix_ids, torch.int32, "prefix_ids"), prefix_ids.numel(),
         _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-        K, T_max, score_mode,
+        K, T_max, ctypes.c_int32(score_mode),
         _ptr(token_logprobs, torch.float32, "token_logprobs"), _ptr(scores, torch.float32, "scores"),
         _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
@@ -218,7 +219,7 @@ class Prefix:
     def __init__(self, model: Model, capacity: int):
         self.model = model
         self.handle = ctypes.c_void_p()
-        _check(_lib.atts_prefix_create(model.handle, capacity, ctypes.byref(self.handle)))
+        _check(_lib.atts_prefix_create(model.handle, ctypes.c_int32(capacity), ctypes.byref(self.handle)))
 
     def close(self) -> None:
         if self.handle:
@@ -244,7 +245,7 @@ def atts_prefix_reset(prefix: Prefix) -> None:
 
 def atts_prefix_extend_workspace_bytes(prefix: Prefix, n: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_prefix_extend_workspace_bytes(prefix.handle, n, ctypes.byref(out)))
+    _check(_lib.atts_prefix_extend_workspace_bytes(prefix.handle, ctypes.c_int32(n), ctypes.byref(out)))
     return out.value
 
 
@@ -264,14 +265,14 @@ def atts_score_drafts_cached(prefix: Prefix, draft_ids: torch.Tensor, draft_lens
         raise AttsError(ERR_INVALID_ARG, "scores / draft_lens must have K elements")
     _check(_lib.atts_score_drafts_cached(
         prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-        K, T_max, score_mode,
+        K, T_max, ctypes.c_int32(score_mode),
         _ptr(token_logprobs, torch.float32, "token_logprobs"), _ptr(scores, torch.float32, "scores"),
         _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
 
 def atts_continue_workspace_bytes(prefix: Prefix, K: int, T: int, n_new: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_continue_workspace_bytes(prefix.handle, K, T, n_new,
+    _check(_lib.atts_continue_workspace_bytes(prefix.handle, ctypes.c_int32(K), ctypes.c_int32(T), ctypes.c_int32(n_new),
                                               ctypes.byref(out)))
     return out.value
 
@@ -282,7 +283,7 @@ def atts_continue_greedy(prefix: Prefix, draft_ids: torch.Tensor, out_ids: torch
     if out_ids.dim() != 2 or out_ids.shape[0] != K or (draft_lens is not None and draft_lens.numel() != K):
         raise AttsError(ERR_INVALID_ARG, "out_ids must be [K, n_new], draft_lens [K]")
     _check(_lib.atts_continue_greedy(prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-                                     K, T, out_ids.shape[1], eos_id,
+                                     K, T, out_ids.shape[1], ctypes.c_int32(eos_id),
                                      _ptr(out_ids, torch.int32, "out_ids"), _ptr(workspace, torch.uint8, "workspace"),
                                      workspace.numel(), _stream()))
 
@@ -296,8 +297,8 @@ def atts_continue_sample(prefix: Prefix, draft_ids: torch.Tensor, temperature: f
     if draft_lens is not None and draft_lens.numel() != K:
         raise AttsError(ERR_INVALID_ARG, "draft_lens must have K elements")
     _check(_lib.atts_continue_sample(prefix.handle, _ptr(draft_ids, torch.int32, "draft_ids"), _ptr(draft_lens, torch.int32, "draft_lens"),
-                                     K, T, out_ids.shape[1], eos_id,
-                                     temperature, _ptr(uniforms, torch.float32, "uniforms"),
+                                     K, T, out_ids.shape[1], ctypes.c_int32(eos_id),
+                                     ctypes.c_float(temperature), _ptr(uniforms, torch.float32, "uniforms"),
                                      _ptr(out_ids, torch.int32, "out_ids"), _ptr(workspace, torch.uint8, "workspace"),
                                      workspace.numel(), _stream()))
 
@@ -368,7 +369,7 @@ class Calib:
 
     def __init__(self, capacity: int):
         self.handle = ctypes.c_void_p()
-        _check(_lib.atts_calib_create(capacity, ctypes.byref(self.handle)))
+        _check(_lib.atts_calib_create(ctypes.c_int64(capacity), ctypes.byref(self.handle)))
 
     def close(self) -> None:
         if self.handle:
@@ -456,7 +457,7 @@ def atts_calib_import(calib: Calib, scores: torch.Tensor) -> None:
 
 def atts_classic_workspace_bytes(n_scores: int) -> int:
     out = ctypes.c_size_t()
-    _check(_lib.atts_classic_workspace_bytes(n_scores, ctypes.byref(out)))
+    _check(_lib.atts_classic_workspace_bytes(ctypes.c_int64(n_scores), ctypes.byref(out)))
     return out.value
 
 
@@ -471,7 +472,7 @@ def atts_classic_threshold(cal_scores: torch.Tensor, alpha: float, tau: torch.Te
     if tau.numel() != 1:
         raise AttsError(ERR_INVALID_ARG, "tau must have one element")
     _check(_lib.atts_classic_threshold(_ptr(cal_scores, torch.float32, "cal_scores"), cal_scores.numel(),
-                                       alpha, _ptr(tau, torch.float32, "tau"),
+                                       ctypes.c_double(alpha), _ptr(tau, torch.float32, "tau"),
                                        _ptr(workspace, torch.uint8, "workspace"), workspace.numel(), _stream()))
 
 
@@ -506,5 +507,5 @@ def atts_profile_enable(on: bool) -> None:
 def atts_profile_read(stage: int):
     """-> (total device milliseconds, launches) of one stage since atts_profile_enable(True)."""
     ms, n = ctypes.c_double(), ctypes.c_int64()
-    _check(_lib.atts_profile_read(stage, ctypes.byref(ms), ctypes.byref(n)))
+    _check(_lib.atts_profile_read(ctypes.c_int32(stage), ctypes.byref(ms), ctypes.byref(n)))
     return ms.value, n.value

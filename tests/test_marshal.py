@@ -46,6 +46,25 @@ def test_import_without_the_native_module(tmp_path, native):
     assert r.returncode == 0 and int(r.stdout) == A.atts_classic_workspace_bytes(100), r.stderr
 
 
+@pytest.mark.parametrize("bad", ["x", None, [1]])
+def test_numbers_of_a_wrong_type(bad, monkeypatch):
+    """A TypeError, whose message says what is wrong, from every entry that takes numbers from its caller."""
+    monkeypatch.setattr(B, "_ptr", lambda *args: None)             # host tensors get as far as the numbers
+    monkeypatch.setattr(B, "_stream", lambda: 0)
+
+    class Handle:
+        handle = None
+    ids, out, x, space = torch.zeros(2, 3, dtype=torch.int32), torch.zeros(2, 4, dtype=torch.int32), torch.zeros(2), torch.zeros(256, dtype=torch.uint8)
+    u = torch.zeros(2, 4)
+    for call in (lambda: A.Calib(bad), lambda: A.Prefix(Handle, bad), lambda: A.atts_score_drafts(Handle, ids[0], ids, None, bad, None, x, space),
+                 lambda: A.atts_score_drafts_cached(Handle, ids, None, bad, None, x, space), lambda: A.atts_prefix_extend_workspace_bytes(Handle, bad),
+                 lambda: A.atts_continue_workspace_bytes(Handle, 1, bad, 1), lambda: A.atts_continue_greedy(Handle, ids, out, space, eos_id=bad),
+                 lambda: A.atts_continue_sample(Handle, ids, bad, u, out, space), lambda: A.atts_classic_workspace_bytes(bad),
+                 lambda: A.atts_classic_threshold(x, bad, x[:1], space), lambda: A.atts_profile_read(bad)):
+        with pytest.raises(TypeError, match="interpreted as an integer|must be real number"):
+            call()
+
+
 @pytest.mark.gpu
 def test_both_ways_make_the_same_call():
     announce("marshal both ways")
