@@ -240,9 +240,14 @@ __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small_kernel(const char
 // 100 x 256 x 1024 (32) 10.4 and 6.2, 64 x 1024 x 4096 (64) 33.2 and 21.8, 1000 x 128 x 512 (128) 7.0 and 6.3, 100 x 768 x 768 (96) 8.6 both;
 // 320 x 512 x 512 (160) 7.0 and 8.4, 300 x 768 x 3072 (240) 27.8 and 50.1: the operands are read twice as often.
 constexpr int kSmall16Unroll = 8;
-// 32 x 32 tiles up to which the smaller ones are taken: 128 up to K = 1024, 80 above (80 x 800 x 4096, 75 tiles, 33.6 and 18.4; 96 x 1024 x 2048, 96
-// tiles, 17.5 and 18.3; 64 x 2048 x 4096, 128 tiles, 33.6 and 37.4)
-static bool use_tiles_of_16(const GemmArgs& g) { return ceil_div(g.M, 32) * ceil_div(g.N, 32) <= (g.Kd <= 1024 ? 128 : 80); }
+// Where the smaller tiles are taken: up to 128 tiles of 32 x 32 (80 above K = 1024), and of those with more than one small tile a compute unit
+// only where the eight steps requested at once are mostly there, or a single one.  Small over large tiles, time: up to 256 small ones 0.55 (K = 4096) to
+// 0.94 (K = 128); more of them K <= 32 0.87 .. 0.94, 36 .. 128 1.00 .. 1.18 (1000 x 100 x 128 3.4 and 4.1 us), 132 .. 800 0.80 .. 1.01, 832 .. 1024
+// 1.00 .. 1.12 (1000 x 128 x 1024 10.6 and 11.6), above that 0.94 .. 1.01 up to 80 large tiles; 96 x 1024 x 2048 (96) 17.5 and 18.3, 64 x 2048 x 4096 (128) 33.6 and 37.4
+static bool use_tiles_of_16(const GemmArgs& g) {
+    if (ceil_div(g.M, 32) * ceil_div(g.N, 32) > (g.Kd <= 1024 ? 128 : 80)) return false;
+    return ceil_div(g.M, 16) * ceil_div(g.N, 16) <= 256 || g.Kd <= 32 || (g.Kd > 128 && g.Kd <= 800) || g.Kd > 1024;
+}
 template <int EPI>
 __global__ __launch_bounds__(64 * kSmallWaves) void gemm_small16_kernel(const char* __restrict__ gA, const char* __restrict__ gW, float* __restrict__ g_out,
                                                                         const SmallDims d) {

@@ -10,9 +10,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("M,N,K", [(1, 1, 4), (1, 16, 8), (16, 16, 16), (17, 15, 20), (15, 33, 60), (33, 17, 64), (16, 48, 68), (320, 128, 512), (5, 130, 516),
                                    (40, 40, 1028), (100, 64, 2052), (31, 100, 4096),
-                                   (128, 1024, 1024), (129, 1024, 1024), (128, 1024, 1028), (64, 1280, 1028), (65, 1280, 1028)])
+                                   (128, 1024, 1024), (129, 1024, 1024), (128, 1024, 1028), (64, 1280, 1028), (65, 1280, 1028),
+                                   (256, 256, 128), (256, 257, 128), (257, 256, 1024), (200, 512, 32), (200, 512, 36), (200, 512, 132), (200, 512, 800), (200, 512, 804)])
 def test_products_in_tiles_of_16(M, N, K):
-    """Edges of the tiles, fewer steps than wavefronts, partly filled steps and batches of steps, the most tiles for short and for long K."""
+    """Edges of the tiles, fewer steps than wavefronts, partly filled steps and batches of steps, the most tiles for short and for long K, both sides of the lines in K."""
     announce("tiles of 16", M, N, K)
     assert A.atts_gemm_routes(torch.float32, M, N, K)[0].kernel == A.KERNEL_SMALL
     g = torch.Generator().manual_seed(M + N + K)
