@@ -62,6 +62,40 @@ def test_partial_sums_of_a_few_rows(cfg, rows):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("cfg,rows", [(NARROW, 2), (NARROW, 16), (NARROW, 33), (NARROW, 64), (WIDE, 17), (WIDE, 64)])
+@pytest.mark.parametrize("values_alone", [False, True])
+def test_every_block_of_columns(cfg, rows, values_alone):
+    """Partial sums column by column: the LM head takes single features of the last hidden state, one of every 32 in turn, each as the target of
+    one row.  O and down as they are; and with O the identity, so that the values (the last columns of QKV) reach the features by themselves."""
+    announce("streamed columns", cfg.d_model, rows, values_alone)
+    d, T = cfg.d_model, rows - 1
+    w = make_weights(cfg, seed=rows, device="cuda")
+    if values_alone:
+        w["wo"][0].copy_(torch.eye(d, cfg.n_q_heads * cfg.head_dim))
+        w["w_down"][0].zero_()
+    ids = np.random.default_rng(rows).permutation(cfg.vocab).astype(np.int32)
+    prefix, drafts = ids[:1], ids[1:rows]                             # every row has a target of its own
+    host = weights_to_numpy(w)
+    hidden = O.rmsnorm(O.decoder_hidden(host, cfg, ids[:rows]), host["final_norm"], cfg.rms_eps)[:T]
+    model, space = A.Model(cfg, w), None
+    for first in range(0, d // 32, T):
+        blocks = np.arange(first, first + T) % (d // 32)
+        columns = 32 * blocks + (5 * blocks + rows) % 32
+        head = torch.zeros(cfg.vocab, d)
+        head[drafts, columns] = 2.0
+        w["lm_head"].copy_(head)
+        lp, sc = torch.full((1, T), float("nan"), device="cuda"), torch.full((1,), float("nan"), device="cuda")
+        space = dirty_ws(A.atts_workspace_bytes(model, 1, 1, T)) if space is None else space
+        A.atts_score_drafts(model, dev(prefix), dev(drafts[None]), None, 0, lp, sc, space)
+        z = np.zeros((T, cfg.vocab))
+        z[:, drafts] = 2.0 * hidden[:, columns]
+        ref = O.log_softmax(z)[np.arange(T), drafts]
+        # features up to 5 stored in bf16, twice: 2 x 5 x 2^-9 = 0.02, half as much again for the roundings ahead; another column's feature is 2 off
+        assert np.abs(lp.cpu().numpy()[0] - ref).max() <= 3e-2, first
+    model.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("d_ffn,rows", [(8320, 2), (8320, 33), (8320, 128), (12416, 16), (12416, 64), (12416, 65), (18944, 4), (18944, 32), (18944, 63),
                                         (18944, 100), (22016, 17), (22016, 48), (22016, 127), (27648, 31), (27648, 64), (27648, 128)])
 def test_every_block_of_features(d_ffn, rows):
