@@ -19,14 +19,17 @@ BF16 = ModelConfig(1, 768, 6, 2, 128, 256, 2304, "bf16")
 @pytest.mark.parametrize("cached", [False, True])
 @pytest.mark.parametrize("mode", [A.SCORE_MEAN_NLL, A.SCORE_SUM_NLL])
 def test_log_probabilities_and_scores(cfg, P, K, T, cached, mode):
-    """Drafts of at most 32 tokens take their scores with their log-probabilities; lengths from none to all tokens, ids outside the
-    vocabulary past a draft's length; the first tokens' hidden state from the tree and from a prefix handle."""
+    """Drafts of at most 32 tokens take their scores with their log-probabilities; lengths from none to all tokens and outside of that, ids
+    outside the vocabulary past a draft's length; the first tokens' hidden state from the tree and from a prefix handle."""
     announce("pass tail", cfg.dtype, P, K, T, cached, mode)
     w = make_weights(cfg, seed=K, device="cuda")
     prefix, drafts = [x.numpy() for x in make_token_ids(cfg.vocab, P, K, T, seed=T)]
     lens = np.random.default_rng(T).integers(1, T + 1, K).astype(np.int32)
     lens[0] = T
-    padded = drafts.copy()
+    for k, out_of_range in ((1, 0), (2, T + 5), (3, -2)):             # no token, and lengths that are read as all and as none
+        if k < K:
+            lens[k] = out_of_range
+    padded, given, lens = drafts.copy(), lens, np.clip(lens, 0, T)
     for k in range(K):
         padded[k, lens[k]:] = -5 if k % 2 else cfg.vocab + 7
     model = A.Model(cfg, w)
@@ -35,17 +38,17 @@ def test_log_probabilities_and_scores(cfg, P, K, T, cached, mode):
     if cached:
         pre = A.Prefix(model, P)
         A.atts_prefix_extend(pre, dev(prefix), dirty_ws(A.atts_prefix_extend_workspace_bytes(pre, P)))
-        A.atts_score_drafts_cached(pre, dev(padded), dev(lens), mode, lp, sc, space)
+        A.atts_score_drafts_cached(pre, dev(padded), dev(given), mode, lp, sc, space)
     else:
-        A.atts_score_drafts(model, dev(prefix), dev(padded), dev(lens), mode, lp, sc, space)
+        A.atts_score_drafts(model, dev(prefix), dev(padded), dev(given), mode, lp, sc, space)
     no_lp, again = None, torch.full((K,), float("nan"), device="cuda")
     if not cached:                                                    # scores alone
-        A.atts_score_drafts(model, dev(prefix), dev(padded), dev(lens), mode, no_lp, again, space)
+        A.atts_score_drafts(model, dev(prefix), dev(padded), dev(given), mode, no_lp, again, space)
         assert torch.equal(again, sc)
     ref_lp = O.score_drafts(weights_to_numpy(w), cfg, prefix, drafts)[0]
     live = np.arange(T)[None, :] < lens[:, None]
     got, tol = lp.cpu().numpy(), 1e-4 if cfg.dtype == "fp32" else 2e-2
     assert np.abs(got - ref_lp * live).max() <= tol and (got[~live] == 0).all()
     total = -(ref_lp * live).sum(axis=1)
-    want = total / lens if mode == A.SCORE_MEAN_NLL else total
+    want = total / np.maximum(lens, 1) if mode == A.SCORE_MEAN_NLL else total
     assert np.abs(sc.cpu().numpy() - want).max() <= tol * (1 if mode == A.SCORE_MEAN_NLL else T)
