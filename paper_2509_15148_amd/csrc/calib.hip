@@ -157,27 +157,17 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
         if (threadIdx.x < 2) split[threadIdx.x] = splits[blockIdx.x + threadIdx.x];
     } else
     // Merge-path split of both segment ends at once, one wavefront each: "a[i] <= b[diag - 1 - i]" is true below the split, and
-    // every round probes 512 evenly spaced candidates of the range that is left, eight a lane requested together.  One load
-    // latency a round, two rounds up to 2^18 candidates, and nothing to wait for but the wavefront's own loads (128 candidates a
-    // round with counts and limits through LDS and three barriers: 3.6 us of a workgroup's 6 at 2^20 + 65,536 keys).
+    // every round probes 64 evenly spaced candidates of the range that is left, one a lane.  One load latency a round, three rounds
+    // up to 2^18 candidates, and nothing to wait for but the wavefront's own loads: 2.2 us of a workgroup at 2^20 + 65,536 keys (128
+    // candidates a round with counts and limits through LDS and three barriers 3.6; 512, eight a lane, keep the address unit busy
+    // longer than the round that they save takes: the launch 11.8 -> 15.5).
     if (threadIdx.x < 128) {
-        constexpr int kProbes = 1;
         const int h = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
         const int64_t diag = h ? o1 : o0;
         int64_t lo = diag > nb ? diag - nb : 0, hi = diag < na ? diag : na;
         while (lo < hi) {
-            const int64_t step = (hi - lo + 64 * kProbes - 1) / (64 * kProbes);
-            uint32_t x[kProbes], y[kProbes];
-#pragma unroll
-            for (int u = 0; u < kProbes; ++u) {
-                const int64_t i = min(lo + (int64_t)(64 * u + lane) * step, hi - 1);
-                x[u] = a[i];
-                y[u] = batch_key(diag - 1 - i);
-            }
-            int64_t below = 0;
-#pragma unroll
-            for (int u = 0; u < kProbes; ++u)
-                below += __popcll(__ballot(lo + (int64_t)(64 * u + lane) * step < hi && x[u] <= y[u]));
+            const int64_t step = (hi - lo + 63) / 64, probe = lo + lane * step, i = min(probe, hi - 1);
+            const int64_t below = __popcll(__ballot(a[i] <= batch_key(diag - 1 - i) && probe < hi));
             // the last true candidate and the one behind it (or the end) enclose the split
             hi = min(lo + below * step, hi);
             lo = below > 0 ? lo + (below - 1) * step + 1 : lo;
@@ -217,7 +207,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeJob job, cons
     const int ib = d0 - ia;
     // The PER smallest of the next PER keys of both sides, all read together: min(a[e], b[PER - 1 - e]) is a bitonic sequence of
     // them, sorted by the last stages of a network (equal keys are alike, so which side one comes from does not matter).  Taken
-    // one by one, each key waits for the LDS read that the choice before it made: 1.2 us a workgroup instead of 0.4.
+    // one by one, each key waits for the LDS read that the choice before it made: 1.3 us a workgroup instead of 0.7.
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         const uint32_t x = ia + e < la ? buf[lds_pad(ia + e)] : kPadKey;
@@ -298,8 +288,6 @@ struct ClassifyLevels {
     int32_t n_alpha;
 };
 
-constexpr int64_t kFewScores = (int64_t)1 << 17;     // test scores up to which a call is a chain of latencies (65,536 in 2^20 6.5 -> 5.2 us, 524,287 in 500,000
-                                                    // 10.9 -> 11.3 with that form)
 constexpr int kTopEntries = 8192;   // LDS copy of the coarsest level (or of every 2^top_shift-th entry of it): 32 KB
 
 struct SearchIndex {
@@ -361,15 +349,17 @@ __device__ __forceinline__ int quad_descend(const uint32_t* __restrict__ L, int6
     return quad_rounds<4>(L, len, t, x);
 }
 
-// kFew: the few scores of a small call, for which the chain of latencies counts; many want fewer LDS reads and no clamped loads instead (524,288
-// scores in 5000 keys 8.3 us, with the other form 10.5), and LDS and registers for 32 wavefronts a CU.  kOne: every thread has one score, which
-// it requests ahead of the staged level (524,288 in 5000 keys 8.3 -> 6.0 us, in 2^23 25.9 -> 22.5, 200,000 in 5000 5.7 -> 5.4); carried from round to
-// round of a loop it costs the register that makes it 24 wavefronts.
-template <int THREADS, bool kFew, bool kOne>
+// Workgroups of 256 threads are for calls whose chain of latencies counts (kFew): the level staged in 16-byte pieces and searched by three probes
+// a step.  512 threads want fewer LDS reads and no clamped loads instead (524,288 scores in 5000 keys 8.3 us, with the other form 10.5), and LDS
+// and registers for 32 wavefronts a CU.  kOne: every thread has one score, which it requests ahead of the staged level (524,288 in 5000 keys
+// 8.3 -> 6.0 us, in 2^23 25.9 -> 22.5); carried from round to round of a loop it costs the register that makes it 24 wavefronts.
+template <int THREADS, bool kOne>
 __global__ __launch_bounds__(THREADS) void classify_kernel(SearchIndex ix, const float* __restrict__ test, int64_t m,
                                                        ClassifyLevels lv, int32_t* __restrict__ ranks,
                                                        float* __restrict__ pvalues, uint8_t* __restrict__ classes,
                                                        float* __restrict__ thresholds) {
+    constexpr bool kFew = THREADS == 256;
+    static_assert(!kFew || kOne, "the levels and scores of a few are requested together");
     __shared__ __attribute__((aligned(16))) uint32_t top[kTopEntries + (kFew ? 4 : 0)];
     const uint32_t* __restrict__ T = ix.lvl[ix.top_level];
     const int64_t top_len = ix.len[ix.top_level], n = ix.len[0];
@@ -815,11 +805,12 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
     while (ceil_div(ix.len[ix.top_level], (int64_t)1 << ix.top_shift) > kTopEntries) ++ix.top_shift;
     // Enough workgroups to fill the chip, few enough that staging the top level stays a small part of the work.  A search is a
     // chain of memory latencies, so many scores take workgroups of 512 threads: the staged 32 KB leave room for five workgroups on
-    // a CU (four with kFew's spare entries, which two fill), which are 20 wavefronts of 32 with 256 threads.  With both changes (quad_rounds) 2^24 scores against 2^28 keys take
-    // 713 us for 770 (5.0 GB of lines from beyond the L2 by the counters: 7 TB/s, bandwidth now bounds it), with many ties 330 for 488, 2^22 against 2^26
-    // 153 for 174, 2^19 against 2^23 20 for 27; few scores stay spread over more CUs.
+    // a CU (four with kFew's spare entries, of which 2^19 scores take up to eight), which are 20 wavefronts of 32 with 256 threads.  With both
+    // changes (quad_rounds) 2^24 scores against 2^28 keys take 713 us for 770 (5.0 GB of lines from beyond the L2 by the counters: 7 TB/s, bandwidth
+    // now bounds it), with many ties 330 for 488, 2^22 against 2^26 153 for 174.  Fewer stay spread over more CUs, in the form for few at every
+    // size: against halving and plain staging 65,536 scores in 8192 keys 3.6 and 6.5 us, in 2^20 4.75 and 4.9, 200,000 in 5000 4.2 and 5.3,
+    // 524,287 in 2^23 18.9 and 34.9, in 500,000 10.6 and 10.5.
     const bool large = M >= (int64_t)256 * 2048;
-    const bool few = M < kFewScores;
     const int threads = large ? 512 : 256;
     int64_t per = M / ((int64_t)threads * 1024);
     ix.per_thread = (int32_t)(per < 1 ? 1 : (per > 16 ? 16 : per));
@@ -829,10 +820,9 @@ int32_t atts_classify_ordinal(const atts_calib* c, const float* test_scores, int
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3((unsigned)threads), 0, static_cast<hipStream_t>(hip_stream), ix, test_scores, M, lv, ranks,
                            pvalues, classes, thresholds);
     };
-    if (large && ix.per_thread > 1) launch(classify_kernel<512, false, false>);
-    else if (large) launch(classify_kernel<512, false, true>);
-    else if (few) launch(classify_kernel<256, true, true>);
-    else launch(classify_kernel<256, false, true>);
+    if (ix.per_thread > 1) launch(classify_kernel<512, false>);
+    else if (large) launch(classify_kernel<512, true>);
+    else launch(classify_kernel<256, true>);
     ATTS_LAUNCH_CHECK("classify_kernel");
     return ATTS_OK;
 }
