@@ -8,7 +8,7 @@
 // This is exactly K independent causal sequences [prefix ; draft_k], evaluated without
 // recomputing or re-storing the prefix.
 //
-// Three kernels:
+// Four kernels:
 //   * attn_mfma_kernel  bf16, head_dim 128: flash-style, 128 or 256 query rows of one head per
 //     workgroup, key/value tiles of 64 rows staged in LDS and shared by its wavefronts.
 //     Works on transposed products so that no register transpose is needed:
@@ -122,8 +122,8 @@ __global__ __launch_bounds__(64) void attn_simple_kernel(const T* __restrict__ q
 // the lanes that summed them, and the groups meet only in the maximum, the sum and the output; longer contexts go on in batches with a
 // running maximum.  What bounds it is a memory latency and a chain of about 300 vector instructions a batch; the kernel above, a lane a
 // key and scores through LDS, waits for five latencies and reads 64 rows with every load.  us before and now: fp32, hd 32: 4 heads, 64 + 8 x 32
-// rows 6.2 -> 5.5 alone and 8 -> 4.6 inside a pass; 4 heads, 400 + 16 x 64 45.7 -> 25.3; 32 query and 8 key heads, 500 + 4 x 500 963 -> 453;
-// bf16, hd 64: 8.5 -> 5.3, 58.5 -> 32.9, 1534 -> 589; 30 + 2 x 20 rows the same.
+// rows 6.0 -> 4.55; 30 + 2 x 20 3.55 -> 3.35; 400 + 16 x 64 46 -> 27.3; 32 query and 8 key heads, 500 + 4 x 500 982 -> 436; bf16, hd 64: 8.5 -> 5.3,
+// 8 query and 2 key heads, 300 + 4 x 200 80 -> 44, 500 + 4 x 500 1530 -> 570; hd 256 of 16 heads, 1500 + 4 x 100 3684 -> 1234.
 template <typename T, int PIECES>
 __global__ __launch_bounds__(64) void attn_rows_kernel(const T* __restrict__ qkv, T* __restrict__ out, int row0, int P, int Tn, int nq, int nkv,
                                                       float scale) {
@@ -795,6 +795,8 @@ int32_t launch_attention(int32_t dtype, const void* qkv, const void* vt, int64_t
         ATTS_LAUNCH_CHECK("attn_mfma_kernel");
         return ATTS_OK;
     }
+    // The limit of the general kernel's scores in LDS holds for both: whether the other one takes a call depends on the buffers' address, which is
+    // no reason to serve or refuse a context.
     const size_t lds = simple_attention_lds(hd, s.P, s.T);
     if (lds > kSimpleLdsMax) return fail(ATTS_ERR_SHAPE, "attention: context of %d keys is too long for this dtype/head_dim", s.P + s.T);
     dim3 grid(R - row0, nq);

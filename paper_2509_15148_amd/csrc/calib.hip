@@ -45,8 +45,8 @@ namespace atts {
 namespace {
 
 constexpr int kMergeThreads = 256;
-// outputs per merge workgroup: the shorter chain of 1024 while a workgroup a CU covers them (100,000 + 2000 keys 15.4 -> 14.7 us
-// with their ranks, 3,000,000 + 100 16.8 and 17.4)
+// outputs per merge workgroup: the shorter chain of 1024 while a workgroup a CU covers them (2048 and 1024, us: 1000 + 16 keys 6.8 and 6.4,
+// 100,000 + 2000 with their sort 11.4 and 10.7, 250,000 + 2000 11.5 and 10.8, 500,000 + 2000 11.8 both, 3,000,000 + 100 13.4 and 13.5)
 constexpr int kMergeSegTiny = 1024;
 constexpr int64_t kMergeTinyTo = (int64_t)kMergeSegTiny * 256;
 constexpr int kMergeSegSmall = 2048;   // ... cache-resident sizes (more workgroups)
@@ -54,10 +54,10 @@ constexpr int kMergeSegLarge = 4096;   // ... and streaming sizes (split search 
 constexpr int64_t kMergeLargeFrom = (int64_t)1 << 22;
 // Appends of up to kInlineMax scores into sets of up to kInlineTotal keys are sorted by the merge workgroups themselves, each for
 // itself: one launch instead of two.  Up to kRankMax scores every thread ranks one against all others (its time grows with the
-// square: 1000 + 16 scores 5.6 us, 64 7.2, 256 13.4), more go through the register network of one wavefront (16: 6.3, 64: 6.8,
-// 256: 8.1, 512: 8.4), a sort of its own ahead of the merge costs a launch (8.2, 8.3, 9.2, 9.7).  Every workgroup repeats the
-// sort, so sets whose merge has more than four workgroups a CU keep it apart (2,000,000 + 256: 9.7 inside, 10.7 apart; 4,000,000:
-// 15.8 and 13.7).
+// square: 1000 + 16 scores 6.4 us, 48 7.7, 64 8.1, 256 13.3), more go through the register network of one wavefront (16: 7.3, 48: 7.8,
+// 64: 7.8, 256: 8.2, 512: 8.4), a sort of its own ahead of the merge costs a launch (9.6, 10.1, 10.1, 10.4, 10.5).  Every workgroup repeats the
+// sort, so sets whose merge has more than four workgroups a CU keep it apart (2,000,000 + 256: 10.6 inside, 12.0 apart; 4,000,000:
+// 16.0 and 15.2).
 constexpr int kInlineMax = kWaveKeys;
 constexpr int kRankMax = 48;
 constexpr int64_t kInlineTotal = (int64_t)kMergeSegSmall * 1024;

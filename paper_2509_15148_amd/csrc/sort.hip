@@ -32,7 +32,7 @@ constexpr int kFewRuns = 32;
 // a bucket's keys lie strictly between two splitters with at most q samples between them: at most kSpacing q keys, and from
 // every run fewer than kSpacing more
 static_assert(kSpacing * (kSamplesMax + kMaxRuns) <= kBucketCap && kSmallSortMax / kSpacing <= kBucketCap, "a workgroup holds a bucket, and all samples");
-static_assert(kSpacing * (kSamplesMin + kFewRuns) <= kPer * kFewThreads && kFewRuns * 16 <= kFewThreads && kMaxRuns * 16 <= kBucketThreads, "");
+static_assert(kSpacing * (16 + kFewRuns) <= kPer * kFewThreads && kFewRuns * 16 <= kFewThreads && kMaxRuns * 16 <= kBucketThreads, "");
 static_assert(kMaxRuns * kRunMax == kSmallSortMax && kSamplesMin % kPer == 0 && kSmallSortMax / kSpacing / kSamplesMax <= kBucketThreads, "");
 
 // Every workgroup turns 8 THREADS scores into one ascending run; samples != NULL: every kSpacing-th key of it also goes there,
@@ -66,8 +66,9 @@ __global__ __launch_bounds__(THREADS) void block_sort_kernel(const float* __rest
 // run (the samples lead to one block of 64 keys, read in 16-byte pieces), gathers the segments between them and sorts those.
 // What bounds it is its chain of steps (two sorts, the limits, the gathering), one bucket per CU: 65,536 scores 12 us behind
 // 5.2 for the runs, where runs of 8192 keys merged through LDS and one pass that searched every key's place in the other runs took
-// 25 + 14; 262,144 scores 31 us in all and 524,288 43, by radix sort 76 and 78 (which is why the line to it lies here: its
-// launches are a floor, and 64 runs of one workgroup's keys end at 2^19).  Up to 32 runs by workgroups of 512 threads: 0.6 us less.
+// 25 + 14.  With the merge into an empty set 131,072 scores take 27 us, 262,144 33 and 524,288 47, by radix sort 65, 66 and 69 (which is why the
+// line to it lies here: its launches are a floor, and 64 runs of one workgroup's keys end at 2^19).  Up to 32 runs by workgroups of 512
+// threads: 0.6 us less.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void bucket_sort_kernel(const uint32_t* __restrict__ runs, int64_t n, int run_len, int n_runs,
                                                               const uint32_t* __restrict__ samples, int n_samples, int q,
