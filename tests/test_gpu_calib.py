@@ -500,7 +500,7 @@ def test_export_import_round_trip():
 
 
 @pytest.mark.parametrize("n", [1, 1000, 20001])
-@pytest.mark.parametrize("m", [(1 << 17) - 1, 1 << 17, (1 << 19) - 1, 1 << 19])
+@pytest.mark.parametrize("m", [(1 << 17) - 1, 1 << 17, (1 << 19) - 1, 1 << 19, (1 << 20) - 1, 1 << 20])
 def test_rank_search_on_both_sides_of_its_sizes(n, m):
     """The three forms of the rank search, on each side of the numbers of scores where one follows the other: ranks,
     classes, thresholds and p-values exactly the oracle's.  Half of the scores tie with the set's."""
